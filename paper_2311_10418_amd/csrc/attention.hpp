@@ -41,5 +41,10 @@ bool attn_mfma_supported(const AttnArgs& a);
 ds_status attn_fwd_mfma(const AttnArgs& a, hipStream_t st);
 ds_status attn_bwd_mfma(const AttnArgs& a, hipStream_t st);
 
+// fp32 matrix-core paths (attention_f32.hip), for aligned operands
+bool attn_f32_mfma_supported(const AttnArgs& a);
+ds_status attn_fwd_f32_mfma(const AttnArgs& a, hipStream_t st);
+ds_status attn_bwd_f32_mfma(const AttnArgs& a, hipStream_t st);
+
 ds_status launch_attention_fwd(const AttnArgs& a, bool force_generic, hipStream_t st);
 ds_status launch_attention_bwd(const AttnArgs& a, bool force_generic, hipStream_t st);

@@ -16,6 +16,7 @@ ds_status launch_attention_fwd(const AttnArgs& a, bool force_generic, hipStream_
     ds_status s = check(a);
     if (s != DS_OK) return s;
     if (!force_generic && attn_mfma_supported(a)) return attn_fwd_mfma(a, st);
+    if (!force_generic && attn_f32_mfma_supported(a)) return attn_fwd_f32_mfma(a, st);
     return attn_fwd_generic(a, st);
 }
 
@@ -26,6 +27,7 @@ ds_status launch_attention_bwd(const AttnArgs& a, bool force_generic, hipStream_
     if (!force_generic && attn_mfma_supported(a)) return attn_bwd_mfma(a, st);      // computes delta itself
     s = attn_delta(a, st);
     if (s != DS_OK) return s;
+    if (!force_generic && attn_f32_mfma_supported(a)) return attn_bwd_f32_mfma(a, st);
     return attn_bwd_generic(a, st);
 }
 

@@ -1,0 +1,368 @@
+// fp32 variable-length attention on the matrix cores (v_mfma_f32_16x16x4_f32), any head size up to 128, causal or
+// unmasked, forward and backward.  fp32 operands, products and sums throughout: the probabilities are not rounded.
+//
+// A wavefront owns 16 "column" items (queries in forward and dQ, keys in dK/dV) and computes TRANSPOSED score blocks: 16
+// rows of the other side x its 16 columns, lane = (column lane % 16, rows 4 g + e with g = lane / 16, e = 0..3).  What is
+// per column (running maximum and sum, log-sum-exp, delta) is then a per-lane scalar, and register e of a block is, as it
+// stands, the B operand of the second product for the contraction step over rows {4 g + e}: probabilities never move.
+// Both products read the other side's tile from LDS, token-major, rows of HD + 4 floats: the first product 4 consecutive
+// features per lane (float4; 16 rows 4 banks apart cover the 64 banks), the second one float per step (4 rows that lie 4
+// rows apart start 16 banks apart).  HD is the head size rounded up to 32, 64, 96 or 128; features beyond it are zeros.
+//
+// The bound is the fp32 matrix rate: per 16 x 16 block HD/4 MFMAs of 32 cycles for each product (two forward, three in
+// dQ, four in dK/dV) against 4 exponentials per lane.  Tiles go global -> registers -> LDS, the next tile's reads in
+// flight during the current tile's products; 4 wavefronts per work-group (64 columns), 18 - 51 KB of LDS, so several
+// work-groups per CU cover each other's two barriers per tile.  Sequences are taken last to first: a plan lists them by
+// ascending length, and the long ones should start first.  Measured at
+// 7 684 tokens in 64 sequences (up to 512), 4 heads of 64, causal: forward 37 us, dQ 42, dK/dV 86, against 508, 435 and
+// 581 for one wavefront per query / key row with shuffled probabilities (attention_generic.hip, which keeps the operands
+// that float4 cannot read): those read every row of the other side once per row of this one.
+#include "attention.hpp"
+
+namespace {
+
+constexpr float kLog2eF = 1.4426950408889634f;
+constexpr float kLn2F = 0.6931471805599453f;
+
+__device__ __forceinline__ f32x4_t mfma4(float a, float b, f32x4_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f32x4_t zero4() { f32x4_t z = {0.f, 0.f, 0.f, 0.f}; return z; }
+
+template <int HD, int NT = 256> struct F32Tile {                     // NT threads
+    static constexpr int ROWS = HD <= 96 ? 64 : 32;                   // rows of the other side per tile
+    static constexpr int LD = HD + 4;
+    static constexpr int FLOATS = ROWS * LD;
+    static constexpr int NV = ROWS * HD / 4 / NT;                     // float4 per thread
+    static_assert(ROWS * HD / 4 % NT == 0, "whole float4s per thread");
+    float4 v[NV];
+    // rows r0 .. r0 + ROWS - 1 of a [n_rows][hd] block with row stride ld; beyond either extent: zeros
+    __device__ __forceinline__ void load(const float* __restrict__ src, long long ld, int r0, int n_rows, int hd, int t) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int u = t + NT * i, r = r0 + u / (HD / 4), d = (u % (HD / 4)) * 4;
+            v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (r < n_rows && d < hd) v[i] = *reinterpret_cast<const float4*>(src + (long long)r * ld + d);
+        }
+    }
+    __device__ __forceinline__ void store(float* tile, int t) const {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int u = t + NT * i;
+            *reinterpret_cast<float4*>(tile + (u / (HD / 4)) * LD + (u % (HD / 4)) * 4) = v[i];
+        }
+    }
+};
+
+// this lane's column item: features 16 s + 4 g .. + 3 of `row`
+template <int HD>
+__device__ __forceinline__ void load_column(const float* __restrict__ row, int hd, int g, float4 (&f)[HD / 16]) {
+#pragma unroll
+    for (int s = 0; s < HD / 16; ++s) {
+        const int d = 16 * s + 4 * g;
+        f[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (d < hd) f[s] = *reinterpret_cast<const float4*>(row + d);
+    }
+}
+
+// rows rb .. rb+15 of a tile times this lane's column item, contracted over the features
+template <int HD>
+__device__ __forceinline__ f32x4_t first_product(const float* tile, int rb, int lane, const float4 (&f)[HD / 16]) {
+    const float* p = tile + (rb + (lane & 15)) * F32Tile<HD>::LD + 4 * (lane >> 4);
+    f32x4_t acc = zero4();
+#pragma unroll
+    for (int s = 0; s < HD / 16; ++s) {
+        const float4 x = *reinterpret_cast<const float4*>(p + 16 * s);
+        acc = mfma4(x.x, f[s].x, acc);
+        acc = mfma4(x.y, f[s].y, acc);
+        acc = mfma4(x.z, f[s].z, acc);
+        acc = mfma4(x.w, f[s].w, acc);
+    }
+    return acc;
+}
+
+// out^T[feature][column] += tile[rows rb .. rb+15]^T * w, w = a 16 x 16 block in score layout
+template <int HD>
+__device__ __forceinline__ void second_product(const float* tile, int rb, int lane, const f32x4_t& w, f32x4_t (&out)[HD / 16]) {
+    const float* p = tile + (rb + 4 * (lane >> 4)) * F32Tile<HD>::LD + (lane & 15);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int dt = 0; dt < HD / 16; ++dt) out[dt] = mfma4(p[e * F32Tile<HD>::LD + 16 * dt], w[e], out[dt]);
+}
+
+template <int HD>
+__device__ __forceinline__ void store_column(const f32x4_t (&acc)[HD / 16], float mul, float* __restrict__ row, int hd, int g) {
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt) {
+        const int d = 16 * dt + 4 * g;
+        if (d < hd) *reinterpret_cast<float4*>(row + d) = make_float4(acc[dt][0] * mul, acc[dt][1] * mul, acc[dt][2] * mul, acc[dt][3] * mul);
+    }
+}
+
+// largest / sum over the four 16-lane groups, which hold different rows of the same columns
+__device__ __forceinline__ float groups_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
+__device__ __forceinline__ float groups_sum(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
+
+// ---------------------------------------------------------------- forward
+template <int HD>
+__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
+    typedef F32Tile<HD> Tile;
+    constexpr int KT = Tile::ROWS, NB = KT / 16;
+    __shared__ __attribute__((aligned(16))) float sK[Tile::FLOATS];
+    __shared__ __attribute__((aligned(16))) float sV[Tile::FLOATS];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4;
+    const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 64;
+    const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
+    if (q0 >= ql) return;
+    const long long qrow0 = a.q_row[s], krow0 = a.k_row[s];
+    const float* K = (const float*)a.k + krow0 * a.ldk + h * hd;
+    const float* V = (const float*)a.v + krow0 * a.ldv + h * hd;
+    const int qw0 = q0 + wave * 16, qi = qw0 + (lane & 15), qi_c = qi < ql ? qi : ql - 1;
+    float4 qf[HD / 16];
+    load_column<HD>((const float*)a.q + (qrow0 + qi_c) * a.ldq + h * hd, hd, g, qf);
+    f32x4_t oacc[HD / 16];
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt) oacc[dt] = zero4();
+    const float c = a.scale * kLog2eF;
+    float m = -INFINITY, lsum = 0.f;                                  // running maximum (exp2 domain), this lane's part of the sum
+    const int kv_end = a.mask ? min(kl, q0 + 64) : kl;
+    const int wave_last = a.mask ? min(kl - 1, qw0 + 15) : kl - 1;    // last key this wavefront can see
+    Tile tk, tv;
+    if (kv_end > 0) {
+        tk.load(K, a.ldk, 0, kl, hd, t);
+        tv.load(V, a.ldv, 0, kl, hd, t);
+    }
+    for (int k0 = 0; k0 < kv_end; k0 += KT) {
+        __syncthreads();                                              // the previous tile has been read by everybody
+        tk.store(sK, t);
+        tv.store(sV, t);
+        __syncthreads();
+        if (k0 + KT < kv_end) {
+            tk.load(K, a.ldk, k0 + KT, kl, hd, t);
+            tv.load(V, a.ldv, k0 + KT, kl, hd, t);
+        }
+        if (k0 > wave_last || qw0 >= ql) continue;
+        f32x4_t sc[NB];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kt = 0; kt < NB; ++kt) {
+            sc[kt] = first_product<HD>(sK, 16 * kt, lane, qf);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int key = k0 + 16 * kt + 4 * g + e;
+                if (key >= kl || (a.mask && key > qi)) sc[kt][e] = -INFINITY;
+                mx = fmaxf(mx, sc[kt][e]);
+            }
+        }
+        const float m_new = fmaxf(m, groups_max(mx) * c);             // finite: every column sees a key of every tile it visits
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;         // (a clamped column past the end may see none)
+        const float alpha = __builtin_amdgcn_exp2f(m - m_use);
+        float rs = 0.f;
+#pragma unroll
+        for (int kt = 0; kt < NB; ++kt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                sc[kt][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kt][e], c, -m_use));
+                rs += sc[kt][e];
+            }
+        lsum = lsum * alpha + rs;
+#pragma unroll
+        for (int dt = 0; dt < HD / 16; ++dt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) oacc[dt][e] *= alpha;
+        m = m_new;
+#pragma unroll
+        for (int kt = 0; kt < NB; ++kt) second_product<HD>(sV, 16 * kt, lane, sc[kt], oacc);
+    }
+    if (qi >= ql) return;
+    const float l = groups_sum(lsum);
+    const long long row = qrow0 + qi;
+    store_column<HD>(oacc, l > 0.f ? 1.0f / l : 0.f, (float*)a.o + row * a.ldo + h * hd, hd, g);      // (no keys: zero output)
+    if (g == 0) a.lse[(size_t)h * a.lse_stride + row] = (m + log2f(l)) * kLn2F;
+}
+
+// ---------------------------------------------------------------- backward: dQ
+template <int HD>
+__global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
+    typedef F32Tile<HD> Tile;
+    constexpr int KT = Tile::ROWS;
+    __shared__ __attribute__((aligned(16))) float sK[Tile::FLOATS];
+    __shared__ __attribute__((aligned(16))) float sV[Tile::FLOATS];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4;
+    const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 64;
+    const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
+    if (q0 >= ql) return;
+    const long long qrow0 = a.q_row[s], krow0 = a.k_row[s];
+    const float* K = (const float*)a.k + krow0 * a.ldk + h * hd;
+    const float* V = (const float*)a.v + krow0 * a.ldv + h * hd;
+    const int qw0 = q0 + wave * 16, qi = qw0 + (lane & 15), qi_c = qi < ql ? qi : ql - 1;
+    float4 qf[HD / 16], dof[HD / 16];
+    load_column<HD>((const float*)a.q + (qrow0 + qi_c) * a.ldq + h * hd, hd, g, qf);
+    load_column<HD>((const float*)a.d_o + (qrow0 + qi_c) * a.ldo + h * hd, hd, g, dof);
+    const float lse2 = a.lse[(size_t)h * a.lse_stride + qrow0 + qi_c] * kLog2eF;
+    const float delta = a.delta[(size_t)h * a.lse_stride + qrow0 + qi_c];
+    const float c = a.scale * kLog2eF;
+    f32x4_t gacc[HD / 16];
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt) gacc[dt] = zero4();
+    const int kv_end = a.mask ? min(kl, q0 + 64) : kl;
+    const int wave_last = a.mask ? min(kl - 1, qw0 + 15) : kl - 1;
+    Tile tk, tv;
+    if (kv_end > 0) {
+        tk.load(K, a.ldk, 0, kl, hd, t);
+        tv.load(V, a.ldv, 0, kl, hd, t);
+    }
+    for (int k0 = 0; k0 < kv_end; k0 += KT) {
+        __syncthreads();
+        tk.store(sK, t);
+        tv.store(sV, t);
+        __syncthreads();
+        if (k0 + KT < kv_end) {
+            tk.load(K, a.ldk, k0 + KT, kl, hd, t);
+            tv.load(V, a.ldv, k0 + KT, kl, hd, t);
+        }
+        if (qw0 >= ql) continue;
+#pragma unroll
+        for (int kt = 0; kt < KT / 16; ++kt) {
+            if (k0 + 16 * kt > wave_last) break;
+            f32x4_t ds = first_product<HD>(sK, 16 * kt, lane, qf);
+            const f32x4_t dp = first_product<HD>(sV, 16 * kt, lane, dof);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int key = k0 + 16 * kt + 4 * g + e;
+                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(ds[e], c, -lse2));
+                ds[e] = (key >= kl || (a.mask && key > qi)) ? 0.f : p * (dp[e] - delta);
+            }
+            second_product<HD>(sK, 16 * kt, lane, ds, gacc);
+        }
+    }
+    if (qi < ql) store_column<HD>(gacc, a.scale, (float*)a.dq + (qrow0 + qi) * a.ldq + h * hd, hd, g);
+}
+
+// ---------------------------------------------------------------- backward: dK, dV
+// Eight wavefronts: the first key blocks of a long causal sequence meet every query, and their work-groups set the
+// kernel's length.  Wavefronts w and w + 4 own the same 16 keys and take alternate 16-query blocks of every tile; their
+// accumulators are added through LDS at the end.  116 us with four wavefronts, 107 with eight, 86 with at most 128
+// registers (head size up to 64: two work-groups per CU; the other two kernels spill at 128 and lose).
+template <int HD>
+__global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel(AttnArgs a) {
+    typedef F32Tile<HD, 512> Tile;
+    constexpr int QT = Tile::ROWS;
+    __shared__ __attribute__((aligned(16))) float smem[2 * Tile::FLOATS];
+    static_assert(2 * Tile::FLOATS >= HD / 16 * 4 * 256, "one set of accumulators fits in the tiles");
+    float* sQ = smem;
+    float* sO = smem + Tile::FLOATS;
+    __shared__ __attribute__((aligned(16))) float s_lse[QT], s_delta[QT];
+    const int t = threadIdx.x, lane = t & 63, wave = (t >> 6) & 3, half = t >> 8, g = lane >> 4;
+    const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, k0 = blockIdx.x * 64;
+    const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
+    if (k0 >= kl) return;
+    const long long qrow0 = a.q_row[s], krow0 = a.k_row[s];
+    const float* Q = (const float*)a.q + qrow0 * a.ldq + h * hd;
+    const float* dO = (const float*)a.d_o + qrow0 * a.ldo + h * hd;
+    const float* lse = a.lse + (size_t)h * a.lse_stride + qrow0;
+    const float* delta = a.delta + (size_t)h * a.lse_stride + qrow0;
+    const int kw0 = k0 + wave * 16, ki = kw0 + (lane & 15), ki_c = ki < kl ? ki : kl - 1;
+    float4 kf[HD / 16], vf[HD / 16];
+    load_column<HD>((const float*)a.k + (krow0 + ki_c) * a.ldk + h * hd, hd, g, kf);
+    load_column<HD>((const float*)a.v + (krow0 + ki_c) * a.ldv + h * hd, hd, g, vf);
+    const float c = a.scale * kLog2eF;
+    f32x4_t dkacc[HD / 16], dvacc[HD / 16];
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt) { dkacc[dt] = zero4(); dvacc[dt] = zero4(); }
+    const int q_begin = a.mask ? k0 : 0;                              // causal: only queries at or after the key see it
+    Tile tq, to;
+    float lse_r = 0.f, delta_r = 0.f;
+    auto fetch = [&](int q0) {
+        tq.load(Q, a.ldq, q0, ql, hd, t);
+        to.load(dO, a.ldo, q0, ql, hd, t);
+        const bool in = t < QT && q0 + t < ql;
+        lse_r = in ? lse[q0 + t] * kLog2eF : 0.f;
+        delta_r = in ? delta[q0 + t] : 0.f;
+    };
+    if (q_begin < ql) fetch(q_begin);
+    for (int q0 = q_begin; q0 < ql; q0 += QT) {
+        __syncthreads();
+        tq.store(sQ, t);
+        to.store(sO, t);
+        if (t < QT) { s_lse[t] = lse_r; s_delta[t] = delta_r; }
+        __syncthreads();
+        if (q0 + QT < ql) fetch(q0 + QT);
+        if (kw0 >= kl) continue;
+#pragma unroll
+        for (int qt2 = 0; qt2 < QT / 32; ++qt2) {
+            const int qt = 2 * qt2 + half;
+            const int qb = q0 + 16 * qt;
+            if (qb >= ql || (a.mask && qb + 15 < kw0)) continue;      // no visible query
+            f32x4_t p = first_product<HD>(sQ, 16 * qt, lane, kf);
+            f32x4_t ds = first_product<HD>(sO, 16 * qt, lane, vf);
+            const float4 l4 = *reinterpret_cast<const float4*>(s_lse + 16 * qt + 4 * g);
+            const float4 d4 = *reinterpret_cast<const float4*>(s_delta + 16 * qt + 4 * g);
+            const float lq[4] = {l4.x, l4.y, l4.z, l4.w}, dq[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int q = qb + 4 * g + e;
+                const bool out = q >= ql || (a.mask && q < ki);
+                p[e] = out ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(p[e], c, -lq[e]));
+                ds[e] = p[e] * (ds[e] - dq[e]);
+            }
+            second_product<HD>(sO, 16 * qt, lane, p, dvacc);
+            second_product<HD>(sQ, 16 * qt, lane, ds, dkacc);
+        }
+    }
+    f32x4_t* part = reinterpret_cast<f32x4_t*>(smem);                 // [HD / 16][256], dK then dV
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        f32x4_t (&acc)[HD / 16] = pass ? dvacc : dkacc;
+        __syncthreads();
+        if (half == 1) {
+#pragma unroll
+            for (int dt = 0; dt < HD / 16; ++dt) part[dt * 256 + (t & 255)] = acc[dt];
+        }
+        __syncthreads();
+        if (half == 0) {
+#pragma unroll
+            for (int dt = 0; dt < HD / 16; ++dt) acc[dt] += part[dt * 256 + t];
+        }
+    }
+    if (half == 1 || ki >= kl) return;
+    store_column<HD>(dkacc, a.scale, (float*)a.dk + (krow0 + ki) * a.ldk + h * hd, hd, g);
+    store_column<HD>(dvacc, 1.0f, (float*)a.dv + (krow0 + ki) * a.ldv + h * hd, hd, g);
+}
+
+template <int HD>
+ds_status bwd_f32(const AttnArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<HD>, dim3((a.max_q_len + 63) / 64, a.n_heads, a.n_seq), dim3(256), 0, st, a);
+    DS_LAUNCH_CHECK();
+    hipLaunchKernelGGL(attn_bwd_dkv_f32_kernel<HD>, dim3((a.max_k_len + 63) / 64, a.n_heads, a.n_seq), dim3(512), 0, st, a);
+    DS_LAUNCH_CHECK();
+    return DS_OK;
+}
+
+}  // namespace
+
+// What the float4 accesses need; everything else (strides not a multiple of 4, unaligned tensors) keeps the generic kernels.
+bool attn_f32_mfma_supported(const AttnArgs& a) {
+    if (a.dtype != DS_DTYPE_F32) return false;
+    if (a.ldq % 4 || a.ldk % 4 || a.ldv % 4 || a.ldo % 4) return false;
+    auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+    if (!al(a.q) || !al(a.k) || !al(a.v) || !al(a.o)) return false;
+    return !a.d_o || (al(a.d_o) && al(a.dq) && al(a.dk) && al(a.dv));
+}
+
+ds_status attn_fwd_f32_mfma(const AttnArgs& a, hipStream_t st) {
+    const dim3 grid((a.max_q_len + 63) / 64, a.n_heads, a.n_seq);
+    if (a.head_dim <= 32) hipLaunchKernelGGL(attn_fwd_f32_kernel<32>, grid, dim3(256), 0, st, a);
+    else if (a.head_dim <= 64) hipLaunchKernelGGL(attn_fwd_f32_kernel<64>, grid, dim3(256), 0, st, a);
+    else if (a.head_dim <= 96) hipLaunchKernelGGL(attn_fwd_f32_kernel<96>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(attn_fwd_f32_kernel<128>, grid, dim3(256), 0, st, a);
+    DS_LAUNCH_CHECK();
+    return DS_OK;
+}
+
+// (a.delta is complete: attn_delta runs in front)
+ds_status attn_bwd_f32_mfma(const AttnArgs& a, hipStream_t st) {
+    if (a.head_dim <= 32) return bwd_f32<32>(a, st);
+    if (a.head_dim <= 64) return bwd_f32<64>(a, st);
+    if (a.head_dim <= 96) return bwd_f32<96>(a, st);
+    return bwd_f32<128>(a, st);
+}

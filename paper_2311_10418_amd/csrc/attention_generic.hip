@@ -1,5 +1,5 @@
 // Variable-length attention, generic kernels (any dtype, head_dim <= 128, multiple of 8): the
-// fp32 path and the fallback for shapes the MFMA kernels do not take.  One 64-lane wavefront
+// fallback for the shapes and alignments the matrix-core kernels (bf16 and fp32) do not take.  One 64-lane wavefront
 // per query row (forward, dQ) or per key row (dK/dV); no work is spent on padding because the
 // kernels walk the sequence table, never the padded tensor.
 #include "attention.hpp"

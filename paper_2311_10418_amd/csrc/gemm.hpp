@@ -22,3 +22,8 @@ inline size_t gemm_colsum_rows(int32_t M) { return (size_t)((M + 255) / 256) * 2
 ds_status launch_gemm(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B,
                       void* C, int32_t epilogue, const GemmEpi& p, bool force_generic, float* split_ws,
                       size_t split_ws_floats, hipStream_t st);
+
+// fp32 on the matrix cores (gemm_f32.hip): whether it takes the operands, and its launcher (checked arguments)
+bool gemm_f32_mfma_supported(int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B);
+ds_status launch_gemm_f32_mfma(int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B, void* C,
+                               int32_t epilogue, const GemmEpi& p, float* split_ws, size_t split_ws_floats, hipStream_t st);

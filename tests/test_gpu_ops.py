@@ -473,3 +473,69 @@ def test_mfma_probe_runs_and_is_deterministic():
     assert np.count_nonzero(to_np(sink)) == 0
     with pytest.raises(ds.DsError):
         ds.ds_mfma_probe(ops, sink, 0, 3)
+
+
+@pytest.mark.parametrize("form,M,N,K,use_ws", [
+    ("nn", 1, 8, 4, False), ("nn", 65, 72, 36, False), ("nn", 300, 1032, 132, False), ("nn", 129, 264, 4100, True),
+    ("nt", 64, 64, 32, False), ("nt", 63, 200, 100, False), ("nt", 4200, 1032, 64, False),       # the last: 128-row tiles
+    ("tn", 4, 8, 1, False), ("tn", 68, 200, 31, False), ("tn", 256, 256, 7684, True), ("tn", 260, 520, 129, True)])
+def test_gemm_f32_matrix_cores(form, M, N, K, use_ws):
+    """Edges of the 64 / 128-row and 64-column tiles, of the 32-deep K tiles and of the split contraction, against float64."""
+    rng = np.random.default_rng(31)
+    ta, tb = form == "tn", form == "nt"
+    A, B = _rnd(rng, (K, M) if ta else (M, K), F32), _rnd(rng, (N, K) if tb else (K, N), F32)
+    bias, R = _rnd(rng, (N,), F32), _rnd(rng, (M, N), F32)
+    acc = (A.T if ta else A).astype(np.float64) @ (B.T if tb else B).astype(np.float64)
+    dA, dB, db, dR = (to_dev(x, F32) for x in (A, B, bias, R))
+    c, c2 = (torch.full((M, N), 3.0, dtype=F32, device=DEV) for _ in range(2))
+    kw = dict(trans_a=ta, trans_b=tb, workspace=_ws(1 << 22) if use_ws else None)
+    # fp32 sums of K products in any order: K 2^-24 relative to the sum of magnitudes, about sqrt(K) 2^-24 of the result
+    tol = 1e-5
+    ds.ds_gemm(dA, dB, c, M, N, K, bias=db, **kw)
+    torch.cuda.synchronize()
+    assert both_err(to_np(c), acc + bias) <= tol
+    ds.ds_gemm(dA, dB, c, M, N, K, epilogue=ds.DS_EPI_ACC32, accumulate=False, **kw)
+    ds.ds_gemm(dA, dB, c, M, N, K, epilogue=ds.DS_EPI_ACC32, accumulate=True, **kw)
+    torch.cuda.synchronize()
+    assert both_err(to_np(c), 2 * acc) <= tol
+    ds.ds_gemm(dA, dB, c, M, N, K, epilogue=ds.DS_EPI_RESID, R=dR, bias=db, **kw)
+    torch.cuda.synchronize()
+    assert both_err(to_np(c), acc + bias + R) <= tol
+    ds.ds_gemm(dA, dB, c, M, N, K, epilogue=ds.DS_EPI_DGATE, R=dR, R2=dR, C2=c2, **kw)
+    torch.cuda.synchronize()
+    Rd = R.astype(np.float64)
+    assert both_err(to_np(c), acc * Rd * ost.gelu_grad(Rd)) <= tol and both_err(to_np(c2), acc * ost.gelu(Rd)) <= tol
+
+
+@pytest.mark.parametrize("hd,causal", [(8, True), (24, False), (32, True), (40, True), (64, True), (64, False), (96, True), (128, True), (128, False)])
+def test_attention_f32_matrix_cores(hd, causal):
+    """Every padded head size (32, 64, 96, 128) and lengths on both sides of the 16-column, 32- / 64-row tile edges."""
+    rng = np.random.default_rng(32)
+    h = 2
+    lens = [1, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 200, 333]
+    d, T, rows, qkv, d_o = _varlen_case(rng, lens, h, hd, F32)
+    dq, ddo = to_dev(qkv, F32), to_dev(d_o, F32)
+    o, lse, delta = torch.zeros((T, d), device=DEV), torch.zeros((h, T), device=DEV), torch.zeros((h, T), device=DEV)
+    dqkv = torch.zeros((T, 3 * d), device=DEV)
+    order = rng.permutation(len(lens))
+    t_rows = torch.from_numpy(np.ascontiguousarray(rows[order])).to(DEV)
+    t_lens = torch.tensor([lens[i] for i in order], dtype=torch.int32, device=DEV)
+    b, gb, table = dq.data_ptr(), dqkv.data_ptr(), (t_rows, t_lens, t_rows, t_lens)
+    ds.ds_attention_fwd(b, b + 4 * d, b + 8 * d, o, lse, *table, h, hd, causal, max(lens), max(lens), 3 * d, 3 * d, 3 * d, d, T)
+    ds.ds_attention_bwd(b, b + 4 * d, b + 8 * d, o, ddo, lse, delta, gb, gb + 4 * d, gb + 8 * d, *table, h, hd, causal,
+                        max(lens), max(lens), 3 * d, 3 * d, 3 * d, d, T)
+    torch.cuda.synchronize()
+    o_np, g_np, lse_np = to_np(o), to_np(dqkv), to_np(lse)
+    touched = np.zeros(T, dtype=bool)
+    for r0, l in zip(rows, lens):
+        x = qkv[r0:r0 + l].astype(np.float64)
+        q, k, v = x[:, :d], x[:, d:2 * d], x[:, 2 * d:]
+        ref_o, cache = ost.attention_fwd(q, k, v, h, causal)
+        refs = ost.attention_bwd(d_o[r0:r0 + l].astype(np.float64), cache)
+        assert both_err(o_np[r0:r0 + l], ref_o) <= TOL[F32], (l, "o")
+        for i, ref in enumerate(refs):
+            assert both_err(g_np[r0:r0 + l, i * d:(i + 1) * d], ref) <= TOL[F32], (l, "dq dk dv"[3 * i:3 * i + 2])
+        s = (q[-1, -hd:] @ k[:, -hd:].T) / np.sqrt(hd)                     # last head, last row: sees every key
+        assert abs(lse_np[-1, r0 + l - 1] - np.log(np.exp(s - s.max()).sum()) - s.max()) <= 1e-5
+        touched[r0:r0 + l] = True
+    assert np.all(o_np[~touched] == 0) and np.all(g_np[~touched] == 0)
