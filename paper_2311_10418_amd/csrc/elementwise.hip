@@ -255,7 +255,7 @@ __global__ __launch_bounds__(64 * NW) void norm_fwd_multi_kernel(int rows, int d
 
 // ------------------------------------------------------------------ norm backward
 // dx = resid + rstd * (dy*g - mean(dy*g) - xhat * mean(dy*g*xhat))    (RMS: no mean(dy*g) term)
-// partial[w][0][:] = sum over the rows wave w handled of dy*xhat, partial[w][1][:] = sum of dy.
+// partial[b][0][:] = sum over the rows work-group b handled of dy*xhat, partial[b][1][:] = sum of dy.
 template <class T, bool RMS, int NI>
 __global__ __launch_bounds__(256) void norm_bwd_kernel(int rows, int d, const T* __restrict__ dy, const T* __restrict__ x,
                                                        const T* __restrict__ g, const float* __restrict__ stats,
@@ -317,15 +317,28 @@ __global__ __launch_bounds__(256) void norm_bwd_kernel(int rows, int d, const T*
             }
         }
     }
-    float* p0 = partial + (size_t)gw * 2 * d;
+    // the four wavefronts' sums are added here, so that one partial row per work-group is left to the second kernel
+    __shared__ __attribute__((aligned(16))) float red[4][64 * 8];
+    float* p0 = partial + (size_t)blockIdx.x * 2 * d;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int col = (lane + 64 * i) * 8;
-        if (col < d) {
-            Vec8<float>::store(p0 + col, dg[i]);
-            if (!RMS) Vec8<float>::store(p0 + d + col, db[i]);
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int k = 0; k < (RMS ? 1 : 2); ++k) {
+            Vec8<float>::store(&red[wave][lane * 8], k ? db[i] : dg[i]);
+            __syncthreads();
+            const int c = threadIdx.x * 2, col = 64 * 8 * i + c;
+            if (col < d) {
+                float2 v = *reinterpret_cast<const float2*>(&red[0][c]);
+#pragma unroll
+                for (int w = 1; w < 4; ++w) {
+                    const float2 x = *reinterpret_cast<const float2*>(&red[w][c]);
+                    v.x += x.x;
+                    v.y += x.y;
+                }
+                *reinterpret_cast<float2*>(p0 + (size_t)k * d + col) = v;
+            }
+            __syncthreads();
         }
-    }
 }
 
 // Wide rows (d > 1024): one row per group of NW = 2 or 4 wavefronts (one work-group), each owning d / NW of the
@@ -414,39 +427,66 @@ __global__ __launch_bounds__(64 * NW) void norm_bwd_multi_kernel(int rows, int d
     }
 }
 
-// out[c] = (accumulate ? out[c] : 0) + sum_p partial[p * stride + c];  block = 32 columns x 8 row lanes
+// out[c] = (accumulate ? out[c] : 0) + sum_p partial[p * stride + c].  A work-group owns 32 columns: 8 lanes of float4 (one
+// 128-byte line per partial row) by NT / 8 row lanes, four rows in flight per lane; a wavefront folds its 8 row lanes
+// with shuffles, the wavefronts meet in LDS.  Fixed order of additions for a given (n_partial, n).
 // blockIdx.y = 1 (when launched with two rows of blocks) reduces a second set of partials into out2.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(int n_partial, int n, size_t stride,
-                                                              const float* __restrict__ partial,
-                                                              float* __restrict__ out, int accumulate,
-                                                              const float* __restrict__ partial2 = nullptr,
-                                                              float* __restrict__ out2 = nullptr) {
-    __shared__ float red[8][33];
+// What bounds it is the latency of the chain of loads, not the bytes: with 8 row lanes of single floats, as before, a sum
+// of 2048 rows of 256 columns (512 loads one after another, on 8 work-groups) took 22 us.
+template <int NT>
+__global__ __launch_bounds__(NT) void reduce_partials_kernel(int n_partial, int n, size_t stride,
+                                                             const float* __restrict__ partial,
+                                                             float* __restrict__ out, int accumulate,
+                                                             const float* __restrict__ partial2, float* __restrict__ out2) {
+    constexpr int RL = NT / 8;
+    __shared__ float red[NT / 64][32];
     if (blockIdx.y == 1) {
         partial = partial2;
         out = out2;
     }
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int col = blockIdx.x * 32 + tx;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+    const int cx = threadIdx.x & 7, ry = threadIdx.x >> 3;
+    const int col = blockIdx.x * 32 + cx * 4;                         // n is a multiple of 8
+    f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0, s3 = s0;
     if (col < n) {
-        int p = ty;
-        for (; p + 24 < n_partial; p += 32) {
-            s0 += partial[(size_t)p * stride + col];
-            s1 += partial[(size_t)(p + 8) * stride + col];
-            s2 += partial[(size_t)(p + 16) * stride + col];
-            s3 += partial[(size_t)(p + 24) * stride + col];
+        const float* src = partial + col;
+        int p = ry;
+        for (; p + 3 * RL < n_partial; p += 4 * RL) {
+            s0 += *reinterpret_cast<const f32x4_t*>(src + (size_t)p * stride);
+            s1 += *reinterpret_cast<const f32x4_t*>(src + (size_t)(p + RL) * stride);
+            s2 += *reinterpret_cast<const f32x4_t*>(src + (size_t)(p + 2 * RL) * stride);
+            s3 += *reinterpret_cast<const f32x4_t*>(src + (size_t)(p + 3 * RL) * stride);
         }
-        for (; p < n_partial; p += 8) s0 += partial[(size_t)p * stride + col];
+        for (; p < n_partial; p += RL) s0 += *reinterpret_cast<const f32x4_t*>(src + (size_t)p * stride);
     }
-    red[ty][tx] = (s0 + s1) + (s2 + s3);
+    s0 = (s0 + s1) + (s2 + s3);
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s0[e] += __shfl_xor(s0[e], o, 64);
+    if ((threadIdx.x & 63) < 8) *reinterpret_cast<f32x4_t*>(&red[threadIdx.x >> 6][cx * 4]) = s0;
     __syncthreads();
-    if (ty == 0 && col < n) {
+    const int c = blockIdx.x * 32 + threadIdx.x;
+    if (threadIdx.x < 32 && c < n) {
         float s = 0.f;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) s += red[k][tx];
-        out[col] = accumulate ? out[col] + s : s;
+        for (int k = 0; k < NT / 64; ++k) s += red[k][threadIdx.x];
+        out[c] = accumulate ? out[c] + s : s;
     }
+}
+
+// out2 != nullptr: a second set of partials (same count and stride) is reduced into it by the same launch.
+// wide: work-groups of 1024 threads for long sums.  Not for column sums, which may run beside a GEMM on another stream: a
+// resident GEMM work-group leaves registers for one small wavefront per SIMD, not for four, and a wide work-group would
+// wait for it to end (380 us instead of 15 at 65 536 tokens).
+ds_status reduce_launch(int n_partial, int n, size_t stride, const float* partial, float* out, int accumulate,
+                        const float* partial2, float* out2, bool wide, hipStream_t st) {
+    const dim3 grid((n + 31) / 32, out2 ? 2 : 1);
+    if (wide && n_partial > 256)
+        hipLaunchKernelGGL(reduce_partials_kernel<1024>, grid, dim3(1024), 0, st, n_partial, n, stride, partial, out, accumulate, partial2, out2);
+    else
+        hipLaunchKernelGGL(reduce_partials_kernel<256>, grid, dim3(256), 0, st, n_partial, n, stride, partial, out, accumulate, partial2, out2);
+    DS_LAUNCH_CHECK();
+    return DS_OK;
 }
 
 // ------------------------------------------------------------------ column sums
@@ -460,7 +500,17 @@ __global__ __launch_bounds__(256) void colsum_kernel(int rows, int n, const T* _
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
     if (col < n) {
-        for (int r = blockIdx.y * 4 + ty; r < rows; r += gridDim.y * 4) {
+        // four rows in flight per wavefront
+        const int step = gridDim.y * 4;
+        int r = blockIdx.y * 4 + ty;
+        for (; r < rows - 3 * step; r += 4 * step) {
+            float v[4][8];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) Vec8<T>::load(x + (size_t)(r + k * step) * n + col, v[k]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += (v[0][j] + v[1][j]) + (v[2][j] + v[3][j]);
+        }
+        for (; r < rows; r += step) {
             float v[8];
             Vec8<T>::load(x + (size_t)r * n + col, v);
 #pragma unroll
@@ -501,15 +551,15 @@ ds_status norm_bwd_dispatch(int rows, int d, const T* dy, const T* x, const T* g
                             T* dx, float* dg, float* db, float* partial, int accumulate, hipStream_t st) {
     const int ni = (d + 511) / 512;
     if (ni > 2 && d % 32 == 0) {                 // wide rows: two or four wavefronts per row (see norm_bwd_multi_kernel)
-        const int np = rows < kPartialRows ? rows : kPartialRows;
+        // a group's partial row (8 d bytes) is as much traffic as a bf16 row of all four tensors: beyond 1024 groups (four
+        // per CU) each takes at least four rows
+        int np = rows / 4 > 1024 ? rows / 4 : (rows < 1024 ? rows : 1024);
+        if (np > kPartialRows) np = kPartialRows;
         if (ni > 4) hipLaunchKernelGGL((norm_bwd_multi_kernel<T, RMS, 2, 4>), dim3(np), dim3(256), 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
         else hipLaunchKernelGGL((norm_bwd_multi_kernel<T, RMS, 2, 2>), dim3(np), dim3(128), 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
         DS_LAUNCH_CHECK();
         // dgamma and, for LayerNorm, dbeta in one launch
-        hipLaunchKernelGGL(reduce_partials_kernel, dim3((d + 31) / 32, RMS ? 1 : 2), dim3(256), 0, st, np, d, (size_t)2 * d, partial, dg,
-                           accumulate, (const float*)(partial + d), db);
-        DS_LAUNCH_CHECK();
-        return DS_OK;
+        return reduce_launch(np, d, (size_t)2 * d, partial, dg, accumulate, partial + d, RMS ? nullptr : db, true, st);
     }
     int nblk = (rows + 3) / 4;
     if (nblk > kPartialRows / 4) nblk = kPartialRows / 4;
@@ -519,11 +569,7 @@ ds_status norm_bwd_dispatch(int rows, int d, const T* dy, const T* x, const T* g
     else if (ni <= 4) hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 4>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
     else hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 8>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
     DS_LAUNCH_CHECK();
-    const int np = nblk * 4;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((d + 31) / 32, RMS ? 1 : 2), dim3(256), 0, st, np, d, (size_t)2 * d, partial, dg,
-                       accumulate, (const float*)(partial + d), db);
-    DS_LAUNCH_CHECK();
-    return DS_OK;
+    return reduce_launch(nblk, d, (size_t)2 * d, partial, dg, accumulate, partial + d, RMS ? nullptr : db, true, st);
 }
 
 }  // namespace
@@ -618,17 +664,14 @@ extern "C" ds_status ds_norm_bwd(int32_t dtype, int32_t rms, int32_t rows, int32
 ds_status launch_reduce_partials(int32_t n_partial, int32_t n, const float* partial, float* out, int32_t accumulate,
                                  hipStream_t st) {
     if (n_partial <= 0 || n <= 0 || !partial || !out) return DS_EINVAL;
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((n + 31) / 32), dim3(256), 0, st, n_partial, n, (size_t)n, partial, out, accumulate,
-                       (const float*)nullptr, (float*)nullptr);
-    DS_LAUNCH_CHECK();
-    return DS_OK;
+    return reduce_launch(n_partial, n, (size_t)n, partial, out, accumulate, nullptr, nullptr, false, st);
 }
 
 // Column sums in two kernels: gy partial rows of n floats each (gy <= max_partial_rows), then their sum in a fixed order.
 static ds_status colsum_launch(int32_t dtype, int32_t rows, int32_t n, const void* x, float* out, float* partial,
                                int max_partial_rows, int32_t accumulate, hipStream_t st) {
     const int gx = (n / 8 + 63) / 64;
-    int gy = (rows + 3) / 4;
+    int gy = (rows + 31) / 32;                      // 32 rows per work-group: fewer partial rows than data by as much
     int cap = kPartialRows / gx > 0 ? kPartialRows / gx : 1;
     if (cap > max_partial_rows) cap = max_partial_rows;
     if (gy > cap) gy = cap;
@@ -637,10 +680,7 @@ static ds_status colsum_launch(int32_t dtype, int32_t rows, int32_t n, const voi
     else
         hipLaunchKernelGGL(colsum_kernel<float>, dim3(gx, gy), dim3(256), 0, st, rows, n, (const float*)x, partial);
     DS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((n + 31) / 32), dim3(256), 0, st, gy, n, (size_t)n, partial, out, accumulate,
-                       (const float*)nullptr, (float*)nullptr);
-    DS_LAUNCH_CHECK();
-    return DS_OK;
+    return reduce_launch(gy, n, (size_t)n, partial, out, accumulate, nullptr, nullptr, false, st);
 }
 
 extern "C" ds_status ds_colsum(int32_t dtype, int32_t rows, int32_t n, const void* x, float* out, float* partial,

@@ -539,3 +539,63 @@ def test_attention_f32_matrix_cores(hd, causal):
         assert abs(lse_np[-1, r0 + l - 1] - np.log(np.exp(s - s.max()).sum()) - s.max()) <= 1e-5
         touched[r0:r0 + l] = True
     assert np.all(o_np[~touched] == 0) and np.all(g_np[~touched] == 0)
+
+
+@pytest.mark.parametrize("dt", [F32, BF])
+@pytest.mark.parametrize("rows,n", [(1, 8), (31, 264), (33, 2048), (128, 520), (4097, 256), (9000, 4104)])
+def test_column_reductions_at_their_edges(dt, rows, n):
+    """One to many partial rows (32 rows per work-group, four in flight; both widths of the second kernel), added to what is
+    there.  Sums of at most 9000 fp32 values: 1e-5."""
+    rng = np.random.default_rng(33)
+    x = _rnd(rng, (rows, n), dt)
+    xd = to_dev(x, dt)
+    partial = torch.empty(2048 * max(n, 1024), device=DEV)
+    out = torch.full((n,), 2.0, device=DEV)
+    ds.ds_colsum(xd, out, partial, accumulate=True)
+    torch.cuda.synchronize()
+    assert both_err(to_np(out), x.astype(np.float64).sum(0) + 2.0) <= 1e-5
+    if n <= 4096:
+        for rms in (False, True):
+            dy, g = _rnd(rng, (rows, n), dt), (1.0 + _rnd(rng, (n,), F32, 0.02)).astype(np.float32)
+            b = _rnd(rng, (n,), dt, 0.02)
+            g = wl.to_bf16_grid(g) if dt == BF else g
+            dyd, gd, bd = to_dev(dy, dt), to_dev(g, dt), to_dev(b, dt)
+            y, dx, stats = torch.empty_like(xd), torch.empty_like(xd), torch.empty(2, rows, device=DEV)
+            dg, db = torch.full((n,), 3.0, device=DEV), torch.full((n,), 4.0, device=DEV)
+            part = torch.empty(ds.ds_norm_bwd_scratch_floats(rows, n), device=DEV)
+            ds.ds_norm_fwd(xd, gd, None if rms else bd, y, stats, rms=rms)
+            ds.ds_norm_bwd(dyd, xd, gd, stats, None, dx, dg, db, part, rms=rms, accumulate=True)
+            torch.cuda.synchronize()
+            x64, dy64 = x.astype(np.float64), dy.astype(np.float64)
+            c = x64 if rms else x64 - x64.mean(1, keepdims=True)
+            xh = c / np.sqrt((c * c).mean(1, keepdims=True) + (1e-6 if rms else 1e-5))
+            assert both_err(to_np(dg), (dy64 * xh).sum(0) + 3.0) <= 1e-5
+            if not rms:
+                assert both_err(to_np(db), dy64.sum(0) + 4.0) <= 1e-5
+
+
+def test_attention_worklist_many_sequences():
+    """More sequences than threads of the list kernel, every length class present, empty ones among them: every block of
+    every sequence is visited once (the outputs are complete), on the query and on the key side."""
+    rng = np.random.default_rng(34)
+    h, hd, n = 1, 64, 2300
+    lens = rng.integers(0, 40, n).astype(np.int32)
+    lens[rng.integers(0, n, 40)] = rng.integers(100, 1400, 40)
+    rows = np.cumsum(lens) - lens
+    T, d = int(lens.sum()), h * hd
+    qkv, d_o = to_dev(_rnd(rng, (T, 3 * d), BF), BF), to_dev(_rnd(rng, (T, d), BF), BF)
+    table = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(DEV) for a in (rows, lens, rows, lens)]
+    res = []
+    for force in (False, True):
+        o, lse, delta = torch.full((T, d), 7.0, dtype=BF, device=DEV), torch.zeros((h, T), device=DEV), torch.zeros((h, T), device=DEV)
+        g = torch.full((T, 3 * d), 7.0, dtype=BF, device=DEV)
+        scratch = torch.zeros(ds.ds_attention_scratch_bytes(h, hd, T, T, n), dtype=torch.uint8, device=DEV)
+        b, gb = qkv.data_ptr(), g.data_ptr()
+        ds.ds_attention_fwd(b, b + 2 * d, b + 4 * d, o, lse, *table, h, hd, True, 1400, 1400, 3 * d, 3 * d, 3 * d, d, T,
+                            scratch=scratch, force_generic=force)
+        ds.ds_attention_bwd(b, b + 2 * d, b + 4 * d, o, d_o, lse, delta, gb, gb + 2 * d, gb + 4 * d, *table, h, hd, True, 1400, 1400,
+                            3 * d, 3 * d, 3 * d, d, T, scratch=scratch, force_generic=force)
+        torch.cuda.synchronize()
+        res.append((to_np(o), to_np(g)))
+    for got, ref in zip(*res):
+        assert both_err(got, ref) <= TOL[BF]
