@@ -175,7 +175,8 @@ __device__ __forceinline__ void store_cols(const f32x16_t (&acc)[HD / 32], float
 }
 
 // ------------------------------------------------------------------------------------ work lists
-// items[0 .. n): the (sequence, block) pairs of `block` rows each; n is written to *n_items.  One work-group.
+// items[0 .. n): the (sequence, block) pairs of `block` rows each; n is written to *n_items.  One work-group per
+// list: blockIdx.x = 0 the query side, 1 (when launched) the key side.
 // Order: sequences by descending trip count of their longest block (a block's trip count = the number of
 // 64-row steps its work-group takes), the blocks of one sequence next to each other, longest first.  The
 // grids walk the list with heads fastest and the hardware deals consecutive work-groups round-robin to the
@@ -183,14 +184,21 @@ __device__ __forceinline__ void store_cols(const f32x16_t (&acc)[HD / 32], float
 // the same XCD at about the same time and streams the same K / V (or Q / dO) tiles: all but the first fetch
 // of a tile hit in that XCD's L2.  Long sequences still start first and the list ends with the shortest, so
 // the grid's tail stays fine-grained.
-__global__ __launch_bounds__(1024) void attn_worklist_kernel(int n_seq, const int32_t* __restrict__ own_len,
-                                                             const int32_t* __restrict__ other_len, int causal,
-                                                             int key_side, int max_items, int2* __restrict__ items,
-                                                             int32_t* __restrict__ n_items) {
+// The 1024 bins are summed by a scan over the wavefronts; one thread walking them took 10 of the kernel's 15 us.
+__global__ __launch_bounds__(1024) void attn_worklist_kernel(int n_seq, const int32_t* __restrict__ q_len,
+                                                             const int32_t* __restrict__ k_len, int causal,
+                                                             int max_items_q, int max_items_k, int2* __restrict__ items_q,
+                                                             int2* __restrict__ items_k, int32_t* __restrict__ n_items) {
     constexpr int NB = 1024;
     __shared__ int hist[NB];
     __shared__ int start[NB];
+    __shared__ int wave_total[NB / 64];
     const int tid = threadIdx.x;
+    const bool key_side = blockIdx.x != 0;
+    const int32_t* own_len = key_side ? k_len : q_len;
+    const int32_t* other_len = key_side ? q_len : k_len;
+    const int max_items = key_side ? max_items_k : max_items_q;
+    int2* items = key_side ? items_k : items_q;
     // trip count of the longest block of a sequence: the last query block (it sees every key up to its own
     // end), the first key block (every query from its own start on), any block when nothing is masked
     auto longest = [&](int own, int other) {
@@ -206,11 +214,19 @@ __global__ __launch_bounds__(1024) void attn_worklist_kernel(int n_seq, const in
         if (own > 0) atomicAdd(&hist[longest(own, other_len[s])], (own + 127) >> 7);
     }
     __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int b = NB - 1; b >= 0; --b) { start[b] = run; run += hist[b]; }
-        n_items[0] = min(run, max_items);
+    // start of a bin = items in all higher bins: thread tid owns bin NB - 1 - tid and needs the sum over the threads below
+    const int own_bin = hist[NB - 1 - tid];
+    int run = own_bin;                                                // inclusive within the wavefront
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(run, o, 64);
+        if ((tid & 63) >= o) run += x;
     }
+    if ((tid & 63) == 63) wave_total[tid >> 6] = run;
+    __syncthreads();
+    for (int w = 0; w < (tid >> 6); ++w) run += wave_total[w];
+    start[NB - 1 - tid] = run - own_bin;
+    if (tid == NB - 1) n_items[key_side ? 1 : 0] = min(run, max_items);
     __syncthreads();
     for (int s = tid; s < n_seq; s += NB) {
         const int own = own_len[s];
@@ -858,14 +874,9 @@ ds_status attn_prepare_lists(AttnArgs& a, bool need_key_side, hipStream_t st) {
     a.aug_lse = base + lists_bytes(a.q_total_rows, a.k_total_rows, a.n_seq);
     a.aug_delta = (char*)a.aug_lse + (size_t)a.n_heads * a.q_total_rows * 16;
     if (a.lists_ready) return DS_OK;
-    hipLaunchKernelGGL(attn_worklist_kernel, dim3(1), dim3(1024), 0, st, a.n_seq, a.q_len, a.k_len, a.mask, 0, a.max_items_q,
-                       (int2*)a.items_q, (int32_t*)base);
+    hipLaunchKernelGGL(attn_worklist_kernel, dim3(need_key_side || a.lists_want_both ? 2 : 1), dim3(1024), 0, st, a.n_seq, a.q_len,
+                       a.k_len, a.mask, a.max_items_q, a.max_items_k, (int2*)a.items_q, (int2*)a.items_k, (int32_t*)base);
     DS_LAUNCH_CHECK();
-    if (need_key_side || a.lists_want_both) {
-        hipLaunchKernelGGL(attn_worklist_kernel, dim3(1), dim3(1024), 0, st, a.n_seq, a.k_len, a.q_len, a.mask, 1, a.max_items_k,
-                           (int2*)a.items_k, (int32_t*)base + 1);
-        DS_LAUNCH_CHECK();
-    }
     return DS_OK;
 }
 
