@@ -14,6 +14,7 @@
 #include "gemm_epilogue.hpp"
 
 #include <atomic>
+#include <cmath>
 #include <mutex>
 
 
@@ -667,26 +668,6 @@ __global__ __launch_bounds__(1024) void tail_finish_sums_kernel(int M, int N, in
     }
 }
 
-// sum the split-K partials and apply the epilogue; one thread per 8 columns
-template <int EPI>
-__global__ __launch_bounds__(256) void splitk_finish_kernel(int M, int N, int splits, const float* __restrict__ ws,
-                                                            bf16_t* __restrict__ C, GemmEpi p) {
-    const long long total = (long long)M * (N / 8);
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-        const int m = (int)(i / (N / 8));
-        const int n = (int)(i - (long long)m * (N / 8)) * 8;
-        float v[8];
-        Vec8<float>::load(ws + (size_t)m * N + n, v);
-        for (int s = 1; s < splits; ++s) {
-            float w[8];
-            Vec8<float>::load(ws + ((size_t)s * M + m) * N + n, w);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] += w[j];
-        }
-        epilogue8<bf16_t, EPI>(m, n, N, v, C, p);
-    }
-}
-
 template <class T, int EPI>
 ds_status launch_generic(int ta, int tb, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p,
                          hipStream_t st) {
@@ -701,17 +682,8 @@ ds_status launch_generic(int ta, int tb, int M, int N, int K, const void* A, con
 
 // number of K splits of a weight-gradient GEMM: the fewest that bring the work-group count closest to a whole
 // number of rounds over the compute units (time ~ rounds x split length)
-static int cu_count() {
-    static int n_cu = 0;
-    if (n_cu == 0) {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-        n_cu = v;
-    }
-    return n_cu;
-}
 static int choose_splits(int tiles, int nt, int M, int N, size_t split_ws_floats) {
-    const int n_cu = cu_count();
+    const int n_cu = gemm_cu_count();
     int best = 1;
     double best_cost = 1e30;
     for (int sp = 1; sp <= 16; ++sp) {
@@ -723,6 +695,56 @@ static int choose_splits(int tiles, int nt, int M, int N, size_t split_ws_floats
         if (cost < best_cost - 1e-9) { best_cost = cost; best = sp; }
     }
     return best;
+}
+
+// How a launch of the 256 x 256 kernel divides its tiles: uniform splits (weight gradients), or whole tiles and a tail
+// whose K loops are cut into tail_splits pieces.
+struct BigPlan {
+    int tiles_m, tiles_n, nt;      // nt: K tiles as the kernel counts them (32-deep in the TN form, 64 in the NT form)
+    int splits, n_main, tail_splits;
+};
+static BigPlan plan_big(bool tnf, int epi, int M, int N, int K, size_t split_ws_floats) {
+    BigPlan b;
+    b.tiles_m = (M + BM - 1) / BM;
+    b.tiles_n = N / BN;
+    b.nt = tnf ? (K + NT_DK - 1) / NT_DK : K / 64;
+    const int tiles = b.tiles_m * b.tiles_n;
+    b.splits = epi == DS_EPI_ACC32 && split_ws_floats ? choose_splits(tiles, b.nt, M, N, split_ws_floats) : 1;
+    // tail split-K: the tiles beyond the last whole round over the compute units share that round; a launch with
+    // fewer tiles than compute units (small micro-batches) is all tail, so that the K loop is spread over the chip
+    b.n_main = tiles;
+    b.tail_splits = 1;
+    if (b.splits == 1 && split_ws_floats) {
+        const int n_cu = gemm_cu_count();
+        const int rem = tiles % n_cu;
+        if (rem > 0) {
+            int ts = n_cu / rem;
+            if (ts > 32) ts = 32;
+            if (ts > b.nt / 4) ts = b.nt / 4;
+            while (ts > 1 && (size_t)rem * ts * (BM * BN) > split_ws_floats) --ts;
+            if (ts > 1) {
+                const int per = (b.nt + ts - 1) / ts;
+                ts = (b.nt + per - 1) / per;                    // every split owns at least one K tile
+            }
+            if (ts > 1) { b.n_main = tiles - rem; b.tail_splits = ts; }
+        }
+    }
+    return b;
+}
+
+// Estimated time of that plan in microseconds (see gemm_tile.hip for the other side of the comparison and the fit): 1.15
+// per 64-deep K tile of a 256 x 256 tile and 4 around it, per round over the compute units; 0.1 per piece of partial sums
+// (256 KB written and read back) and 4 for the launch that adds them.
+static double big_cost(const BigPlan& b, bool tnf, int M, int N) {
+    const int n_cu = gemm_cu_count(), tiles = b.tiles_m * b.tiles_n;
+    const double steps = tnf ? 0.5 * b.nt : b.nt;
+    auto rounds = [&](double work_groups) { return std::ceil(work_groups / n_cu); };
+    if (b.splits > 1)
+        return rounds((double)tiles * b.splits) * (steps / b.splits * 1.15 + 4) + 2e-6 * (double)b.splits * M * N + 4;
+    double t = b.n_main ? rounds(b.n_main) * (steps * 1.15 + 4) : 0;
+    const int tail = tiles - b.n_main;
+    if (tail) t += steps / b.tail_splits * 1.15 + 4 + 0.1 * tail * b.tail_splits + 4;
+    return t;
 }
 
 // Tile counters of the persistent form: 64 slots of [8 per-XCD counters, 1 count of finished work-groups], all zero
@@ -760,34 +782,14 @@ ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, 
         DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
         attr_set = true;
     }
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
-    const int nt = TNF ? (K + NT_DK - 1) / NT_DK : K / 64;      // K tiles as the kernel counts them
-    const int tiles = tiles_m * tiles_n;
-    int splits = 1;
-    if (EPI == DS_EPI_ACC32 && split_ws) splits = choose_splits(tiles, nt, M, N, split_ws_floats);
-    // tail split-K: the tiles beyond the last whole round over the compute units share that round; a launch with
-    // fewer tiles than compute units (small micro-batches) is all tail, so that the K loop is spread over the chip
-    int n_main = tiles, tail_splits = 1;
-    if (splits == 1 && split_ws) {
-        const int n_cu = cu_count();
-        const int rem = tiles % n_cu;
-        if (rem > 0) {
-            int ts = n_cu / rem;
-            if (ts > 32) ts = 32;
-            if (ts > nt / 4) ts = nt / 4;
-            while (ts > 1 && (size_t)rem * ts * (BM * BN) > split_ws_floats) --ts;
-            if (ts > 1) {
-                const int per = (nt + ts - 1) / ts;
-                ts = (nt + per - 1) / per;                      // every split owns at least one K tile
-            }
-            if (ts > 1) { n_main = tiles - rem; tail_splits = ts; }
-        }
-    }
+    const BigPlan plan = plan_big(TNF, EPI, M, N, K, split_ws ? split_ws_floats : 0);
+    const int tiles_m = plan.tiles_m, tiles_n = plan.tiles_n, tiles = tiles_m * tiles_n;
+    const int splits = plan.splits, n_main = plan.n_main, tail_splits = plan.tail_splits;
     const int total = splits > 1 ? tiles * splits : n_main + (tiles - n_main) * tail_splits;
     bool launched = false;
     if constexpr (!TNF && NT_PERSISTENT) {
         // persistent form: one resident work-group per compute unit for the unsplit tiles, when each has several to do
-        const int n_cu = cu_count();
+        const int n_cu = gemm_cu_count();
         if (splits == 1 && n_cu % 8 == 0 && n_main >= 2 * n_cu) {
             static bool ps_attr_set = false;
             auto kern_ps = gemm_bf16_nt_kernel<EPI, WM, WN, false, true>;
@@ -811,11 +813,7 @@ ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, 
                            tiles_m, tiles_n, splits, n_main, tail_splits, split_ws, p, 0, (int*)nullptr);
     DS_LAUNCH_CHECK();
     if (splits > 1) {
-        long long items = (long long)M * (N / 8);
-        long long g = (items + 255) / 256;
-        if (g > 8192) g = 8192;
-        hipLaunchKernelGGL(splitk_finish_kernel<EPI>, dim3((int)g), dim3(256), 0, st, M, N, splits, split_ws, (bf16_t*)C, p);
-        DS_LAUNCH_CHECK();
+        return launch_splitk_finish<bf16_t, EPI>(M, N, splits, split_ws, C, p, st);
     } else if (tail_splits > 1) {
         bool with_sums = false;
         if constexpr (EPI == DS_EPI_DGELU || EPI == DS_EPI_MULR) {
@@ -842,6 +840,17 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
         const bool ok_b = tb ? (K % BK == 0) : true;
         const bool aligned = ((uintptr_t)A % 16 == 0) && ((uintptr_t)B % 16 == 0) && ((uintptr_t)C % 16 == 0);
         if (ok_n && ok_a && ok_b && aligned && M >= 1 && K >= 1) {
+            // launches that do not fill the chip with 256 x 256 tiles: smaller ones, where the estimates say so
+            const bool tn = ta && !tb && EPI == DS_EPI_ACC32;
+            if (tn || (!ta && tb)) {
+                const size_t wsf = split_ws ? split_ws_floats : 0;
+                const BigPlan plan = plan_big(tn, EPI, M, N, K, wsf);
+                if (plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
+                    const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, p.colsum != nullptr);
+                    if (pick.kind >= 0 && pick.cost < big_cost(plan, tn, M, N))
+                        return launch_gemm_tile(pick, tn, M, N, K, A, B, C, EPI, p, split_ws, st);
+                }
+            }
             if (!ta && tb) return launch_nt<EPI, false>(M, N, K, A, B, C, p, split_ws, split_ws_floats, st);
             if constexpr (EPI == DS_EPI_ACC32)      // (the TN form addresses a K tile of each operand through a 32-bit buffer length)
                 if (ta && !tb && M <= (1 << 25) && N <= (1 << 25)) return launch_nt<EPI, true>(M, N, K, A, B, C, p, split_ws, split_ws_floats, st);

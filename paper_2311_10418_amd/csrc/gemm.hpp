@@ -27,3 +27,15 @@ ds_status launch_gemm(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t 
 bool gemm_f32_mfma_supported(int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B);
 ds_status launch_gemm_f32_mfma(int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B, void* C,
                                int32_t epilogue, const GemmEpi& p, float* split_ws, size_t split_ws_floats, hipStream_t st);
+
+// bf16 with smaller macro tiles (gemm_tile.hip).  kind: which tile, -1 = none fits; cost: estimated microseconds.
+struct TilePick {
+    int kind, splits;
+    double cost;
+};
+TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum);
+ds_status launch_gemm_tile(const TilePick& pick, bool tn, int32_t M, int32_t N, int32_t K, const void* A, const void* B, void* C,
+                           int32_t epilogue, const GemmEpi& p, float* split_ws, hipStream_t st);
+
+// compute units of the current device (256 where it cannot be asked)
+int gemm_cu_count();

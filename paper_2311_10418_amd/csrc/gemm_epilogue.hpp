@@ -148,4 +148,34 @@ __device__ __forceinline__ void epilogue8(int m, int n, int N, float (&acc)[8], 
     }
 }
 
+// sum the split-K partials ([split][M][N]) in split order and apply the epilogue; one thread per 8 columns
+template <class T, int EPI>
+__global__ __launch_bounds__(256) void splitk_finish_kernel(int M, int N, int splits, const float* __restrict__ ws,
+                                                            T* __restrict__ C, GemmEpi p) {
+    const int n8 = N / 8;
+    const long long total = (long long)M * n8;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
+        const int m = (int)(i / n8);
+        const int n = (int)(i - (long long)m * n8) * 8;
+        float v[8];
+        Vec8<float>::load(ws + (size_t)m * N + n, v);
+        for (int s = 1; s < splits; ++s) {
+            float w[8];
+            Vec8<float>::load(ws + ((size_t)s * M + m) * N + n, w);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] += w[j];
+        }
+        epilogue8<T, EPI>(m, n, N, v, C, p);
+    }
+}
+
+template <class T, int EPI>
+ds_status launch_splitk_finish(int M, int N, int splits, const float* ws, void* C, const GemmEpi& p, hipStream_t st) {
+    long long blocks = ((long long)M * (N / 8) + 255) / 256;
+    if (blocks > 8192) blocks = 8192;
+    hipLaunchKernelGGL((splitk_finish_kernel<T, EPI>), dim3((unsigned)blocks), dim3(256), 0, st, M, N, splits, ws, (T*)C, p);
+    DS_LAUNCH_CHECK();
+    return DS_OK;
+}
+
 }  // namespace

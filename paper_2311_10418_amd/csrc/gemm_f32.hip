@@ -172,40 +172,19 @@ __global__ __launch_bounds__(256 * KW) void gemm_f32_mfma_kernel(int M, int N, i
     }
 }
 
-// sum the split partials in split order and apply the epilogue; one thread per 8 columns
-template <int EPI>
-__global__ __launch_bounds__(256) void split_finish_f32_kernel(int M, int N, int splits, const float* __restrict__ ws,
-                                                               float* __restrict__ C, GemmEpi p) {
-    const int n8 = N / 8;
-    const long long total = (long long)M * n8;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-        const int m = (int)(i / n8);
-        const int n = (int)(i - (long long)m * n8) * 8;
-        float v[8];
-        Vec8<float>::load(ws + (size_t)m * N + n, v);
-        for (int s = 1; s < splits; ++s) {
-            float w[8];
-            Vec8<float>::load(ws + ((size_t)s * M + m) * N + n, w);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] += w[j];
-        }
-        epilogue8<float, EPI>(m, n, N, v, C, p);
-    }
-}
-
 template <int EPI, bool AKC, bool BKC>
 ds_status launch_form(int M, int N, int K, const float* A, const float* B, float* C, const GemmEpi& p, float* split_ws,
                       size_t split_ws_floats, hipStream_t st) {
-    constexpr int N_CU = 256;
+    const int n_cu = gemm_cu_count();
     const int gn = (N + F_BN - 1) / F_BN, gm64 = (M + 63) / 64, gm128 = (M + 127) / 128;
     const long long lda = AKC ? K : M, ldb = BKC ? K : N;
-    const bool big = (long long)gn * gm128 >= 2 * N_CU;
+    const bool big = (long long)gn * gm128 >= 2 * n_cu;
     // A contraction far longer than the output is wide (weight gradients: every token of the batch) is cut into K ranges
     // until about two work-groups per CU run, each range at least 4 tiles deep; the partial sums stay within the workspace.
     int splits = 1;
     if (split_ws && !big) {
         const int tiles = gn * gm64;
-        splits = (2 * N_CU + tiles - 1) / tiles;
+        splits = (2 * n_cu + tiles - 1) / tiles;
         const int by_k = K / (4 * F_BK);
         if (splits > by_k) splits = by_k;
         const size_t by_ws = split_ws_floats / ((size_t)M * N);
@@ -218,19 +197,14 @@ ds_status launch_form(int M, int N, int K, const float* A, const float* B, float
     if (big)
         hipLaunchKernelGGL((gemm_f32_mfma_kernel<EPI, AKC, BKC, 2, 1>), dim3(gn, gm128, splits), dim3(256), 0, st, M, N, K, A, lda, B,
                            ldb, C, per, split_ws, p);
-    else if ((long long)gn * gm64 * splits >= 2 * N_CU)
+    else if ((long long)gn * gm64 * splits >= 2 * n_cu)
         hipLaunchKernelGGL((gemm_f32_mfma_kernel<EPI, AKC, BKC, 1, 1>), dim3(gn, gm64, splits), dim3(256), 0, st, M, N, K, A, lda, B,
                            ldb, C, per, split_ws, p);
     else
         hipLaunchKernelGGL((gemm_f32_mfma_kernel<EPI, AKC, BKC, 1, 2>), dim3(gn, gm64, splits), dim3(512), 0, st, M, N, K, A, lda, B,
                            ldb, C, per, split_ws, p);
     DS_LAUNCH_CHECK();
-    if (splits > 1) {
-        long long blocks = ((long long)M * (N / 8) + 255) / 256;
-        if (blocks > 4096) blocks = 4096;
-        hipLaunchKernelGGL(split_finish_f32_kernel<EPI>, dim3((unsigned)blocks), dim3(256), 0, st, M, N, splits, split_ws, C, p);
-        DS_LAUNCH_CHECK();
-    }
+    if (splits > 1) return launch_splitk_finish<float, EPI>(M, N, splits, split_ws, C, p, st);
     return DS_OK;
 }
 

@@ -1,0 +1,375 @@
+// bf16 GEMMs with smaller macro tiles than the 256 x 256 kernel of gemm.hip, for launches that would not fill the chip with
+// those: the micro-batches of a stage that runs them one after another, the decoder side of an encoder-decoder stage, small
+// models.  There the large tile has to cut K loops into many pieces to occupy the compute units, and writing and reading
+// back 256 KB of partial sums per piece costs more than the products (M = 756, N = K = 2048: 36 us, of which the
+// products are 6).
+//
+// Three tiles, all direct-to-LDS with the operand layouts of the large kernel, 64-deep K tiles in a ring of stages:
+//   128 x 128, 8 wavefronts of 32 x 64, 4 stages (128 KB: one work-group per CU)
+//   128 x  64, 8 wavefronts of 32 x 32, 3 stages ( 72 KB: two per CU)
+//    64 x  64, 4 wavefronts of 32 x 32, 3 stages ( 48 KB: three per CU)
+// What bounds them is LDS bandwidth: per K tile the fragment reads plus the arriving operands are 128, 88 and 48 KB for
+// 2.1, 1.05 and 0.5 MFLOP (the 256 x 256 kernel: 256 KB for 8.4), which at 128 bytes per cycle is 0.46, 0.32 and 0.18 us;
+// measured 0.47 - 0.50, 0.32 and 0.18 - 0.20.  Four wavefronts of 64 x 64 on the 128 x 128 tile (a quarter less LDS
+// traffic) are slower at every shape tried: with one wavefront per SIMD, or two from two work-groups on 32-deep tiles,
+// latency is not covered (N = 2048, K = 8192, M = 1757: 89 and 73 us against 60).
+//
+// Which one: the tile and split count with the smallest estimate (pick_gemm_tile), compared with the same kind of
+// estimate for the large kernel.  Measured, 256 x 256 kernel -> this, us (M, N, K; ds_gemm_ws on an idle card):
+//   NT 256, 768, 256: 10.2 -> 4.8    756, 2048, 2048: 36 -> 12.8    756, 8192, 2048: 43 -> 31    756, 2048, 8192: 50 -> 40
+//      1757, 2048, 2048: 37 -> 19    1757, 6144, 2048: 43 (53 with these: stays)    4173, 1024, 4096: 50 (55: stays)
+//   TN 256, 1024, 250: 17 -> 5       2048, 2048, 756: 47 -> 15       2048, 2048, 1757: 43 -> 25  1024, 4096, 4173: 57 -> 47
+//      2048, 8192, 756: 37 (48: stays)
+#include "gemm_epilogue.hpp"
+
+#include <cmath>
+
+namespace {
+
+constexpr int T_KD = 64;                             // depth of a K tile
+
+// N direct transfers of 64 x 16 bytes under one M0 through ONE raw buffer (see lds_dma16_buffers_2x2: the buffer starts
+// 1024 (N - 1) bytes early and is as much longer, lane offsets come from dma_lane_offset<N>).
+template <int N>
+__device__ __forceinline__ void lds_dma16_buffer_group(i32x4_t buf, const uint32_t (&off)[N], uint32_t lds_addr) {
+    static_assert(N == 1 || N == 2 || N == 4, "group sizes in use");
+    const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_addr);
+    if constexpr (N == 1)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(off[0]), "s"(buf), "s"(m0v) : "memory", "m0");
+    else if constexpr (N == 2)
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds\n\t"
+                     "buffer_load_dwordx4 %1, %2, 0 offen offset:1024 lds"
+                     : : "v"(off[0]), "v"(off[1]), "s"(buf), "s"(m0v) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
+                     "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\tbuffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds"
+                     : : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(buf), "s"(m0v) : "memory", "m0");
+}
+
+// One operand's K tile: ROWS rows (m or n) x 64 k in LDS.
+//   k contiguous (KC): [row][128 bytes], 16-byte chunk c of a row at chunk slot c ^ ((row / 2) % 8); rows past the end of the
+//     tensor are clamped (read, never stored).
+//   k as the row: [64 k][ROWS * 2 bytes], 32-byte unit u of a k row at unit u ^ f(k) with f(k) = k % 8 (ROWS = 128) or
+//     (k / 2) % 4 (ROWS = 64); k rows past the end read zeros through the bounds check of the buffer descriptor.
+// Both swizzles are applied by choosing which global chunk a lane fetches.
+template <int ROWS, bool KC, int NW> struct OperandTile {
+    static constexpr int BYTES = ROWS * T_KD * 2;
+    static constexpr int LP = BYTES / 1024 / NW;                      // transfers per wavefront and tile
+    const char* base;                                                 // KC: tensor at (r0, k = 0); else at (k = 0, r0)
+    long long ld2;                                                    // row stride in bytes
+    int K;
+    uint32_t off[LP];
+    uint32_t lds_wave;                                                // this wavefront's part of a tile
+    __device__ __forceinline__ void setup(const bf16_t* src, long long ld, int r0, int rows, int K_, int wave, int lane) {
+        ld2 = ld * 2;
+        K = K_;
+        lds_wave = (uint32_t)__builtin_amdgcn_readfirstlane(wave) * (LP * 1024);
+        base = reinterpret_cast<const char*>(src) + (KC ? (long long)r0 * ld2 : (long long)r0 * 2);
+#pragma unroll
+        for (int i = 0; i < LP; ++i) {
+            const int u = (wave * LP + i) * 64 + lane;                // 16-byte slot of the tile
+            uint32_t want;
+            if constexpr (KC) {
+                const int row = u / (T_KD / 8), chunk = (u % (T_KD / 8)) ^ chunk_swz(row);
+                const int rc = r0 + row < rows ? row : rows - 1 - r0;
+                want = (uint32_t)(rc * ld2 + chunk * 16);
+            } else {
+                constexpr int CPR = ROWS / 8;                         // chunks per k row
+                const int k = u / CPR, pos = u % CPR;
+                const int unit = (pos >> 1) ^ unit_swz(k);
+                want = (uint32_t)(k * ld2 + (unit * 2 + (pos & 1)) * 16);
+            }
+            off[i] = dma_lane_offset<LP>(want, i);
+        }
+    }
+    __device__ __forceinline__ static int chunk_swz(int row) { return (row >> 1) & 7; }
+    __device__ __forceinline__ static int unit_swz(int k) { return ROWS == 128 ? (k & 7) : ((k >> 1) & 3); }
+    __device__ __forceinline__ void issue(int tile, uint32_t lds) const {
+        if constexpr (KC) {
+            lds_dma16_group<LP>(dma_group_base<LP>(base + (long long)tile * (T_KD * 2)), off, lds + lds_wave);
+        } else {
+            const int left = K - tile * T_KD;
+            const uint32_t bytes = (uint32_t)(left < T_KD ? left : T_KD) * (uint32_t)ld2;
+            const i32x4_t buf = make_raw_buffer(base + (long long)tile * T_KD * ld2 - 1024 * (LP - 1), bytes + 1024u * (LP - 1));
+            lds_dma16_buffer_group<LP>(buf, off, lds + lds_wave);
+        }
+    }
+    // MFMA fragment (16 rows x 32 k) of 16-row unit `unit`, k step ks of a tile; both operands list k in the same order
+    __device__ static __forceinline__ bf16x8_t frag(const char* tile, int unit, int ks, int lane) {
+        if constexpr (KC) {
+            const int row = unit * 16 + (lane & 15), chunk = ks * 4 + (lane >> 4);
+            return *reinterpret_cast<const bf16x8_t*>(tile + row * (T_KD * 2) + ((chunk ^ chunk_swz(row)) << 4));
+        } else {
+            typedef short s16x4_t __attribute__((ext_vector_type(4)));
+            typedef short s16x8_t __attribute__((ext_vector_type(8)));
+            typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
+            const int k = ks * 32 + 4 * (lane >> 4) + ((lane & 15) >> 2);
+            const char* q = tile + k * (ROWS * 2) + ((unit ^ unit_swz(k)) << 5) + (lane & 3) * 8;
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)q);
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(q + 16 * ROWS * 2));
+            return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+    }
+};
+
+// C[M,N] = A B^T (NT: both k-contiguous, K % 64 == 0, N % BN == 0) or A^T B (TN: k rows, M % BM == 0, N % BN == 0, K any).
+// WM x WN wavefronts; gridDim.x = tiles x splits, numbered so that each XCD gets a contiguous run, 8 tile rows to a group;
+// with more than one split the partial sums go to split_ws as [split][M][N].
+// Ring of NS stages, 64-deep K tiles: a tile's transfers are issued NS - 1 tiles ahead, right after the barrier that
+// frees their stage; the fragments of the next 32-deep step are read while the current one is multiplied, across the
+// tile boundary too.  Transfers past the last tile are clamped so that the wait counts never change.
+template <int EPI, bool TNF, int BM, int BN, int WM, int WN, int NS>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
+                                                                      const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
+                                                                      int tiles_m, int tiles_n, int splits, int tiles_per_split,
+                                                                      float* __restrict__ split_ws, GemmEpi p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    constexpr int NW = WM * WN;
+    typedef OperandTile<BM, !TNF, NW> TA;
+    typedef OperandTile<BN, !TNF, NW> TB;
+    constexpr int STAGE = TA::BYTES + TB::BYTES;
+    constexpr int WR = BM / WM, WC = BN / WN;                         // a wavefront's rows and columns
+    constexpr int NA = WR / 16, NB = WC / 16;
+    constexpr int L = TA::LP + TB::LP;
+    static_assert(WR % 32 == 0 && WC % 32 == 0, "the epilogue stages 32 rows of at least 32 columns");
+    static_assert((NS - 1) * L < 64, "vmcnt has 6 bits");
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+
+    int tile_m, tile_n, split;
+    {
+        const int total = gridDim.x, pid = blockIdx.x;
+        const int xcd = pid & 7, per = total >> 3, rem = total & 7;
+        int logical = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (pid >> 3);
+        const int n_tiles = tiles_m * tiles_n;
+        split = logical / n_tiles;
+        logical -= split * n_tiles;
+        constexpr int GROUP = 8;
+        const int group = logical / (GROUP * tiles_n), first = group * GROUP;
+        const int gs = tiles_m - first < GROUP ? tiles_m - first : GROUP;
+        const int in = logical - group * GROUP * tiles_n;
+        tile_m = first + in % gs;
+        tile_n = in / gs;
+    }
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    const int nt = (K + T_KD - 1) / T_KD;
+    const int t_begin = split * tiles_per_split;
+    const int t_end = t_begin + tiles_per_split < nt ? t_begin + tiles_per_split : nt;
+
+    TA ta;
+    TB tb;
+    ta.setup(A, TNF ? M : K, m0, M, K, wave, lane);
+    tb.setup(B, TNF ? N : K, n0, N, K, wave, lane);
+    const uint32_t lds0 = lds_address(smem);
+    auto issue = [&](int tl) {
+        const uint32_t dst = lds0 + (uint32_t)((tl - t_begin) % NS) * STAGE;
+        const int tc = tl < t_end ? tl : t_end - 1;
+        ta.issue(tc, dst);
+        tb.issue(tc, dst + TA::BYTES);
+    };
+    f32x4_t acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+
+    bf16x8_t ax[NA], bx[NB], ay[NA], by[NB];
+    auto read = [&](int stage, int ks, bf16x8_t (&fa)[NA], bf16x8_t (&fb)[NB]) {
+        const char* a = smem + stage * STAGE;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) fb[j] = TB::frag(a + TA::BYTES, wn * NB + j, ks, lane);
+#pragma unroll
+        for (int i = 0; i < NA; ++i) fa[i] = TA::frag(a, wm * NA + i, ks, lane);
+    };
+    auto mma = [&](const bf16x8_t (&fa)[NA], const bf16x8_t (&fb)[NB]) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int jj = 0; jj < NB; ++jj) {
+                const int j = (i & 1) ? NB - 1 - jj : jj;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+            }
+    };
+#pragma unroll
+    for (int s = 0; s < NS; ++s) issue(t_begin + s);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 1) * L));              // the first tile: this wavefront's part ...
+    __builtin_amdgcn_s_barrier();                                     // ... and everyone's
+    read(0, 0, ax, bx);
+    int stage = 0;
+    for (int tl = t_begin; tl < t_end; ++tl) {
+        const int next = stage + 1 == NS ? 0 : stage + 1;
+        read(stage, 1, ay, by);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(ax, bx);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * L) & 0xF0FF); // tile tl + 1 has landed; lgkmcnt(0): reads of tile tl are done
+        __builtin_amdgcn_s_barrier();
+        issue(tl + NS);                                               // into the stage of tile tl
+        read(next, 0, ax, bx);                                        // (past the last tile: a reloaded copy of it, unused)
+        __builtin_amdgcn_sched_barrier(0);
+        mma(ay, by);
+        __builtin_amdgcn_sched_barrier(0);
+        stage = next;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);                               // no transfer may still be writing the LDS the epilogue uses
+    __builtin_amdgcn_s_barrier();
+
+    // epilogue: 32 rows at a time through a block of LDS that is private to the wavefront
+    constexpr int LDC = WC + 4, LPR = WC / 8, RPP = 64 / LPR, NP = 32 / RPP;
+    static_assert(NW * 32 * LDC * 4 <= NS * STAGE, "the staging blocks fit in the ring");
+    float* stg = reinterpret_cast<float*>(smem) + wave * (32 * LDC);
+    const int rd_row = lane / LPR, rd_col = (lane % LPR) * 8;
+    const int n = n0 + wn * WC + rd_col;
+    const bool direct = splits == 1;
+    EpiPre<bf16_t> pre[WR / 32][NP];
+    if (epilogue_reads<EPI>() && direct) {
+#pragma unroll
+        for (int i = 0; i < WR / 32; ++i)
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const int m = m0 + wm * WR + i * 32 + q * RPP + rd_row;
+                if (m < M) epilogue_prefetch<bf16_t, EPI>(m, n, N, p, pre[i][q]);
+            }
+    }
+    float csum[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) csum[j] = 0.f;
+#pragma unroll
+    for (int i = 0; i < WR / 32; ++i) {
+        wave_lds_sync();
+#pragma unroll
+        for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const f32x4_t a4 = acc[2 * i + i2][j];
+                *reinterpret_cast<float4*>(stg + (i2 * 16 + (lane & 15)) * LDC + j * 16 + 4 * (lane >> 4)) = make_float4(a4[0], a4[1], a4[2], a4[3]);
+            }
+        wave_lds_sync();
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int row = q * RPP + rd_row, m = m0 + wm * WR + i * 32 + row;
+            if (m >= M) continue;
+            float v[8];
+            Vec8<float>::load(stg + row * LDC + rd_col, v);
+            if (!direct) {
+                Vec8<float>::store(split_ws + ((size_t)split * M + m) * N + n, v);
+            } else {
+                epilogue8<bf16_t, EPI>(m, n, N, v, C, p, epilogue_reads<EPI>() ? &pre[i][q] : nullptr);
+                if constexpr (EPI == DS_EPI_DGELU || EPI == DS_EPI_MULR) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) csum[j] += v[j];
+                }
+            }
+        }
+    }
+    if constexpr ((EPI == DS_EPI_DGELU || EPI == DS_EPI_MULR) && BM == 128) {
+        // one row of partial column sums per tile row: the wavefronts of a column add theirs in LDS
+        if (p.colsum) {
+#pragma unroll
+            for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) csum[j] += __shfl_xor(csum[j], o, 64);
+            __syncthreads();
+            float* red = reinterpret_cast<float*>(smem);              // [WM][BN]
+            if (lane < LPR) Vec8<float>::store(red + wm * BN + wn * WC + rd_col, csum);
+            __syncthreads();
+            if (t < BN) {
+                float s = red[t];
+#pragma unroll
+                for (int w = 1; w < WM; ++w) s += red[w * BN + t];
+                p.colsum[(size_t)tile_m * N + n0 + t] = s;
+                // gemm_colsum_rows() counts two rows per 256: the last one may have no tile
+                if (tile_m + 1 == tiles_m && (tiles_m & 1)) p.colsum[(size_t)(tile_m + 1) * N + n0 + t] = 0.f;
+            }
+        }
+    }
+}
+
+struct TileShape { int bm, bn, waves, stages; double step, fixed; };
+// step: microseconds per K tile of one work-group per CU (LDS bandwidth, see above); fixed: around the K loop
+constexpr TileShape kShapes[3] = {{128, 128, 8, 4, 0.49, 3.0}, {128, 64, 8, 3, 0.32, 2.5}, {64, 64, 4, 3, 0.20, 2.5}};
+
+template <int EPI, bool TNF, int KIND, int WM, int WN>
+ds_status launch_kind(int splits, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
+                      hipStream_t st) {
+    constexpr TileShape s = kShapes[KIND];
+    constexpr int smem = s.stages * (s.bm + s.bn) * T_KD * 2;
+    static_assert(WM * WN == s.waves, "wavefront grid");
+    static bool attr_set = false;
+    auto kern = gemm_bf16_tile_kernel<EPI, TNF, s.bm, s.bn, WM, WN, s.stages>;
+    if (!attr_set) {
+        DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        attr_set = true;
+    }
+    const int tiles_m = (M + s.bm - 1) / s.bm, tiles_n = N / s.bn;
+    const int nt = (K + T_KD - 1) / T_KD, per = (nt + splits - 1) / splits;      // (the pick leaves no split empty)
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n * splits)), dim3(s.waves * 64), smem, st, M, N, K, (const bf16_t*)A,
+                       (const bf16_t*)B, (bf16_t*)C, tiles_m, tiles_n, splits, per, split_ws, p);
+    DS_LAUNCH_CHECK();
+    if (splits > 1) return launch_splitk_finish<bf16_t, EPI>(M, N, splits, split_ws, C, p, st);
+    return DS_OK;
+}
+
+template <int EPI, bool TNF>
+ds_status launch_form(const TilePick& k, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
+                      hipStream_t st) {
+    if (k.kind == 0) return launch_kind<EPI, TNF, 0, 4, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
+    if (k.kind == 1) return launch_kind<EPI, TNF, 1, 4, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
+    return launch_kind<EPI, TNF, 2, 2, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
+}
+
+}  // namespace
+
+int gemm_cu_count() {
+    static const int n_cu = [] {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
+        return v;
+    }();
+    return n_cu;
+}
+
+// The caller has established what the operands of the 256 x 256 kernel need (N, and M in the TN form, a multiple of 256;
+// K a multiple of 64 in the NT form; 16-byte alignment), which covers every tile here.
+//   estimate = rounds over the CUs x K tiles per split x step + fixed; several splits add the round trip of the partial sums
+//   at 4 TB/s and 5 us for the launch that adds them.
+// colsum: the epilogue's column sums are wanted, which takes 128-row tiles and whole K loops.
+TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum) {
+    TilePick best{-1, 1, 0.0};
+    if (tn && (M > (1 << 24) || N > (1 << 24))) return best;          // a K tile is addressed through a 32-bit buffer length
+    const int n_cu = gemm_cu_count(), nt = (K + T_KD - 1) / T_KD;
+    for (int k = 0; k < 3; ++k) {
+        const TileShape& s = kShapes[k];
+        if (colsum && s.bm != 128) continue;
+        const double tiles = std::ceil((double)M / s.bm) * (N / s.bn);
+        for (int sp = 1; sp <= 32; ++sp) {
+            if (sp > 1 && (colsum || sp > nt / 4 || (size_t)sp * M * N > split_ws_floats)) break;
+            const int per = (nt + sp - 1) / sp;
+            if ((nt + per - 1) / per != sp || tiles * sp > 1e9) continue;         // every split owns at least one K tile
+            double cost = std::ceil(tiles * sp / n_cu) * per * s.step + s.fixed;
+            if (sp > 1) cost += 2e-6 * sp * (double)M * N + 5;
+            if (best.kind < 0 || cost < best.cost) best = TilePick{k, sp, cost};
+        }
+    }
+    return best;
+}
+
+ds_status launch_gemm_tile(const TilePick& pick, bool tn, int32_t M, int32_t N, int32_t K, const void* A, const void* B, void* C,
+                           int32_t epilogue, const GemmEpi& p, float* split_ws, hipStream_t st) {
+    if (tn) return epilogue == DS_EPI_ACC32 ? launch_form<DS_EPI_ACC32, true>(pick, M, N, K, A, B, C, p, split_ws, st) : DS_EINVAL;
+    switch (epilogue) {
+    case DS_EPI_NONE: return launch_form<DS_EPI_NONE, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    case DS_EPI_GELU: return launch_form<DS_EPI_GELU, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    case DS_EPI_RESID: return launch_form<DS_EPI_RESID, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    case DS_EPI_DGELU: return launch_form<DS_EPI_DGELU, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    case DS_EPI_ACC32: return launch_form<DS_EPI_ACC32, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    case DS_EPI_GATE: return launch_form<DS_EPI_GATE, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    case DS_EPI_DGATE: return launch_form<DS_EPI_DGATE, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    case DS_EPI_GELU_D: return launch_form<DS_EPI_GELU_D, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    case DS_EPI_MULR: return launch_form<DS_EPI_MULR, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    }
+    return DS_EINVAL;
+}

@@ -599,3 +599,43 @@ def test_attention_worklist_many_sequences():
         res.append((to_np(o), to_np(g)))
     for got, ref in zip(*res):
         assert both_err(got, ref) <= TOL[BF]
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 256, 64), (63, 256, 128), (65, 256, 1024), (129, 512, 320), (250, 1024, 256), (300, 256, 4096), (756, 2048, 2048)])
+def test_gemm_smaller_tiles_nt(M, N, K):
+    """Launches too small for 256 x 256 tiles: row edges of the 64- and 128-row tiles, one to many K tiles, with and without
+    a workspace to split the contraction; rows beyond M stay untouched."""
+    rng = np.random.default_rng(35)
+    A, B = _rnd(rng, (M, K), BF), _rnd(rng, (N, K), BF, 0.1)
+    bias, R = _rnd(rng, (N,), BF), _rnd(rng, (M, N), BF)
+    acc = A.astype(np.float64) @ B.astype(np.float64).T
+    dA, dB, db, dR = (to_dev(x, BF) for x in (A, B, bias, R))
+    valid = np.where(rng.random(M) < 0.8, 1, -1).astype(np.int32)
+    for ws in (None, _ws(1 << 22)):
+        c, c2 = (torch.full((M + 3, N), 7.0, dtype=BF, device=DEV) for _ in range(2))
+        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, bias=db, workspace=ws)
+        torch.cuda.synchronize()
+        assert both_err(to_np(c)[:M], acc + bias) <= 4e-3 and np.all(to_np(c)[M:] == 7.0)       # one bf16 rounding: 2^-9
+        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, epilogue=ds.DS_EPI_RESID, bias=db, R=dR, row_valid=torch.from_numpy(valid).to(DEV), workspace=ws)
+        torch.cuda.synchronize()
+        assert both_err(to_np(c)[:M], (acc + bias + R) * (valid[:, None] >= 0)) <= 4e-3 and np.all(to_np(c)[:M][valid < 0] == 0)
+        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, epilogue=ds.DS_EPI_GELU_D, bias=db, C2=c2, workspace=ws)
+        torch.cuda.synchronize()
+        assert both_err(to_np(c)[:M], ost.gelu_grad(acc + bias)) <= 4e-3 and both_err(to_np(c2)[:M], ost.gelu(acc + bias)) <= 4e-3
+        assert np.all(to_np(c)[M:] == 7.0) and np.all(to_np(c2)[M:] == 7.0)
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 256, 1), (256, 512, 31), (512, 256, 64), (256, 1024, 250), (768, 256, 577), (256, 256, 9001), (2048, 2048, 756)])
+def test_gemm_smaller_tiles_weight_gradient(M, N, K):
+    """The same for weight gradients: ragged contractions around the 64-deep K tile, split and whole; fp32 sums: 1e-5."""
+    rng = np.random.default_rng(36)
+    X, dY = _rnd(rng, (K, M), BF), _rnd(rng, (K, N), BF)
+    ref = X.astype(np.float64).T @ dY.astype(np.float64)
+    # rows behind the last valid one hold NaN: the bounds check must keep them out of the sums
+    dX, ddY = (torch.cat([to_dev(a, BF), torch.full((64, a.shape[1]), float("nan"), dtype=BF, device=DEV)]) for a in (X, dY))
+    for ws in (None, _ws(1 << 22)):
+        c = torch.full((M, N), 3.0, dtype=F32, device=DEV)
+        ds.ds_gemm(dX, ddY, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, accumulate=False, workspace=ws)
+        ds.ds_gemm(dX, ddY, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, accumulate=True, workspace=ws)
+        torch.cuda.synchronize()
+        assert both_err(to_np(c), 2 * ref) <= 1e-5
