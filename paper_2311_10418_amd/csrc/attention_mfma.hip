@@ -37,6 +37,7 @@
 // owner: no atomics, results are bit-reproducible.  Sequences are addressed through (row, length)
 // tables, so padding rows cost nothing and packed layouts need no mask.
 #include "attention.hpp"
+#include "gemm.hpp"
 #include <type_traits>
 
 namespace {
@@ -154,6 +155,30 @@ template <int HD> struct TileLoader {
     }
 };
 
+// Loader of 64-row tiles through a raw buffer whose length ends at the last valid row: rows past the end arrive as zeros,
+// so that every tile, ragged or not, is fetched by the same instructions with the same per-lane offsets.
+template <int HD> struct BufferTileLoader {
+    static constexpr int PW = HD / 32;
+    const char* base;
+    long long ld2;
+    int n_valid, wave;
+    uint32_t off[PW];
+    __device__ __forceinline__ void setup(const bf16_t* base_, long long ld_, int n_valid_, int wave_, int lane) {
+        base = (const char*)base_; ld2 = ld_ * 2; n_valid = n_valid_; wave = wave_;
+#pragma unroll
+        for (int i = 0; i < PW; ++i) {
+            const int u = (wave * PW + i) * 64 + lane;
+            off[i] = dma_lane_offset<PW>((uint32_t)(TileLoader<HD>::row_of(u) * (int)ld2 + TileLoader<HD>::chunk_of(u) * 16), i);
+        }
+    }
+    // rows r0 .. r0+63 -> the tile at LDS address lds_tile; 0 <= r0 < n_valid
+    __device__ __forceinline__ void issue(uint32_t lds_tile, int r0) const {
+        const uint32_t bytes = (uint32_t)min(64, n_valid - r0) * (uint32_t)ld2;
+        const i32x4_t buf = make_raw_buffer(base + (long long)r0 * ld2 - 1024 * (PW - 1), bytes + 1024u * (PW - 1));
+        lds_dma16_buffer_group<PW>(buf, off, lds_tile + wave * (PW * 1024));
+    }
+};
+
 // this wavefront's direct loads have landed, then everybody's; the stage read in the previous step is free
 __device__ __forceinline__ void wait_tiles_and_sync() {
     __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
@@ -173,6 +198,9 @@ __device__ __forceinline__ void store_cols(const f32x16_t (&acc)[HD / 32], float
             *reinterpret_cast<bf16x4_t*>(out_row + dt * 32 + 8 * q4 + 4 * g) = v;
         }
 }
+
+// the scratch starts with the two list lengths; from this int on, 16 for the draw counters (see WorkDraw)
+constexpr int kCtrHeader = 16;
 
 // ------------------------------------------------------------------------------------ work lists
 // items[0 .. n): the (sequence, block) pairs of `block` rows each; n is written to *n_items.  One work-group per
@@ -195,6 +223,7 @@ __global__ __launch_bounds__(1024) void attn_worklist_kernel(int n_seq, const in
     __shared__ int wave_total[NB / 64];
     const int tid = threadIdx.x;
     const bool key_side = blockIdx.x != 0;
+    if (key_side && tid >= kCtrHeader && tid < kCtrHeader + 16) n_items[tid] = 0;     // the draw counters of the dK/dV kernel
     const int32_t* own_len = key_side ? k_len : q_len;
     const int32_t* other_len = key_side ? q_len : k_len;
     const int max_items = key_side ? max_items_k : max_items_q;
@@ -238,18 +267,53 @@ __global__ __launch_bounds__(1024) void attn_worklist_kernel(int n_seq, const in
     }
 }
 
+// Items of a persistent kernel.  The (item, head) pairs of the list, heads fastest, are dealt to the XCDs in turn as a plain
+// grid would be, so that the blocks of one (sequence, head) stay on one XCD; a work-group starts with pair
+// blockIdx.x and draws further ones of its XCD from a counter.  Counters: 8 per-XCD draws and the number of finished
+// work-groups, in the scratch header (the list kernel clears them, the last work-group of a launch leaves them cleared;
+// calls that share a scratch do not overlap).  The grid is a multiple of 8.
+struct WorkDraw {
+    int32_t* ctr;
+    int total, xcd, k;
+    __device__ __forceinline__ WorkDraw(const AttnArgs& a, int list) {       // list: 0 the query side, 1 the key side
+        ctr = const_cast<int32_t*>(a.n_items) + kCtrHeader;
+        total = a.n_items[list] * a.n_heads;
+        xcd = blockIdx.x & 7;
+        k = blockIdx.x >> 3;
+    }
+    __device__ __forceinline__ int index() const { return 8 * k + xcd; }
+    __device__ __forceinline__ bool valid() const { return index() < total; }
+    // thread 0 draws; the other threads' result is meaningless
+    __device__ __forceinline__ int take() const {
+        int next = 0;
+        if (threadIdx.x == 0)
+            next = ((int)gridDim.x >> 3) + __hip_atomic_fetch_add(ctr + xcd, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return next;
+    }
+    __device__ __forceinline__ void advance(int next) { k = next; }
+    __device__ __forceinline__ void finish() const {
+        if (threadIdx.x != 0) return;
+        if (__hip_atomic_fetch_add(ctr + 8, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) ctr[i] = 0;
+        }
+    }
+};
+__host__ __device__ constexpr bool dkv_persistent(int hd) { return hd == 128; }
+
 // ------------------------------------------------------------------------------------ forward
 template <int HD, bool CAUSAL>
-__global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, HD == 64 ? 4 : 2) void attn_fwd_mfma_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int TILE = 64 * HD * 2;                  // bytes of one K tile == one V tile
+    constexpr int AHEAD_K = HD == 64 ? 2 : FWD_AHEAD, AHEAD_V = HD == 64 ? 2 : PV_AHEAD;
     const uint32_t lds0 = lds_address(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
     const int item = blockIdx.x / a.n_heads, h = blockIdx.x - item * a.n_heads;
+    const int2 it = a.items_q[item];                    // (within the list's capacity; read beside its length, not behind it)
     if (item >= a.n_items[0]) return;
-    const int2 it = a.items_q[item];
     const int s = it.x, q0 = it.y * 128;
     const int ql = a.q_len[s], kl = a.k_len[s];
     const long long qrow0 = a.q_row[s];
@@ -265,7 +329,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
     for (int ks = 0; ks < HD / 16; ++ks)
         qf[ks] = *reinterpret_cast<const bf16x8_t*>(Q + (long long)qi_c * a.ldq + ks * 16 + g * 8);
 
-    TileLoader<HD> ldK, ldV;
+    BufferTileLoader<HD> ldK, ldV;
     ldK.setup(K, a.ldk, kl, wave, lane);
     ldV.setup(V, a.ldv, kl, wave, lane);
     TrOffsets<HD> tro;
@@ -296,27 +360,25 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
         // The transfers of block b+1.  A wavefront cannot issue anything else while a transfer of its own passes the
         // address stage of the texture path (measured with timestamps: one burst of 8 transfers with an M0 each held
         // a wavefront for about 600 cycles of a 4400-cycle step; grouped under one M0 per tile, 250), so a wavefront
-        // that computes in this step hands out the two groups between the MFMAs of its first product; only a ragged
-        // last block (its per-lane offsets are recomputed) and wavefronts without work issue them at once.
-        const bool have_next = b + 1 < nb;
+        // that computes in this step hands out the two groups between the MFMAs of its first product (after the last
+        // block: the last tiles again, into the free stage); wavefronts without work issue them at once.
+        const int kv_next = min(kv0 + 64, (nb - 1) * 64);
         const bool active = !(kv0 > wave_last || qw0 >= ql);
-        const bool spread = have_next && active && kv0 + 128 <= kl;
         const uint32_t nK_lds = lds0 + ((b + 1) & 1) * (2 * TILE);
-        if (have_next && !spread) {
-            ldK.issue(nK_lds, kv0 + 64);
-            ldV.issue(nK_lds + TILE, kv0 + 64);
+        if (!active) {
+            ldK.issue(nK_lds, kv_next);
+            ldV.issue(nK_lds + TILE, kv_next);
+            continue;
         }
-        if (!active) continue;
 
         f32x16_t sacc[2];
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
             for (int e = 0; e < 16; ++e) sacc[kt][e] = 0.f;
-        // first product, S^T = K Q^T: fragment reads FWD_AHEAD MFMAs in front of their use, the order pinned by fences
-        // (see the dK/dV kernel); two copies, with and without the transfers, so that neither holds a branch
-        auto first_product = [&](auto with_dma) {
-            constexpr bool DMA = decltype(with_dma)::value;
+        // first product, S^T = K Q^T: fragment reads AHEAD_K MFMAs in front of their use, the order pinned by fences
+        // (see the dK/dV kernel)
+        {
             constexpr int NF = 2 * (HD / 16);
             bf16x8_t fk[NF];
             auto read_k = [&](int i) {
@@ -324,31 +386,29 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
                 fk[i] = *reinterpret_cast<const bf16x8_t*>(sK + kt * (32 * HD * 2) + rbase + (((ks * 2 + g) ^ rsw) << 4));
             };
 #pragma unroll
-            for (int i = 0; i < FWD_AHEAD; ++i) read_k(i);
+            for (int i = 0; i < AHEAD_K; ++i) read_k(i);
 #pragma unroll
             for (int i = 0; i < NF; ++i) {
-                if (i + FWD_AHEAD < NF) read_k(i + FWD_AHEAD);
+                if (i + AHEAD_K < NF) read_k(i + AHEAD_K);
                 __builtin_amdgcn_sched_barrier(kFence);
                 sacc[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[i], qf[i >> 1], sacc[i & 1], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(kFence);
-                if (DMA && i == NF / 4 - 1) {           // the next K tile after a quarter of the product ...
-                    ldK.issue(nK_lds, kv0 + 64);
+                if (i == NF / 4 - 1) {                  // the next K tile after a quarter of the product ...
+                    ldK.issue(nK_lds, kv_next);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if (DMA && i == 3 * NF / 4 - 1) {       // ... the next V tile after three quarters
-                    ldV.issue(nK_lds + TILE, kv0 + 64);
+                if (i == 3 * NF / 4 - 1) {              // ... the next V tile after three quarters
+                    ldV.issue(nK_lds + TILE, kv_next);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-        };
-        if (spread) first_product(std::true_type{});
-        else first_product(std::false_type{});
+        }
         // the first V^T fragments of the second product are fetched now and land during the softmax
         constexpr int NV = 4 * (HD / 32);
         bf16x8_t fv[NV];
         auto read_v = [&](int i) { fv[i] = read_tr<HD>(sV, tro, i / (HD / 32), i % (HD / 32)); };
 #pragma unroll
-        for (int i = 0; i < PV_AHEAD; ++i) read_v(i);
+        for (int i = 0; i < AHEAD_V; ++i) read_v(i);
         __builtin_amdgcn_sched_barrier(kFence);
         const bool need_mask = (kv0 + 64 > kl) || (CAUSAL && kv0 + 63 > qw0);
         if (need_mask) {
@@ -356,13 +416,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
             // its ~130 compare / select instructions would run on every step, not just on the diagonal and the tail
             int kbase = kv0;
             asm volatile("" : "+s"(kbase));
+            const int last = (CAUSAL ? min(kl - 1, qi) : kl - 1) - kbase - 4 * g;      // last visible row, as this lane counts them
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int key = kbase + kt * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
-                    if (key >= kl || (CAUSAL && key > qi)) sacc[kt][e] = -INFINITY;
-                }
+                for (int e = 0; e < 16; ++e)
+                    if (kt * 32 + 8 * (e >> 2) + (e & 3) > last) sacc[kt][e] = -INFINITY;
         }
         float mx = -INFINITY;
 #pragma unroll
@@ -388,17 +447,18 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnArgs a) {
                 for (int e = 0; e < 16; ++e) oacc[dt][e] *= alpha;
         }
         m = m_new;
-        // second product, O^T += V^T P^T: transpose reads PV_AHEAD MFMAs in front of their use
+        // second product, O^T += V^T P^T: transpose reads AHEAD_V MFMAs in front of their use
         bf16x8_t pf;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            if (i + PV_AHEAD < NV) read_v(i + PV_AHEAD);
+            if (i + AHEAD_V < NV) read_v(i + AHEAD_V);
             if (i % (HD / 32) == 0) pf = frag_from_acc(sacc[(i / (HD / 32)) >> 1], (i / (HD / 32)) & 1);
             __builtin_amdgcn_sched_barrier(kFence);
             oacc[i % (HD / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv[i], pf, oacc[i % (HD / 32)], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(kFence);
         }
     }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                 // no transfer may still be writing LDS when the work-group ends
     lsum += __shfl_xor(lsum, 32, 64);
     if (qi < ql) {
         const long long row = qrow0 + qi;
@@ -520,11 +580,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a) {
                 // the chain of exponentials into sixteen basic blocks
                 int kbase = kv0 + kt * 32;
                 asm volatile("" : "+s"(kbase));
+                const int last = (CAUSAL ? min(kl - 1, qi) : kl - 1) - kbase - 4 * g;  // last visible row, as this lane counts them
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int key = kbase + 8 * (e >> 2) + 4 * g + (e & 3);
-                    if (key >= kl || (CAUSAL && key > qi)) sacc[e] = 0.f;
-                }
+                for (int e = 0; e < 16; ++e)
+                    if (8 * (e >> 2) + (e & 3) > last) sacc[e] = 0.f;
             }
 #pragma unroll
             for (int e = 0; e < 16; ++e) sacc[e] *= pacc[e] - delta;          // dS^T
@@ -546,6 +605,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(AttnArgs a) {
 // LDS, a ring of four stages of: Q tile, dO tile ([64][HD]) and the two statistics tiles ([64 rows][8] bf16:
 // {hi, lo, 0 x 6} of lse/scale and of delta, as the dQ kernel left them).  Three blocks are in flight while one is
 // consumed: with one wavefront per SIMD (about 370 registers) nothing else hides the latency of the transfers.
+//
+// Persistent work-groups at head size 128 (PS): as many as fit on the chip, each drawing its next item (key block, head) while it works on the
+// current one, and requesting that item's first three query blocks and its K / V fragments BEFORE it stores the current
+// results.  With a work-group per item nothing hid what lies between two items (the end of one work-group, the start of
+// the next, three dependent table reads, the first tiles): about 10 of 27 us per item at 65 536 tokens of mean length 385,
+// where an item has 7.5 steps on average (1015 -> 962 us).  Not at head size 64, where two work-groups share a CU and
+// the dispatcher's replacement is quicker than a draw (one-step items 47 us, 59 with draws).
 template <int HD, bool CAUSAL>
 __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kernel(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -555,31 +621,20 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
-    const int item = blockIdx.x / a.n_heads, h = blockIdx.x - item * a.n_heads;
-    if (item >= a.n_items[1]) return;
-    const int2 it = a.items_k[item];
-    const int s = it.x, k0 = it.y * 128;
-    const int ql = a.q_len[s], kl = a.k_len[s];
-    const long long qrow0 = a.q_row[s], krow0 = a.k_row[s];
-    const bf16_t* Q = (const bf16_t*)a.q + qrow0 * a.ldq + h * HD;
-    const bf16_t* dO = (const bf16_t*)a.d_o + qrow0 * a.ldo + h * HD;
-    const bf16_t* K = (const bf16_t*)a.k + krow0 * a.ldk + h * HD;
-    const bf16_t* V = (const bf16_t*)a.v + krow0 * a.ldv + h * HD;
-    const int kw0 = k0 + wave * 32;
-    const int ki = kw0 + col;
-    const int ki_c = ki < kl ? ki : kl - 1;
-
-    const int q_begin = CAUSAL ? k0 : 0;
-    const int nb = (ql - q_begin + 63) / 64;            // >= 1: a key block exists only below the query count when causal
+    const uint32_t lds0 = lds_address(smem);
+    volatile int* s_next = reinterpret_cast<volatile int*>(smem + NS * STAGE);
     TileLoader<HD> ldQ, ldO;
-    ldQ.setup(Q, a.ldq, ql, wave, lane);
-    ldO.setup(dO, a.ldo, ql, wave, lane);
-    const char* aug_src = reinterpret_cast<const char*>(wave == 0 ? a.aug_lse : a.aug_delta) +
-                          ((size_t)h * a.lse_stride + qrow0) * 16;
+    ldQ.setup(nullptr, a.ldq, 0, wave, lane);
+    ldO.setup(nullptr, a.ldo, 0, wave, lane);
+    constexpr bool PS = dkv_persistent(HD);
+    WorkDraw draw(a, 1);
+    int kw0, ki, kl, ql, h, q_begin, nb;
+    long long krow0;
+    const char* aug_src;
+    bf16x8_t kf[HD / 16], vf[HD / 16];
     // block blk -> stage blk % 4: Q tile, dO tile, and (wavefronts 0 and 1) the two statistics tiles, all by direct
     // transfers; indices past the last block are clamped (redundant transfers into a free stage keep the count of
     // outstanding transfers the same at every step)
-    const uint32_t lds0 = lds_address(smem);
     auto issue_block = [&](int blk) {
         const uint32_t n = lds0 + (blk & (NS - 1)) * STAGE;
         const int bc = blk < nb ? blk : nb - 1;
@@ -592,18 +647,43 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
             lds_dma16_at(aug_src + (size_t)r * 16, n + 2 * TILE + wave * 1024);
         }
     };
-    if (nb > 0) {
-        issue_block(0);
-        issue_block(1);
-        issue_block(2);
-    }
-
-    bf16x8_t kf[HD / 16], vf[HD / 16];
+    // take up the item `draw` stands at: its tables, the first three blocks, the K / V fragments
+    auto begin_item = [&] {
+        const int item = draw.index() / a.n_heads;
+        h = draw.index() - item * a.n_heads;
+        const int2 it = a.items_k[item];
+        const int s = __builtin_amdgcn_readfirstlane(it.x), k0 = __builtin_amdgcn_readfirstlane(it.y) * 128;
+        ql = __builtin_amdgcn_readfirstlane(a.q_len[s]);
+        kl = __builtin_amdgcn_readfirstlane(a.k_len[s]);
+        const long long qrow0 = __builtin_amdgcn_readfirstlane(a.q_row[s]);
+        krow0 = __builtin_amdgcn_readfirstlane(a.k_row[s]);
+        kw0 = k0 + wave * 32;
+        ki = kw0 + col;
+        q_begin = CAUSAL ? k0 : 0;
+        nb = (ql - q_begin + 63) / 64;                  // (none: keys beyond the last query of a causal sequence)
+        ldQ.base = reinterpret_cast<const char*>((const bf16_t*)a.q + qrow0 * a.ldq + h * HD);
+        ldO.base = reinterpret_cast<const char*>((const bf16_t*)a.d_o + qrow0 * a.ldo + h * HD);
+        ldQ.n_valid = ldO.n_valid = ql;
+        aug_src = reinterpret_cast<const char*>(wave == 0 ? a.aug_lse : a.aug_delta) + ((size_t)h * a.lse_stride + qrow0) * 16;
+        if (nb > 0) {
+            issue_block(0);
+            issue_block(1);
+            issue_block(2);
+        }
+        const int ki_c = ki < kl ? ki : kl - 1;
+        const bf16_t* K = (const bf16_t*)a.k + (krow0 + ki_c) * a.ldk + h * HD;
+        const bf16_t* V = (const bf16_t*)a.v + (krow0 + ki_c) * a.ldv + h * HD;
 #pragma unroll
-    for (int ks = 0; ks < HD / 16; ++ks) {
-        kf[ks] = *reinterpret_cast<const bf16x8_t*>(K + (long long)ki_c * a.ldk + ks * 16 + g * 8);
-        vf[ks] = *reinterpret_cast<const bf16x8_t*>(V + (long long)ki_c * a.ldv + ks * 16 + g * 8);
+        for (int ks = 0; ks < HD / 16; ++ks) {
+            kf[ks] = *reinterpret_cast<const bf16x8_t*>(K + ks * 16 + g * 8);
+            vf[ks] = *reinterpret_cast<const bf16x8_t*>(V + ks * 16 + g * 8);
+        }
+    };
+    if (!draw.valid()) {
+        if (PS) draw.finish();
+        return;
     }
+    begin_item();
     bf16x8_t neg_ones;                                  // contraction slots 0, 1 (lane half 0) pick -hi - lo
 #pragma unroll
     for (int j = 0; j < 8; ++j) neg_ones[j] = (bf16_t)((g == 0 && j < 2) ? -1.0f : 0.0f);
@@ -615,18 +695,22 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
     const int rsw = swz<HD>(col);
 
     f32x16_t dkacc[HD / 32], dvacc[HD / 32];
+    for (;;) {
 #pragma unroll
     for (int dt = 0; dt < HD / 32; ++dt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) { dkacc[dt][e] = 0.f; dvacc[dt][e] = 0.f; }
 
-    // the K / V fragments (ordinary loads) are complete before the loop: left to the compiler, its waits for them
-    // would sit inside the loop as "nothing outstanding", which would also drain the transfers in flight
+    int next = 0;
+    if (PS) next = draw.take();                         // (needed after the loop)
+    // the K / V fragments (ordinary loads) and the stores of the item before are complete before the loop: left to the
+    // compiler, its waits for them would sit inside the loop as "nothing outstanding", which would also drain the
+    // transfers in flight
     __builtin_amdgcn_s_waitcnt(0x0F70);
-    // One step = one 64-query block.  The step exists in two versions, with and without the mask, and the loop is
-    // cut into three: the (at most two) blocks on the diagonal, the blocks in the middle, the ragged last block.  The
-    // middle loop, where the time goes, is then straight code: a mask test inside it, even one that is never taken,
-    // splits the live ranges of the 128 accumulator registers and costs hundreds of register copies per step.
+    // One step = one 64-query block, straight code: any branch inside it, even one that is never taken, splits the live
+    // ranges of the 128 accumulator registers and costs hundreds of register copies per step.  The step exists in two
+    // versions, with the mask as selects and without, and the loop is cut into three: the (at most two) blocks on the
+    // diagonal, the blocks in the middle, the ragged last block.
     const bool wave_has_keys = kw0 < kl;
     auto step = [&](int b, auto masked_t) {
         constexpr bool MASKED = decltype(masked_t)::value;
@@ -643,130 +727,59 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
         issue_block(b + 3);
         if (!wave_has_keys) return;
         if (MASKED && CAUSAL && q0 + 63 < kw0) return;
-        if constexpr (!MASKED) {
-            // Middle blocks: the two 32-query halves software-pipelined.  The exp / product work of half 0 sits between
-            // the MFMAs of half 1's first products, that of half 1 between the MFMAs of half 0's second products, so
-            // that the one wavefront of this SIMD keeps the matrix pipe and the vector ALU busy at the same time.
-            constexpr int NA = HD / 16 + 1, AHEAD = 3, ND = 2 * (HD / 32), AHEAD_D = 2;
-            f32x16_t sa[2], pa[2];
-            bf16x8_t fq[NA], fo[NA], td[ND], tq[ND], pf[2], dsf[2];
-            auto read_a = [&](int qt, int i) {
-                if (i < HD / 16) {
-                    const int o = qt * (32 * HD * 2) + rbase + (((i * 2 + g) ^ rsw) << 4);
-                    fq[i] = *reinterpret_cast<const bf16x8_t*>(sQ + o);
-                    fo[i] = *reinterpret_cast<const bf16x8_t*>(sdO + o);
-                } else {
-                    fq[i] = *reinterpret_cast<const bf16x8_t*>(s_lse + (qt * 32 + col) * 16);
-                    fo[i] = *reinterpret_cast<const bf16x8_t*>(s_delta + (qt * 32 + col) * 16);
-                }
-            };
-            auto softmax2 = [&](int qt, int e0) {         // two elements of half qt: P and dS in place
+        // queries of the block that see this lane's key, as this lane counts its rows: first .. first + visible - 1
+        const int first = (CAUSAL ? max(ki - q0, 0) : 0) - 4 * g;
+        const unsigned visible = (unsigned)max(ql - q0 - 4 * g - first, 0);
+        // The two 32-query halves software-pipelined.  The exp / product work of half 0 sits between
+        // the MFMAs of half 1's first products, that of half 1 between the MFMAs of half 0's second products, so
+        // that the one wavefront of this SIMD keeps the matrix pipe and the vector ALU busy at the same time.
+        constexpr int NA = HD / 16 + 1, AHEAD = 3, ND = 2 * (HD / 32), AHEAD_D = 2;
+        f32x16_t sa[2], pa[2];
+        bf16x8_t fq[NA], fo[NA], td[ND], tq[ND], pf[2], dsf[2];
+        auto read_a = [&](int qt, int i) {
+            if (i < HD / 16) {
+                const int o = qt * (32 * HD * 2) + rbase + (((i * 2 + g) ^ rsw) << 4);
+                fq[i] = *reinterpret_cast<const bf16x8_t*>(sQ + o);
+                fo[i] = *reinterpret_cast<const bf16x8_t*>(sdO + o);
+            } else {
+                fq[i] = *reinterpret_cast<const bf16x8_t*>(s_lse + (qt * 32 + col) * 16);
+                fo[i] = *reinterpret_cast<const bf16x8_t*>(s_delta + (qt * 32 + col) * 16);
+            }
+        };
+        auto softmax2 = [&](int qt, int e0) {         // two elements of half qt: P and dS in place
 #pragma unroll
-                for (int e = e0; e < e0 + 2; ++e) {
-                    const float p = __builtin_amdgcn_exp2f(sa[qt][e] * c);
-                    sa[qt][e] = p;
-                    pa[qt][e] = p * pa[qt][e];
-                }
-            };
-            auto phase_a = [&](int qt, bool with_prev) {
+            for (int e = e0; e < e0 + 2; ++e) {
+                float p = __builtin_amdgcn_exp2f(sa[qt][e] * c);
+                if (MASKED && (unsigned)(qt * 32 + 8 * (e >> 2) + (e & 3) - first) >= visible) p = 0.f;
+                sa[qt][e] = p;
+                pa[qt][e] = p * pa[qt][e];
+            }
+        };
+        auto phase_a = [&](int qt, bool with_prev) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) { sa[qt][e] = 0.f; pa[qt][e] = 0.f; }
+            for (int e = 0; e < 16; ++e) { sa[qt][e] = 0.f; pa[qt][e] = 0.f; }
 #pragma unroll
-                for (int i = 0; i < AHEAD; ++i) read_a(qt, i);
-#pragma unroll
-                for (int i = 0; i < NA; ++i) {
-                    if (i + AHEAD < NA) read_a(qt, i + AHEAD);
-                    __builtin_amdgcn_sched_barrier(kFence);
-                    sa[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[i], i < HD / 16 ? kf[i < HD / 16 ? i : 0] : neg_ones, sa[qt], 0, 0, 0);
-                    pa[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[i], i < HD / 16 ? vf[i < HD / 16 ? i : 0] : neg_ones, pa[qt], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(kFence);
-                    if (with_prev && i < NA - 1) {          // 16 / (NA - 1) elements of the other half per slice
-#pragma unroll
-                        for (int e = i * (16 / (NA - 1)); e < (i + 1) * (16 / (NA - 1)); e += 2) softmax2(qt ^ 1, e);
-                    }
-                }
-            };
-            auto phase_d = [&](int qt, bool with_next) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u) { pf[u] = frag_from_acc(sa[qt], u); dsf[u] = frag_from_acc(pa[qt], u); }
-                auto read_d = [&](int j) {
-                    td[j] = read_tr<HD>(sdO, tro, 2 * qt + j / (HD / 32), j % (HD / 32));
-                    tq[j] = read_tr<HD>(sQ, tro, 2 * qt + j / (HD / 32), j % (HD / 32));
-                };
-#pragma unroll
-                for (int j = 0; j < AHEAD_D; ++j) read_d(j);
-#pragma unroll
-                for (int j = 0; j < ND; ++j) {
-                    if (j + AHEAD_D < ND) read_d(j + AHEAD_D);
-                    __builtin_amdgcn_sched_barrier(kFence);
-                    dvacc[j % (HD / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(td[j], pf[j / (HD / 32)], dvacc[j % (HD / 32)], 0, 0, 0);
-                    dkacc[j % (HD / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq[j], dsf[j / (HD / 32)], dkacc[j % (HD / 32)], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(kFence);
-                    if (with_next) {
-#pragma unroll
-                        for (int e = j * (16 / ND); e < (j + 1) * (16 / ND); e += 2) softmax2(qt ^ 1, e);
-                    }
-                }
-            };
-            phase_a(0, false);
-            phase_a(1, true);          // + exp / products of half 0
-            phase_d(0, true);          // + exp / products of half 1
-            phase_d(1, false);
-            return;
-        }
-#pragma unroll
-        for (int qt = 0; qt < 2; ++qt) {
-            if (MASKED && (q0 + qt * 32 >= ql || (CAUSAL && q0 + qt * 32 + 31 < kw0))) continue;   // no visible query
-            f32x16_t sacc, pacc;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) { sacc[e] = 0.f; pacc[e] = 0.f; }
-            // S^T and dP^T: NA = HD/16 + 1 contraction slices (the last one is the appended statistics), two MFMAs each.
-            // The fragment reads run AHEAD slices in front of the MFMAs that use them (left alone, the compiler puts
-            // every read right before its MFMA, in the same four registers, and each MFMA waits a full LDS round
-            // trip); the fences keep LDS reads and MFMAs in this order, other instructions may move across.
-            constexpr int NA = HD / 16 + 1, AHEAD = 3;
-            bf16x8_t fq[NA], fo[NA];
-            auto read_a = [&](int i) {
-                if (i < HD / 16) {
-                    const int o = qt * (32 * HD * 2) + rbase + (((i * 2 + g) ^ rsw) << 4);
-                    fq[i] = *reinterpret_cast<const bf16x8_t*>(sQ + o);
-                    fo[i] = *reinterpret_cast<const bf16x8_t*>(sdO + o);
-                } else {
-                    fq[i] = *reinterpret_cast<const bf16x8_t*>(s_lse + (qt * 32 + col) * 16);
-                    fo[i] = *reinterpret_cast<const bf16x8_t*>(s_delta + (qt * 32 + col) * 16);
-                }
-            };
-#pragma unroll
-            for (int i = 0; i < AHEAD; ++i) read_a(i);
+            for (int i = 0; i < AHEAD; ++i) read_a(qt, i);
 #pragma unroll
             for (int i = 0; i < NA; ++i) {
-                if (i + AHEAD < NA) read_a(i + AHEAD);
+                if (i + AHEAD < NA) read_a(qt, i + AHEAD);
                 __builtin_amdgcn_sched_barrier(kFence);
-                // (last slice: score - lse/scale and dP - delta through the constant [-1, -1] operand)
-                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[i], i < HD / 16 ? kf[i < HD / 16 ? i : 0] : neg_ones, sacc, 0, 0, 0);
-                pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[i], i < HD / 16 ? vf[i < HD / 16 ? i : 0] : neg_ones, pacc, 0, 0, 0);
+                sa[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[i], i < HD / 16 ? kf[i < HD / 16 ? i : 0] : neg_ones, sa[qt], 0, 0, 0);
+                pa[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[i], i < HD / 16 ? vf[i < HD / 16 ? i : 0] : neg_ones, pa[qt], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(kFence);
-            }
+                if (with_prev && i < NA - 1) {          // 16 / (NA - 1) elements of the other half per slice
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                float p = __builtin_amdgcn_exp2f(sacc[e] * c);
-                if (MASKED) {
-                    const int q = q0 + qt * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
-                    if (q >= ql || (CAUSAL && q < ki)) p = 0.f;
+                    for (int e = i * (16 / (NA - 1)); e < (i + 1) * (16 / (NA - 1)); e += 2) softmax2(qt ^ 1, e);
                 }
-                sacc[e] = p;                                           // P
-                pacc[e] = p * pacc[e];                                 // dS
             }
-            // dV += dO^T P^T and dK += Q^T dS^T: ND = 2 * HD/32 pairs of MFMAs, transpose reads AHEAD_D pairs in front
-            constexpr int ND = 2 * (HD / 32), AHEAD_D = 2;
-            bf16x8_t td[ND], tq[ND];
+        };
+        auto phase_d = [&](int qt, bool with_next) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) { pf[u] = frag_from_acc(sa[qt], u); dsf[u] = frag_from_acc(pa[qt], u); }
             auto read_d = [&](int j) {
                 td[j] = read_tr<HD>(sdO, tro, 2 * qt + j / (HD / 32), j % (HD / 32));
                 tq[j] = read_tr<HD>(sQ, tro, 2 * qt + j / (HD / 32), j % (HD / 32));
             };
-            bf16x8_t pf[2], dsf[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) { pf[u] = frag_from_acc(sacc, u); dsf[u] = frag_from_acc(pacc, u); }
 #pragma unroll
             for (int j = 0; j < AHEAD_D; ++j) read_d(j);
 #pragma unroll
@@ -776,8 +789,16 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
                 dvacc[j % (HD / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(td[j], pf[j / (HD / 32)], dvacc[j % (HD / 32)], 0, 0, 0);
                 dkacc[j % (HD / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq[j], dsf[j / (HD / 32)], dkacc[j % (HD / 32)], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(kFence);
+                if (with_next) {
+#pragma unroll
+                    for (int e = j * (16 / ND); e < (j + 1) * (16 / ND); e += 2) softmax2(qt ^ 1, e);
+                }
             }
-        }
+        };
+        phase_a(0, false);
+        phase_a(1, true);          // + exp / products of half 0
+        phase_d(0, true);          // + exp / products of half 1
+        phase_d(1, false);
     };
     const int n_diag = CAUSAL ? min(2, nb) : 0;         // causal: queries k0 .. k0+127 meet this block's own keys
     const int n_full = (ql - q_begin) / 64;             // blocks b < n_full have all their 64 rows
@@ -785,11 +806,26 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
     for (; b < n_diag; ++b) step(b, std::true_type{});
     for (; b < n_full; ++b) step(b, std::false_type{});
     for (; b < nb; ++b) step(b, std::true_type{});
-    __builtin_amdgcn_s_waitcnt(0x0F70);                 // no transfer may still be writing LDS when the work-group ends
-    if (ki < kl) {
-        store_cols<HD>(dkacc, a.scale, (bf16_t*)a.dk + (krow0 + ki) * a.ldk + h * HD, g);
-        store_cols<HD>(dvacc, 1.0f, (bf16_t*)a.dv + (krow0 + ki) * a.ldv + h * HD, g);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                 // no transfer may still be writing LDS ...
+    const bool store = ki < kl;
+    bf16_t* dk = (bf16_t*)a.dk + (krow0 + ki) * a.ldk + h * HD;
+    bf16_t* dv = (bf16_t*)a.dv + (krow0 + ki) * a.ldv + h * HD;
+    bool more = false;
+    if constexpr (PS) {
+        if (tid == 0) *s_next = next;
+        __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();                   // ... and nobody is reading it any more
+        draw.advance(__builtin_amdgcn_readfirstlane(*s_next));
+        more = draw.valid();
+        if (more) begin_item();
     }
+    if (store) {
+        store_cols<HD>(dkacc, a.scale, dk, g);
+        store_cols<HD>(dvacc, 1.0f, dv, g);
+    }
+    if (!more) break;
+    }   // for (;;): the next item
+    if (PS) draw.finish();
 }
 
 template <class Kern>
@@ -799,6 +835,12 @@ ds_status set_smem(Kern kern, int bytes, bool& done) {
         done = true;
     }
     return DS_OK;
+}
+
+// work-groups of a persistent kernel, one to a compute unit: no more than there are items, a multiple of 8
+unsigned persistent_grid(unsigned items) {
+    const unsigned n_cu = (unsigned)gemm_cu_count(), n = items < n_cu ? items : n_cu;
+    return (n + 7) / 8 * 8;
 }
 
 template <int HD, bool CAUSAL>
@@ -819,14 +861,15 @@ ds_status bwd_launch(const AttnArgs& a, hipStream_t st) {
     auto kq = attn_bwd_dq_mfma_kernel<HD, CAUSAL>;
     auto kkv = attn_bwd_dkv_mfma_kernel<HD, CAUSAL>;
     const int smem_q = 4 * (64 * HD * 2);
-    const int smem_kv = 4 * (2 * (64 * HD * 2) + 2048);
+    const int smem_kv = 4 * (2 * (64 * HD * 2) + 2048) + 64;
     ds_status r = set_smem(kq, smem_q, attr_q);
     if (r != DS_OK) return r;
     r = set_smem(kkv, smem_kv, attr_kv);
     if (r != DS_OK) return r;
     hipLaunchKernelGGL(kq, dim3((unsigned)a.max_items_q * a.n_heads), dim3(256), smem_q, st, a);
     DS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(kkv, dim3((unsigned)a.max_items_k * a.n_heads), dim3(256), smem_kv, st, a);
+    const unsigned items_kv = (unsigned)a.max_items_k * a.n_heads;
+    hipLaunchKernelGGL(kkv, dim3(dkv_persistent(HD) ? persistent_grid(items_kv) : items_kv), dim3(256), smem_kv, st, a);
     DS_LAUNCH_CHECK();
     return DS_OK;
 }

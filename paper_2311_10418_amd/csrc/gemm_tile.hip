@@ -28,25 +28,6 @@ namespace {
 
 constexpr int T_KD = 64;                             // depth of a K tile
 
-// N direct transfers of 64 x 16 bytes under one M0 through ONE raw buffer (see lds_dma16_buffers_2x2: the buffer starts
-// 1024 (N - 1) bytes early and is as much longer, lane offsets come from dma_lane_offset<N>).
-template <int N>
-__device__ __forceinline__ void lds_dma16_buffer_group(i32x4_t buf, const uint32_t (&off)[N], uint32_t lds_addr) {
-    static_assert(N == 1 || N == 2 || N == 4, "group sizes in use");
-    const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_addr);
-    if constexpr (N == 1)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(off[0]), "s"(buf), "s"(m0v) : "memory", "m0");
-    else if constexpr (N == 2)
-        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds\n\t"
-                     "buffer_load_dwordx4 %1, %2, 0 offen offset:1024 lds"
-                     : : "v"(off[0]), "v"(off[1]), "s"(buf), "s"(m0v) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
-                     "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\tbuffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
-                     "buffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds"
-                     : : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(buf), "s"(m0v) : "memory", "m0");
-}
-
 // One operand's K tile: ROWS rows (m or n) x 64 k in LDS.
 //   k contiguous (KC): [row][128 bytes], 16-byte chunk c of a row at chunk slot c ^ ((row / 2) % 8); rows past the end of the
 //     tensor are clamped (read, never stored).
