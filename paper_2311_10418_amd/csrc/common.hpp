@@ -253,7 +253,24 @@ ds_status launch_gather_rows(int32_t dtype, int32_t out_rows, int32_t d, const v
 // out[c] = (accumulate ? out[c] : 0) + sum over p < n_partial of partial[p * n + c]   (float32, fixed summation order)
 ds_status launch_reduce_partials(int32_t n_partial, int32_t n, const float* partial, float* out, int32_t accumulate,
                                  hipStream_t st);
-// out[c][r] = in[r][c] (bf16); out leading dimension rows_pad, columns rows..rows_pad-1 zero-filled
-ds_status launch_transpose_bf16(int32_t rows, int32_t cols, int32_t rows_pad, const void* in, void* out, hipStream_t st);
+// out[i][c][r] = in[i][r][c] (bf16, rows and cols multiples of 8) for i < n; first_block is filled in by the launcher
+constexpr int kTransposeBatch = 24;
+struct TransposeBatch {
+    int n = 0;
+    const void* in[kTransposeBatch];
+    void* out[kTransposeBatch];
+    int32_t rows[kTransposeBatch], cols[kTransposeBatch], first_block[kTransposeBatch];
+};
+ds_status launch_transpose_bf16(TransposeBatch& b, hipStream_t st);
+// rows r < rows with row_valid[r] < 0 of n buffers (row_bytes a multiple of 16) are written as zeros
+constexpr int kZeroPadBatch = 32;
+struct ZeroPadBatch {
+    int n = 0;
+    void* buf[kZeroPadBatch];
+    int32_t row_bytes[kZeroPadBatch];
+};
+ds_status launch_zero_pad_rows(const ZeroPadBatch& b, int32_t rows, const int32_t* row_valid, hipStream_t st);
+// up to this many rows ds_colsum is a single launch
+constexpr int kColsumSmallRows = 512;
 ds_status launch_scatter_rows(int32_t dtype, int32_t in_rows, int32_t d, const void* in, void* out,
                               const int32_t* dst_row, hipStream_t st);

@@ -37,6 +37,19 @@ __global__ __launch_bounds__(256) void mask_rows_kernel(int rows, int d8, const 
     }
 }
 
+// blockIdx.y = buffer; one wavefront per row; only padding rows are written
+__global__ __launch_bounds__(256) void zero_pad_rows_kernel(ZeroPadBatch b, int rows, const int32_t* __restrict__ row_valid) {
+    const int w = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63;
+    const int nw = (gridDim.x * blockDim.x) >> 6;
+    const int row16 = b.row_bytes[blockIdx.y] / 16;
+    uint4* buf = static_cast<uint4*>(b.buf[blockIdx.y]);
+    for (int r = w; r < rows; r += nw) {
+        if (row_valid[r] >= 0) continue;
+        uint4* p = buf + (size_t)r * row16;
+        for (int c = lane; c < row16; c += 64) p[c] = make_uint4(0u, 0u, 0u, 0u);
+    }
+}
+
 template <class T>
 __global__ __launch_bounds__(256) void gather_rows_kernel(int out_rows, int d8, const T* __restrict__ in, T* __restrict__ out,
                                                           const int32_t* __restrict__ src_row) {
@@ -72,35 +85,38 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(int in_rows, int d8, 
 }
 
 // ------------------------------------------------------------------ bf16 transpose
-// out[c][r] = in[r][c] for r < rows, zero for rows <= r < rows_pad (out has leading dimension rows_pad).
-// One wavefront per 64x64 tile as 8x8 blocks of 8x8 elements: each lane loads 8 rows of 16 bytes,
-// transposes them in registers (v_perm_b32) and stores 8 rows of 16 bytes; lanes are arranged 8x8 so
+// out[c][r] = in[r][c] for up to kTransposeBatch matrices in one launch (the weight copies of a stage: one launch of a few
+// microseconds per matrix is mostly launch).  One wavefront per 64x64 tile as 8x8 blocks of 8x8 elements: each lane loads
+// 8 rows of 16 bytes, transposes them in registers (v_perm_b32) and stores 8 rows of 16 bytes; lanes are arranged 8x8 so
 // that both the loads and the stores form 128-byte contiguous segments.  No LDS.
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(int rows, int cols, int rows_pad, const bf16_t* __restrict__ in,
-                                                             bf16_t* __restrict__ out) {
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(TransposeBatch b) {
+    int i = 0;
+    while (i + 1 < b.n && (int)blockIdx.x >= b.first_block[i + 1]) ++i;
+    const bf16_t* in = static_cast<const bf16_t*>(b.in[i]);
+    bf16_t* out = static_cast<bf16_t*>(b.out[i]);
+    const int rows = b.rows[i], cols = b.cols[i];
+    const int block = blockIdx.x - b.first_block[i], gx = (cols + 63) / 64;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int bx = lane & 7, by = lane >> 3;
-    const int c0 = blockIdx.x * 64 + bx * 8;
-    const int r0 = (blockIdx.y * 4 + wave) * 64 + by * 8;
-    if (r0 >= rows_pad || c0 >= cols) return;
+    const int c0 = (block % gx) * 64 + bx * 8;
+    const int r0 = ((block / gx) * 4 + wave) * 64 + by * 8;
+    if (r0 >= rows || c0 >= cols) return;
     uint32_t v[8][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = r0 + i;
-        uint4 x = make_uint4(0u, 0u, 0u, 0u);
-        if (r < rows) x = *reinterpret_cast<const uint4*>(in + (size_t)r * cols + c0);
-        v[i][0] = x.x; v[i][1] = x.y; v[i][2] = x.z; v[i][3] = x.w;
+    for (int k = 0; k < 8; ++k) {
+        const uint4 x = *reinterpret_cast<const uint4*>(in + (size_t)(r0 + k) * cols + c0);
+        v[k][0] = x.x; v[k][1] = x.y; v[k][2] = x.z; v[k][3] = x.w;
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {          // output row c0+i gathers element i of the 8 loaded rows
-        const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-        const int w = i >> 1;
+    for (int k = 0; k < 8; ++k) {          // output row c0+k gathers element k of the 8 loaded rows
+        const uint32_t sel = (k & 1) ? 0x07060302u : 0x05040100u;
+        const int w = k >> 1;
         uint4 o;
         o.x = __builtin_amdgcn_perm(v[1][w], v[0][w], sel);
         o.y = __builtin_amdgcn_perm(v[3][w], v[2][w], sel);
         o.z = __builtin_amdgcn_perm(v[5][w], v[4][w], sel);
         o.w = __builtin_amdgcn_perm(v[7][w], v[6][w], sel);
-        *reinterpret_cast<uint4*>(out + (size_t)(c0 + i) * rows_pad + r0) = o;
+        *reinterpret_cast<uint4*>(out + (size_t)(c0 + k) * rows + r0) = o;
     }
 }
 
@@ -528,6 +544,38 @@ __global__ __launch_bounds__(256) void colsum_kernel(int rows, int n, const T* _
     }
 }
 
+// Few rows: one launch.  A work-group owns 32 columns (4 lanes of 8) and all rows, 64 row lanes.
+template <class T>
+__global__ __launch_bounds__(256) void colsum_small_kernel(int rows, int n, const T* __restrict__ x, float* __restrict__ out, int accumulate) {
+    __shared__ float red[4][32];
+    const int cx = threadIdx.x & 3, ry = threadIdx.x >> 2;
+    const int col = blockIdx.x * 32 + cx * 8;
+    float acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+    if (col < n)
+        for (int r = ry; r < rows; r += 64) {
+            float v[8];
+            Vec8<T>::load(x + (size_t)r * n + col, v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += v[j];
+        }
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], o, 64);
+    if ((threadIdx.x & 63) < 4) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) red[threadIdx.x >> 6][cx * 8 + j] = acc[j];
+    }
+    __syncthreads();
+    const int c = blockIdx.x * 32 + threadIdx.x;
+    if (threadIdx.x < 32 && c < n) {
+        const float s = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+        out[c] = accumulate ? out[c] + s : s;
+    }
+}
+
 template <class T, bool RMS>
 ds_status norm_fwd_dispatch(int rows, int d, const T* x, const T* g, const T* b, T* y, float* stats, hipStream_t st) {
     const int ni = (d + 511) / 512;
@@ -589,6 +637,15 @@ ds_status launch_mask_rows(int32_t dtype, int32_t rows, int32_t d, const void* i
     return DS_OK;
 }
 
+ds_status launch_zero_pad_rows(const ZeroPadBatch& b, int32_t rows, const int32_t* row_valid, hipStream_t st) {
+    if (rows <= 0 || b.n <= 0) return DS_OK;
+    int blocks = (rows + 3) / 4;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(zero_pad_rows_kernel, dim3(blocks, b.n), dim3(256), 0, st, b, rows, row_valid);
+    DS_LAUNCH_CHECK();
+    return DS_OK;
+}
+
 ds_status launch_gather_rows(int32_t dtype, int32_t out_rows, int32_t d, const void* in, void* out,
                              const int32_t* src_row, hipStream_t st) {
     if (out_rows <= 0) return DS_OK;
@@ -619,10 +676,15 @@ ds_status launch_scatter_rows(int32_t dtype, int32_t in_rows, int32_t d, const v
     return DS_OK;
 }
 
-ds_status launch_transpose_bf16(int32_t rows, int32_t cols, int32_t rows_pad, const void* in, void* out, hipStream_t st) {
-    if (rows <= 0 || cols <= 0 || cols % 8 || rows_pad < rows || rows_pad % 8 || !in || !out) return DS_EINVAL;
-    dim3 grid((cols + 63) / 64, (rows_pad + 255) / 256);
-    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, st, rows, cols, rows_pad, (const bf16_t*)in, (bf16_t*)out);
+ds_status launch_transpose_bf16(TransposeBatch& b, hipStream_t st) {
+    int blocks = 0;
+    for (int i = 0; i < b.n; ++i) {
+        if (b.rows[i] <= 0 || b.cols[i] <= 0 || b.rows[i] % 8 || b.cols[i] % 8 || !b.in[i] || !b.out[i]) return DS_EINVAL;
+        b.first_block[i] = blocks;
+        blocks += ((b.cols[i] + 63) / 64) * ((b.rows[i] + 255) / 256);
+    }
+    if (blocks == 0) return DS_OK;
+    hipLaunchKernelGGL(transpose_bf16_kernel, dim3(blocks), dim3(256), 0, st, b);
     DS_LAUNCH_CHECK();
     return DS_OK;
 }
@@ -667,9 +729,17 @@ ds_status launch_reduce_partials(int32_t n_partial, int32_t n, const float* part
     return reduce_launch(n_partial, n, (size_t)n, partial, out, accumulate, nullptr, nullptr, false, st);
 }
 
-// Column sums in two kernels: gy partial rows of n floats each (gy <= max_partial_rows), then their sum in a fixed order.
+// Column sums: one kernel for few rows (eight rows per lane: the second launch costs more than they do); otherwise two,
+// gy partial rows of n floats each (gy <= max_partial_rows), then their sum in a fixed order.
 static ds_status colsum_launch(int32_t dtype, int32_t rows, int32_t n, const void* x, float* out, float* partial,
                                int max_partial_rows, int32_t accumulate, hipStream_t st) {
+    if (rows <= kColsumSmallRows) {
+        const dim3 grid((n + 31) / 32);
+        if (dtype == DS_DTYPE_BF16) hipLaunchKernelGGL(colsum_small_kernel<bf16_t>, grid, dim3(256), 0, st, rows, n, (const bf16_t*)x, out, accumulate);
+        else hipLaunchKernelGGL(colsum_small_kernel<float>, grid, dim3(256), 0, st, rows, n, (const float*)x, out, accumulate);
+        DS_LAUNCH_CHECK();
+        return DS_OK;
+    }
     const int gx = (n / 8 + 63) / 64;
     int gy = (rows + 31) / 32;                      // 32 rows per work-group: fewer partial rows than data by as much
     int cap = kPartialRows / gx > 0 ? kPartialRows / gx : 1;

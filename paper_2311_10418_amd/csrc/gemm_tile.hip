@@ -83,7 +83,6 @@ template <int ROWS, bool KC, int NW> struct OperandTile {
             return *reinterpret_cast<const bf16x8_t*>(tile + row * (T_KD * 2) + ((chunk ^ chunk_swz(row)) << 4));
         } else {
             typedef short s16x4_t __attribute__((ext_vector_type(4)));
-            typedef short s16x8_t __attribute__((ext_vector_type(8)));
             typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
             const int k = ks * 32 + 4 * (lane >> 4) + ((lane & 15) >> 2);
             const char* q = tile + k * (ROWS * 2) + ((unit ^ unit_swz(k)) << 5) + (lane & 3) * 8;

@@ -27,18 +27,6 @@
 
 namespace {
 
-__global__ __launch_bounds__(256) void zero_pad_rows_kernel(int rows, int row_bytes16, uint4* __restrict__ buf,
-                                                            const int32_t* __restrict__ row_valid) {
-    // one wavefront per row; only padding rows are written
-    const int w = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63;
-    const int nw = (gridDim.x * blockDim.x) >> 6;
-    for (int r = w; r < rows; r += nw) {
-        if (row_valid[r] >= 0) continue;
-        uint4* p = buf + (size_t)r * row_bytes16;
-        for (int c = lane; c < row_bytes16; c += 64) p[c] = make_uint4(0u, 0u, 0u, 0u);
-    }
-}
-
 // Bump allocator over the workspace.  With base == nullptr it only measures.
 struct Arena {
     char* base = nullptr;
@@ -85,6 +73,7 @@ struct ds_stage {
     int32_t* h_tables = nullptr;       // pinned staging for table uploads
     hipEvent_t upload_done = nullptr;
     uint64_t bound_uid = 0;
+    uint64_t pads_uid = 0;             // the layout whose padding rows zero_pads_of_layout has cleared
     std::vector<GptBufs> gpt;
     std::vector<T5Bufs> enc, dec;
     // backward temporaries (sized for the longer stream)
@@ -260,6 +249,7 @@ ds_status bind_layout(ds_stage* s, const ds_layout* lo, hipStream_t st) {
     // a previous upload may still be reading the staging buffer
     DS_HIP_CHECK(hipEventSynchronize(s->upload_done));
     s->bound_uid = 0;
+    s->pads_uid = 0;
     DS_TRY(upload_stream(s, s->main, s->h_tables, s->cfg.max_rows, lo->total_rows, lo->n_seq, lo->seq_row, lo->seq_len,
                          lo->total_tokens, st));
     if (t5)
@@ -335,18 +325,32 @@ struct Ops {
         return gemm_raw(DS_PROF_GEMM_WGRAD, 1, 0, K, N, sm.R, X, dY, dW, DS_EPI_ACC32, nullptr, nullptr, nullptr, nullptr,
                         nullptr, accumulate);
     }
-    ds_status weight_t(int K, int N, const void* W, void* Wt) {      // [K][N] -> [N][K]
-        s->launches++;
-        return launch_transpose_bf16(K, N, K, W, Wt, st);
+    // [K][N] -> [N][K] copies of the weights, gathered into as few launches as the batch allows
+    TransposeBatch tb;
+    ds_status weight_t(int K, int N, const void* W, void* Wt) {
+        if (tb.n == kTransposeBatch) DS_TRY(weights_t_flush());
+        tb.in[tb.n] = W;
+        tb.out[tb.n] = Wt;
+        tb.rows[tb.n] = K;
+        tb.cols[tb.n++] = N;
+        return DS_OK;
+    }
+    ds_status weights_t_flush() {
+        if (tb.n == 0) return DS_OK;
+        s->launches += tb.n;                        // (the rough count keeps one per matrix copied, however many a launch takes)
+        const ds_status r = launch_transpose_bf16(tb, st);
+        tb.n = 0;
+        return r;
     }
     ds_status colsum(const Stream& sm, int n, const void* x, void* out) {
-        s->launches += 2;
+        s->launches += sm.R <= kColsumSmallRows ? 1 : 2;
         return timed(s, DS_PROF_COLSUM, st, [&] { return ds_colsum(dt, sm.R, n, x, (float*)out, s->partial, accumulate, st); });
     }
     // The same on the side stream: starts once everything enqueued so far on the main stream is done, runs beside
-    // what is enqueued after it.  x must stay as it is, and out untouched, until join_side().
+    // what is enqueued after it.  x must stay as it is, and out untouched, until join_side().  A sum over few rows is one
+    // short launch, less than the four calls that fork and join the streams.
     ds_status colsum_side(const Stream& sm, int n, const void* x, void* out) {
-        if (!s->side) return colsum(sm, n, x, out);
+        if (!s->side || sm.R <= kColsumSmallRows) return colsum(sm, n, x, out);
         s->launches += 2;
         DS_HIP_CHECK(hipEventRecord(s->ev_fork, st));
         DS_HIP_CHECK(hipStreamWaitEvent(s->side, s->ev_fork, 0));
@@ -379,15 +383,38 @@ struct Ops {
     }
     ds_status zero_pad(const Stream& sm, void* buf, int cols) {
         if (!sm.has_pad) return DS_OK;
-        return timed(s, DS_PROF_OTHER, st, [&] {
-            const int row16 = (int)((size_t)cols * s->es / 16);
-            int blocks = (sm.R + 3) / 4;
-            if (blocks > 4096) blocks = 4096;
-            hipLaunchKernelGGL(zero_pad_rows_kernel, dim3(blocks), dim3(256), 0, st, sm.R, row16, (uint4*)buf, sm.row_valid);
-            DS_LAUNCH_CHECK();
+        ZeroPadBatch z;
+        z.n = 1;
+        z.buf[0] = buf;
+        z.row_bytes[0] = (int)((size_t)cols * s->es);
+        s->launches++;
+        return timed(s, DS_PROF_OTHER, st, [&] { return launch_zero_pad_rows(z, sm.R, sm.row_valid, st); });
+    }
+    // Decoder-only stage: the padding rows of every layer's attention output and of dqkv.  Only the attention kernels write
+    // these buffers, and only valid rows, so the zeros stay until another layout is bound: cleared once per layout, all
+    // buffers in one launch.
+    ds_status zero_pads_of_layout(const Stream& sm) {
+        if (!sm.has_pad || s->pads_uid == s->bound_uid) return DS_OK;
+        s->pads_uid = 0;
+        ZeroPadBatch z;
+        auto flush = [&] {
             s->launches++;
+            const ds_status r = timed(s, DS_PROF_OTHER, st, [&] { return launch_zero_pad_rows(z, sm.R, sm.row_valid, st); });
+            z.n = 0;
+            return r;
+        };
+        auto add = [&](void* buf, size_t cols) -> ds_status {
+            if (z.n == kZeroPadBatch) DS_TRY(flush());
+            z.buf[z.n] = buf;
+            z.row_bytes[z.n++] = (int32_t)(cols * s->es);
             return DS_OK;
-        });
+        };
+        DS_TRY(add(s->dqkv, 3 * (size_t)d));
+        for (size_t l = 0; l < s->gpt.size(); ++l)
+            if (l == 0 || s->gpt[l].o != s->gpt[0].o) DS_TRY(add(s->gpt[l].o, (size_t)d));
+        DS_TRY(flush());
+        s->pads_uid = s->bound_uid;
+        return DS_OK;
     }
     AttnArgs attn_args(const Stream& q, const Stream& k, int mask) {
         const int h = s->cfg.n_heads, hd = d / h;
@@ -432,7 +459,7 @@ struct Ops {
         s->launches += a.lists_ready ? 1 : 3;
         DS_TRY(timed(s, DS_PROF_ATTN_FWD, st, [&] { return launch_attention_fwd(a, false, st); }));
         lists_built(a);
-        return zero_pad(sm, o, d);
+        return s->cfg.model == DS_MODEL_GPT ? DS_OK : zero_pad(sm, o, d);
     }
     ds_status self_bwd(const Stream& sm, int mask, const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv) {
         AttnArgs a = attn_args(sm, sm, mask);
@@ -445,7 +472,7 @@ struct Ops {
         s->launches += a.lists_ready ? 2 : 4;
         DS_TRY(timed(s, DS_PROF_ATTN_BWD, st, [&] { return launch_attention_bwd(a, false, st); }));
         lists_built(a);
-        return zero_pad(sm, dqkv, 3 * d);
+        return s->cfg.model == DS_MODEL_GPT ? DS_OK : zero_pad(sm, dqkv, 3 * d);
     }
 };
 
@@ -467,10 +494,12 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
                 DS_TRY(op.weight_t(d, F, w[l].w_1, b.w1_t));
                 DS_TRY(op.weight_t(F, d, w[l].w_2, b.w2_t));
             }
-            return DS_OK;
+            return op.weights_t_flush();
         }));
         s->wt_key.assign((const char*)w, (const char*)w + key_bytes);
     }
+
+    DS_TRY(op.zero_pads_of_layout(sm));
 
     // ---------------- forward (ForwardPass of every micro-batch)
     const void* x_in = io->act_in;
@@ -614,7 +643,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
                 DS_TRY(op.weight_t(d, F, wd[l].w_u, b.wu_t));
                 DS_TRY(op.weight_t(F, d, wd[l].w_2, b.w2_t));
             }
-            return DS_OK;
+            return op.weights_t_flush();
         }));
         s->wt_key.assign((const char*)we, (const char*)we + key_e);
         s->wt_key.insert(s->wt_key.end(), (const char*)wd, (const char*)wd + key_d);
