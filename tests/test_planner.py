@@ -140,3 +140,35 @@ def test_planner_is_reentrant():
     with concurrent.futures.ThreadPoolExecutor(max_workers=4) as ex:
         res = list(ex.map(run, range(8)))
     assert len(set(res)) == 1
+
+
+def test_many_equal_sums_and_non_monotone_costs():
+    """The incremental recurrence: costs of few distinct values (every candidate admits many slices at once, most sums tie),
+    not monotone in the slice, more than 64 positions, with and without a cap that leaves gaps; the number of stages decides
+    where the cut-off falls."""
+    rng = np.random.default_rng(24)
+    for _ in range(120):
+        n = int(rng.integers(30, 140))
+        lmax = int(rng.integers(1, 6))
+        lens = rng.integers(1, lmax + 1, size=n).astype(np.int32)
+        table = rng.integers(1, int(rng.choice([3, 8, 40])), size=(n, lmax)).astype(np.int64)
+        cap = int(rng.choice([lmax, 4 * lmax, n * lmax]))
+        _same(lens, cap, int(rng.choice([1, 2, 3, 8, 64])), kind=ds.DS_COST_TABLE, table=table)
+
+
+@pytest.mark.parametrize("fixed", [2 ** 55, 2 ** 58, 2 ** 60, 2 ** 61])
+def test_costs_near_the_integer_limit(fixed):
+    """Where slice costs, sums or objectives leave int64 the planner reports what it reported when every candidate scanned
+    every slice: either the oracle's plan or an overflow."""
+    rng = np.random.default_rng(25)
+    for _ in range(20):
+        n = int(rng.integers(1, 12))
+        lens = rng.integers(1, 9, size=n).astype(np.int32)
+        c, cap = int(rng.choice([1, 2, 4])), int(rng.choice([9, 40]))
+        try:
+            lo = ds.dp_plan(lens, ds.make_cost_model(fixed=fixed, lin=1), cap, c)
+        except ds.DsError as e:
+            assert e.code == ds.DS_EOVERFLOW
+            continue
+        ref = oplan.plan(lens, cap, c, fixed=fixed, lin=1)
+        assert list(lo.cuts) == list(ref["cuts"]) and lo.objective == ref["objective"] and lo.t_max == ref["t_max"]
