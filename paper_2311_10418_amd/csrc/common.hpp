@@ -248,8 +248,15 @@ static inline size_t dtype_size(int32_t dtype) { return dtype == DS_DTYPE_BF16 ?
 // ---- launchers shared between translation units (all enqueue on `st`, return ds_status)
 ds_status launch_mask_rows(int32_t dtype, int32_t rows, int32_t d, const void* in, void* out,
                            const int32_t* row_valid, hipStream_t st);
-ds_status launch_gather_rows(int32_t dtype, int32_t out_rows, int32_t d, const void* in, void* out,
-                             const int32_t* src_row, hipStream_t st);
+// Segments of a padded stream in ascending row order: rows row[i] .. + len[i] - 1 are the canonical rows canon[i] .., the
+// rows from there to row[i + 1] (of the last one: to end) are padding.  3 KB, passed by value.
+constexpr int kRowSegments = 250;
+struct RowSegments {
+    int32_t n = 0, end = 0;
+    int32_t row[kRowSegments], len[kRowSegments], canon[kRowSegments];
+};
+// to_stream: canonical -> stream, padding rows zeroed; otherwise stream -> canonical.  row_bytes: a multiple of 16
+ds_status launch_move_rows(const RowSegments& b, int32_t row_bytes, const void* in, void* out, bool to_stream, hipStream_t st);
 // out[c] = (accumulate ? out[c] : 0) + sum over p < n_partial of partial[p * n + c]   (float32, fixed summation order)
 ds_status launch_reduce_partials(int32_t n_partial, int32_t n, const float* partial, float* out, int32_t accumulate,
                                  hipStream_t st);
@@ -272,5 +279,3 @@ struct ZeroPadBatch {
 ds_status launch_zero_pad_rows(const ZeroPadBatch& b, int32_t rows, const int32_t* row_valid, hipStream_t st);
 // up to this many rows ds_colsum is a single launch
 constexpr int kColsumSmallRows = 512;
-ds_status launch_scatter_rows(int32_t dtype, int32_t in_rows, int32_t d, const void* in, void* out,
-                              const int32_t* dst_row, hipStream_t st);

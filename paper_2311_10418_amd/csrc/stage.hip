@@ -23,6 +23,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <numeric>
 #include <vector>
 
 namespace {
@@ -915,9 +916,8 @@ extern "C" ds_status stage_fwd_bwd(ds_stage* s, const ds_layout* lo, const void*
 }
 
 // ---------------------------------------------------------------------------- pack / unpack
-// canonical: sequences back to back in ORIGINAL sample order.  Builds the row map on the host,
-// uploads it, runs one gather / scatter kernel.  Helper outside any timed region: it allocates
-// and synchronises.
+// canonical: sequences back to back in ORIGINAL sample order.  The segments of the stream go out as kernel arguments, one
+// launch per kRowSegments of them; the call returns when the rows have been moved.
 static ds_status pack_common(const ds_layout* lo, int which, int dtype, int d, const void* src, void* dst, bool to_stream,
                              hipStream_t st) {
     if (!lo || !src || !dst || d <= 0 || d % 8) return DS_EINVAL;
@@ -926,27 +926,44 @@ static ds_status pack_common(const ds_layout* lo, int which, int dtype, int d, c
     if (which == 1 && !lo->has_tgt) return DS_ELAYOUT;
     const std::vector<int32_t>& seq_row = which ? lo->seq_row_tgt : lo->seq_row;
     const std::vector<int32_t>& seq_len = which ? lo->seq_len_tgt : lo->seq_len;
-    const int rows = which ? lo->total_rows_tgt : lo->total_rows;
-    // canonical offset of each original sample
-    std::vector<int64_t> canon(lo->n_seq + 1, 0);
-    {
-        std::vector<int32_t> len_orig(lo->n_seq);
-        for (int sidx = 0; sidx < lo->n_seq; ++sidx) len_orig[lo->perm[sidx]] = seq_len[sidx];
-        for (int i = 0; i < lo->n_seq; ++i) canon[i + 1] = canon[i] + len_orig[i];
+    const int rows = which ? lo->total_rows_tgt : lo->total_rows, n = lo->n_seq;
+    try {
+        // canonical offset of each original sample
+        std::vector<int32_t> canon(n), order(n);
+        for (int i = 0; i < n; ++i) canon[lo->perm[i]] = seq_len[i];
+        int64_t at = 0;
+        for (int32_t& c : canon) {
+            const int32_t l = c;
+            c = (int32_t)at;
+            at += l;
+        }
+        if (at > INT32_MAX) return DS_EOVERFLOW;
+        std::iota(order.begin(), order.end(), 0);
+        std::sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return seq_row[a] < seq_row[b]; });
+        RowSegments b;
+        auto flush = [&](int end) -> ds_status {
+            b.end = end;
+            const ds_status r = launch_move_rows(b, d * (int)dtype_size(dtype), src, dst, to_stream, st);
+            b.n = 0;
+            return r;
+        };
+        auto add = [&](int row, int len, int c) {
+            b.row[b.n] = row;
+            b.len[b.n] = len;
+            b.canon[b.n++] = c;
+        };
+        if (n == 0 || seq_row[order[0]] > 0) add(0, 0, 0);              // padding in front of the first sequence
+        for (int k = 0; k < n; ++k) {
+            const int s = order[k];
+            if (b.n == kRowSegments) DS_TRY(flush(seq_row[s]));
+            add(seq_row[s], seq_len[s], canon[lo->perm[s]]);
+        }
+        DS_TRY(flush(rows));
+    } catch (const std::bad_alloc&) {
+        return DS_ENOMEM;
     }
-    std::vector<int32_t> map(rows, -1);
-    for (int sidx = 0; sidx < lo->n_seq; ++sidx)
-        for (int r = 0; r < seq_len[sidx]; ++r) map[seq_row[sidx] + r] = (int32_t)(canon[lo->perm[sidx]] + r);
-    int32_t* dmap = nullptr;
-    DS_HIP_CHECK(hipMalloc((void**)&dmap, sizeof(int32_t) * (size_t)rows));
-    ds_status r = DS_OK;
-    if (hipMemcpyAsync(dmap, map.data(), sizeof(int32_t) * (size_t)rows, hipMemcpyHostToDevice, st) != hipSuccess) r = DS_EHIP;
-    if (r == DS_OK)
-        r = to_stream ? launch_gather_rows(dtype, rows, d, src, dst, dmap, st)
-                      : launch_scatter_rows(dtype, rows, d, src, dst, dmap, st);
-    if (hipStreamSynchronize(st) != hipSuccess && r == DS_OK) r = DS_EHIP;
-    (void)hipFree(dmap);
-    return r;
+    DS_HIP_CHECK(hipStreamSynchronize(st));
+    return DS_OK;
 }
 
 extern "C" ds_status ds_pack(const ds_layout* lo, int32_t which, int32_t dtype, int32_t d, const void* canonical,

@@ -639,3 +639,36 @@ def test_gemm_smaller_tiles_weight_gradient(M, N, K):
         ds.ds_gemm(dX, ddY, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, accumulate=True, workspace=ws)
         torch.cuda.synchronize()
         assert both_err(to_np(c), 2 * ref) <= 1e-5
+
+
+@pytest.mark.parametrize("dt", [F32, BF])
+@pytest.mark.parametrize("form,n,d", [("dp", 1, 8), ("dp", 40, 264), ("packed", 60, 128), ("fixed", 600, 24), ("dp", 1000, 16), ("target", 300, 72)])
+def test_pack_unpack_forms(dt, form, n, d):
+    """Layouts in and out of row order, gaps at every kind of place, more sequences than one launch's arguments hold, a target
+    stream: every value moved once, padding rows zeroed over what was there."""
+    rng = np.random.default_rng(37)
+    lens = np.clip(np.rint(rng.lognormal(2.5, 0.8, n)), 1, 90).astype(np.int32)
+    if form == "packed":
+        lo = ds.ds_layout_packed(lens, 96, 3)
+    elif form == "fixed":
+        lo = ds.ds_layout_from_cuts(lens, list(range(0, n, 7)) + [n], perm=rng.permutation(n).astype(np.int32), pad_to=95)
+    elif form == "target":
+        lo = ds.ds_layout_from_cuts(np.full(n, 3, np.int32), list(range(0, n, 7)) + [n], lengths_tgt=lens)
+    else:
+        lo = ds.dp_plan(lens, ds.make_cost_model(fixed=3_000_00, lin=1), 1024, 2)
+    which = 1 if form == "target" else 0
+    rows = lo.total_rows_tgt if which else lo.total_rows
+    seq_row, seq_len = (lo.seq_row_tgt, lo.seq_len_tgt) if which else (lo.seq_row, lo.seq_len)
+    canon = _rnd(rng, (int(lens.sum()), d), dt)
+    start = np.cumsum(lens) - lens
+    ref = np.zeros((rows, d))
+    for s in range(n):
+        i = int(lo.perm[s])
+        ref[seq_row[s]:seq_row[s] + seq_len[s]] = canon[start[i]:start[i] + lens[i]]
+    cd, stream = to_dev(canon, dt), torch.full((rows + 1, d), 7.0, dtype=dt, device=DEV)
+    ds.ds_pack(lo, cd, stream, which=which)
+    back = torch.full((canon.shape[0] + 1, d), 7.0, dtype=dt, device=DEV)
+    ds.ds_unpack(lo, stream, back, which=which)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_np(stream)[:rows], ref) and np.all(to_np(stream)[rows] == 7.0)
+    assert np.array_equal(to_np(back)[:-1], canon) and np.all(to_np(back)[-1] == 7.0)
