@@ -846,8 +846,9 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
                 const size_t wsf = split_ws ? split_ws_floats : 0;
                 const BigPlan plan = plan_big(tn, EPI, M, N, K, wsf);
                 if (plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
-                    const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, p.colsum != nullptr);
-                    if (pick.kind >= 0 && pick.cost < big_cost(plan, tn, M, N))
+                    const double out_us = gemm_output_us(EPI, M, N, p.accumulate);
+                    const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, p.colsum != nullptr, out_us);
+                    if (pick.kind >= 0 && pick.cost < 0.95 * (big_cost(plan, tn, M, N) + out_us))      // (ties go to the large tile)
                         return launch_gemm_tile(pick, tn, M, N, K, A, B, C, EPI, p, split_ws, st);
                 }
             }

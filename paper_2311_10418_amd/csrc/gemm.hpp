@@ -33,7 +33,12 @@ struct TilePick {
     int kind, splits;
     double cost;
 };
-TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum);
+TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us);
+// microseconds (4 TB/s) to write an fp32 output and, when it is added to, to read it first: weight gradients of few tokens
+// take about as long for this as for the products
+inline double gemm_output_us(int epilogue, int32_t M, int32_t N, int accumulate) {
+    return epilogue == DS_EPI_ACC32 ? 1e-6 * (accumulate ? 2.0 : 1.0) * M * N : 0.0;
+}
 ds_status launch_gemm_tile(const TilePick& pick, bool tn, int32_t M, int32_t N, int32_t K, const void* A, const void* B, void* C,
                            int32_t epilogue, const GemmEpi& p, float* split_ws, hipStream_t st);
 

@@ -5,23 +5,26 @@
 // products are 6).
 //
 // Three tiles, all direct-to-LDS with the operand layouts of the large kernel, 64-deep K tiles in a ring of stages:
-//   128 x 128, 8 wavefronts of 32 x 64, 4 stages (128 KB: one work-group per CU)
-//   128 x  64, 8 wavefronts of 32 x 32, 3 stages ( 72 KB: two per CU)
-//    64 x  64, 4 wavefronts of 32 x 32, 3 stages ( 48 KB: three per CU)
-// What bounds them is LDS bandwidth: per K tile the fragment reads plus the arriving operands are 128, 88 and 48 KB for
-// 2.1, 1.05 and 0.5 MFLOP (the 256 x 256 kernel: 256 KB for 8.4), which at 128 bytes per cycle is 0.46, 0.32 and 0.18 us;
-// measured 0.47 - 0.50, 0.32 and 0.18 - 0.20.  Four wavefronts of 64 x 64 on the 128 x 128 tile (a quarter less LDS
-// traffic) are slower at every shape tried: with one wavefront per SIMD, or two from two work-groups on 32-deep tiles,
-// latency is not covered (N = 2048, K = 8192, M = 1757: 89 and 73 us against 60).
+//   0: 128 x 128, 8 wavefronts of 64 x 32, 4 stages (128 KB: one work-group per CU)
+//   3: the same with 2 stages (64 KB: two per CU)
+//   1: 128 x  64, 8 wavefronts of 32 x 32, 3 stages ( 72 KB: two per CU)
+//   2:  64 x  64, 4 wavefronts of 32 x 32, 3 stages ( 48 KB: three per CU)
+// What bounds them is what one work-group can do between two barriers: more stages change nothing (3, 4 and 5 within 2 %),
+// a second work-group on the CU does.  With one tile per CU the deep ring is the better one (M = 1757, N = K = 2048: 19.8 us,
+// two stages 22.1), with more the shallow one (M = 756, N = 6144, K = 2048: 27.9 against 39.7).  Time per K tile of a CU:
+// 0.49 us for kind 0, 0.32 and 0.20 for 1 and 2, for kind 3 0.39 while the chip is not full and 0.55 - 0.62 per tile when every CU
+// works on two.  Four wavefronts of 64 x 64 on the 128 x 128 tile are slower at every shape tried (N = 2048, K = 8192,
+// M = 1757: 89 us and, with 32-deep tiles and two work-groups per CU, 73, against 60).
 //
 // Which one: the tile and split count with the smallest estimate (pick_gemm_tile), compared with the same kind of
 // estimate for the large kernel.  Measured, 256 x 256 kernel -> this, us (M, N, K; ds_gemm_ws on an idle card):
-//   NT 256, 768, 256: 10.2 -> 4.8    756, 2048, 2048: 36 -> 12.8    756, 8192, 2048: 43 -> 31    756, 2048, 8192: 50 -> 40
-//      1757, 2048, 2048: 37 -> 19    1757, 6144, 2048: 43 (53 with these: stays)    4173, 1024, 4096: 50 (55: stays)
-//   TN 256, 1024, 250: 17 -> 5       2048, 2048, 756: 47 -> 15       2048, 2048, 1757: 43 -> 25  1024, 4096, 4173: 57 -> 47
-//      2048, 8192, 756: 37 (48: stays)
+//   NT 256, 768, 256: 10.2 -> 4.8    756, 2048, 2048: 36 -> 13      756, 8192, 2048: 43 -> 29    756, 2048, 8192: 50 -> 40
+//      1757, 2048, 2048: 37 -> 20    1757, 6144, 2048: 43 (50 with these: stays)    756, 6144, 2048: 42 -> 28
+//   TN 256, 1024, 250: 17 -> 5       2048, 2048, 756: 47 -> 16       2048, 2048, 1757: 43 -> 25  1024, 4096, 4173: 57 -> 46
+//      2048, 6144, 756: 37 -> 34     2048, 6144, 1757: 53 (56: stays)
 #include "gemm_epilogue.hpp"
 
+#include <algorithm>
 #include <cmath>
 
 namespace {
@@ -199,7 +202,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
 
     // epilogue: 32 rows at a time through a block of LDS that is private to the wavefront
     constexpr int LDC = WC + 4, LPR = WC / 8, RPP = 64 / LPR, NP = 32 / RPP;
-    static_assert(NW * 32 * LDC * 4 <= NS * STAGE, "the staging blocks fit in the ring");
     float* stg = reinterpret_cast<float*>(smem) + wave * (32 * LDC);
     const int rd_row = lane / LPR, rd_col = (lane % LPR) * 8;
     const int n = n0 + wn * WC + rd_col;
@@ -269,14 +271,17 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
 }
 
 struct TileShape { int bm, bn, waves, stages; double step, fixed; };
-// step: microseconds per K tile of one work-group per CU (LDS bandwidth, see above); fixed: around the K loop
-constexpr TileShape kShapes[3] = {{128, 128, 8, 4, 0.49, 3.0}, {128, 64, 8, 3, 0.32, 2.5}, {64, 64, 4, 3, 0.20, 2.5}};
+// step: microseconds per K tile of a CU that has one tile; fixed: around the K loop
+constexpr int kKinds = 4;
+constexpr TileShape kShapes[kKinds] = {{128, 128, 8, 4, 0.49, 3.0}, {128, 64, 8, 3, 0.32, 2.5}, {64, 64, 4, 3, 0.20, 2.5}, {128, 128, 8, 2, 0.39, 3.0}};
+constexpr double kBusyStep3 = 0.62;                  // kind 3, per tile, when every CU works on two (0.55 on operands that are warm in L2)
 
 template <int EPI, bool TNF, int KIND, int WM, int WN>
 ds_status launch_kind(int splits, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
                       hipStream_t st) {
     constexpr TileShape s = kShapes[KIND];
-    constexpr int smem = s.stages * (s.bm + s.bn) * T_KD * 2;
+    constexpr int ring = s.stages * (s.bm + s.bn) * T_KD * 2, staging = s.waves * 32 * (s.bn / WN + 4) * 4;
+    constexpr int smem = ring > staging ? ring : staging;
     static_assert(WM * WN == s.waves, "wavefront grid");
     static bool attr_set = false;
     auto kern = gemm_bf16_tile_kernel<EPI, TNF, s.bm, s.bn, WM, WN, s.stages>;
@@ -296,7 +301,8 @@ ds_status launch_kind(int splits, int M, int N, int K, const void* A, const void
 template <int EPI, bool TNF>
 ds_status launch_form(const TilePick& k, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
                       hipStream_t st) {
-    if (k.kind == 0) return launch_kind<EPI, TNF, 0, 4, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
+    if (k.kind == 0) return launch_kind<EPI, TNF, 0, 2, 4>(k.splits, M, N, K, A, B, C, p, split_ws, st);
+    if (k.kind == 3) return launch_kind<EPI, TNF, 3, 2, 4>(k.splits, M, N, K, A, B, C, p, split_ws, st);
     if (k.kind == 1) return launch_kind<EPI, TNF, 1, 4, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
     return launch_kind<EPI, TNF, 2, 2, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
 }
@@ -314,14 +320,15 @@ int gemm_cu_count() {
 
 // The caller has established what the operands of the 256 x 256 kernel need (N, and M in the TN form, a multiple of 256;
 // K a multiple of 64 in the NT form; 16-byte alignment), which covers every tile here.
-//   estimate = rounds over the CUs x K tiles per split x step + fixed; several splits add the round trip of the partial sums
-//   at 4 TB/s and 5 us for the launch that adds them.
+//   estimate = rounds over the CUs x K tiles per split x step + fixed + what of out_us is not hidden; several splits add the
+//   round trip of the partial sums at 4 TB/s and 5 us for the launch that adds them.
+// out_us: moving an fp32 output (see gemm_output_us); half of it is hidden where a CU has other tiles to work on meanwhile.
 // colsum: the epilogue's column sums are wanted, which takes 128-row tiles and whole K loops.
-TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum) {
+TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us) {
     TilePick best{-1, 1, 0.0};
     if (tn && (M > (1 << 24) || N > (1 << 24))) return best;          // a K tile is addressed through a 32-bit buffer length
     const int n_cu = gemm_cu_count(), nt = (K + T_KD - 1) / T_KD;
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < kKinds; ++k) {
         const TileShape& s = kShapes[k];
         if (colsum && s.bm != 128) continue;
         const double tiles = std::ceil((double)M / s.bm) * (N / s.bn);
@@ -329,7 +336,11 @@ TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_w
             if (sp > 1 && (colsum || sp > nt / 4 || (size_t)sp * M * N > split_ws_floats)) break;
             const int per = (nt + sp - 1) / sp;
             if ((nt + per - 1) / per != sp || tiles * sp > 1e9) continue;         // every split owns at least one K tile
-            double cost = std::ceil(tiles * sp / n_cu) * per * s.step + s.fixed;
+            const double rounds = std::ceil(tiles * sp / n_cu);
+            if (k == 3 && rounds < 2) continue;                       // kind 0 is the better one
+            double cost = rounds * per * s.step;
+            if (k == 3) cost = std::max(cost, tiles * sp / n_cu * per * kBusyStep3);
+            cost += s.fixed + (k == 0 || rounds <= 2 ? out_us : 0.5 * out_us);
             if (sp > 1) cost += 2e-6 * sp * (double)M * N + 5;
             if (best.kind < 0 || cost < best.cost) best = TilePick{k, sp, cost};
         }
