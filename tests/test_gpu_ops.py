@@ -477,10 +477,10 @@ def test_mfma_probe_runs_and_is_deterministic():
 
 @pytest.mark.parametrize("form,M,N,K,use_ws", [
     ("nn", 1, 8, 4, False), ("nn", 65, 72, 36, False), ("nn", 300, 1032, 132, False), ("nn", 129, 264, 4100, True),
-    ("nt", 64, 64, 32, False), ("nt", 63, 200, 100, False), ("nt", 4200, 1032, 64, False),       # the last: 128-row tiles
+    ("nt", 64, 64, 32, False), ("nt", 63, 200, 100, False), ("nt", 4200, 1032, 64, False),       # the last: more tiles than two per CU
     ("tn", 4, 8, 1, False), ("tn", 68, 200, 31, False), ("tn", 256, 256, 7684, True), ("tn", 260, 520, 129, True)])
 def test_gemm_f32_matrix_cores(form, M, N, K, use_ws):
-    """Edges of the 64 / 128-row and 64-column tiles, of the 32-deep K tiles and of the split contraction, against float64."""
+    """Edges of the 64-row and 64-column tiles, of the 32-deep K tiles and of the split contraction, against float64."""
     rng = np.random.default_rng(31)
     ta, tb = form == "tn", form == "nt"
     A, B = _rnd(rng, (K, M) if ta else (M, K), F32), _rnd(rng, (N, K) if tb else (K, N), F32)
