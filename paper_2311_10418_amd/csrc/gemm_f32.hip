@@ -6,8 +6,10 @@
 // direct-to-LDS machinery is needed; what the shapes of this path (a few thousand rows, 128 .. 512 columns) lack is
 // work-groups.  Hence 64 x 64 tiles: 4 wavefronts stacked along M, each 16 x 64, 32-deep K tiles staged global ->
 // registers -> LDS in two stages (37 KB: four work-groups per CU cover each other's waits), the tile after the next
-// requested while one is multiplied (one tile ahead: 1477 us for the stage below, two: 1450).  128-row tiles gain at most
-// 2 % (4096^3: 112 TFLOP/s against 110) and lose more (12 288 x 512 x 2048: 87 against 105); 64-deep K tiles are mixed (99 - 111).
+// requested while one is multiplied (one tile ahead: 1477 us for the stage below, two: 1450).  128-row tiles are
+// mixed: at 4096^3 NT 117 TFLOP/s against 111, NN 112 against 109, TN 110 against 116; NT 12 288 x 512 x 2048 87 against 105,
+// NN 7684 x 768 x 256 82 against 87.  A stage's widths here are the latter kind, so they are left out; 64-deep K tiles are
+// mixed too (4096^3: NN 99 against 110, NT 111 against 111).
 // Where the tiles do not give every CU two work-groups, KW = 2: eight wavefronts per work-group, the second four taking
 // the second half of every K tile into accumulators of their own (added at the end through LDS), so that every SIMD still
 // has two wavefronts (weight gradients of the d = 256 stage: 56 -> 42 us).
