@@ -622,7 +622,11 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
     const uint32_t lds0 = lds_address(smem);
+    // the next draw, in two words used in turn: an item may have no step (a sequence without queries, keys beyond the last
+    // query of a causal one) and then no other barrier than the one behind the write, so the word written for an item must
+    // not be the one that a slower wavefront may still be reading for the item before
     volatile int* s_next = reinterpret_cast<volatile int*>(smem + NS * STAGE);
+    int turn = 0;
     TileLoader<HD> ldQ, ldO;
     ldQ.setup(nullptr, a.ldq, 0, wave, lane);
     ldO.setup(nullptr, a.ldo, 0, wave, lane);
@@ -812,10 +816,11 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
     bf16_t* dv = (bf16_t*)a.dv + (krow0 + ki) * a.ldv + h * HD;
     bool more = false;
     if constexpr (PS) {
-        if (tid == 0) *s_next = next;
+        if (tid == 0) s_next[turn] = next;
         __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();                   // ... and nobody is reading it any more
-        draw.advance(__builtin_amdgcn_readfirstlane(*s_next));
+        draw.advance(__builtin_amdgcn_readfirstlane(s_next[turn]));
+        turn ^= 1;
         more = draw.valid();
         if (more) begin_item();
     }

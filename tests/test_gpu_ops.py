@@ -672,3 +672,44 @@ def test_pack_unpack_forms(dt, form, n, d):
     torch.cuda.synchronize()
     assert np.array_equal(to_np(stream)[:rows], ref) and np.all(to_np(stream)[rows] == 7.0)
     assert np.array_equal(to_np(back)[:-1], canon) and np.all(to_np(back)[-1] == 7.0)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+def test_attention_128_items_without_steps(causal):
+    """Head size 128, many more (key block, head) pairs than compute units, so that every work-group of the dK/dV kernel takes
+    several: among them blocks that no query sees (sequences without queries, causal ones with more keys than queries),
+    whose gradients are zero and which pass no barrier but the draw's.  Against the generic kernels, sequence by sequence (P
+    and dS rounded to bf16, 2^-9 of each term; the gradients of a few keys under many queries are tens of times those of
+    many keys, so that one scale for all sequences would say nothing); twice on one scratch, bit for bit the same."""
+    rng = np.random.default_rng(38)
+    h, hd, n = 8, 128, 150
+    d = h * hd
+    kl = rng.integers(64, 600, n).astype(np.int32)
+    ql = np.where(rng.random(n) < 0.4, 0, rng.integers(32, 300, n)).astype(np.int32)
+    qr, kr = (np.cumsum(a) - a for a in (ql, kl))
+    Tq, Tk = int(ql.sum()), int(kl.sum())
+    assert h * int(((kl + 127) // 128).sum()) > 3 * 256
+    q, kv, d_o = (to_dev(_rnd(rng, s, BF), BF) for s in ((Tq, d), (Tk, 2 * d), (Tq, d)))
+    table = [torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(DEV) for a in (qr, ql, kr, kl)]
+    scratch = torch.zeros(ds.ds_attention_scratch_bytes(h, hd, Tq, Tk, n), dtype=torch.uint8, device=DEV)
+    mx = (int(ql.max()), int(kl.max()))
+    res = []
+    for force in (False, False, True):
+        o, lse, delta = torch.zeros((Tq, d), dtype=BF, device=DEV), torch.zeros((h, Tq), device=DEV), torch.zeros((h, Tq), device=DEV)
+        dq, dkv = (torch.full((t, w), 7.0, dtype=BF, device=DEV) for t, w in ((Tq, d), (Tk, 2 * d)))
+        b, gb = kv.data_ptr(), dkv.data_ptr()
+        ds.ds_attention_fwd(q, b, b + 2 * d, o, lse, *table, h, hd, causal, *mx, d, 2 * d, 2 * d, d, Tq, k_total_rows=Tk,
+                            scratch=scratch, force_generic=force)
+        ds.ds_attention_bwd(q, b, b + 2 * d, o, d_o, lse, delta, dq, gb, gb + 2 * d, *table, h, hd, causal, *mx, d, 2 * d, 2 * d, d,
+                            Tq, k_total_rows=Tk, scratch=scratch, force_generic=force)
+        torch.cuda.synchronize()
+        res.append([to_np(x) for x in (o, dq, dkv)])
+    unseen = np.concatenate([np.arange(l) >= (m if causal or m == 0 else l) for l, m in zip(kl, ql)])
+    assert unseen.sum() > 1000 and np.all(res[0][2][unseen] == 0)
+    for got, again in zip(res[0], res[1]):
+        assert np.array_equal(got, again)
+    (o, dq, dkv), _, (ref_o, ref_dq, ref_dkv) = res
+    for i in np.flatnonzero(ql):
+        qs, ks = slice(qr[i], qr[i] + ql[i]), slice(kr[i], kr[i] + (min(kl[i], ql[i]) if causal else kl[i]))
+        assert both_err(o[qs], ref_o[qs]) <= TOL[BF] and both_err(dq[qs], ref_dq[qs]) <= TOL[BF], i
+        assert both_err(dkv[ks, :d], ref_dkv[ks, :d]) <= TOL[BF] and both_err(dkv[ks, d:], ref_dkv[ks, d:]) <= TOL[BF], i
