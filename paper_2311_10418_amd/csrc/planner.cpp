@@ -262,7 +262,7 @@ static ds_status plan_impl(const int32_t* len, const int32_t* len_tgt, int32_t n
         // better (the cut-off below would stop at the first one), so larger slices need not be sorted.
         int64_t t_top = 0, t_beyond = kInf;
         for (int32_t pos = n; pos > 0; pos = arg[pos]) t_top = std::max(t_top, f_cost[pos]);
-        if (!quantised(t_top, &t_top)) return DS_EOVERFLOW;
+        if (!quantised(t_top, &t_top)) t_top = kInf;                  // not representable: an error only if the scan gets there
         size_t kept = 0;
         for (const Slice& sl : slices) {
             if (sl.t <= t_top) slices[kept++] = sl;

@@ -156,19 +156,104 @@ def test_many_equal_sums_and_non_monotone_costs():
         _same(lens, cap, int(rng.choice([1, 2, 3, 8, 64])), kind=ds.DS_COST_TABLE, table=table)
 
 
-@pytest.mark.parametrize("fixed", [2 ** 55, 2 ** 58, 2 ** 60, 2 ** 61])
-def test_costs_near_the_integer_limit(fixed):
-    """Where slice costs, sums or objectives leave int64 the planner reports what it reported when every candidate scanned
-    every slice: either the oracle's plan or an overflow."""
-    rng = np.random.default_rng(25)
-    for _ in range(20):
-        n = int(rng.integers(1, 12))
-        lens = rng.integers(1, 9, size=n).astype(np.int32)
-        c, cap = int(rng.choice([1, 2, 4])), int(rng.choice([9, 40]))
-        try:
-            lo = ds.dp_plan(lens, ds.make_cost_model(fixed=fixed, lin=1), cap, c)
-        except ds.DsError as e:
-            assert e.code == ds.DS_EOVERFLOW
+INT64_MAX = 2 ** 63 - 1
+
+
+def _scan(lens, table, cap, stages, quantum):
+    """dp_plan (quantum 0) and dp_plan_sampled as they are defined, every candidate t_max scanning every admitted slice, in
+    integers of any size with a range check wherever the planner has an int64: (cuts, objective, t_max) or an error code."""
+    srt, n, w = sorted(lens), len(lens), stages - 1
+    over = lambda *vs: any(v > INT64_MAX for v in vs)
+    slices = [(int(table[j - i - 1][srt[j - 1] - 1]), j, i) for i in range(n) for j in range(i + 1, n + 1) if (j - i) * srt[j - 1] <= cap]
+
+    def recurrence(admitted):
+        f, arg = [0] + [INT64_MAX] * n, [-1] * (n + 1)          # (the largest value stands for "no partition")
+        for j in range(1, n + 1):
+            for t, i in sorted(admitted[j], key=lambda e: e[1]):
+                if f[i] == INT64_MAX:
+                    continue
+                if over(f[i] + t):
+                    return None, None
+                if f[i] + t < f[j]:
+                    f[j], arg[j] = f[i] + t, i
+        return f, arg
+
+    def by_end(sl):
+        return [[(t, i) for t, j, i in sl if j == e] for e in range(n + 1)]
+
+    f, _ = recurrence(by_end(slices))
+    if f is None:
+        return ds.DS_EOVERFLOW
+    f_inf = f[n]
+    if f_inf == INT64_MAX:
+        return ds.DS_EINFEASIBLE
+    best, done = None, -1
+    for t in sorted({t for t, _, _ in slices}):
+        if t <= done:
             continue
-        ref = oplan.plan(lens, cap, c, fixed=fixed, lin=1)
-        assert list(lo.cuts) == list(ref["cuts"]) and lo.objective == ref["objective"] and lo.t_max == ref["t_max"]
+        done = T = -(-t // quantum) * quantum if quantum else t
+        if over(T) or (best and over(w * T, w * T + f_inf)):
+            return ds.DS_EOVERFLOW
+        if best and w * T + f_inf >= best[0]:
+            break
+        f, arg = recurrence(by_end([sl for sl in slices if sl[0] <= T]))
+        if f is None:
+            return ds.DS_EOVERFLOW
+        if f[n] == INT64_MAX:
+            continue
+        if over(w * T, w * T + f[n]):
+            return ds.DS_EOVERFLOW
+        if not best or w * T + f[n] < best[0]:
+            best = (w * T + f[n], T, arg)
+    objective, t_max, arg = best
+    cuts = [n]
+    while cuts[0]:
+        cuts.insert(0, arg[cuts[0]])
+    if quantum:
+        ts = [int(table[b - a - 1][srt[b - 1] - 1]) for a, b in zip(cuts, cuts[1:])]
+        objective, t_max = w * max(ts) + sum(ts), max(ts)
+        if over(sum(ts), w * max(ts), objective):
+            return ds.DS_EOVERFLOW
+    return cuts, objective, t_max
+
+
+def _same_as_scan(lens, table, cap, stages, quantum):
+    cm = ds.make_cost_model(kind=ds.DS_COST_TABLE, table=np.asarray(table, dtype=np.int64))
+    lens = np.asarray(lens, dtype=np.int32)
+    want = _scan([int(l) for l in lens], table, cap, stages, quantum)
+    try:
+        lo = ds.dp_plan_sampled(lens, cm, cap, stages, quantum) if quantum else ds.dp_plan(lens, cm, cap, stages)
+        got = (list(lo.cuts), lo.objective, lo.t_max)
+    except ds.DsError as e:
+        got = e.code
+    assert got == want, (list(lens), cap, stages, quantum)
+    return want
+
+
+@pytest.mark.parametrize("top", [2 ** 55, 2 ** 58, 2 ** 60, 2 ** 61, 2 ** 62, 2 ** 63 - 2])
+def test_costs_near_the_integer_limit(top):
+    """Where slice costs, sums, objectives or sampled t_max leave int64 the planner reports what scanning every slice for every
+    candidate reports, the plan or the status."""
+    rng = np.random.default_rng(25)
+    kinds = set()
+    for _ in range(150):
+        n = int(rng.integers(1, 9))
+        lmax = int(rng.integers(1, 7))
+        lens = rng.integers(1, lmax + 1, size=n).astype(np.int32)
+        unit = int(rng.choice([1, top // 8, top // 2]))          # few distinct values: sums tie
+        table = [[int(rng.integers(0, top // unit + 1)) * unit for _ in range(lmax)] for _ in range(n)]
+        quantum = int(rng.choice([0, 1, top // 3 + 1, top // 2 + 1, top]))
+        kinds.add(type(_same_as_scan(lens, table, int(rng.choice([lmax, 3 * lmax, n * lmax])), int(rng.choice([1, 2, 3])), quantum)))
+    assert top < 2 ** 60 or kinds == {int, tuple}
+
+
+def test_sampled_cost_that_no_candidate_reaches():
+    """Two partitions of the same sum; the planner's lower bound comes from the one whose largest slice, rounded up to the
+    interval, leaves int64.  One stage: the scan stops before that candidate, so it is no error."""
+    big, half = 3 * 2 ** 61 + 2, 3 * 2 ** 60
+    #        length 1    2            3
+    table = [[half,     2 ** 62 + 5,  1],                        # one sample
+             [1,        big,          half + 3],                 # two
+             [1,        1,            big + 2]]                  # three
+    assert _same_as_scan([1, 2, 3], table, 9, 1, 2 ** 61) == ([0, 1, 3], big + 1, half + 3)
+    assert _same_as_scan([1, 2, 3], table, 9, 2, 2 ** 61) == ds.DS_EOVERFLOW
