@@ -17,7 +17,7 @@
 // 7 684 tokens in 64 sequences (up to 512), 4 heads of 64, causal: forward 37 us, dQ 42, dK/dV 86, against 508, 435 and
 // 581 for one wavefront per query / key row with shuffled probabilities (attention_generic.hip, which keeps the operands
 // that float4 cannot read): those read every row of the other side once per row of this one.
-#include "attention.hpp"
+#include "attention_rows.hpp"
 
 namespace {
 
@@ -34,6 +34,13 @@ template <int HD, int NT = 256> struct F32Tile {                     // NT threa
     static constexpr int NV = ROWS * HD / 4 / NT;                     // float4 per thread
     static_assert(ROWS * HD / 4 % NT == 0, "whole float4s per thread");
     float4 v[NV];
+    __device__ __forceinline__ bool not_finite() const {              // any of this thread's values
+        float zero = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            zero = __builtin_fmaf(v[i].x, 0.f, __builtin_fmaf(v[i].y, 0.f, __builtin_fmaf(v[i].z, 0.f, __builtin_fmaf(v[i].w, 0.f, zero))));
+        return !(zero == 0.f);
+    }
     // rows r0 .. r0 + ROWS - 1 of a [n_rows][hd] block with row stride ld; beyond either extent: zeros
     __device__ __forceinline__ void load(const float* __restrict__ src, long long ld, int r0, int n_rows, int hd, int t) {
 #pragma unroll
@@ -102,6 +109,12 @@ __device__ __forceinline__ void store_column(const f32x4_t (&acc)[HD / 16], floa
 __device__ __forceinline__ float groups_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
 __device__ __forceinline__ float groups_sum(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
 
+// Causal masks and values that are not finite.  A score that a column does not see is replaced whatever it is; but the second
+// product contracts over whole blocks, with weight 0 for the rows a column does not see, and 0 x Inf would reach it.  So a
+// work-group looks at the operand of its second product as it stores the tiles on its diagonal (the positions of its own
+// 64 columns; tiles beyond them it does not visit), and if anything there is not finite every wavefront computes its
+// columns one at a time in the end (attention_rows.hpp).
+
 // ---------------------------------------------------------------- forward
 template <int HD>
 __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
@@ -109,7 +122,9 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
     constexpr int KT = Tile::ROWS, NB = KT / 16;
     __shared__ __attribute__((aligned(16))) float sK[Tile::FLOATS];
     __shared__ __attribute__((aligned(16))) float sV[Tile::FLOATS];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4;
+    __shared__ float s_row[4][HD];
+    __shared__ int s_by_rows;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), g = lane >> 4;
     const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 64;
     const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
     if (q0 >= ql) return;
@@ -126,6 +141,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
     float m = -INFINITY, lsum = 0.f;                                  // running maximum (exp2 domain), this lane's part of the sum
     const int kv_end = a.mask ? min(kl, q0 + 64) : kl;
     const int wave_last = a.mask ? min(kl - 1, qw0 + 15) : kl - 1;    // last key this wavefront can see
+    if (t == 0) s_by_rows = 0;
     Tile tk, tv;
     if (kv_end > 0) {
         tk.load(K, a.ldk, 0, kl, hd, t);
@@ -135,6 +151,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
         __syncthreads();                                              // the previous tile has been read by everybody
         tk.store(sK, t);
         tv.store(sV, t);
+        if (a.mask && k0 >= q0 && tv.not_finite()) s_by_rows = 1;
         __syncthreads();
         if (k0 + KT < kv_end) {
             tk.load(K, a.ldk, k0 + KT, kl, hd, t);
@@ -173,10 +190,20 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
 #pragma unroll
         for (int kt = 0; kt < NB; ++kt) second_product<HD>(sV, 16 * kt, lane, sc[kt], oacc);
     }
+    if (a.mask && kv_end > 0 && s_by_rows) {
+        for (int q = qw0; q < min(qw0 + 16, ql); ++q) {
+            wave_lds_sync();
+            stage_row(s_row[wave], (const float*)a.q + (qrow0 + q) * a.ldq + h * hd, hd, a.scale, lane);
+            wave_lds_sync();
+            attn_fwd_row<float>(a, s, h, q, s_row[wave], lane);
+        }
+        return;
+    }
     if (qi >= ql) return;
     const float l = groups_sum(lsum);
     const long long row = qrow0 + qi;
-    store_column<HD>(oacc, l > 0.f ? 1.0f / l : 0.f, (float*)a.o + row * a.ldo + h * hd, hd, g);      // (no keys: zero output)
+    // (no keys: zero output; every score -Inf: l = 0 and NaN, like the quotient)
+    store_column<HD>(oacc, kl > 0 ? 1.0f / l : 0.f, (float*)a.o + row * a.ldo + h * hd, hd, g);
     if (g == 0) a.lse[(size_t)h * a.lse_stride + row] = (m + log2f(l)) * kLn2F;
 }
 
@@ -187,7 +214,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
     constexpr int KT = Tile::ROWS;
     __shared__ __attribute__((aligned(16))) float sK[Tile::FLOATS];
     __shared__ __attribute__((aligned(16))) float sV[Tile::FLOATS];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, g = lane >> 4;
+    __shared__ float s_row[4][2][HD];
+    __shared__ int s_by_rows;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), g = lane >> 4;
     const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 64;
     const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
     if (q0 >= ql) return;
@@ -206,6 +235,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
     for (int dt = 0; dt < HD / 16; ++dt) gacc[dt] = zero4();
     const int kv_end = a.mask ? min(kl, q0 + 64) : kl;
     const int wave_last = a.mask ? min(kl - 1, qw0 + 15) : kl - 1;
+    if (t == 0) s_by_rows = 0;
     Tile tk, tv;
     if (kv_end > 0) {
         tk.load(K, a.ldk, 0, kl, hd, t);
@@ -215,6 +245,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
         __syncthreads();
         tk.store(sK, t);
         tv.store(sV, t);
+        if (a.mask && k0 >= q0 && tk.not_finite()) s_by_rows = 1;
         __syncthreads();
         if (k0 + KT < kv_end) {
             tk.load(K, a.ldk, k0 + KT, kl, hd, t);
@@ -235,6 +266,16 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
             second_product<HD>(sK, 16 * kt, lane, ds, gacc);
         }
     }
+    if (a.mask && kv_end > 0 && s_by_rows) {
+        for (int q = qw0; q < min(qw0 + 16, ql); ++q) {
+            wave_lds_sync();
+            stage_row(s_row[wave][0], (const float*)a.q + (qrow0 + q) * a.ldq + h * hd, hd, a.scale, lane);
+            stage_row(s_row[wave][1], (const float*)a.d_o + (qrow0 + q) * a.ldo + h * hd, hd, 1.0f, lane);
+            wave_lds_sync();
+            attn_bwd_dq_row<float>(a, s, h, q, s_row[wave][0], s_row[wave][1], lane);
+        }
+        return;
+    }
     if (qi < ql) store_column<HD>(gacc, a.scale, (float*)a.dq + (qrow0 + qi) * a.ldq + h * hd, hd, g);
 }
 
@@ -252,7 +293,10 @@ __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel
     float* sQ = smem;
     float* sO = smem + Tile::FLOATS;
     __shared__ __attribute__((aligned(16))) float s_lse[QT], s_delta[QT];
-    const int t = threadIdx.x, lane = t & 63, wave = (t >> 6) & 3, half = t >> 8, g = lane >> 4;
+    __shared__ float s_row[4][2][HD];
+    __shared__ int s_by_rows;
+    const int t = threadIdx.x, lane = t & 63, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6) & 3, half = __builtin_amdgcn_readfirstlane(t >> 8);
     const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, k0 = blockIdx.x * 64;
     const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
     if (k0 >= kl) return;
@@ -270,6 +314,7 @@ __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel
 #pragma unroll
     for (int dt = 0; dt < HD / 16; ++dt) { dkacc[dt] = zero4(); dvacc[dt] = zero4(); }
     const int q_begin = a.mask ? k0 : 0;                              // causal: only queries at or after the key see it
+    if (t == 0) s_by_rows = 0;
     Tile tq, to;
     float lse_r = 0.f, delta_r = 0.f;
     auto fetch = [&](int q0) {
@@ -284,6 +329,7 @@ __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel
         __syncthreads();
         tq.store(sQ, t);
         to.store(sO, t);
+        if (a.mask && q0 < k0 + 64 && (tq.not_finite() || to.not_finite())) s_by_rows = 1;
         if (t < QT) { s_lse[t] = lse_r; s_delta[t] = delta_r; }
         __syncthreads();
         if (q0 + QT < ql) fetch(q0 + QT);
@@ -303,7 +349,7 @@ __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel
                 const int q = qb + 4 * g + e;
                 const bool out = q >= ql || (a.mask && q < ki);
                 p[e] = out ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(p[e], c, -lq[e]));
-                ds[e] = p[e] * (ds[e] - dq[e]);
+                ds[e] = out ? 0.f : p[e] * (ds[e] - dq[e]);
             }
             second_product<HD>(sO, 16 * qt, lane, p, dvacc);
             second_product<HD>(sQ, 16 * qt, lane, ds, dkacc);
@@ -324,7 +370,18 @@ __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel
             for (int dt = 0; dt < HD / 16; ++dt) acc[dt] += part[dt * 256 + t];
         }
     }
-    if (half == 1 || ki >= kl) return;
+    if (half == 1) return;
+    if (s_by_rows) {
+        for (int k = kw0; k < min(kw0 + 16, kl); ++k) {
+            wave_lds_sync();
+            stage_row(s_row[wave][0], (const float*)a.k + (krow0 + k) * a.ldk + h * hd, hd, a.scale, lane);
+            stage_row(s_row[wave][1], (const float*)a.v + (krow0 + k) * a.ldv + h * hd, hd, 1.0f, lane);
+            wave_lds_sync();
+            attn_bwd_dkv_row<float>(a, s, h, k, s_row[wave][0], s_row[wave][1], lane);
+        }
+        return;
+    }
+    if (ki >= kl) return;
     store_column<HD>(dkacc, a.scale, (float*)a.dk + (krow0 + ki) * a.ldk + h * hd, hd, g);
     store_column<HD>(dvacc, 1.0f, (float*)a.dv + (krow0 + ki) * a.ldv + h * hd, hd, g);
 }

@@ -713,3 +713,42 @@ def test_attention_128_items_without_steps(causal):
         qs, ks = slice(qr[i], qr[i] + ql[i]), slice(kr[i], kr[i] + (min(kl[i], ql[i]) if causal else kl[i]))
         assert both_err(o[qs], ref_o[qs]) <= TOL[BF] and both_err(dq[qs], ref_dq[qs]) <= TOL[BF], i
         assert both_err(dkv[ks, :d], ref_dkv[ks, :d]) <= TOL[BF] and both_err(dkv[ks, d:], ref_dkv[ks, d:]) <= TOL[BF], i
+
+
+@pytest.mark.parametrize("hd", [32, 64, 96, 128])
+def test_attention_f32_causal_with_values_that_are_not_finite(hd):
+    """An infinity or NaN in one token of a causal sequence: everything that does not see the token is what it is without it,
+    everything else is not finite where the generic kernels, which read only what a row sees, say so.  The token lies at
+    the start, in the middle and at the end of 16-token blocks and of tiles."""
+    rng = np.random.default_rng(39)
+    h = 2
+    poison = [(l, part, pos, val) for part in "qkvo" for l, pos, val in
+              ((40, 25, np.inf), (70, 69, np.nan), (130, 64, -np.inf), (200, 15, np.nan), (200, 143, np.inf), (33, 0, -np.inf))]
+    lens = [p[0] for p in poison]
+    d, T, rows, qkv, d_o = _varlen_case(rng, lens, h, hd, F32)
+    for (l, part, pos, val), r0 in zip(poison, rows):
+        if part == "o":
+            d_o[r0 + pos, hd + 5] = val
+        else:
+            qkv[r0 + pos, "qkv".index(part) * d + hd + 5] = val             # second head only
+    x, ddo = to_dev(qkv, F32), to_dev(d_o, F32)
+    t_rows, t_lens = torch.from_numpy(rows).to(DEV), torch.tensor(lens, dtype=torch.int32, device=DEV)
+    res = []
+    for force in (False, True):
+        o, lse, delta = torch.zeros((T, d), device=DEV), torch.zeros((h, T), device=DEV), torch.zeros((h, T), device=DEV)
+        g = torch.zeros((T, 3 * d), device=DEV)
+        b, gb, table = x.data_ptr(), g.data_ptr(), (t_rows, t_lens, t_rows, t_lens)
+        ds.ds_attention_fwd(b, b + 4 * d, b + 8 * d, o, lse, *table, h, hd, True, max(lens), max(lens), 3 * d, 3 * d, 3 * d, d, T, force_generic=force)
+        ds.ds_attention_bwd(b, b + 4 * d, b + 8 * d, o, ddo, lse, delta, gb, gb + 4 * d, gb + 8 * d, *table, h, hd, True,
+                            max(lens), max(lens), 3 * d, 3 * d, 3 * d, d, T, force_generic=force)
+        torch.cuda.synchronize()
+        res.append(np.concatenate([to_np(o), to_np(g)], axis=1))
+    for p, r0 in zip(poison, rows):
+        got, ref = (r[r0:r0 + p[0]] for r in res)
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref)), p
+        if p[1] != "o" or p[2] > 0:
+            assert not np.isfinite(ref).all(), p
+        assert np.isfinite(ref[:p[2], :d]).all(), p                         # outputs in front of the token
+        for i in range(4):
+            a, b = (np.where(np.isfinite(m), m, 0.0)[:, i * d:(i + 1) * d] for m in (got, ref))
+            assert both_err(a, b) <= TOL[F32], (p, i)
