@@ -627,6 +627,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
     // not be the one that a slower wavefront may still be reading for the item before
     volatile int* s_next = reinterpret_cast<volatile int*>(smem + NS * STAGE);
     int turn = 0;
+    char* s_zero = smem + NS * STAGE + 64;              // 32 rows of zeros, see phase_d
     TileLoader<HD> ldQ, ldO;
     ldQ.setup(nullptr, a.ldq, 0, wave, lane);
     ldO.setup(nullptr, a.ldo, 0, wave, lane);
@@ -688,6 +689,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
         return;
     }
     begin_item();
+    for (int i = tid; i < 64 * HD / 16; i += 256) reinterpret_cast<uint4*>(s_zero)[i] = make_uint4(0u, 0u, 0u, 0u);
     bf16x8_t neg_ones;                                  // contraction slots 0, 1 (lane half 0) pick -hi - lo
 #pragma unroll
     for (int j = 0; j < 8; ++j) neg_ones[j] = (bf16_t)((g == 0 && j < 2) ? -1.0f : 0.0f);
@@ -709,8 +711,8 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
     if (PS) next = draw.take();                         // (needed after the loop)
     // the K / V fragments (ordinary loads) and the stores of the item before are complete before the loop: left to the
     // compiler, its waits for them would sit inside the loop as "nothing outstanding", which would also drain the
-    // transfers in flight
-    __builtin_amdgcn_s_waitcnt(0x0F70);
+    // transfers in flight.  So are the zeros of s_zero, in front of the first step's barrier.
+    __builtin_amdgcn_s_waitcnt(0x0070);
     // One step = one 64-query block, straight code: any branch inside it, even one that is never taken, splits the live
     // ranges of the 128 accumulator registers and costs hundreds of register copies per step.  The step exists in two
     // versions, with the mask as selects and without, and the loop is cut into three: the (at most two) blocks on the
@@ -753,10 +755,10 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
         auto softmax2 = [&](int qt, int e0) {         // two elements of half qt: P and dS in place
 #pragma unroll
             for (int e = e0; e < e0 + 2; ++e) {
-                float p = __builtin_amdgcn_exp2f(sa[qt][e] * c);
-                if (MASKED && (unsigned)(qt * 32 + 8 * (e >> 2) + (e & 3) - first) >= visible) p = 0.f;
-                sa[qt][e] = p;
-                pa[qt][e] = p * pa[qt][e];
+                const float p = __builtin_amdgcn_exp2f(sa[qt][e] * c);
+                const bool out = MASKED && (unsigned)(qt * 32 + 8 * (e >> 2) + (e & 3) - first) >= visible;
+                sa[qt][e] = out ? 0.f : p;
+                pa[qt][e] = out ? 0.f : p * pa[qt][e];
             }
         };
         auto phase_a = [&](int qt, bool with_prev) {
@@ -780,9 +782,13 @@ __global__ __launch_bounds__(256, HD == 64 ? 2 : 1) void attn_bwd_dkv_mfma_kerne
         auto phase_d = [&](int qt, bool with_next) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) { pf[u] = frag_from_acc(sa[qt], u); dsf[u] = frag_from_acc(pa[qt], u); }
+            // a half that no key of this wavefront sees: zeros instead of its rows, which may hold infinities (0 x Inf is NaN)
+            const bool hidden = MASKED && (qt ? q0 + 32 >= ql : CAUSAL && q0 + 31 < kw0);
+            const char* rO = hidden ? s_zero - qt * (32 * HD * 2) : sdO;
+            const char* rQ = hidden ? s_zero - qt * (32 * HD * 2) : sQ;
             auto read_d = [&](int j) {
-                td[j] = read_tr<HD>(sdO, tro, 2 * qt + j / (HD / 32), j % (HD / 32));
-                tq[j] = read_tr<HD>(sQ, tro, 2 * qt + j / (HD / 32), j % (HD / 32));
+                td[j] = read_tr<HD>(rO, tro, 2 * qt + j / (HD / 32), j % (HD / 32));
+                tq[j] = read_tr<HD>(rQ, tro, 2 * qt + j / (HD / 32), j % (HD / 32));
             };
 #pragma unroll
             for (int j = 0; j < AHEAD_D; ++j) read_d(j);
@@ -866,7 +872,7 @@ ds_status bwd_launch(const AttnArgs& a, hipStream_t st) {
     auto kq = attn_bwd_dq_mfma_kernel<HD, CAUSAL>;
     auto kkv = attn_bwd_dkv_mfma_kernel<HD, CAUSAL>;
     const int smem_q = 4 * (64 * HD * 2);
-    const int smem_kv = 4 * (2 * (64 * HD * 2) + 2048) + 64;
+    const int smem_kv = 4 * (2 * (64 * HD * 2) + 2048) + 64 + 64 * HD;      // stages, draws, zeros
     ds_status r = set_smem(kq, smem_q, attr_q);
     if (r != DS_OK) return r;
     r = set_smem(kkv, smem_kv, attr_kv);

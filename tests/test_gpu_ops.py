@@ -752,3 +752,39 @@ def test_attention_f32_causal_with_values_that_are_not_finite(hd):
         for i in range(4):
             a, b = (np.where(np.isfinite(m), m, 0.0)[:, i * d:(i + 1) * d] for m in (got, ref))
             assert both_err(a, b) <= TOL[F32], (p, i)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_attention_bf16_hidden_half_blocks_with_values_that_are_not_finite(hd):
+    """dK / dV, causal: the kernel multiplies 32-query halves of its 64-query blocks by zero where a wavefront's 32 keys see none
+    of a half's queries.  An infinity or NaN in a query (Q or dO) reaches no key of a later group of 32, and the copies of
+    the last row that fill a ragged block add nothing to it."""
+    rng = np.random.default_rng(40)
+    h = 2
+    cases = [(200, "q", 10, np.inf), (200, "o", 10, np.nan), (300, "q", 150, np.nan), (300, "o", 159, -np.inf), (96, "o", 95, np.inf)]
+    lens = [c[0] for c in cases]
+    d, T, rows, qkv, d_o = _varlen_case(rng, lens, h, hd, BF)
+    for (l, part, pos, val), r0 in zip(cases, rows):
+        (d_o if part == "o" else qkv)[r0 + pos, hd + 5] = val
+    x, ddo = to_dev(qkv, BF), to_dev(d_o, BF)
+    t_rows, t_lens = torch.from_numpy(rows).to(DEV), torch.tensor(lens, dtype=torch.int32, device=DEV)
+    scratch = torch.zeros(ds.ds_attention_scratch_bytes(h, hd, T, T, len(lens)), dtype=torch.uint8, device=DEV)
+    res = []
+    for force in (False, True):
+        o, lse, delta = torch.zeros((T, d), dtype=BF, device=DEV), torch.zeros((h, T), device=DEV), torch.zeros((h, T), device=DEV)
+        g = torch.zeros((T, 3 * d), dtype=BF, device=DEV)
+        b, gb, table = x.data_ptr(), g.data_ptr(), (t_rows, t_lens, t_rows, t_lens)
+        ds.ds_attention_fwd(b, b + 2 * d, b + 4 * d, o, lse, *table, h, hd, True, max(lens), max(lens), 3 * d, 3 * d, 3 * d, d, T,
+                            scratch=scratch, force_generic=force)
+        ds.ds_attention_bwd(b, b + 2 * d, b + 4 * d, o, ddo, lse, delta, gb, gb + 2 * d, gb + 4 * d, *table, h, hd, True,
+                            max(lens), max(lens), 3 * d, 3 * d, 3 * d, d, T, scratch=scratch, force_generic=force)
+        torch.cuda.synchronize()
+        res.append(to_np(g)[:, d:])
+    for (l, part, pos, val), r0 in zip(cases, rows):
+        got, ref = (r[r0:r0 + l] for r in res)
+        seen = pos // 32 * 32 + 32                                          # keys from here on do not meet the query
+        assert np.isfinite(got[seen:]).all() and np.isfinite(ref[pos + 1:]).all()
+        if seen < l:
+            for i in range(2):
+                assert both_err(got[seen:, i * d:(i + 1) * d], ref[seen:, i * d:(i + 1) * d]) <= TOL[BF]
+    assert np.isinf(got[:, d + hd + 5]).all() and np.array_equal(np.isnan(got[:, d:]), np.isnan(ref[:, d:]))       # dV of the last case
