@@ -348,9 +348,9 @@ def _ws(floats):
 @pytest.mark.parametrize("use_ws", [False, True])
 @pytest.mark.parametrize("M,N,K", [(700, 256, 128), (1037, 512, 1024), (5157, 3328, 1024)])
 def test_gemm_nt_epilogues(use_ws, M, N, K):
-    """C = A B^T with B given as [N, K] (forward with transposed weights, input gradients): every epilogue, ragged M,
-    launches with fewer tiles than compute units (all tiles split over K when a workspace is given) and with more
-    (whole rounds unsplit, the remaining tiles split)."""
+    """C = A B^T with B given as [N, K] (forward with transposed weights, input gradients): every epilogue, ragged M; the first
+    two shapes run on 64 x 64 tiles, the last one on 128 x 128 tiles without a workspace and on 256 x 256 tiles with one
+    (whole rounds unsplit, the remaining tiles split over K).  test_gemm_every_macro_tile_nt has the rest."""
     rng = np.random.default_rng(12)
     A, B = _rnd(rng, (M, K), BF), _rnd(rng, (N, K), BF, 0.1)
     bias, R, R2 = _rnd(rng, (N,), BF), _rnd(rng, (M, N), BF), _rnd(rng, (M, N), BF)
@@ -391,8 +391,9 @@ def test_gemm_nt_epilogues(use_ws, M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(512, 768, 2085), (256, 256, 4100), (2048, 2048, 1031)])
 def test_gemm_weight_gradient_split_over_the_contraction(M, N, K):
-    """dW = X^T dY with a workspace: the contraction is cut into ranges (ragged last tile), partial sums added by the
-    second kernel; overwrite and accumulate; same result as the unsplit launch up to summation order."""
+    """dW = X^T dY with a workspace, in which the contraction may be cut into ranges (ragged last tile) whose partial sums a
+    second kernel adds (256 x 256 x 4100 is; the others run whole, on 64 x 64 and 128 x 128 tiles); overwrite and
+    accumulate; same result as without a workspace up to summation order."""
     rng = np.random.default_rng(13)
     X, dY = _rnd(rng, (K, M), BF), _rnd(rng, (K, N), BF)
     ref = X.astype(np.float64).T @ dY.astype(np.float64)
@@ -788,3 +789,50 @@ def test_attention_bf16_hidden_half_blocks_with_values_that_are_not_finite(hd):
             for i in range(2):
                 assert both_err(got[seen:, i * d:(i + 1) * d], ref[seen:, i * d:(i + 1) * d]) <= TOL[BF]
     assert np.isinf(got[:, d + hd + 5]).all() and np.array_equal(np.isnan(got[:, d:]), np.isnan(ref[:, d:]))       # dV of the last case
+
+
+@pytest.mark.parametrize("M,N,K,ws_floats", [
+    # 128 x 64 tiles (three stages): one to five K tiles, row edges, the contraction split
+    (129, 5632, 64, 0), (129, 5632, 128, 0), (129, 5632, 320, 0), (256, 8192, 320, 0), (641, 512, 4096, 1 << 22),
+    # 128 x 128, four stages
+    (383, 5632, 320, 0), (384, 5632, 320, 0), (385, 5632, 320, 0), (385, 7680, 256, 0), (129, 2304, 8192, 1 << 22),
+    # 128 x 128, two stages
+    (1537, 3840, 128, 0), (1537, 3840, 192, 0), (767, 6144, 320, 0), (768, 6144, 320, 0), (769, 6144, 320, 0), (756, 6144, 2048, 0),
+    (385, 4864, 8192, 1 << 22),
+    # 256 x 256: whole tiles of one and three K tiles; whole tiles and a split remainder; every tile split
+    (3073, 4608, 64, 0), (3073, 4608, 192, 0), (3329, 4864, 1024, 1 << 22), (385, 2816, 8192, 1 << 24)])
+def test_gemm_every_macro_tile_nt(M, N, K, ws_floats):
+    """C = A B^T at shapes that the estimates send to each of the macro tiles, whole and split over the contraction (the groups
+    above, on 256 compute units).  bf16 results: one rounding, 2^-9 of each value."""
+    rng = np.random.default_rng(41)
+    dA, dB, dR = (to_dev(_rnd(rng, s, BF, f), BF) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((M, N), 1.0)))
+    acc = torch.matmul(dA.double(), dB.double().t().contiguous())
+    ws = _ws(ws_floats) if ws_floats else None
+    c = torch.full((M + 1, N), 7.0, dtype=BF, device=DEV)
+    for kw, ref in ((dict(), acc), (dict(epilogue=ds.DS_EPI_MULR, R=dR), acc * dR.double())):
+        c.fill_(7.0)
+        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        assert both_err(to_np(c)[:M], ref.cpu().numpy()) <= 4e-3 and np.all(to_np(c)[M] == 7.0)
+
+
+@pytest.mark.parametrize("M,N,K,ws_floats", [
+    # 128 x 64 tiles: one and three (ragged) K tiles, split; 128 x 128 with four stages, whole and split; with two, two to four K tiles
+    (256, 4352, 33, 0), (256, 4352, 129, 0), (256, 1536, 6000, 1 << 22), (1792, 1792, 577, 0), (256, 2816, 9001, 1 << 22),
+    (2560, 3328, 65, 0), (2560, 3328, 129, 0), (2560, 3328, 200, 0),
+    # 256 x 256 (32-deep K tiles): one, a ragged few, ranges of the contraction, whole tiles and a split remainder
+    (10240, 3328, 1, 0), (10240, 3328, 97, 0), (256, 5632, 12000, 1 << 24), (10240, 3328, 250, 1 << 22)])
+def test_gemm_every_macro_tile_weight_gradient(M, N, K, ws_floats):
+    """The same for weight gradients, overwriting and adding; rows behind the last one hold NaN.  fp32 sums: 1e-5."""
+    rng = np.random.default_rng(42)
+    X, dY = _rnd(rng, (K, M), BF), _rnd(rng, (K, N), BF)
+    dX, ddY = (torch.cat([to_dev(a, BF), torch.full((64, a.shape[1]), float("nan"), dtype=BF, device=DEV)]) for a in (X, dY))
+    ref = torch.matmul(dX[:K].double().t().contiguous(), ddY[:K].double()).cpu().numpy()
+    ws = _ws(ws_floats) if ws_floats else None
+    c = torch.full((M, N), 3.0, dtype=F32, device=DEV)
+    ds.ds_gemm(dX, ddY, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, accumulate=False, workspace=ws)
+    torch.cuda.synchronize()
+    assert both_err(to_np(c), ref) <= 1e-5
+    ds.ds_gemm(dX, ddY, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, accumulate=True, workspace=ws)
+    torch.cuda.synchronize()
+    assert both_err(to_np(c), 2 * ref) <= 1e-5

@@ -224,3 +224,36 @@ def test_back_to_back_calls_on_a_caller_stream_without_host_synchronisation():
     for a, b in zip(ref, [out, dx] + [g[k] for g in grads for k in g]):
         assert torch.equal(a, b)
     stage.close()
+
+
+@pytest.mark.parametrize("d_ff,rows", [(1024, [1, 127, 128, 129, 256, 257, 385]), (5632, [129, 257, 384, 385, 641, 769])])
+def test_bias_gradient_from_partial_column_sums(d_ff, rows):
+    """The bias gradient of the MLP's first projection is summed from one partial row per 128 rows, of which an odd count is
+    padded to an even one: even and odd counts, full and ragged last tiles, after a larger call with gradients a thousand
+    times as large has filled the partial rows.  Every gradient is the one a fresh stage gives, bit for bit, and b_1 is
+    the oracle's."""
+    from helpers import params_to_dev
+    cfg = dict(n_layers=1, d_model=256, n_heads=4, d_ff=d_ff)
+    params = wl.draw_params(wl.GPT_KEYS, 1, 256, d_ff, seed=3, bf16=True)
+
+    def case(r, scale=1.0):
+        lens = np.array([r], np.int32)
+        xs = wl.draw_embedded_tokens(lens, 256, seed=r, bf16=True)
+        dys = [scale * y for y in wl.draw_rows(lens, 256, seed=r, tag=5, bf16=True)]
+        return ds.ds_layout_from_cuts(lens, [0, 1]), xs, dys
+
+    top = 2 * max(rows)
+    used = ds.Stage(ds.DS_MODEL_GPT, ds.DS_DTYPE_BF16, 1, 256, 4, d_ff, max_rows=top, max_seqs=4)
+    for r in rows:
+        lo, xs, dys = case(top, 1000.0)
+        run_gpt_stage(lo, cfg, params, xs, dys, ds.DS_DTYPE_BF16, stage=used)
+        lo, xs, dys = case(r)
+        got = run_gpt_stage(lo, cfg, params, xs, dys, ds.DS_DTYPE_BF16, stage=used)
+        fresh = ds.Stage(ds.DS_MODEL_GPT, ds.DS_DTYPE_BF16, 1, 256, 4, d_ff, max_rows=top, max_seqs=4)
+        want = run_gpt_stage(lo, cfg, params, xs, dys, ds.DS_DTYPE_BF16, stage=fresh)
+        fresh.close()
+        for k, v in want[2][0].items():
+            assert np.array_equal(got[2][0][k], v), (r, k)
+        ref = ost.gpt_stage_fwd_bwd(xs, dys, params, 4)
+        check(got[2][0]["b_1"], ref[2][0]["b_1"], TOL[ds.DS_DTYPE_BF16], "b_1 %d" % r)
+    used.close()
