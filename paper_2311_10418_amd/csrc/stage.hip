@@ -338,7 +338,7 @@ struct Ops {
     }
     ds_status weights_t_flush() {
         if (tb.n == 0) return DS_OK;
-        s->launches += tb.n;                        // (the rough count keeps one per matrix copied, however many a launch takes)
+        s->launches += tb.n;                        // (counted per matrix, however many a launch takes)
         const ds_status r = launch_transpose_bf16(tb, st);
         tb.n = 0;
         return r;
@@ -443,6 +443,12 @@ struct Ops {
                          s->lists_kind[cur_slot] == cur_kind) ? 1 : 0;
         return a;
     }
+    // kernels of one attention call: the matrix-core kernels build their lists first unless they are there, the others
+    // compute delta in a launch of its own
+    static int attn_launches(const AttnArgs& a, bool bwd) {
+        const int first = attn_mfma_supported(a) ? !a.lists_ready : bwd;
+        return first + (bwd ? 2 : 1);
+    }
     // after a launch that went through the matrix-core kernels: the scratch now holds both lists of this kind
     void lists_built(const AttnArgs& a) {
         if (attn_mfma_supported(a)) {
@@ -457,7 +463,7 @@ struct Ops {
         a.q = base; a.k = base + (size_t)d * s->es; a.v = base + (size_t)2 * d * s->es;
         a.ldq = a.ldk = a.ldv = 3 * d;
         a.o = o; a.lse = lse;
-        s->launches += a.lists_ready ? 1 : 3;
+        s->launches += attn_launches(a, false);
         DS_TRY(timed(s, DS_PROF_ATTN_FWD, st, [&] { return launch_attention_fwd(a, false, st); }));
         lists_built(a);
         return s->cfg.model == DS_MODEL_GPT ? DS_OK : zero_pad(sm, o, d);
@@ -470,7 +476,7 @@ struct Ops {
         a.o = const_cast<void*>(o); a.d_o = d_o; a.lse = const_cast<float*>(lse); a.delta = s->delta;
         char* g = (char*)dqkv;
         a.dq = g; a.dk = g + (size_t)d * s->es; a.dv = g + (size_t)2 * d * s->es;
-        s->launches += a.lists_ready ? 2 : 4;
+        s->launches += attn_launches(a, true);
         DS_TRY(timed(s, DS_PROF_ATTN_BWD, st, [&] { return launch_attention_bwd(a, false, st); }));
         lists_built(a);
         return s->cfg.model == DS_MODEL_GPT ? DS_OK : zero_pad(sm, dqkv, 3 * d);
@@ -690,7 +696,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
             a.q = b.qc; a.ldq = d;
             a.k = b.kvc; a.v = (const char*)b.kvc + (size_t)d * s->es; a.ldk = a.ldv = 2 * d;
             a.o = b.oc; a.lse = b.lsec;
-            s->launches += 2;
+            s->launches += Ops::attn_launches(a, false);
             DS_TRY(timed(s, DS_PROF_ATTN_FWD, st, [&] { return launch_attention_fwd(a, false, st); }));
             op.lists_built(a);
             DS_TRY(op.zero_pad(D, b.oc, d));
@@ -732,7 +738,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
             a.k = b.kvc; a.v = (const char*)b.kvc + (size_t)d * s->es; a.ldk = a.ldv = 2 * d;
             a.o = b.oc; a.d_o = s->d_o; a.lse = b.lsec; a.delta = s->delta;
             a.dq = s->dqc; a.dk = s->dkvc; a.dv = (char*)s->dkvc + (size_t)d * s->es;
-            s->launches += 4;
+            s->launches += Ops::attn_launches(a, true);
             DS_TRY(timed(s, DS_PROF_ATTN_BWD, st, [&] { return launch_attention_bwd(a, false, st); }));
             op.lists_built(a);
             DS_TRY(op.zero_pad(D, s->dqc, d));

@@ -257,3 +257,20 @@ def test_bias_gradient_from_partial_column_sums(d_ff, rows):
         ref = ost.gpt_stage_fwd_bwd(xs, dys, params, 4)
         check(got[2][0]["b_1"], ref[2][0]["b_1"], TOL[ds.DS_DTYPE_BF16], "b_1 %d" % r)
     used.close()
+
+
+@pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
+def test_launch_count_of_a_first_and_a_later_call(dtype_code):
+    """The first call with a layout makes both attention work lists in one launch more (bf16) and clears the padding rows of
+    the attention buffers in another; later calls do neither."""
+    cfg, lens, params, xs, dys = _small_case(True, n_seq=6)
+    for cuts, first_more in (([0, 6], 1), (list(range(7)), 0)):           # padded to the longest; no padding
+        lo = ds.ds_layout_from_cuts(lens, cuts)
+        stage = ds.Stage(ds.DS_MODEL_GPT, dtype_code, cfg["n_layers"], cfg["d_model"], cfg["n_heads"], cfg["d_ff"],
+                         max_rows=lo.total_rows, max_seqs=8)
+        n = []
+        for _ in range(3):
+            run_gpt_stage(lo, cfg, params, xs, dys, dtype_code, stage=stage)
+            n.append(stage.last_launch_count())
+        stage.close()
+        assert n[1] == n[2] and n[0] - n[1] == first_more + (dtype_code == ds.DS_DTYPE_BF16), (cuts, n)
