@@ -474,11 +474,11 @@ ds_status ds_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t M, in
                   const void* A, const void* B, void* C, int32_t epilogue, const void* bias,
                   const void* R, const void* R2, void* C2, const int32_t* row_valid, int32_t accumulate,
                   int32_t force_generic, void* hip_stream);
-/* ds_gemm with a DEVICE float32 workspace of workspace_floats entries (16-byte aligned), which lets the bf16
- * matrix-core kernels split the contraction the way the stage does: weight-gradient launches (ACC32,
- * trans_a = 1, trans_b = 0) into K ranges whose partial sums a second kernel adds up in a fixed order, all other
- * launches for the tiles of their last, partly filled round over the compute units.  The result differs from
- * ds_gemm's only in the order of fp32 additions; a workspace too small for a split is simply not used.
+/* ds_gemm with a DEVICE float32 workspace of workspace_floats entries (16-byte aligned), which lets the
+ * matrix-core kernels, bf16 and fp32, split the contraction the way the stage does: into K ranges whose partial
+ * sums a second kernel adds up in a fixed order, for all tiles of a launch or, on the largest tiles, for those of
+ * the last, partly filled round over the compute units.  The result differs from ds_gemm's only in the order of
+ * fp32 additions; a workspace too small for a split is simply not used.
  * Calls sharing a workspace must not overlap. */
 ds_status ds_gemm_ws(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t M, int32_t N, int32_t K,
                      const void* A, const void* B, void* C, int32_t epilogue, const void* bias,
@@ -502,7 +502,11 @@ int64_t ds_attention_scratch_bytes(int32_t n_heads, int32_t head_dim, int32_t q_
  * gets zero outputs / gradients.  scratch (DEVICE, 16-byte aligned, at least
  * ds_attention_scratch_bytes) enables the bf16 matrix-core kernels; with scratch = NULL, or a
  * shape they do not take, the generic kernels run.  k_total_rows: rows of the k / v tensors (the
- * q / o tensors have lse_stride rows). */
+ * q / o tensors have lse_stride rows).
+ * Values that are not finite: a row is affected by the rows it sees.  The bf16 matrix-core kernels
+ * multiply whole blocks by probabilities that are 0 where mask = 1 hides a token, so that an
+ * infinity or NaN may also reach rows up to 63 tokens in front of it in the output, up to 31 in dq
+ * (31 behind it in dk and dv). */
 ds_status ds_attention_fwd(int32_t dtype, int32_t n_seq, int32_t n_heads, int32_t head_dim, int32_t mask,
                            const int32_t* q_row, const int32_t* q_len, const int32_t* k_row, const int32_t* k_len,
                            int32_t max_q_len, int32_t max_k_len,

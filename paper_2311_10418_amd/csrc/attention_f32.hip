@@ -11,7 +11,7 @@
 //
 // The bound is the fp32 matrix rate: per 16 x 16 block HD/4 MFMAs of 32 cycles for each product (two forward, three in
 // dQ, four in dK/dV) against 4 exponentials per lane.  Tiles go global -> registers -> LDS, the next tile's reads in
-// flight during the current tile's products; 4 wavefronts per work-group (64 columns), 18 - 51 KB of LDS, so several
+// flight during the current tile's products; 4 wavefronts per work-group (64 columns), 19 - 54 KB of LDS, so several
 // work-groups per CU cover each other's two barriers per tile.  Sequences are taken last to first: a plan lists them by
 // ascending length, and the long ones should start first.  Measured at
 // 7 684 tokens in 64 sequences (up to 512), 4 heads of 64, causal: forward 37 us, dQ 42, dK/dV 86, against 508, 435 and
@@ -283,7 +283,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
 // Eight wavefronts: the first key blocks of a long causal sequence meet every query, and their work-groups set the
 // kernel's length.  Wavefronts w and w + 4 own the same 16 keys and take alternate 16-query blocks of every tile; their
 // accumulators are added through LDS at the end.  116 us with four wavefronts, 107 with eight, 86 with at most 128
-// registers (head size up to 64: two work-groups per CU; the other two kernels spill at 128 and lose).
+// registers (head size up to 64: two work-groups per CU).  At head size 64 that limit spills 2 registers here; the other
+// two kernels need 10 to 25 more than 128 there and lose with it (dQ 53 us instead of 42).
 template <int HD>
 __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel(AttnArgs a) {
     typedef F32Tile<HD, 512> Tile;

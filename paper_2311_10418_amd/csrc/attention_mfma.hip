@@ -199,7 +199,7 @@ __device__ __forceinline__ void store_cols(const f32x16_t (&acc)[HD / 32], float
         }
 }
 
-// the scratch starts with the two list lengths; from this int on, 16 for the draw counters (see WorkDraw)
+// the scratch starts with the two list lengths; from this int on, 16 for the draw counters (see lists_bytes)
 constexpr int kCtrHeader = 16;
 
 // ------------------------------------------------------------------------------------ work lists
@@ -889,8 +889,10 @@ int items_bound(int total_rows, int n_seq) { return total_rows / 128 + n_seq; }
 
 }  // namespace
 
-// Scratch: two counters, two work lists (query-side and key-side blocks), then the two statistics tensors the
-// backward kernels hand over ([n_heads][q_total_rows] entries of 16 bytes each).
+// Scratch: a header of 256 bytes (int 0, 1: lengths of the two lists; 16 .. 23: the per-XCD draws and 24: the finished
+// work-groups of a persistent kernel, see WorkDraw; the list kernel clears 16 .. 31), the two work lists (query-side and
+// key-side blocks), then the two statistics tensors the backward kernels hand over ([n_heads][q_total_rows] entries of 16
+// bytes each).
 static size_t lists_bytes(int q_total_rows, int k_total_rows, int n_seq) {
     const size_t b = 256 + sizeof(int2) * ((size_t)items_bound(q_total_rows, n_seq) + (size_t)items_bound(k_total_rows, n_seq));
     return (b + 255) & ~(size_t)255;

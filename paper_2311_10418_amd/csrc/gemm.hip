@@ -867,7 +867,8 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
 
 bool gemm_colsum_fused(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B,
                        const void* C, int32_t epilogue) {
-    // the conditions under which dispatch_epi takes launch_nt<DS_EPI_DGELU or DS_EPI_MULR, false>
+    // the conditions under which dispatch_epi takes launch_nt<DS_EPI_DGELU or DS_EPI_MULR, false> (two rows of partial column
+    // sums per tile row) or, with p.colsum set, a 128-row tile of gemm_tile.hip (one per tile row)
     static_assert(NT_WM == 2, "two rows of partial column sums per tile row");
     if ((epilogue != DS_EPI_DGELU && epilogue != DS_EPI_MULR) || dtype != DS_DTYPE_BF16 || ta || !tb) return false;
     if (N % BN || K % BK || M < 1 || K < 1) return false;

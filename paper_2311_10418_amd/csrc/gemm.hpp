@@ -9,8 +9,9 @@ struct GemmEpi {
     void* C2;                  // second output
     const int32_t* row_valid;  // rows with a negative entry are written as zeros (RESID epilogue)
     int accumulate;            // ACC32: add to C instead of overwriting
-    // DGELU epilogue, direct-to-LDS NT kernel only (see gemm_colsum_fused): partial column sums of the OUTPUT (before
-    // its rounding to bf16), float32 [gemm_colsum_rows(M)][N], every entry written; NULL = not wanted
+    // DGELU and MULR epilogues of the bf16 NT kernels (gemm_colsum_fused says when; 256 x 256 tiles or 128-row ones): partial
+    // column sums of the OUTPUT (before its rounding to bf16), float32 [gemm_colsum_rows(M)][N], every entry written;
+    // NULL = not wanted
     float* colsum;
 };
 

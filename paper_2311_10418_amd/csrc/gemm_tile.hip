@@ -20,8 +20,11 @@
 // estimate for the large kernel.  Measured, 256 x 256 kernel -> this, us (M, N, K; ds_gemm_ws on an idle card):
 //   NT 256, 768, 256: 10.2 -> 4.8    756, 2048, 2048: 36 -> 13      756, 8192, 2048: 43 -> 29    756, 2048, 8192: 50 -> 40
 //      1757, 2048, 2048: 37 -> 20    1757, 6144, 2048: 43 (50 with these: stays)    756, 6144, 2048: 42 -> 28
-//   TN 256, 1024, 250: 17 -> 5       2048, 2048, 756: 47 -> 16       2048, 2048, 1757: 43 -> 25  1024, 4096, 4173: 57 -> 46
-//      2048, 6144, 756: 37 -> 34     2048, 6144, 1757: 53 (56: stays)
+//   TN 256, 1024, 250: 17 -> 5       2048, 2048, 756: 47 -> 18       2048, 2048, 1757: 43 -> 26  1024, 4096, 4173: 58 -> 47
+//      2048, 6144, 756: 34 (stays)   2048, 6144, 1757: 53 (56: stays)
+// with the operands warm in the caches (each from memory: 2 to 12 us more in the NT form, 1 to 2 in the TN form).  The
+// estimates are short of these for weight gradients (13, 21 and 40 us for the last three that change), by about as much
+// for every tile; the margin of 5 % in dispatch_epi keeps the large kernel where the two are close.
 #include "gemm_epilogue.hpp"
 
 #include <algorithm>
