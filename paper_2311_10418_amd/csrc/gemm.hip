@@ -733,17 +733,17 @@ static BigPlan plan_big(bool tnf, int epi, int M, int N, int K, size_t split_ws_
 }
 
 // Estimated time of that plan in microseconds (see gemm_tile.hip for the other side of the comparison and the fit): 1.15
-// per 64-deep K tile of a 256 x 256 tile and 4 around it, per round over the compute units; 0.1 per piece of partial sums
-// (256 KB written and read back) and 4 for the launch that adds them.
+// (TN) or 1.25 (NT, operands from memory; 1.15 warm) per 64-deep K tile of a 256 x 256 tile and 4 around it, per round over
+// the compute units; 0.1 per piece of partial sums (256 KB written and read back) and 4 for the launch that adds them.
 static double big_cost(const BigPlan& b, bool tnf, int M, int N) {
     const int n_cu = gemm_cu_count(), tiles = b.tiles_m * b.tiles_n;
-    const double steps = tnf ? 0.5 * b.nt : b.nt;
+    const double steps = tnf ? 0.5 * b.nt : b.nt, step = tnf ? 1.15 : 1.25;
     auto rounds = [&](double work_groups) { return std::ceil(work_groups / n_cu); };
     if (b.splits > 1)
-        return rounds((double)tiles * b.splits) * (steps / b.splits * 1.15 + 4) + 2e-6 * (double)b.splits * M * N + 4;
-    double t = b.n_main ? rounds(b.n_main) * (steps * 1.15 + 4) : 0;
+        return rounds((double)tiles * b.splits) * (steps / b.splits * step + 4) + 2e-6 * (double)b.splits * M * N + 4;
+    double t = b.n_main ? rounds(b.n_main) * (steps * step + 4) : 0;
     const int tail = tiles - b.n_main;
-    if (tail) t += steps / b.tail_splits * 1.15 + 4 + 0.1 * tail * b.tail_splits + 4;
+    if (tail) t += steps / b.tail_splits * step + 4 + 0.1 * tail * b.tail_splits + 4;
     return t;
 }
 
@@ -847,8 +847,8 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
                 const BigPlan plan = plan_big(tn, EPI, M, N, K, wsf);
                 if (plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
                     const double out_us = gemm_output_us(EPI, M, N, p.accumulate);
-                    const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, p.colsum != nullptr, out_us);
-                    if (pick.kind >= 0 && pick.cost < 0.95 * (big_cost(plan, tn, M, N) + out_us))      // (ties go to the large tile)
+                    const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, p.colsum != nullptr, out_us, p.accumulate != 0);
+                    if (pick.kind >= 0 && pick.versus_large < 0.95 * (big_cost(plan, tn, M, N) + out_us))      // (ties go to the large tile)
                         return launch_gemm_tile(pick, tn, M, N, K, A, B, C, EPI, p, split_ws, st);
                 }
             }

@@ -29,12 +29,13 @@ bool gemm_f32_mfma_supported(int32_t ta, int32_t tb, int32_t M, int32_t N, int32
 ds_status launch_gemm_f32_mfma(int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B, void* C,
                                int32_t epilogue, const GemmEpi& p, float* split_ws, size_t split_ws_floats, hipStream_t st);
 
-// bf16 with smaller macro tiles (gemm_tile.hip).  kind: which tile, -1 = none fits; cost: estimated microseconds.
+// bf16 with smaller macro tiles (gemm_tile.hip).  kind: which tile, -1 = none fits; cost: estimated microseconds, what the
+// kinds are ranked by; versus_large: the estimate to compare with that of the 256 x 256 kernel.
 struct TilePick {
     int kind, splits;
-    double cost;
+    double cost, versus_large;
 };
-TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us);
+TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us, bool out_read);
 // microseconds (4 TB/s) to write an fp32 output and, when it is added to, to read it first: weight gradients of few tokens
 // take about as long for this as for the products
 inline double gemm_output_us(int epilogue, int32_t M, int32_t N, int accumulate) {

@@ -22,9 +22,7 @@
 //      1757, 2048, 2048: 37 -> 20    1757, 6144, 2048: 43 (50 with these: stays)    756, 6144, 2048: 42 -> 28
 //   TN 256, 1024, 250: 17 -> 5       2048, 2048, 756: 47 -> 18       2048, 2048, 1757: 43 -> 26  1024, 4096, 4173: 58 -> 47
 //      2048, 6144, 756: 34 (stays)   2048, 6144, 1757: 53 (56: stays)
-// with the operands warm in the caches (each from memory: 2 to 12 us more in the NT form, 1 to 2 in the TN form).  The
-// estimates are short of these for weight gradients (13, 21 and 40 us for the last three that change), by about as much
-// for every tile; the margin of 5 % in dispatch_epi keeps the large kernel where the two are close.
+// with the operands warm in the caches (each from memory: 2 to 12 us more in the NT form, 1 to 2 in the TN form).
 #include "gemm_epilogue.hpp"
 
 #include <algorithm>
@@ -278,6 +276,9 @@ struct TileShape { int bm, bn, waves, stages; double step, fixed; };
 constexpr int kKinds = 4;
 constexpr TileShape kShapes[kKinds] = {{128, 128, 8, 4, 0.49, 3.0}, {128, 64, 8, 3, 0.32, 2.5}, {64, 64, 4, 3, 0.20, 2.5}, {128, 128, 8, 2, 0.39, 3.0}};
 constexpr double kBusyStep3 = 0.62;                  // kind 3, per tile, when every CU works on two (0.55 on operands that are warm in L2)
+constexpr double kBusyStep0 = 0.64;                  // kind 0, per tile, several of them one after the other
+constexpr double kLoneStep1 = 0.36, kLoneStep2 = 0.24;                // TN form, one tile per CU: nothing covers its waits
+constexpr double kColdStep0Nt = 0.51, kColdStep0Tn = 0.55;           // kind 0, operands from memory
 
 template <int EPI, bool TNF, int KIND, int WM, int WN>
 ds_status launch_kind(int splits, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
@@ -327,8 +328,14 @@ int gemm_cu_count() {
 //   round trip of the partial sums at 4 TB/s and 5 us for the launch that adds them.
 // out_us: moving an fp32 output (see gemm_output_us); half of it is hidden where a CU has other tiles to work on meanwhile.
 // colsum: the epilogue's column sums are wanted, which takes 128-row tiles and whole K loops.
-TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us) {
-    TilePick best{-1, 1, 0.0};
+// versus_large differs in two places that matter only against the other kernel, whose constants hold for operands from memory:
+// kind 0 counts its step from memory, and of the output only the reading (out_read: half of out_us) is hidden, by half;
+// writing goes at the rate of the memory either way (2048 x 8192 over 126 tokens: 30.9 us on 128 x 64 tiles, 24.5 on
+// 256 x 256 ones).  Of 1 500 random shapes of stages with d = 256 .. 2048 (96 to 16 000 rows, operands from memory) 12 take
+// over 3 % longer than on the large kernel, at most 12 %; with the rates of warm operands throughout it was 40 of 1 100, up to
+// 21 %.
+TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us, bool out_read) {
+    TilePick best{-1, 1, 0.0, 0.0};
     if (tn && (M > (1 << 24) || N > (1 << 24))) return best;          // a K tile is addressed through a 32-bit buffer length
     const int n_cu = gemm_cu_count(), nt = (K + T_KD - 1) / T_KD;
     for (int k = 0; k < kKinds; ++k) {
@@ -341,11 +348,15 @@ TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_w
             if ((nt + per - 1) / per != sp || tiles * sp > 1e9) continue;         // every split owns at least one K tile
             const double rounds = std::ceil(tiles * sp / n_cu);
             if (k == 3 && rounds < 2) continue;                       // kind 0 is the better one
-            double cost = rounds * per * s.step;
-            if (k == 3) cost = std::max(cost, tiles * sp / n_cu * per * kBusyStep3);
-            cost += s.fixed + (k == 0 || rounds <= 2 ? out_us : 0.5 * out_us);
-            if (sp > 1) cost += 2e-6 * sp * (double)M * N + 5;
-            if (best.kind < 0 || cost < best.cost) best = TilePick{k, sp, cost};
+            double loop = rounds * per * s.step;
+            if (k == 0 && rounds > 1) loop = rounds * per * kBusyStep0;
+            if (tn && rounds == 1 && (k == 1 || k == 2)) loop = per * (k == 1 ? kLoneStep1 : kLoneStep2);
+            if (k == 3) loop = std::max(loop, tiles * sp / n_cu * per * kBusyStep3);
+            const double around = s.fixed + (sp > 1 ? 2e-6 * sp * (double)M * N + 5 : 0.0);
+            const bool hides = k != 0 && rounds > 2;
+            const double cost = loop + around + (hides ? 0.5 * out_us : out_us);
+            if (best.kind < 0 || cost < best.cost)
+                best = TilePick{k, sp, cost, (k == 0 ? rounds * per * (tn ? kColdStep0Tn : kColdStep0Nt) : loop) + around + (hides && out_read ? 0.75 * out_us : out_us)};
         }
     }
     return best;

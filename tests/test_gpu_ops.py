@@ -800,7 +800,7 @@ def test_attention_bf16_hidden_half_blocks_with_values_that_are_not_finite(hd):
     (1537, 3840, 128, 0), (1537, 3840, 192, 0), (767, 6144, 320, 0), (768, 6144, 320, 0), (769, 6144, 320, 0), (756, 6144, 2048, 0),
     (385, 4864, 8192, 1 << 22),
     # 256 x 256: whole tiles of one and three K tiles; whole tiles and a split remainder; every tile split
-    (3073, 4608, 64, 0), (3073, 4608, 192, 0), (3329, 4864, 1024, 1 << 22), (385, 2816, 8192, 1 << 24)])
+    (3073, 4608, 64, 0), (3073, 4608, 192, 0), (3329, 4864, 1024, 1 << 22), (129, 5888, 8192, 1 << 24)])
 def test_gemm_every_macro_tile_nt(M, N, K, ws_floats):
     """C = A B^T at shapes that the estimates send to each of the macro tiles, whole and split over the contraction (the groups
     above, on 256 compute units).  bf16 results: one rounding, 2^-9 of each value."""
@@ -818,8 +818,9 @@ def test_gemm_every_macro_tile_nt(M, N, K, ws_floats):
 
 @pytest.mark.parametrize("M,N,K,ws_floats", [
     # 128 x 64 tiles: one and three (ragged) K tiles, split; 128 x 128 with four stages, whole and split; with two, two to four K tiles
+    # (the first two of these when they add, else 256 x 256)
     (256, 4352, 33, 0), (256, 4352, 129, 0), (256, 1536, 6000, 1 << 22), (1792, 1792, 577, 0), (256, 2816, 9001, 1 << 22),
-    (2560, 3328, 65, 0), (2560, 3328, 129, 0), (2560, 3328, 200, 0),
+    (2560, 3328, 129, 0), (2560, 3328, 200, 0), (2560, 6656, 65, 0),
     # 256 x 256 (32-deep K tiles): one, a ragged few, ranges of the contraction, whole tiles and a split remainder
     (10240, 3328, 1, 0), (10240, 3328, 97, 0), (256, 5632, 12000, 1 << 24), (10240, 3328, 250, 1 << 22)])
 def test_gemm_every_macro_tile_weight_gradient(M, N, K, ws_floats):
