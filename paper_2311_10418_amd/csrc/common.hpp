@@ -257,6 +257,8 @@ struct RowSegments {
 };
 // to_stream: canonical -> stream, padding rows zeroed; otherwise stream -> canonical.  row_bytes: a multiple of 16
 ds_status launch_move_rows(const RowSegments& b, int32_t row_bytes, const void* in, void* out, bool to_stream, hipStream_t st);
+// The same for all `rows` rows of a stream through a DEVICE map: canonical row of each stream row, -1 for padding
+ds_status launch_move_rows_map(int32_t rows, const int32_t* map, int32_t row_bytes, const void* in, void* out, bool to_stream, hipStream_t st);
 // out[c] = (accumulate ? out[c] : 0) + sum over p < n_partial of partial[p * n + c]   (float32, fixed summation order)
 ds_status launch_reduce_partials(int32_t n_partial, int32_t n, const float* partial, float* out, int32_t accumulate,
                                  hipStream_t st);

@@ -643,10 +643,10 @@ def test_gemm_smaller_tiles_weight_gradient(M, N, K):
 
 
 @pytest.mark.parametrize("dt", [F32, BF])
-@pytest.mark.parametrize("form,n,d", [("dp", 1, 8), ("dp", 40, 264), ("packed", 60, 128), ("fixed", 600, 24), ("dp", 1000, 16), ("target", 300, 72)])
+@pytest.mark.parametrize("form,n,d", [("dp", 1, 8), ("dp", 40, 264), ("packed", 60, 128), ("fixed", 600, 24), ("dp", 1000, 16), ("target", 300, 72), ("packed", 2500, 8), ("target", 3000, 264)])
 def test_pack_unpack_forms(dt, form, n, d):
-    """Layouts in and out of row order, gaps at every kind of place, more sequences than one launch's arguments hold, a target
-    stream: every value moved once, padding rows zeroed over what was there."""
+    """Layouts in and out of row order, gaps at every kind of place, more sequences than one launch's arguments hold (few enough
+    for several launches, and so many that the row map goes through memory), a target stream: every value moved once, padding rows zeroed over what was there."""
     rng = np.random.default_rng(37)
     lens = np.clip(np.rint(rng.lognormal(2.5, 0.8, n)), 1, 90).astype(np.int32)
     if form == "packed":
