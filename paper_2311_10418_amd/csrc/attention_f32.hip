@@ -14,7 +14,7 @@
 // flight during the current tile's products; 4 wavefronts per work-group (64 columns), 19 - 54 KB of LDS, so several
 // work-groups per CU cover each other's two barriers per tile.  Sequences are taken last to first: a plan lists them by
 // ascending length, and the long ones should start first.  Measured at
-// 7 684 tokens in 64 sequences (up to 512), 4 heads of 64, causal: forward 37 us, dQ 42, dK/dV 86, against 508, 435 and
+// 7 684 tokens in 64 sequences (up to 512), 4 heads of 64, causal: forward 40 us, dQ 44, dK/dV 87, against 508, 435 and
 // 581 for one wavefront per query / key row with shuffled probabilities (attention_generic.hip, which keeps the operands
 // that float4 cannot read): those read every row of the other side once per row of this one.
 #include "attention_rows.hpp"
