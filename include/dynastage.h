@@ -433,7 +433,7 @@ ds_status ds_stage_profile_read(ds_stage* stage, float* ms, int32_t* count);
 ds_status ds_stage_weights_unchanged(ds_stage* stage, int32_t unchanged);
 
 /* Rough count of the kernels one stage_fwd_bwd call launches (diagnostics): a GEMM counts one, also where a second
- * launch adds up its partial sums; a transposed weight copy counts one per matrix, though one launch makes many. */
+ * launch adds up its partial sums, and so do the weight gradients of a layer that go out in one launch; a transposed weight copy counts one per matrix, though one launch makes many. */
 int32_t ds_stage_last_launch_count(const ds_stage* stage);
 
 /*

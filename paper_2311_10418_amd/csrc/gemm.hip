@@ -16,7 +16,7 @@
 #include <atomic>
 #include <cmath>
 #include <mutex>
-
+#include <type_traits>
 
 namespace {
 
@@ -131,14 +131,18 @@ __host__ __device__ __forceinline__ void nt_tile_coords(int logical, int tiles_m
 // starts (into stage 0, while the epilogue stages through LDS above it), so neither the latency of that first fetch
 // nor the end of one work-group and the start of the next leaves the matrix cores idle.  The last work-group to
 // finish puts the counters back to zero (ps_ctr[8] counts the finished ones).
-template <int EPI, int WM, int WN, bool TNF, bool PS>
+//
+// GRP (TN form): the work-groups of several weight gradients over the same K rows (grp), problem after problem.
+template <int EPI, int WM, int WN, bool TNF, bool PS, bool GRP = false>
 __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
                                                                        const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
                                                                        int tiles_m, int tiles_n, int splits,
                                                                        int n_main, int tail_splits,
                                                                        float* __restrict__ split_ws, GemmEpi p,
-                                                                       int ps_wgs, int* __restrict__ ps_ctr) {
+                                                                       int ps_wgs, int* __restrict__ ps_ctr,
+                                                                       std::conditional_t<GRP, TnGroup, NoGroup> grp) {
     static_assert(!(PS && TNF), "the persistent form exists for the NT kernel only");
+    static_assert(!GRP || (TNF && EPI == DS_EPI_ACC32), "groups are of weight gradients");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int NW = WM * WN;                    // wavefronts
     constexpr int TM = 256 / WM / 32, TN = 256 / WN / 32;   // 32x32 MFMA tiles per wavefront
@@ -155,8 +159,21 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
     //    run unsplit; each of the remaining tiles is cut into tail_splits K ranges so that the last, partly filled
     //    round costs 1/tail_splits of a round; their partial sums go to split_ws as [tail tile][split][256][256].
     // Tiles are numbered so that each XCD works on contiguous runs, in groups of 8 tile rows (L2 reuse).
-    const int n_tiles = tiles_m * tiles_n;
     int logical, split, nsplit;
+    if constexpr (GRP) {
+        logical = xcd_contiguous(blockIdx.x, gridDim.x);
+        const int i = tn_group_problem(grp, logical);
+        M = grp.p[i].M;
+        N = grp.p[i].N;
+        A = reinterpret_cast<const bf16_t*>(grp.p[i].A);
+        B = reinterpret_cast<const bf16_t*>(grp.p[i].B);
+        C = reinterpret_cast<bf16_t*>(grp.p[i].C);
+        // one block of the workspace per (tile, split): tile_index * splits + split, tiles counted over the whole group
+        if (splits > 1) split_ws = grp.block(grp.first[i] + logical);
+        tiles_m = M / BM;
+        tiles_n = N / BN;
+    }
+    const int n_tiles = tiles_m * tiles_n;
     bool tail = false;
     const bool persistent = PS && (int)blockIdx.x < ps_wgs;
     int run_start = 0, run_cnt = 0;                 // persistent: this XCD's run of unsplit tiles
@@ -168,14 +185,15 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
         logical = run_start + (blockIdx.x >> 3);    // (the host launches this form only with n_main >= 2 ps_wgs)
         split = 0;
         nsplit = 1;
+    } else if constexpr (GRP) {
+        split = logical / n_tiles;
+        logical -= split * n_tiles;
+        nsplit = splits;
     } else {
         const int pid = PS ? (int)blockIdx.x - ps_wgs + n_main : (int)blockIdx.x;
         const int total = splits > 1 ? n_tiles * splits : n_main;
         if (pid < total) {
-            const int xcd = pid & 7, local = pid >> 3;
-            const int per = total >> 3, rem = total & 7;
-            const int start = xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per;
-            logical = start + local;
+            logical = xcd_contiguous(pid, total);
             split = logical / n_tiles;
             logical -= split * n_tiles;
             nsplit = splits;
@@ -488,6 +506,19 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
 #pragma unroll
             for (int i = 0; i < TM; ++i) prefetch_pass(i);
         }
+        // accumulation: what is added to, fetched one pass ahead (the four gradients of a layer at d = 2048, d_ff = 8192 over 1 797
+        // tokens: 252 -> 242 us; streaming stores and lines requested at the start of the K loop: slower)
+        constexpr bool PRE_OLD = EPI == DS_EPI_ACC32 && TNF;
+        const bool adds = PRE_OLD && direct && p.accumulate;
+        float old[2][NPSS][8];
+        auto fetch_old = [&](int i, float (&dst)[NPSS][8]) {
+#pragma unroll
+            for (int pss = 0; pss < NPSS; ++pss) {
+                const int m = em0 + wm * (TM * 32) + i * 32 + pss * (64 / LPR) + rd_row;
+                if (m < M) Vec8<float>::load(reinterpret_cast<const float*>(C) + (size_t)m * N + en0 + wn * (TN * 32) + rd_col, dst[pss]);
+            }
+        };
+        if (adds) fetch_old(0, old[0]);
         if constexpr (EPI == DS_EPI_NONE) {
             // Plain output (+ bias): nothing is computed after the transposition, so the bias is added and the value
             // rounded to bf16 BEFORE staging: half the LDS traffic of the fp32 staging below, which bounds the epilogue.
@@ -536,6 +567,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             if (epilogue_reads<EPI>() && direct && !PRE_ALL) prefetch_pass(i);
+            if (adds && i + 1 < TM) fetch_old(i + 1, old[(i + 1) & 1]);
             wave_lds_sync();            // the staging block is private to the wavefront: no work-group barrier (which would
                                         // also wait for the global stores of the previous pass to be acknowledged)
 #pragma unroll
@@ -557,7 +589,9 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
                     const float4 x0 = *reinterpret_cast<const float4*>(stage + row * STG_LD + rd_col);
                     const float4 x1 = *reinterpret_cast<const float4*>(stage + row * STG_LD + rd_col + 4);
                     v[0] = x0.x; v[1] = x0.y; v[2] = x0.z; v[3] = x0.w; v[4] = x1.x; v[5] = x1.y; v[6] = x1.z; v[7] = x1.w;
-                    if (tail) {
+                    if (GRP && splits > 1) {
+                        Vec8<float>::store(split_ws + (size_t)(m - em0) * BN + (n - en0), v);
+                    } else if (tail) {
                         Vec8<float>::store(split_ws + ((size_t)((elogical - n_main) * tail_splits + split) * BM + (m - em0)) * BN + (n - en0), v);
                     } else if (splits > 1) {
                         Vec8<float>::store(split_ws + ((size_t)split * M + m) * N + n, v);
@@ -567,6 +601,12 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
 #pragma unroll
                             for (int j = 0; j < 8; ++j) csum[j] += v[j];
                         }
+                    } else if (PRE_OLD) {
+                        if (adds) {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) v[j] += old[i & 1][pss][j];
+                        }
+                        Vec8<float>::store(reinterpret_cast<float*>(C) + (size_t)m * N + n, v);
                     } else {
                         epilogue8<bf16_t, EPI>(m, n, N, v, C, p);
                     }
@@ -803,14 +843,14 @@ ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, 
             if (ctr) {
                 hipLaunchKernelGGL(kern_ps, dim3(n_cu + (tiles - n_main) * tail_splits), dim3(WM * WN * 64), smem_ps, st, M, N, K,
                                    (const bf16_t*)A, (const bf16_t*)B, (bf16_t*)C, tiles_m, tiles_n, splits, n_main, tail_splits,
-                                   split_ws, p, n_cu, ctr);
+                                   split_ws, p, n_cu, ctr, NoGroup{});
                 launched = true;
             }
         }
     }
     if (!launched)
         hipLaunchKernelGGL(kern, dim3(total), dim3(WM * WN * 64), smem, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, (bf16_t*)C,
-                           tiles_m, tiles_n, splits, n_main, tail_splits, split_ws, p, 0, (int*)nullptr);
+                           tiles_m, tiles_n, splits, n_main, tail_splits, split_ws, p, 0, (int*)nullptr, NoGroup{});
     DS_LAUNCH_CHECK();
     if (splits > 1) {
         return launch_splitk_finish<bf16_t, EPI>(M, N, splits, split_ws, C, p, st);
@@ -908,6 +948,53 @@ ds_status launch_gemm(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t 
         return dispatch_epi<DS_EPI_DGATE>(dtype, ta, tb, M, N, K, A, B, C, p, force_generic, split_ws, split_ws_floats, st);
     }
     return DS_EINVAL;
+}
+
+// adds up the partial sums of a group's tiles; blockIdx.y = tile, counted over the whole group
+__global__ __launch_bounds__(256) void tn_group_finish_kernel(TnGroup g) {
+    int at = blockIdx.y * g.splits;                                   // work-group number of the tile's first split, were they in turn
+    const int i = tn_group_problem(g, at);
+    const int N = g.p[i].N, tiles_m = g.p[i].M / BM, tiles_n = N / BN, tile = at / g.splits;
+    int tile_m, tile_n;
+    nt_tile_coords(tile, tiles_m, tiles_n, tile_m, tile_n);
+    float* C = reinterpret_cast<float*>(g.p[i].C);
+    GemmEpi p{};
+    p.accumulate = g.accumulate;
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < BM * (BN / 8); e += gridDim.x * blockDim.x) {
+        const int r = e / (BN / 8), c8 = (e % (BN / 8)) * 8;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = 0.f;
+#pragma unroll 4
+        for (int sp = 0; sp < g.splits; ++sp) {
+            float w[8];
+            Vec8<float>::load(g.block(g.first[i] + sp * tiles_m * tiles_n + tile) + (size_t)r * BN + c8, w);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] += w[j];
+        }
+        epilogue8<float, DS_EPI_ACC32>(tile_m * BM + r, tile_n * BN + c8, N, v, C, p);
+    }
+}
+
+ds_status launch_tn_group_big(TnGroup& g, int blocks, hipStream_t st) {
+    auto kern = gemm_bf16_nt_kernel<DS_EPI_ACC32, NT_WM, NT_WN, true, false, true>;
+    constexpr int stg = NT_WM * NT_WN * 32 * ((256 / NT_WN) + 4) * 4;
+    constexpr int smem = NT_NS * NT_STAGE > stg ? NT_NS * NT_STAGE : stg;
+    static bool attr_set = false;
+    if (!attr_set) {
+        DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        attr_set = true;
+    }
+    GemmEpi p{};
+    p.accumulate = g.accumulate;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NT_WM * NT_WN * 64), smem, st, 0, 0, g.K, (const bf16_t*)nullptr,
+                       (const bf16_t*)nullptr, (bf16_t*)nullptr, 0, 0, g.splits, 0, 1, (float*)nullptr, p, 0, (int*)nullptr, g);
+    DS_LAUNCH_CHECK();
+    if (g.splits > 1) {
+        hipLaunchKernelGGL(tn_group_finish_kernel, dim3(8, (unsigned)(blocks / g.splits)), dim3(256), 0, st, g);
+        DS_LAUNCH_CHECK();
+    }
+    return DS_OK;
 }
 
 extern "C" ds_status ds_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t M, int32_t N, int32_t K,

@@ -44,5 +44,42 @@ inline double gemm_output_us(int epilogue, int32_t M, int32_t N, int accumulate)
 ds_status launch_gemm_tile(const TilePick& pick, bool tn, int32_t M, int32_t N, int32_t K, const void* A, const void* B, void* C,
                            int32_t epilogue, const GemmEpi& p, float* split_ws, hipStream_t st);
 
+// Weight gradients that contract over the same K token rows (those of one layer), as one launch:
+// C[M,N] (+)= A[K,M]^T B[K,N], bf16 operands, fp32 result; M and N multiples of 256, pointers 16-byte aligned.
+constexpr int kTnGroup = 8;
+struct TnProblem {
+    const void* A;
+    const void* B;
+    void* C;
+    int32_t M, N;
+};
+struct TnGroup {
+    int32_t n = 0, K = 0, accumulate = 0;
+    TnProblem p[kTnGroup];
+    // Room for partial sums, in blocks of 256 x 256 floats: block u lies in the first slab i with u < slab_end[i]
+    static constexpr int kSlabs = 3;
+    float* slab[kSlabs];
+    int32_t slab_end[kSlabs];
+    // filled in by launch_tn_group: K loops per tile, and the first work-group of each problem
+    int32_t splits = 1;
+    int32_t first[kTnGroup];
+    __host__ __device__ float* block(int u) const {
+        const int i = u < slab_end[0] ? 0 : u < slab_end[1] ? 1 : 2;
+        return slab[i] + ((size_t)(u - (i ? slab_end[i - 1] : 0)) << 16);
+    }
+};
+// which tile (a kind of gemm_tile.hip, kTnBig = the 256 x 256 kernel, -1: one launch each instead) and how many splits
+constexpr int kTnBig = 4;
+struct TnPick {
+    int kind, splits;
+};
+TnPick pick_tn_group(const TnGroup& g);
+ds_status launch_tn_group(const TnPick& pick, TnGroup& g, hipStream_t st);
+ds_status launch_tn_group_big(TnGroup& g, int blocks, hipStream_t st);     // gemm.hip's part of it
+inline bool tn_group_takes(const TnProblem& q, int32_t K) {
+    return q.M > 0 && q.N > 0 && K > 0 && q.M % 256 == 0 && q.N % 256 == 0 && q.M <= (1 << 24) && q.N <= (1 << 24) &&
+           (((uintptr_t)q.A | (uintptr_t)q.B | (uintptr_t)q.C) & 15) == 0;
+}
+
 // compute units of the current device (256 where it cannot be asked)
 int gemm_cu_count();

@@ -4,6 +4,22 @@
 
 namespace {
 
+// ---------------------------------------------------------------------------- work-group ids
+// Work-group id -> logical number such that each XCD (ids are dealt to the XCDs in turn) gets a contiguous run.
+__device__ __forceinline__ int xcd_contiguous(int pid, int total) {
+    const int xcd = pid & 7, per = total >> 3, rem = total & 7;
+    return (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (pid >> 3);
+}
+// kernel argument of the forms that run one problem
+struct NoGroup {};
+// the problem of a group that logical work-group `l` belongs to; l becomes its number within that problem
+__device__ __forceinline__ int tn_group_problem(const TnGroup& g, int& l) {
+    int i = 0;
+    while (i + 1 < g.n && l >= g.first[i + 1]) ++i;
+    l -= g.first[i];
+    return i;
+}
+
 // ---------------------------------------------------------------------------- epilogues
 // Applied to 8 consecutive columns n..n+7 of row m; acc holds the fp32 accumulators.
 // What an epilogue reads besides the accumulators, fetched ahead of time (8 elements of R, of R2, the row flag),

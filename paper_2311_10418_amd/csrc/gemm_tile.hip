@@ -27,6 +27,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace {
 
@@ -103,11 +104,14 @@ template <int ROWS, bool KC, int NW> struct OperandTile {
 // Ring of NS stages, 64-deep K tiles: a tile's transfers are issued NS - 1 tiles ahead, right after the barrier that
 // frees their stage; the fragments of the next 32-deep step are read while the current one is multiplied, across the
 // tile boundary too.  Transfers past the last tile are clamped so that the wait counts never change.
-template <int EPI, bool TNF, int BM, int BN, int WM, int WN, int NS>
+// GRP (TN form): the work-groups of several weight gradients over the same K rows (grp), problem after problem.
+template <int EPI, bool TNF, int BM, int BN, int WM, int WN, int NS, bool GRP = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
                                                                       const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
                                                                       int tiles_m, int tiles_n, int splits, int tiles_per_split,
-                                                                      float* __restrict__ split_ws, GemmEpi p) {
+                                                                      float* __restrict__ split_ws, GemmEpi p,
+                                                                      std::conditional_t<GRP, TnGroup, NoGroup> grp) {
+    static_assert(!GRP || (TNF && EPI == DS_EPI_ACC32), "groups are of weight gradients");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int NW = WM * WN;
     typedef OperandTile<BM, !TNF, NW> TA;
@@ -123,9 +127,17 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
 
     int tile_m, tile_n, split;
     {
-        const int total = gridDim.x, pid = blockIdx.x;
-        const int xcd = pid & 7, per = total >> 3, rem = total & 7;
-        int logical = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (pid >> 3);
+        int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+        if constexpr (GRP) {
+            const int i = tn_group_problem(grp, logical);
+            M = grp.p[i].M;
+            N = grp.p[i].N;
+            A = reinterpret_cast<const bf16_t*>(grp.p[i].A);
+            B = reinterpret_cast<const bf16_t*>(grp.p[i].B);
+            C = reinterpret_cast<bf16_t*>(grp.p[i].C);
+            tiles_m = M / BM;
+            tiles_n = N / BN;
+        }
         const int n_tiles = tiles_m * tiles_n;
         split = logical / n_tiles;
         logical -= split * n_tiles;
@@ -296,9 +308,28 @@ ds_status launch_kind(int splits, int M, int N, int K, const void* A, const void
     const int tiles_m = (M + s.bm - 1) / s.bm, tiles_n = N / s.bn;
     const int nt = (K + T_KD - 1) / T_KD, per = (nt + splits - 1) / splits;      // (the pick leaves no split empty)
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n * splits)), dim3(s.waves * 64), smem, st, M, N, K, (const bf16_t*)A,
-                       (const bf16_t*)B, (bf16_t*)C, tiles_m, tiles_n, splits, per, split_ws, p);
+                       (const bf16_t*)B, (bf16_t*)C, tiles_m, tiles_n, splits, per, split_ws, p, NoGroup{});
     DS_LAUNCH_CHECK();
     if (splits > 1) return launch_splitk_finish<bf16_t, EPI>(M, N, splits, split_ws, C, p, st);
+    return DS_OK;
+}
+
+template <int KIND, int WM, int WN>
+ds_status launch_group_kind(const TnGroup& g, int blocks, hipStream_t st) {
+    constexpr TileShape s = kShapes[KIND];
+    constexpr int ring = s.stages * (s.bm + s.bn) * T_KD * 2, staging = s.waves * 32 * (s.bn / WN + 4) * 4;
+    constexpr int smem = ring > staging ? ring : staging;
+    static bool attr_set = false;
+    auto kern = gemm_bf16_tile_kernel<DS_EPI_ACC32, true, s.bm, s.bn, WM, WN, s.stages, true>;
+    if (!attr_set) {
+        DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        attr_set = true;
+    }
+    GemmEpi p{};
+    p.accumulate = g.accumulate;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(s.waves * 64), smem, st, 0, 0, g.K, (const bf16_t*)nullptr,
+                       (const bf16_t*)nullptr, (bf16_t*)nullptr, 0, 0, 1, (g.K + T_KD - 1) / T_KD, (float*)nullptr, p, g);
+    DS_LAUNCH_CHECK();
     return DS_OK;
 }
 
@@ -375,6 +406,73 @@ ds_status launch_gemm_tile(const TilePick& pick, bool tn, int32_t M, int32_t N, 
     case DS_EPI_DGATE: return launch_form<DS_EPI_DGATE, false>(pick, M, N, K, A, B, C, p, split_ws, st);
     case DS_EPI_GELU_D: return launch_form<DS_EPI_GELU_D, false>(pick, M, N, K, A, B, C, p, split_ws, st);
     case DS_EPI_MULR: return launch_form<DS_EPI_MULR, false>(pick, M, N, K, A, B, C, p, split_ws, st);
+    }
+    return DS_EINVAL;
+}
+
+// Weight gradients over `per` 64-deep K tiles with mn output elements in one launch: the kind and split count with the
+// smallest estimate, in microseconds:
+//   6 + rounds over the CUs x K tiles x step + the fp32 output at 4 TB/s (+ 5 and the round trip of the partial sums)
+// with the step a CU takes for a K tile, operands from memory, when it has one tile / several:
+//   128 x 128 0.85 / 0.85, 128 x 64 0.60 / 0.50, 64 x 64 0.45 / 0.36, 128 x 128 two per CU 0.85 / 0.75, 256 x 256 1.60.
+// Splits only with 256 x 256 tiles (smaller ones have enough work-groups), as far as the blocks for partial sums go.
+// Estimate / measured (d, d_ff, tokens; the four gradients of a layer): 2048, 8192, 16384: 1335 / 1334; 1024, 4096, 16384 (4
+// splits) 443 / 408; 768, 3072, 1500 (128 x 128, two per CU) 43 / 51; 512, 2048, 9000 (5 splits) 95 / 97; 256, 1024, 228 (64 x 64)
+// 9 / 10.
+static double tn_cost(double mn, int per, double out_us, int blocks, TnPick& best) {
+    struct Rate { double lone, busy; };
+    constexpr Rate rate[kKinds + 1] = {{0.85, 0.85}, {0.60, 0.50}, {0.45, 0.36}, {0.85, 0.75}, {1.60, 1.60}};
+    best = TnPick{-1, 1};
+    double best_cost = 0;
+    for (int k = 0; k <= kTnBig; ++k) {
+        const double tiles = mn / (k == kTnBig ? 65536.0 : (double)kShapes[k].bm * kShapes[k].bn);
+        for (int sp = 1; sp <= (k == kTnBig ? 16 : 1); ++sp) {
+            const int len = (per + sp - 1) / sp;
+            if (sp > 1 && (len < 4 || tiles * sp > blocks)) break;
+            if ((per + len - 1) / len != sp) continue;                            // every split owns at least one K tile
+            const double load = tiles * sp / gemm_cu_count();
+            const double rounds = k == 3 ? std::max(load, 1.0) : std::ceil(load);     // (kind 3: two work-groups per CU even it out)
+            const double c = 6 + rounds * len * (load <= 1 ? rate[k].lone : rate[k].busy) + out_us + (sp > 1 ? 5 + 2e-6 * sp * mn : 0);
+            if (best.kind < 0 || c < best_cost) {
+                best = TnPick{k, sp};
+                best_cost = c;
+            }
+        }
+    }
+    return best_cost;
+}
+
+// One launch for the group, unless the launches of the problems one by one are estimated within 5 % of it: over very long
+// contractions of many tiles (d = 4096 and 32 768 tokens: 9471 us one by one, 9903 together) the work-groups of a launch drift
+// apart along K and share less in L2, and launch boundaries bring them together again.
+TnPick pick_tn_group(const TnGroup& g) {
+    const int per = (g.K + T_KD - 1) / T_KD;
+    double mn = 0, separate = 0;
+    TnPick pick;
+    for (int i = 0; i < g.n; ++i) {
+        const double q = (double)g.p[i].M * g.p[i].N;
+        mn += q;
+        separate += tn_cost(q, per, (g.accumulate ? 2e-6 : 1e-6) * q, g.slab_end[0], pick);
+    }
+    const double together = tn_cost(mn, per, (g.accumulate ? 2e-6 : 1e-6) * mn, g.slab_end[TnGroup::kSlabs - 1], pick);
+    return together < 0.95 * separate ? pick : TnPick{-1, 1};
+}
+
+ds_status launch_tn_group(const TnPick& pick, TnGroup& g, hipStream_t st) {
+    const int bm = pick.kind == kTnBig ? 256 : kShapes[pick.kind].bm, bn = pick.kind == kTnBig ? 256 : kShapes[pick.kind].bn;
+    g.splits = pick.kind == kTnBig ? pick.splits : 1;
+    long long blocks = 0;
+    for (int i = 0; i < g.n; ++i) {
+        g.first[i] = (int32_t)blocks;
+        blocks += (long long)(g.p[i].M / bm) * (g.p[i].N / bn) * g.splits;
+        if (blocks > 0x7fffffff) return DS_EOVERFLOW;
+    }
+    switch (pick.kind) {
+    case 0: return launch_group_kind<0, 2, 4>(g, (int)blocks, st);
+    case 1: return launch_group_kind<1, 4, 2>(g, (int)blocks, st);
+    case 2: return launch_group_kind<2, 2, 2>(g, (int)blocks, st);
+    case 3: return launch_group_kind<3, 2, 4>(g, (int)blocks, st);
+    case kTnBig: return launch_tn_group_big(g, (int)blocks, st);
     }
     return DS_EINVAL;
 }

@@ -22,8 +22,10 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <initializer_list>
 #include <new>
 #include <numeric>
+#include <utility>
 #include <vector>
 
 namespace {
@@ -100,6 +102,7 @@ struct ds_stage {
     uint64_t lists_uid[3] = {0, 0, 0};
     int lists_kind[3] = {-1, -1, -1};
     size_t split_ws_floats = 0;
+    size_t rows_max = 0;               // of the two streams: rows of the backward temporaries
     int32_t launches = 0;
     // transposed weight copies: whose weights they were made from, and whether the caller promised those stay as they are
     bool weights_unchanged = false;
@@ -127,6 +130,7 @@ void carve(ds_stage* s) {
     const size_t es = s->es, d = c.d_model, F = c.d_ff, h = c.n_heads;
     const size_t R = c.max_rows, Rt = c.model == DS_MODEL_T5 ? c.max_rows_tgt : 0, Rm = std::max(R, Rt);
     const size_t S = c.max_seqs;
+    s->rows_max = Rm;
     const bool nt = s->nt_mode;
     auto f32 = [&](size_t n) { return (float*)ar.take(n * 4); };
     // Full recomputation: only a layer's output (the next layer's input) is kept per layer; what a layer saves for its
@@ -322,9 +326,48 @@ struct Ops {
         return colsum(sm, K, dZ, bias_grad);
     }
     // dW[K,N] (+)= X[rows,K]^T dY[rows,N]
-    ds_status wgrad(const Stream& sm, int K, int N, const void* X, const void* dY, void* dW) {
-        return gemm_raw(DS_PROF_GEMM_WGRAD, 1, 0, K, N, sm.R, X, dY, dW, DS_EPI_ACC32, nullptr, nullptr, nullptr, nullptr,
+    ds_status wgrad_now(int rows, int K, int N, const void* X, const void* dY, void* dW) {
+        return gemm_raw(DS_PROF_GEMM_WGRAD, 1, 0, K, N, rows, X, dY, dW, DS_EPI_ACC32, nullptr, nullptr, nullptr, nullptr,
                         nullptr, accumulate);
+    }
+    // The weight gradients of a layer as one launch (nt mode).  Between wgrads_begin, which is told the layer's shapes and
+    // decides, and wgrads_end they are collected: X and dY must stay as they are until then.
+    TnGroup wg;
+    TnPick wg_pick{-1, 1};
+    void wgrads_begin(const Stream& sm, std::initializer_list<std::pair<int, int>> shapes) {
+        wg_pick.kind = -1;
+        wg.n = 0;
+        if (!nt || shapes.size() > (size_t)kTnGroup) return;
+        wg.K = sm.R;
+        wg.accumulate = accumulate;
+        for (const auto& q : shapes) {
+            wg.p[wg.n] = TnProblem{nullptr, nullptr, nullptr, q.first, q.second};
+            if (!tn_group_takes(wg.p[wg.n++], sm.R)) return;
+        }
+        // room for partial sums: the workspace of the other GEMMs and two temporaries that are dead at the end of a layer
+        float* const slab[TnGroup::kSlabs] = {s->split_ws, (float*)s->du, (float*)s->d_o};
+        const size_t temp = s->rows_max * d * s->es / 4, floats[TnGroup::kSlabs] = {s->split_ws_floats, temp, temp};
+        int64_t end = 0;
+        for (int i = 0; i < TnGroup::kSlabs; ++i) {
+            end = std::min<int64_t>(end + (int64_t)(floats[i] >> 16), INT32_MAX);
+            wg.slab[i] = slab[i];
+            wg.slab_end[i] = (int32_t)end;
+        }
+        wg_pick = pick_tn_group(wg);
+        wg.n = 0;
+    }
+    ds_status wgrad(const Stream& sm, int K, int N, const void* X, const void* dY, void* dW) {
+        const TnProblem q{X, dY, dW, K, N};
+        if (wg_pick.kind < 0 || wg.n == kTnGroup || !tn_group_takes(q, sm.R)) return wgrad_now(sm.R, K, N, X, dY, dW);
+        wg.p[wg.n++] = q;
+        return DS_OK;
+    }
+    ds_status wgrads_end() {
+        if (wg.n == 0) return DS_OK;
+        s->launches++;
+        const ds_status r = timed(s, DS_PROF_GEMM_WGRAD, st, [&] { return launch_tn_group(wg_pick, wg, st); });
+        wg.n = 0;
+        return r;
     }
     // [K][N] -> [N][K] copies of the weights, gathered into as few launches as the batch allows
     TransposeBatch tb;
@@ -548,6 +591,7 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
         void* dx_in = (l == 0) ? io->grad_in : pp[flip];
         // the shared buffers still hold the last layer's forward; every other layer's is run again
         if (recompute && l != L - 1) DS_TRY(layer_fwd(l, xl_in, nullptr));
+        op.wgrads_begin(sm, {{F, d}, {d, F}, {d, d}, {d, 3 * d}});
         // MLP
         DS_TRY(op.colsum_side(sm, d, dy, g[l].b_2));        // (each column sum right behind its producer, beside the next GEMM)
         DS_TRY(op.wgrad(sm, F, d, b.a, dy, g[l].w_2));
@@ -564,6 +608,7 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
         DS_TRY(op.wgrad(sm, d, 3 * d, b.u1, s->dqkv, g[l].w_qkv));
         DS_TRY(op.dgrad(sm, d, 3 * d, s->dqkv, w[l].w_qkv, s->du, DS_EPI_NONE, nullptr, nullptr, nullptr));
         DS_TRY(op.norm_bwd(sm, 0, s->du, xl_in, w[l].ln1_g, b.stats1, s->dx1, dx_in, g[l].ln1_g, g[l].ln1_b));
+        DS_TRY(op.wgrads_end());
         // the next layer overwrites dx1 and dqkv, which the column sums on the side stream may still be reading
         DS_TRY(op.join_side());
         dy = dx_in;
@@ -726,6 +771,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         const void* yl_in = (l == 0) ? y0 : s->dec[l - 1].xout;
         void* dy_in = (l == 0) ? io->grad_in_tgt : pp[flip];
         if (recompute && l != Ld - 1) DS_TRY(dec_layer_fwd(l, yl_in, nullptr));
+        op.wgrads_begin(D, {{F, d}, {d, F}, {d, F}, {d, d}, {d, d}, {d, d}, {d, 3 * d}});
         // MLP: gradient of x2 into dx2
         DS_TRY(t5_mlp_bwd(op, D, dy, b.x2, s->dx2, b, wd[l].ln2_g, wd[l].w_g, wd[l].w_u, wd[l].w_2, gd[l].ln2_g, gd[l].w_g,
                           gd[l].w_u, gd[l].w_2));
@@ -745,7 +791,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
             DS_TRY(op.zero_pad(E, s->dkvc, 2 * d));
         }
         DS_TRY(op.wgrad(D, d, d, b.uc, s->dqc, gd[l].w_cq));
-        DS_TRY(op.wgrad(E, d, 2 * d, enc_out, s->dkvc, gd[l].w_ckv));
+        DS_TRY(op.wgrad_now(E.R, d, 2 * d, enc_out, s->dkvc, gd[l].w_ckv));
         if (!de_set) {
             DS_TRY(op.dgrad(E, d, 2 * d, s->dkvc, wd[l].w_ckv, de_cur, DS_EPI_NONE, nullptr, nullptr, nullptr));
             de_set = true;
@@ -758,6 +804,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         // causal self-attention: gradient of the layer input
         DS_TRY(t5_self_bwd(op, D, 1, s->dx1, yl_in, dy_in, b, wd[l].ln1_g, wd[l].w_qkv, wd[l].w_o, gd[l].ln1_g, gd[l].w_qkv,
                            gd[l].w_o));
+        DS_TRY(op.wgrads_end());
         dy = dy_in;
         flip ^= 1;
     }
@@ -770,10 +817,12 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         const void* xl_in = (l == 0) ? x0 : s->enc[l - 1].xout;
         void* dx_in = (l == 0) ? io->grad_in : pp[flip];
         if (recompute && l != Le - 1) DS_TRY(enc_layer_fwd(l, xl_in, false));
+        op.wgrads_begin(E, {{F, d}, {d, F}, {d, F}, {d, d}, {d, 3 * d}});
         DS_TRY(t5_mlp_bwd(op, E, dx, b.x1, s->dx1, b, we[l].ln2_g, we[l].w_g, we[l].w_u, we[l].w_2, ge[l].ln2_g, ge[l].w_g,
                           ge[l].w_u, ge[l].w_2));
         DS_TRY(t5_self_bwd(op, E, 0, s->dx1, xl_in, dx_in, b, we[l].ln1_g, we[l].w_qkv, we[l].w_o, ge[l].ln1_g, ge[l].w_qkv,
                            ge[l].w_o));
+        DS_TRY(op.wgrads_end());
         dx = dx_in;
         flip ^= 1;
     }

@@ -259,6 +259,29 @@ def test_bias_gradient_from_partial_column_sums(d_ff, rows):
     used.close()
 
 
+# d, d_ff, tokens -> the tile that the weight gradients of a layer go out with, in one launch: 64 x 64; 128 x 64; 128 x 128 one
+# per CU; two per CU; 256 x 256; 256 x 256 with split contractions.  Token counts that are no multiple of a K tile.
+@pytest.mark.parametrize("d,F,tokens", [(256, 1024, 33), (256, 2048, 301), (512, 2048, 1001), (768, 3072, 1501), (1024, 4096, 701),
+                                        (512, 1536, 9001)])
+def test_weight_gradients_of_a_layer_in_one_launch(d, F, tokens):
+    """Every weight gradient against the oracle, overwritten (what was there before is gone) and then added to."""
+    cfg = dict(d_model=d, d_ff=F, n_heads=d // 64, n_layers=1)
+    rng = np.random.default_rng(d + tokens)
+    lens = []
+    while sum(lens) < tokens:
+        lens.append(int(min(rng.integers(1, 300), tokens - sum(lens))))
+    lens = np.asarray(lens)
+    params = wl.draw_params(wl.GPT_KEYS, 1, d, F, seed=4, bf16=True)
+    xs, dys = wl.draw_rows(lens, d, seed=4, tag=3, bf16=True), wl.draw_rows(lens, d, seed=4, tag=5, bf16=True)
+    lo = ds.ds_layout_from_cuts(lens, list(range(len(lens) + 1)))
+    ref = ost.gpt_stage_fwd_bwd(xs, dys, params, cfg["n_heads"])
+    grads = [{k: torch.full(v.shape, 3.0, dtype=torch.float32, device="cuda:0") for k, v in params[0].items()}]
+    _compare("%d %d %d" % (d, F, tokens), run_gpt_stage(lo, cfg, params, xs, dys, ds.DS_DTYPE_BF16, grads=grads), ref, TOL[ds.DS_DTYPE_BF16])
+    twice = run_gpt_stage(lo, cfg, params, xs, dys, ds.DS_DTYPE_BF16, grads=grads, accumulate=True)[2]
+    for k, v in ref[2][0].items():
+        check(twice[0][k], 2 * v, TOL[ds.DS_DTYPE_BF16], k)
+
+
 @pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
 def test_launch_count_of_a_first_and_a_later_call(dtype_code):
     """The first call with a layout makes both attention work lists in one launch more (bf16) and clears the padding rows of
