@@ -262,6 +262,26 @@ ds_status launch_move_rows_map(int32_t rows, const int32_t* map, int32_t row_byt
 // out[c] = (accumulate ? out[c] : 0) + sum over p < n_partial of partial[p * n + c]   (float32, fixed summation order)
 ds_status launch_reduce_partials(int32_t n_partial, int32_t n, const float* partial, float* out, int32_t accumulate,
                                  hipStream_t st);
+// The row sums of a layer that nothing in the layer waits for, together: out[c] = (accumulate ? out[c] : 0) + sum over r of
+// src[r * stride + c], src of the stage's type (`typed`) or float32 partial sums.
+constexpr int kSumGroup = 12;
+struct SumItem {
+    const void* src;
+    float* out;
+    int32_t rows, n, stride, typed;
+};
+struct SumGroup {
+    int32_t n = 0, accumulate = 0;
+    SumItem it[kSumGroup];
+    int32_t first[kSumGroup], chunks[kSumGroup];       // filled in by the launcher
+};
+// launches kernels (1 or 2, returned in *launches); partial: room for partial sums
+ds_status launch_sum_group(int32_t dtype, SumGroup& g, float* partial, size_t partial_floats, hipStream_t st, int* launches);
+// ds_norm_bwd without its second stage: partial[p][0][:] and, for LayerNorm, partial[p][1][:] (d each) are left for
+// p < norm_bwd_partial_rows(rows, d)
+int norm_bwd_partial_rows(int32_t rows, int32_t d);
+ds_status launch_norm_bwd_partials(int32_t dtype, int32_t rms, int32_t rows, int32_t d, const void* dy, const void* x, const void* g,
+                                   const float* stats, const void* resid, void* dx, float* partial, hipStream_t st);
 // out[i][c][r] = in[i][r][c] (bf16, rows and cols multiples of 8) for i < n; first_block is filled in by the launcher
 constexpr int kTransposeBatch = 24;
 struct TransposeBatch {

@@ -613,30 +613,201 @@ ds_status norm_fwd_dispatch(int rows, int d, const T* x, const T* g, const T* b,
     return DS_OK;
 }
 
-template <class T, bool RMS>
-ds_status norm_bwd_dispatch(int rows, int d, const T* dy, const T* x, const T* g, const float* stats, const T* resid,
-                            T* dx, float* dg, float* db, float* partial, int accumulate, hipStream_t st) {
-    const int ni = (d + 511) / 512;
-    if (ni > 2 && d % 32 == 0) {                 // wide rows: two or four wavefronts per row (see norm_bwd_multi_kernel)
+// Work-groups of the norm backward kernels, each of which leaves one partial row of 2 d floats.
+int norm_bwd_groups(int rows, int d) {
+    if (d > 1024 && d % 32 == 0) {
         // a group's partial row (8 d bytes) is as much traffic as a bf16 row of all four tensors: beyond 1024 groups (four
         // per CU) each takes at least four rows
-        int np = rows / 4 > 1024 ? rows / 4 : (rows < 1024 ? rows : 1024);
-        if (np > kPartialRows) np = kPartialRows;
-        if (ni > 4) hipLaunchKernelGGL((norm_bwd_multi_kernel<T, RMS, 2, 4>), dim3(np), dim3(256), 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
-        else hipLaunchKernelGGL((norm_bwd_multi_kernel<T, RMS, 2, 2>), dim3(np), dim3(128), 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
-        DS_LAUNCH_CHECK();
-        // dgamma and, for LayerNorm, dbeta in one launch
-        return reduce_launch(np, d, (size_t)2 * d, partial, dg, accumulate, partial + d, RMS ? nullptr : db, true, st);
+        const int np = rows / 4 > 1024 ? rows / 4 : (rows < 1024 ? rows : 1024);
+        return np > kPartialRows ? kPartialRows : np;
     }
-    int nblk = (rows + 3) / 4;
-    if (nblk > kPartialRows / 4) nblk = kPartialRows / 4;
-    dim3 grid(nblk), block(256);
-    if (ni <= 1) hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 1>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
-    else if (ni <= 2) hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 2>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
-    else if (ni <= 4) hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 4>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
-    else hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 8>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
+    const int nblk = (rows + 3) / 4;
+    return nblk > kPartialRows / 4 ? kPartialRows / 4 : nblk;
+}
+template <class T, bool RMS>
+ds_status norm_bwd_partials(int rows, int d, const T* dy, const T* x, const T* g, const float* stats, const T* resid, T* dx,
+                            float* partial, hipStream_t st) {
+    const int ni = (d + 511) / 512;
+    const dim3 grid(norm_bwd_groups(rows, d));
+    if (ni > 2 && d % 32 == 0) {                 // wide rows: two or four wavefronts per row (see norm_bwd_multi_kernel)
+        if (ni > 4) hipLaunchKernelGGL((norm_bwd_multi_kernel<T, RMS, 2, 4>), grid, dim3(256), 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
+        else hipLaunchKernelGGL((norm_bwd_multi_kernel<T, RMS, 2, 2>), grid, dim3(128), 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
+    } else {
+        const dim3 block(256);
+        if (ni <= 1) hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 1>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
+        else if (ni <= 2) hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 2>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
+        else if (ni <= 4) hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 4>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
+        else hipLaunchKernelGGL((norm_bwd_kernel<T, RMS, 8>), grid, block, 0, st, rows, d, dy, x, g, stats, resid, dx, partial);
+    }
     DS_LAUNCH_CHECK();
-    return reduce_launch(nblk, d, (size_t)2 * d, partial, dg, accumulate, partial + d, RMS ? nullptr : db, true, st);
+    return DS_OK;
+}
+
+// ------------------------------------------------------------------ the sums of a layer together
+__device__ __forceinline__ int sum_group_item(const SumGroup& g, int& block) {
+    int i = 0;
+    while (i + 1 < g.n && block >= g.first[i + 1]) ++i;
+    block -= g.first[i];
+    return i;
+}
+
+// First stage of long sums: a work-group (64 lanes of 8 columns, 4 row lanes) adds up one chunk of an item's rows; chunk c of
+// item i leaves row c of the [chunks][n] floats that end up as the item's source.
+template <class T>
+__global__ __launch_bounds__(256) void sum_group_chunks_kernel(SumGroup g, float* __restrict__ partial) {
+    __shared__ float red[4][64][9];
+    int block = blockIdx.x, off = 0;
+    const int i = sum_group_item(g, block);
+    for (int k = 0; k < i; ++k) off += g.chunks[k] * g.it[k].n;
+    const int rows = g.it[i].rows, n = g.it[i].n, stride = g.it[i].stride, chunks = g.chunks[i];
+    const T* x = reinterpret_cast<const T*>(g.it[i].src);
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6, chunk = block % chunks;
+    const int col = (block / chunks * 64 + tx) * 8;
+    float acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+    if (col < n) {
+        const int step = chunks * 4;
+        int r = chunk * 4 + ty;
+        for (; r < rows - 3 * step; r += 4 * step) {                  // four rows in flight per wavefront
+            float v[4][8];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) Vec8<T>::load(x + (size_t)(r + k * step) * stride + col, v[k]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += (v[0][j] + v[1][j]) + (v[2][j] + v[3][j]);
+        }
+        for (; r < rows; r += step) {
+            float v[8];
+            Vec8<T>::load(x + (size_t)r * stride + col, v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += v[j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) red[ty][tx][j] = acc[j];
+    __syncthreads();
+    if (ty == 0 && col < n) {
+        float o[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = (red[0][tx][j] + red[1][tx][j]) + (red[2][tx][j] + red[3][tx][j]);
+        Vec8<float>::store(partial + off + (size_t)chunk * n + col, o);
+    }
+}
+
+// Sums whose rows one work-group can walk: 32 columns per work-group of 512 threads, in 16-byte lanes (8 of float32, 4 of bf16), four
+// rows in flight per lane, added up in a fixed order.  One launch for everything a layer's backward pass leaves to be summed (bias
+// gradients, norm gradients): what these sums cost is their launches, 5 us each whatever they add up to a few thousand rows.
+template <class T>
+__global__ __launch_bounds__(512) void sum_group_kernel(SumGroup g) {
+    constexpr int NW = 512 / 64;
+    __shared__ float red[NW][32];
+    int block = blockIdx.x;
+    const int i = sum_group_item(g, block);
+    const int rows = g.it[i].rows, n = g.it[i].n;
+    const size_t stride = g.it[i].stride;
+    float* out = g.it[i].out;
+    const int c0 = block * 32, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (sizeof(T) == 2 && g.it[i].typed) {
+        constexpr int RL = 512 / 4;
+        const int cx = threadIdx.x & 3, col = c0 + cx * 8;
+        const T* x = reinterpret_cast<const T*>(g.it[i].src) + col;
+        float a[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a[j] = 0.f;
+        if (col < n) {
+            int r = threadIdx.x >> 2;
+            for (; r + 3 * RL < rows; r += 4 * RL) {
+                float v[4][8];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) Vec8<T>::load(x + (size_t)(r + k * RL) * stride, v[k]);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a[j] += (v[0][j] + v[1][j]) + (v[2][j] + v[3][j]);
+            }
+            for (; r < rows; r += RL) {
+                float v[8];
+                Vec8<T>::load(x + (size_t)r * stride, v);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a[j] += v[j];
+            }
+        }
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a[j] += __shfl_xor(a[j], o, 64);
+        if (lane < 4) Vec8<float>::store(&red[wave][cx * 8], a);
+    } else {
+        constexpr int RL = 512 / 8;
+        const int cx = threadIdx.x & 7, col = c0 + cx * 4;
+        const float* x = reinterpret_cast<const float*>(g.it[i].src) + col;
+        f32x4_t a = {0.f, 0.f, 0.f, 0.f};
+        if (col < n) {
+            int r = threadIdx.x >> 3;
+            for (; r + 3 * RL < rows; r += 4 * RL) {
+                f32x4_t v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const f32x4_t*>(x + (size_t)(r + k * RL) * stride);
+                a += (v[0] + v[1]) + (v[2] + v[3]);
+            }
+            for (; r < rows; r += RL) a += *reinterpret_cast<const f32x4_t*>(x + (size_t)r * stride);
+        }
+#pragma unroll
+        for (int o = 8; o < 64; o <<= 1)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] += __shfl_xor(a[e], o, 64);
+        if (lane < 8) *reinterpret_cast<f32x4_t*>(&red[wave][cx * 4]) = a;
+    }
+    __syncthreads();
+    const int c = c0 + threadIdx.x;
+    if (threadIdx.x < 32 && c < n) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) s += red[k][threadIdx.x];
+        out[c] = g.accumulate ? out[c] + s : s;
+    }
+}
+
+template <class T>
+ds_status sum_group_run(SumGroup& g, float* partial, size_t partial_floats, hipStream_t st, int* launches) {
+    // Tensors of more than kColsumSmallRows rows go through a first stage, cut into chunks of at least 32 rows (as many as there is
+    // room for); the items of that stage and of the last one are listed by the same struct.
+    SumGroup c;
+    c.accumulate = 0;
+    size_t cols = 0;
+    for (int i = 0; i < g.n; ++i)
+        if (g.it[i].typed && g.it[i].rows > kColsumSmallRows) cols += (size_t)g.it[i].n;
+    int blocks = 0;
+    size_t off = 0;
+    for (int i = 0; i < g.n; ++i) {
+        SumItem& q = g.it[i];
+        if (!q.typed || q.rows <= kColsumSmallRows) continue;
+        int chunks = (q.rows + 31) / 32;
+        const size_t room = partial_floats / cols;
+        if ((size_t)chunks > room) chunks = (int)room;
+        if (chunks > 512) chunks = 512;
+        if (chunks < 1) return DS_EINVAL;
+        c.it[c.n] = q;
+        c.first[c.n] = blocks;
+        c.chunks[c.n++] = chunks;
+        blocks += chunks * ((q.n / 8 + 63) / 64);
+        q.src = partial + off;
+        q.rows = chunks;
+        q.stride = q.n;
+        q.typed = 0;
+        off += (size_t)chunks * q.n;
+    }
+    if (blocks) {
+        hipLaunchKernelGGL(sum_group_chunks_kernel<T>, dim3(blocks), dim3(256), 0, st, c, partial);
+        DS_LAUNCH_CHECK();
+    }
+    *launches = blocks ? 2 : 1;
+    blocks = 0;
+    for (int i = 0; i < g.n; ++i) {
+        g.first[i] = blocks;
+        blocks += (g.it[i].n + 31) / 32;
+    }
+    hipLaunchKernelGGL(sum_group_kernel<T>, dim3(blocks), dim3(512), 0, st, g);
+    DS_LAUNCH_CHECK();
+    return DS_OK;
 }
 
 }  // namespace
@@ -721,6 +892,26 @@ extern "C" ds_status ds_norm_fwd(int32_t dtype, int32_t rms, int32_t rows, int32
     return norm_fwd_dispatch<float, false>(rows, d, (const float*)x, (const float*)g, (const float*)b, (float*)y, stats, st);
 }
 
+int norm_bwd_partial_rows(int32_t rows, int32_t d) { return norm_bwd_groups(rows, d); }
+ds_status launch_norm_bwd_partials(int32_t dtype, int32_t rms, int32_t rows, int32_t d, const void* dy, const void* x, const void* g,
+                                   const float* stats, const void* resid, void* dx, float* partial, hipStream_t st) {
+    if (dtype == DS_DTYPE_BF16) {
+        if (rms) return norm_bwd_partials<bf16_t, true>(rows, d, (const bf16_t*)dy, (const bf16_t*)x, (const bf16_t*)g, stats, (const bf16_t*)resid, (bf16_t*)dx, partial, st);
+        return norm_bwd_partials<bf16_t, false>(rows, d, (const bf16_t*)dy, (const bf16_t*)x, (const bf16_t*)g, stats, (const bf16_t*)resid, (bf16_t*)dx, partial, st);
+    }
+    if (rms) return norm_bwd_partials<float, true>(rows, d, (const float*)dy, (const float*)x, (const float*)g, stats, (const float*)resid, (float*)dx, partial, st);
+    return norm_bwd_partials<float, false>(rows, d, (const float*)dy, (const float*)x, (const float*)g, stats, (const float*)resid, (float*)dx, partial, st);
+}
+
+ds_status launch_sum_group(int32_t dtype, SumGroup& g, float* partial, size_t partial_floats, hipStream_t st, int* launches) {
+    *launches = 0;
+    if (g.n <= 0) return DS_OK;
+    for (int i = 0; i < g.n; ++i)
+        if (!g.it[i].src || !g.it[i].out || g.it[i].rows <= 0 || g.it[i].n <= 0 || g.it[i].n % 8) return DS_EINVAL;
+    if (dtype == DS_DTYPE_BF16) return sum_group_run<bf16_t>(g, partial, partial_floats, st, launches);
+    return sum_group_run<float>(g, partial, partial_floats, st, launches);
+}
+
 extern "C" ds_status ds_norm_bwd(int32_t dtype, int32_t rms, int32_t rows, int32_t d, const void* dy, const void* x,
                                  const void* g, const float* stats, const void* resid, void* dx, float* dg, float* db,
                                  float* partial, int32_t accumulate, void* hip_stream) {
@@ -728,12 +919,10 @@ extern "C" ds_status ds_norm_bwd(int32_t dtype, int32_t rms, int32_t rows, int32
         return DS_EINVAL;
     if (dtype != DS_DTYPE_F32 && dtype != DS_DTYPE_BF16) return DS_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
-    if (dtype == DS_DTYPE_BF16) {
-        if (rms) return norm_bwd_dispatch<bf16_t, true>(rows, d, (const bf16_t*)dy, (const bf16_t*)x, (const bf16_t*)g, stats, (const bf16_t*)resid, (bf16_t*)dx, dg, db, partial, accumulate, st);
-        return norm_bwd_dispatch<bf16_t, false>(rows, d, (const bf16_t*)dy, (const bf16_t*)x, (const bf16_t*)g, stats, (const bf16_t*)resid, (bf16_t*)dx, dg, db, partial, accumulate, st);
-    }
-    if (rms) return norm_bwd_dispatch<float, true>(rows, d, (const float*)dy, (const float*)x, (const float*)g, stats, (const float*)resid, (float*)dx, dg, db, partial, accumulate, st);
-    return norm_bwd_dispatch<float, false>(rows, d, (const float*)dy, (const float*)x, (const float*)g, stats, (const float*)resid, (float*)dx, dg, db, partial, accumulate, st);
+    const ds_status r = launch_norm_bwd_partials(dtype, rms, rows, d, dy, x, g, stats, resid, dx, partial, st);
+    if (r != DS_OK) return r;
+    // dgamma and, for LayerNorm, dbeta in one launch
+    return reduce_launch(norm_bwd_groups(rows, d), d, (size_t)2 * d, partial, dg, accumulate, partial + d, rms ? nullptr : db, true, st);
 }
 
 ds_status launch_reduce_partials(int32_t n_partial, int32_t n, const float* partial, float* out, int32_t accumulate,

@@ -30,6 +30,8 @@
 
 namespace {
 
+constexpr size_t kPartialSideFloats = (size_t)2048 * 1024;
+
 // Bump allocator over the workspace.  With base == nullptr it only measures.
 struct Arena {
     char* base = nullptr;
@@ -201,7 +203,7 @@ void carve(ds_stage* s) {
     }
     const size_t partial_floats = std::max<size_t>((size_t)ds_norm_bwd_scratch_floats(1, (int)d), (size_t)2048 * 1024);
     s->partial = f32(partial_floats);
-    s->partial_side = c.model == DS_MODEL_GPT ? f32((size_t)2048 * 1024) : nullptr;
+    s->partial_side = c.model == DS_MODEL_GPT ? f32(kPartialSideFloats) : nullptr;
     s->colsum_rows = (c.model == DS_MODEL_GPT && s->nt_mode) ? f32(gemm_colsum_rows((int32_t)R) * F) : nullptr;
     s->split_ws_floats = 4 * std::max(d * 3 * d, d * F);
     s->split_ws = f32(s->split_ws_floats);
@@ -317,12 +319,20 @@ struct Ops {
         if (s->colsum_rows && gemm_colsum_fused(dt, 0, 1, sm.R, K, N, dY, W, dZ, DS_EPI_MULR)) {
             DS_TRY(gemm_raw(DS_PROF_GEMM_DGRAD, 0, 1, sm.R, K, N, dY, W, dZ, DS_EPI_MULR, nullptr, G, nullptr, nullptr, nullptr, 0,
                             s->colsum_rows));
+            if (sums_together) {
+                sums.it[sums.n++] = SumItem{s->colsum_rows, (float*)bias_grad, (int32_t)gemm_colsum_rows(sm.R), K, K, 0};
+                return DS_OK;
+            }
             s->launches++;
             return timed(s, DS_PROF_COLSUM, st, [&] {
                 return launch_reduce_partials((int32_t)gemm_colsum_rows(sm.R), K, s->colsum_rows, (float*)bias_grad, accumulate, st);
             });
         }
         DS_TRY(dgrad(sm, K, N, dY, W, dZ, DS_EPI_MULR, G, nullptr, nullptr));
+        if (sums_together) {
+            sums.it[sums.n++] = SumItem{dZ, (float*)bias_grad, sm.R, K, K, 1};
+            return DS_OK;
+        }
         return colsum(sm, K, dZ, bias_grad);
     }
     // dW[K,N] (+)= X[rows,K]^T dY[rows,N]
@@ -386,15 +396,45 @@ struct Ops {
         tb.n = 0;
         return r;
     }
+    // The sums that nothing in a layer's backward pass waits for (bias gradients, norm gradients) go out together at its end, in one or
+    // two launches, where the tensors they read are small: three forks to the side stream and the second stages of the norms
+    // cost 35 us at any size, reading the tensors inline their bytes.  A layer's call, us, side stream / together, by MB of those
+    // tensors: 12 MB 516 / 490, 39 MB 903 / 886, 78 MB 910 / 889, 156 MB 1411 / 1420, 312 MB 2737 / 2758 (bf16); 15 MB 494 / 457, 117 MB
+    // 2967 / 2955 (fp32).  Between sums_begin and sums_end they are
+    // collected: what they read must stay as it is until then.  norms: how many norm backward passes the layer has; their partial
+    // rows share `partial`.  tensor_cols: columns of the tensors to be summed.
+    static constexpr size_t kSumsTogetherBytes = 96u << 20;
+    SumGroup sums;
+    bool sums_together = false;
+    int norms_taken = 0, norm_rows = 0;
+    void sums_begin(const Stream& sm, int norms, size_t tensor_cols) {
+        sums.n = norms_taken = 0;
+        sums.accumulate = accumulate;
+        norm_rows = norm_bwd_partial_rows(sm.R, d);
+        sums_together = (size_t)norm_rows * norms * 2 * d <= (size_t)ds_norm_bwd_scratch_floats(1, d) &&
+                        (size_t)sm.R * tensor_cols * s->es <= kSumsTogetherBytes;
+    }
+    ds_status sums_end() {
+        sums_together = false;
+        if (sums.n == 0) return DS_OK;
+        int launched = 0;
+        const ds_status r = timed(s, DS_PROF_COLSUM, st, [&] { return launch_sum_group(dt, sums, s->partial_side, kPartialSideFloats, st, &launched); });
+        s->launches += launched;
+        sums.n = 0;
+        return r;
+    }
     ds_status colsum(const Stream& sm, int n, const void* x, void* out) {
-        s->launches += sm.R <= kColsumSmallRows ? 1 : 2;
+        s->launches += 2;
         return timed(s, DS_PROF_COLSUM, st, [&] { return ds_colsum(dt, sm.R, n, x, (float*)out, s->partial, accumulate, st); });
     }
     // The same on the side stream: starts once everything enqueued so far on the main stream is done, runs beside
-    // what is enqueued after it.  x must stay as it is, and out untouched, until join_side().  A sum over few rows is one
-    // short launch, less than the four calls that fork and join the streams.
+    // what is enqueued after it.  x must stay as it is, and out untouched, until join_side().
     ds_status colsum_side(const Stream& sm, int n, const void* x, void* out) {
-        if (!s->side || sm.R <= kColsumSmallRows) return colsum(sm, n, x, out);
+        if (sums_together) {
+            sums.it[sums.n++] = SumItem{x, (float*)out, sm.R, n, n, 1};
+            return DS_OK;
+        }
+        if (!s->side) return colsum(sm, n, x, out);
         s->launches += 2;
         DS_HIP_CHECK(hipEventRecord(s->ev_fork, st));
         DS_HIP_CHECK(hipStreamWaitEvent(s->side, s->ev_fork, 0));
@@ -416,6 +456,13 @@ struct Ops {
     }
     ds_status norm_bwd(const Stream& sm, int rms, const void* dy, const void* x, const void* g, const float* stats,
                        const void* resid, void* dx, void* dg, void* db) {
+        if (sums_together) {
+            float* part = s->partial + (size_t)norms_taken++ * norm_rows * 2 * d;
+            sums.it[sums.n++] = SumItem{part, (float*)dg, norm_rows, d, 2 * d, 0};
+            if (db) sums.it[sums.n++] = SumItem{part + d, (float*)db, norm_rows, d, 2 * d, 0};
+            s->launches++;
+            return timed(s, DS_PROF_NORM, st, [&] { return launch_norm_bwd_partials(dt, rms, sm.R, d, dy, x, g, stats, resid, dx, part, st); });
+        }
         s->launches += 2;
         return timed(s, DS_PROF_NORM, st, [&] {
             return ds_norm_bwd(dt, rms, sm.R, d, dy, x, g, stats, resid, dx, (float*)dg, (float*)db, s->partial, accumulate, st);
@@ -592,6 +639,7 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
         // the shared buffers still hold the last layer's forward; every other layer's is run again
         if (recompute && l != L - 1) DS_TRY(layer_fwd(l, xl_in, nullptr));
         op.wgrads_begin(sm, {{F, d}, {d, F}, {d, d}, {d, 3 * d}});
+        op.sums_begin(sm, 2, 5 * (size_t)d + (s->colsum_rows ? 0 : F));
         // MLP
         DS_TRY(op.colsum_side(sm, d, dy, g[l].b_2));        // (each column sum right behind its producer, beside the next GEMM)
         DS_TRY(op.wgrad(sm, F, d, b.a, dy, g[l].w_2));
@@ -609,6 +657,7 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
         DS_TRY(op.dgrad(sm, d, 3 * d, s->dqkv, w[l].w_qkv, s->du, DS_EPI_NONE, nullptr, nullptr, nullptr));
         DS_TRY(op.norm_bwd(sm, 0, s->du, xl_in, w[l].ln1_g, b.stats1, s->dx1, dx_in, g[l].ln1_g, g[l].ln1_b));
         DS_TRY(op.wgrads_end());
+        DS_TRY(op.sums_end());
         // the next layer overwrites dx1 and dqkv, which the column sums on the side stream may still be reading
         DS_TRY(op.join_side());
         dy = dx_in;
@@ -772,6 +821,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         void* dy_in = (l == 0) ? io->grad_in_tgt : pp[flip];
         if (recompute && l != Ld - 1) DS_TRY(dec_layer_fwd(l, yl_in, nullptr));
         op.wgrads_begin(D, {{F, d}, {d, F}, {d, F}, {d, d}, {d, d}, {d, d}, {d, 3 * d}});
+        op.sums_begin(D, 3, 0);
         // MLP: gradient of x2 into dx2
         DS_TRY(t5_mlp_bwd(op, D, dy, b.x2, s->dx2, b, wd[l].ln2_g, wd[l].w_g, wd[l].w_u, wd[l].w_2, gd[l].ln2_g, gd[l].w_g,
                           gd[l].w_u, gd[l].w_2));
@@ -805,6 +855,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         DS_TRY(t5_self_bwd(op, D, 1, s->dx1, yl_in, dy_in, b, wd[l].ln1_g, wd[l].w_qkv, wd[l].w_o, gd[l].ln1_g, gd[l].w_qkv,
                            gd[l].w_o));
         DS_TRY(op.wgrads_end());
+        DS_TRY(op.sums_end());
         dy = dy_in;
         flip ^= 1;
     }
@@ -817,12 +868,14 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         const void* xl_in = (l == 0) ? x0 : s->enc[l - 1].xout;
         void* dx_in = (l == 0) ? io->grad_in : pp[flip];
         if (recompute && l != Le - 1) DS_TRY(enc_layer_fwd(l, xl_in, false));
+        op.sums_begin(E, 2, 0);
         op.wgrads_begin(E, {{F, d}, {d, F}, {d, F}, {d, d}, {d, 3 * d}});
         DS_TRY(t5_mlp_bwd(op, E, dx, b.x1, s->dx1, b, we[l].ln2_g, we[l].w_g, we[l].w_u, we[l].w_2, ge[l].ln2_g, ge[l].w_g,
                           ge[l].w_u, ge[l].w_2));
         DS_TRY(t5_self_bwd(op, E, 0, s->dx1, xl_in, dx_in, b, we[l].ln1_g, we[l].w_qkv, we[l].w_o, ge[l].ln1_g, ge[l].w_qkv,
                            ge[l].w_o));
         DS_TRY(op.wgrads_end());
+        DS_TRY(op.sums_end());
         dx = dx_in;
         flip ^= 1;
     }

@@ -282,6 +282,26 @@ def test_weight_gradients_of_a_layer_in_one_launch(d, F, tokens):
         check(twice[0][k], 2 * v, TOL[ds.DS_DTYPE_BF16], k)
 
 
+# rows up to and beyond what one work-group walks (512), row lanes with and without a row, narrow and wide norm kernels
+@pytest.mark.parametrize("d,rows", [(256, 5), (256, 512), (256, 513), (768, 1100), (1536, 129)])
+@pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
+def test_bias_and_norm_gradients_summed_together(dtype_code, d, rows):
+    """Bias and norm gradients of a layer, overwritten and then added to, against the oracle."""
+    bf16, tol = dtype_code == ds.DS_DTYPE_BF16, TOL[dtype_code]
+    cfg = dict(d_model=d, d_ff=256, n_heads=d // 64, n_layers=1)
+    lens = np.asarray([5] if rows == 5 else [rows - 100, 99, 1])
+    params = wl.draw_params(wl.GPT_KEYS, 1, d, 256, seed=6, bf16=bf16)
+    xs, dys = wl.draw_rows(lens, d, seed=6, tag=3, bf16=bf16), wl.draw_rows(lens, d, seed=6, tag=5, bf16=bf16)
+    lo = ds.ds_layout_from_cuts(lens, [0, len(lens)] if rows == 512 else list(range(len(lens) + 1)))
+    ref = ost.gpt_stage_fwd_bwd(xs, dys, params, cfg["n_heads"])[2][0]
+    grads = [{k: torch.full(v.shape, 3.0, dtype=torch.float32, device="cuda:0") for k, v in params[0].items()}]
+    once = run_gpt_stage(lo, cfg, params, xs, dys, dtype_code, grads=grads)[2][0]
+    twice = run_gpt_stage(lo, cfg, params, xs, dys, dtype_code, grads=grads, accumulate=True)[2][0]
+    for k in ("b_qkv", "b_o", "b_1", "b_2", "ln1_g", "ln1_b", "ln2_g", "ln2_b"):
+        check(once[k], ref[k], tol, k)
+        check(twice[k], 2 * ref[k], tol, k)
+
+
 @pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
 def test_launch_count_of_a_first_and_a_later_call(dtype_code):
     """The first call with a layout makes both attention work lists in one launch more (bf16) and clears the padding rows of
