@@ -45,7 +45,7 @@ ds_status launch_gemm_tile(const TilePick& pick, bool tn, int32_t M, int32_t N, 
                            int32_t epilogue, const GemmEpi& p, float* split_ws, hipStream_t st);
 
 // Weight gradients that contract over the same K token rows (those of one layer), as one launch:
-// C[M,N] (+)= A[K,M]^T B[K,N], bf16 operands, fp32 result; M and N multiples of 256, pointers 16-byte aligned.
+// C[M,N] (+)= A[K,M]^T B[K,N], fp32 result, pointers 16-byte aligned; bf16 operands: M and N multiples of 256; fp32: M of 4, N of 8.
 constexpr int kTnGroup = 8;
 struct TnProblem {
     const void* A;
@@ -54,9 +54,11 @@ struct TnProblem {
     int32_t M, N;
 };
 struct TnGroup {
-    int32_t n = 0, K = 0, accumulate = 0;
+    int32_t n = 0, K = 0, accumulate = 0, f32 = 0;
     TnProblem p[kTnGroup];
-    // Room for partial sums, in blocks of 256 x 256 floats: block u lies in the first slab i with u < slab_end[i]
+    // Room for partial sums, in blocks of one tile (256 x 256 floats, fp32 operands 64 x 128): block u lies in the first slab i with
+    // u < slab_end[i]
+    __host__ __device__ int block_log2() const { return f32 ? 13 : 16; }
     static constexpr int kSlabs = 3;
     float* slab[kSlabs];
     int32_t slab_end[kSlabs];
@@ -65,19 +67,22 @@ struct TnGroup {
     int32_t first[kTnGroup];
     __host__ __device__ float* block(int u) const {
         const int i = u < slab_end[0] ? 0 : u < slab_end[1] ? 1 : 2;
-        return slab[i] + ((size_t)(u - (i ? slab_end[i - 1] : 0)) << 16);
+        return slab[i] + ((size_t)(u - (i ? slab_end[i - 1] : 0)) << block_log2());
     }
 };
-// which tile (a kind of gemm_tile.hip, kTnBig = the 256 x 256 kernel, -1: one launch each instead) and how many splits
-constexpr int kTnBig = 4;
+// which tile (a kind of gemm_tile.hip, kTnBig = the 256 x 256 kernel, kTnF32 = the fp32 one, -1: one launch each instead) and how
+// many splits
+constexpr int kTnBig = 4, kTnF32 = 5;
 struct TnPick {
     int kind, splits;
 };
 TnPick pick_tn_group(const TnGroup& g);
 ds_status launch_tn_group(const TnPick& pick, TnGroup& g, hipStream_t st);
-ds_status launch_tn_group_big(TnGroup& g, int blocks, hipStream_t st);     // gemm.hip's part of it
-inline bool tn_group_takes(const TnProblem& q, int32_t K) {
-    return q.M > 0 && q.N > 0 && K > 0 && q.M % 256 == 0 && q.N % 256 == 0 && q.M <= (1 << 24) && q.N <= (1 << 24) &&
+ds_status launch_tn_group_big(TnGroup& g, int blocks, hipStream_t st);     // gemm.hip's and gemm_f32.hip's parts of them
+TnPick pick_tn_group_f32(const TnGroup& g);
+ds_status launch_tn_group_f32(TnGroup& g, hipStream_t st);
+inline bool tn_group_takes(const TnProblem& q, int32_t K, bool f32) {
+    return q.M > 0 && q.N > 0 && K > 0 && q.M % (f32 ? 4 : 256) == 0 && q.N % (f32 ? 8 : 256) == 0 && q.M <= (1 << 24) && q.N <= (1 << 24) &&
            (((uintptr_t)q.A | (uintptr_t)q.B | (uintptr_t)q.C) & 15) == 0;
 }
 

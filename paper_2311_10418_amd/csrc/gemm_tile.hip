@@ -446,6 +446,7 @@ static double tn_cost(double mn, int per, double out_us, int blocks, TnPick& bes
 // contractions of many tiles (d = 4096 and 32 768 tokens: 9471 us one by one, 9903 together) the work-groups of a launch drift
 // apart along K and share less in L2, and launch boundaries bring them together again.
 TnPick pick_tn_group(const TnGroup& g) {
+    if (g.f32) return pick_tn_group_f32(g);
     const int per = (g.K + T_KD - 1) / T_KD;
     double mn = 0, separate = 0;
     TnPick pick;
@@ -459,8 +460,9 @@ TnPick pick_tn_group(const TnGroup& g) {
 }
 
 ds_status launch_tn_group(const TnPick& pick, TnGroup& g, hipStream_t st) {
+    g.splits = pick.kind >= kTnBig ? pick.splits : 1;
+    if (pick.kind == kTnF32) return launch_tn_group_f32(g, st);
     const int bm = pick.kind == kTnBig ? 256 : kShapes[pick.kind].bm, bn = pick.kind == kTnBig ? 256 : kShapes[pick.kind].bn;
-    g.splits = pick.kind == kTnBig ? pick.splits : 1;
     long long blocks = 0;
     for (int i = 0; i < g.n; ++i) {
         g.first[i] = (int32_t)blocks;

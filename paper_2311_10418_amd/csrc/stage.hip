@@ -340,26 +340,27 @@ struct Ops {
         return gemm_raw(DS_PROF_GEMM_WGRAD, 1, 0, K, N, rows, X, dY, dW, DS_EPI_ACC32, nullptr, nullptr, nullptr, nullptr,
                         nullptr, accumulate);
     }
-    // The weight gradients of a layer as one launch (nt mode).  Between wgrads_begin, which is told the layer's shapes and
+    // The weight gradients of a layer as one launch.  Between wgrads_begin, which is told the layer's shapes and
     // decides, and wgrads_end they are collected: X and dY must stay as they are until then.
     TnGroup wg;
     TnPick wg_pick{-1, 1};
     void wgrads_begin(const Stream& sm, std::initializer_list<std::pair<int, int>> shapes) {
         wg_pick.kind = -1;
         wg.n = 0;
-        if (!nt || shapes.size() > (size_t)kTnGroup) return;
+        wg.f32 = dt == DS_DTYPE_F32;
+        if ((!nt && !wg.f32) || shapes.size() > (size_t)kTnGroup) return;
         wg.K = sm.R;
         wg.accumulate = accumulate;
         for (const auto& q : shapes) {
             wg.p[wg.n] = TnProblem{nullptr, nullptr, nullptr, q.first, q.second};
-            if (!tn_group_takes(wg.p[wg.n++], sm.R)) return;
+            if (!tn_group_takes(wg.p[wg.n++], sm.R, wg.f32)) return;
         }
         // room for partial sums: the workspace of the other GEMMs and two temporaries that are dead at the end of a layer
         float* const slab[TnGroup::kSlabs] = {s->split_ws, (float*)s->du, (float*)s->d_o};
         const size_t temp = s->rows_max * d * s->es / 4, floats[TnGroup::kSlabs] = {s->split_ws_floats, temp, temp};
         int64_t end = 0;
         for (int i = 0; i < TnGroup::kSlabs; ++i) {
-            end = std::min<int64_t>(end + (int64_t)(floats[i] >> 16), INT32_MAX);
+            end = std::min<int64_t>(end + (int64_t)(floats[i] >> wg.block_log2()), INT32_MAX);
             wg.slab[i] = slab[i];
             wg.slab_end[i] = (int32_t)end;
         }
@@ -368,7 +369,7 @@ struct Ops {
     }
     ds_status wgrad(const Stream& sm, int K, int N, const void* X, const void* dY, void* dW) {
         const TnProblem q{X, dY, dW, K, N};
-        if (wg_pick.kind < 0 || wg.n == kTnGroup || !tn_group_takes(q, sm.R)) return wgrad_now(sm.R, K, N, X, dY, dW);
+        if (wg_pick.kind < 0 || wg.n == kTnGroup || !tn_group_takes(q, sm.R, wg.f32)) return wgrad_now(sm.R, K, N, X, dY, dW);
         wg.p[wg.n++] = q;
         return DS_OK;
     }

@@ -254,6 +254,48 @@ def test_attention_empty_sequences(dt, force):
     assert both_err(dkv_np[70:210, d:], rv) <= tol
 
 
+# ragged rows, columns (not a multiple of a tile) and K: 64 x 64 and 64 x 128 tiles of the fp32 products on the bf16 matrix cores
+@pytest.mark.parametrize("form", ["NN", "NT"])
+@pytest.mark.parametrize("M,N,K", [(4003, 264, 36), (2050, 520, 100), (4096, 256, 256), (8203, 520, 516)])
+def test_gemm_f32_as_bf16_products(form, M, N, K):
+    """Within the error of fp32 sums: per product less than 2^-22 is left out and every addition rounds by 2^-24, over K of them
+    sqrt(K) 2^-24 in the mean; values from 2^-40 to 2^40 in the same row."""
+    rng = np.random.default_rng(M + K)
+    A = (_rnd(rng, (M, K), F32) * np.exp2(rng.integers(-40, 41, (M, 1)))).astype(np.float32)
+    B = _rnd(rng, (N, K) if form == "NT" else (K, N), F32)
+    c = torch.full((M, N), 3.0, dtype=F32, device=DEV)
+    ds.ds_gemm(to_dev(A, F32), to_dev(B, F32), c, M, N, K, trans_b=form == "NT")
+    torch.cuda.synchronize()
+    ref = A.astype(np.float64) @ (B.T if form == "NT" else B).astype(np.float64)
+    err = np.linalg.norm(to_np(c) - ref, axis=1) / np.linalg.norm(ref, axis=1)          # every row on its own scale
+    assert err.max() <= 4 * np.sqrt(K) * 2.0 ** -24
+
+
+def test_gemm_f32_values_that_bf16_products_do_not_represent():
+    """Inf, NaN, values next to the largest and rows of tiny ones: as with fp32 products."""
+    rng = np.random.default_rng(77)
+    M, N, K = 4096, 256, 64
+    A, B = _rnd(rng, (M, K), F32), _rnd(rng, (K, N), F32)
+    A[3, 5], A[700, 1], A[701, 2], A[1500, 3] = np.inf, np.nan, -np.inf, 3.4e38
+    A[2000] *= np.float32(1e-36)
+    B[:, 17] *= np.float32(0.25)
+    c = torch.zeros((M, N), dtype=F32, device=DEV)
+    ds.ds_gemm(to_dev(A, F32), to_dev(B, F32), c, M, N, K)
+    torch.cuda.synchronize()
+    c = c.cpu().numpy()
+    with np.errstate(all="ignore"):
+        ref = A.astype(np.float64) @ B.astype(np.float64)
+        ref32 = ref.astype(np.float32)
+    special = [3, 700, 701, 1500]
+    for r in special[:3]:
+        assert np.array_equal(np.isnan(c[r]), np.isnan(ref32[r])) and np.array_equal(np.isposinf(c[r]), np.isposinf(ref32[r]))
+    ok = np.isfinite(ref32[1500])
+    assert np.all(np.abs(c[1500][ok] - ref[1500][ok]) <= 1e-6 * np.abs(ref[1500][ok]).max())
+    rest = np.setdiff1d(np.arange(M), special)
+    err = np.linalg.norm(c[rest].astype(np.float64) - ref[rest], axis=1) / np.linalg.norm(ref[rest], axis=1)
+    assert err.max() <= 4 * np.sqrt(K) * 2.0 ** -24
+
+
 @pytest.mark.parametrize("dt", [F32, BF])
 @pytest.mark.parametrize("rms", [False, True])
 @pytest.mark.parametrize("d", [256, 1024, 1536, 2048, 3072, 4096])

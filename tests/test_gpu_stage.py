@@ -260,10 +260,13 @@ def test_bias_gradient_from_partial_column_sums(d_ff, rows):
 
 
 # d, d_ff, tokens -> the tile that the weight gradients of a layer go out with, in one launch: 64 x 64; 128 x 64; 128 x 128 one
-# per CU; two per CU; 256 x 256; 256 x 256 with split contractions.  Token counts that are no multiple of a K tile.
-@pytest.mark.parametrize("d,F,tokens", [(256, 1024, 33), (256, 2048, 301), (512, 2048, 1001), (768, 3072, 1501), (1024, 4096, 701),
-                                        (512, 1536, 9001)])
-def test_weight_gradients_of_a_layer_in_one_launch(d, F, tokens):
+# per CU; two per CU; 256 x 256; 256 x 256 with split contractions; fp32: ragged tiles of 64 x 128, whole and split.  Token counts that
+# are no multiple of a K tile.
+@pytest.mark.parametrize("d,F,tokens,code", [(256, 1024, 33, ds.DS_DTYPE_BF16), (256, 2048, 301, ds.DS_DTYPE_BF16),
+                                             (512, 2048, 1001, ds.DS_DTYPE_BF16), (768, 3072, 1501, ds.DS_DTYPE_BF16),
+                                             (1024, 4096, 701, ds.DS_DTYPE_BF16), (512, 1536, 9001, ds.DS_DTYPE_BF16),
+                                             (192, 328, 77, ds.DS_DTYPE_F32), (192, 328, 1301, ds.DS_DTYPE_F32)])
+def test_weight_gradients_of_a_layer_in_one_launch(d, F, tokens, code):
     """Every weight gradient against the oracle, overwritten (what was there before is gone) and then added to."""
     cfg = dict(d_model=d, d_ff=F, n_heads=d // 64, n_layers=1)
     rng = np.random.default_rng(d + tokens)
@@ -271,15 +274,16 @@ def test_weight_gradients_of_a_layer_in_one_launch(d, F, tokens):
     while sum(lens) < tokens:
         lens.append(int(min(rng.integers(1, 300), tokens - sum(lens))))
     lens = np.asarray(lens)
-    params = wl.draw_params(wl.GPT_KEYS, 1, d, F, seed=4, bf16=True)
-    xs, dys = wl.draw_rows(lens, d, seed=4, tag=3, bf16=True), wl.draw_rows(lens, d, seed=4, tag=5, bf16=True)
+    bf16 = code == ds.DS_DTYPE_BF16
+    params = wl.draw_params(wl.GPT_KEYS, 1, d, F, seed=4, bf16=bf16)
+    xs, dys = wl.draw_rows(lens, d, seed=4, tag=3, bf16=bf16), wl.draw_rows(lens, d, seed=4, tag=5, bf16=bf16)
     lo = ds.ds_layout_from_cuts(lens, list(range(len(lens) + 1)))
     ref = ost.gpt_stage_fwd_bwd(xs, dys, params, cfg["n_heads"])
     grads = [{k: torch.full(v.shape, 3.0, dtype=torch.float32, device="cuda:0") for k, v in params[0].items()}]
-    _compare("%d %d %d" % (d, F, tokens), run_gpt_stage(lo, cfg, params, xs, dys, ds.DS_DTYPE_BF16, grads=grads), ref, TOL[ds.DS_DTYPE_BF16])
-    twice = run_gpt_stage(lo, cfg, params, xs, dys, ds.DS_DTYPE_BF16, grads=grads, accumulate=True)[2]
+    _compare("%d %d %d" % (d, F, tokens), run_gpt_stage(lo, cfg, params, xs, dys, code, grads=grads), ref, TOL[code])
+    twice = run_gpt_stage(lo, cfg, params, xs, dys, code, grads=grads, accumulate=True)[2]
     for k, v in ref[2][0].items():
-        check(twice[0][k], 2 * v, TOL[ds.DS_DTYPE_BF16], k)
+        check(twice[0][k], 2 * v, TOL[code], k)
 
 
 # rows up to and beyond what one work-group walks (512), row lanes with and without a row, narrow and wide norm kernels
