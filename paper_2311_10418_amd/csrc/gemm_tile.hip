@@ -5,16 +5,20 @@
 // products are 6).
 //
 // Three tiles, all direct-to-LDS with the operand layouts of the large kernel, 64-deep K tiles in a ring of stages:
-//   0: 128 x 128, 8 wavefronts of 64 x 32, 4 stages (128 KB: one work-group per CU)
-//   3: the same with 2 stages (64 KB: two per CU)
+//   0: 128 x 128, 8 wavefronts, 4 stages (128 KB: one work-group per CU): four of 64 x 64 twice, each four taking one of the two
+//      32-deep steps of every K tile (KS = 2); the halves of the contraction meet in LDS at the end
+//   3: 128 x 128, 8 wavefronts of 64 x 32, 2 stages (64 KB: two per CU)
 //   1: 128 x  64, 8 wavefronts of 32 x 32, 3 stages ( 72 KB: two per CU)
 //   2:  64 x  64, 4 wavefronts of 32 x 32, 3 stages ( 48 KB: three per CU)
 // What bounds them is what one work-group can do between two barriers: more stages change nothing (3, 4 and 5 within 2 %),
 // a second work-group on the CU does.  With one tile per CU the deep ring is the better one (M = 1757, N = K = 2048: 19.8 us,
 // two stages 22.1), with more the shallow one (M = 756, N = 6144, K = 2048: 27.9 against 39.7).  Time per K tile of a CU:
 // 0.49 us for kind 0, 0.32 and 0.20 for 1 and 2, for kind 3 0.39 while the chip is not full and 0.55 - 0.62 per tile when every CU
-// works on two.  Four wavefronts of 64 x 64 on the 128 x 128 tile are slower at every shape tried (N = 2048, K = 8192,
-// M = 1757: 89 us and, with 32-deep tiles and two work-groups per CU, 73, against 60).
+// works on two.  Four wavefronts of 64 x 64 alone on the 128 x 128 tile are slower at every shape tried (N = 2048, K = 8192,
+// M = 1757: 89 us and, with 32-deep tiles and two work-groups per CU, 73, against 60); eight of them, two to a SIMD, with half the
+// K steps each read a third less from LDS than eight of 64 x 32 and have one burst of 16 MFMAs per barrier: 1024 x 4096 TN over
+// 4173 tokens, operands warm, 55 -> 51 us, NT 4096 x 1024 x 4096 43.2 -> 40.6; from memory as before (54, 52): there the transfers are
+// the limit (timing build without the products 52 and 48).  At 128 x 64 the same changes nothing.
 //
 // Which one: the tile and split count with the smallest estimate (pick_gemm_tile), compared with the same kind of
 // estimate for the large kernel.  Measured, 256 x 256 kernel -> this, us (M, N, K; ds_gemm_ws on an idle card):
@@ -104,16 +108,17 @@ template <int ROWS, bool KC, int NW> struct OperandTile {
 // Ring of NS stages, 64-deep K tiles: a tile's transfers are issued NS - 1 tiles ahead, right after the barrier that
 // frees their stage; the fragments of the next 32-deep step are read while the current one is multiplied, across the
 // tile boundary too.  Transfers past the last tile are clamped so that the wait counts never change.
+// KS = 2: WM x WN wavefronts twice, each half takes one of the two 32-deep steps of every K tile.
 // GRP (TN form): the work-groups of several weight gradients over the same K rows (grp), problem after problem.
-template <int EPI, bool TNF, int BM, int BN, int WM, int WN, int NS, bool GRP = false>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
+template <int EPI, bool TNF, int BM, int BN, int WM, int WN, int NS, int KS, bool GRP = false>
+__global__ __launch_bounds__(WM * WN * KS * 64) void gemm_bf16_tile_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
                                                                       const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
                                                                       int tiles_m, int tiles_n, int splits, int tiles_per_split,
                                                                       float* __restrict__ split_ws, GemmEpi p,
                                                                       std::conditional_t<GRP, TnGroup, NoGroup> grp) {
     static_assert(!GRP || (TNF && EPI == DS_EPI_ACC32), "groups are of weight gradients");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int NW = WM * WN;
+    constexpr int NW = WM * WN * KS;
     typedef OperandTile<BM, !TNF, NW> TA;
     typedef OperandTile<BN, !TNF, NW> TB;
     constexpr int STAGE = TA::BYTES + TB::BYTES;
@@ -123,7 +128,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
     static_assert(WR % 32 == 0 && WC % 32 == 0, "the epilogue stages 32 rows of at least 32 columns");
     static_assert((NS - 1) * L < 64, "vmcnt has 6 bits");
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = wave / WN, wn = wave % WN;
+    const int wm = wave / WN % WM, wn = wave % WN, kq = wave / (WM * WN);         // KS = 2: kq = the 32-deep step of a tile it takes
 
     int tile_m, tile_n, split;
     {
@@ -193,25 +198,64 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
     for (int s = 0; s < NS; ++s) issue(t_begin + s);
     __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 1) * L));              // the first tile: this wavefront's part ...
     __builtin_amdgcn_s_barrier();                                     // ... and everyone's
-    read(0, 0, ax, bx);
-    int stage = 0;
-    for (int tl = t_begin; tl < t_end; ++tl) {
-        const int next = stage + 1 == NS ? 0 : stage + 1;
-        read(stage, 1, ay, by);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(ax, bx);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * L) & 0xF0FF); // tile tl + 1 has landed; lgkmcnt(0): reads of tile tl are done
-        __builtin_amdgcn_s_barrier();
-        issue(tl + NS);                                               // into the stage of tile tl
-        read(next, 0, ax, bx);                                        // (past the last tile: a reloaded copy of it, unused)
-        __builtin_amdgcn_sched_barrier(0);
-        mma(ay, by);
-        __builtin_amdgcn_sched_barrier(0);
-        stage = next;
+    read(0, KS == 1 ? 0 : kq, ax, bx);
+    if constexpr (KS == 1) {
+        int stage = 0;
+        for (int tl = t_begin; tl < t_end; ++tl) {
+            const int next = stage + 1 == NS ? 0 : stage + 1;
+            read(stage, 1, ay, by);
+            __builtin_amdgcn_sched_barrier(0);
+            mma(ax, bx);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * L) & 0xF0FF); // tile tl + 1 has landed; lgkmcnt(0): reads of tile tl are done
+            __builtin_amdgcn_s_barrier();
+            issue(tl + NS);                                               // into the stage of tile tl
+            read(next, 0, ax, bx);                                        // (past the last tile: a reloaded copy of it, unused)
+            __builtin_amdgcn_sched_barrier(0);
+            mma(ay, by);
+            __builtin_amdgcn_sched_barrier(0);
+            stage = next;
+        }
+    } else {
+        int stage = 0;
+        auto tile = [&](int tl, bf16x8_t (&fa)[NA], bf16x8_t (&fb)[NB], bf16x8_t (&ga)[NA], bf16x8_t (&gb)[NB]) {
+            const int next = stage + 1 == NS ? 0 : stage + 1;
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * L) & 0xF0FF); // tile tl + 1 has landed; lgkmcnt(0): reads of tile tl are done
+            __builtin_amdgcn_s_barrier();
+            issue(tl + NS);                                               // into the stage of tile tl
+            read(next, kq, ga, gb);                                       // (past the last tile: a reloaded copy of it, unused)
+            __builtin_amdgcn_sched_barrier(0);
+            mma(fa, fb);
+            __builtin_amdgcn_sched_barrier(0);
+            stage = next;
+        };
+        int tl = t_begin;
+        for (; tl + 1 < t_end; tl += 2) {
+            tile(tl, ax, bx, ay, by);
+            tile(tl + 1, ay, by, ax, bx);
+        }
+        if (tl < t_end) tile(tl, ax, bx, ay, by);
     }
     __builtin_amdgcn_s_waitcnt(0x0070);                               // no transfer may still be writing the LDS the epilogue uses
     __builtin_amdgcn_s_barrier();
+    if constexpr (KS == 2) {
+        // the two halves of the contraction meet: a wavefront hands the blocks of half its rows to its partner and finishes the others
+        static_assert(NA % 4 == 0, "whole 32-row passes per half");
+        f32x4_t* x = reinterpret_cast<f32x4_t*>(smem) + (wave * (NA / 2) * NB) * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < NA / 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) x[(i * NB + j) * 64] = kq ? acc[i][j] : acc[NA / 2 + i][j];
+        __syncthreads();
+        const f32x4_t* y = reinterpret_cast<const f32x4_t*>(smem) + ((wave ^ (WM * WN)) * (NA / 2) * NB) * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < NA / 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = (kq ? acc[NA / 2 + i][j] : acc[i][j]) + y[(i * NB + j) * 64];
+        __syncthreads();
+    }
+    constexpr int WE = WR / KS;                                       // rows this wavefront finishes, from row m1 on
+    const int m1 = m0 + wm * WR + (KS == 2 ? kq * WE : 0);
 
     // epilogue: 32 rows at a time through a block of LDS that is private to the wavefront
     constexpr int LDC = WC + 4, LPR = WC / 8, RPP = 64 / LPR, NP = 32 / RPP;
@@ -219,13 +263,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
     const int rd_row = lane / LPR, rd_col = (lane % LPR) * 8;
     const int n = n0 + wn * WC + rd_col;
     const bool direct = splits == 1;
-    EpiPre<bf16_t> pre[WR / 32][NP];
+    EpiPre<bf16_t> pre[WE / 32][NP];
     if (epilogue_reads<EPI>() && direct) {
 #pragma unroll
-        for (int i = 0; i < WR / 32; ++i)
+        for (int i = 0; i < WE / 32; ++i)
 #pragma unroll
             for (int q = 0; q < NP; ++q) {
-                const int m = m0 + wm * WR + i * 32 + q * RPP + rd_row;
+                const int m = m1 + i * 32 + q * RPP + rd_row;
                 if (m < M) epilogue_prefetch<bf16_t, EPI>(m, n, N, p, pre[i][q]);
             }
     }
@@ -233,7 +277,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
 #pragma unroll
     for (int j = 0; j < 8; ++j) csum[j] = 0.f;
 #pragma unroll
-    for (int i = 0; i < WR / 32; ++i) {
+    for (int i = 0; i < WE / 32; ++i) {
         wave_lds_sync();
 #pragma unroll
         for (int i2 = 0; i2 < 2; ++i2)
@@ -245,7 +289,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
         wave_lds_sync();
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
-            const int row = q * RPP + rd_row, m = m0 + wm * WR + i * 32 + row;
+            const int row = q * RPP + rd_row, m = m1 + i * 32 + row;
             if (m >= M) continue;
             float v[8];
             Vec8<float>::load(stg + row * LDC + rd_col, v);
@@ -268,13 +312,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
 #pragma unroll
                 for (int j = 0; j < 8; ++j) csum[j] += __shfl_xor(csum[j], o, 64);
             __syncthreads();
-            float* red = reinterpret_cast<float*>(smem);              // [WM][BN]
-            if (lane < LPR) Vec8<float>::store(red + wm * BN + wn * WC + rd_col, csum);
+            float* red = reinterpret_cast<float*>(smem);              // [WM KS][BN]
+            if (lane < LPR) Vec8<float>::store(red + (wm * KS + kq) * BN + wn * WC + rd_col, csum);
             __syncthreads();
             if (t < BN) {
                 float s = red[t];
 #pragma unroll
-                for (int w = 1; w < WM; ++w) s += red[w * BN + t];
+                for (int w = 1; w < WM * KS; ++w) s += red[w * BN + t];
                 p.colsum[(size_t)tile_m * N + n0 + t] = s;
                 // gemm_colsum_rows() counts two rows per 256: the last one may have no tile
                 if (tile_m + 1 == tiles_m && (tiles_m & 1)) p.colsum[(size_t)(tile_m + 1) * N + n0 + t] = 0.f;
@@ -283,10 +327,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_tile_kernel(int M, int
     }
 }
 
-struct TileShape { int bm, bn, waves, stages; double step, fixed; };
+struct TileShape { int bm, bn, waves, stages, ks; double step, fixed; };
 // step: microseconds per K tile of a CU that has one tile; fixed: around the K loop
 constexpr int kKinds = 4;
-constexpr TileShape kShapes[kKinds] = {{128, 128, 8, 4, 0.49, 3.0}, {128, 64, 8, 3, 0.32, 2.5}, {64, 64, 4, 3, 0.20, 2.5}, {128, 128, 8, 2, 0.39, 3.0}};
+constexpr TileShape kShapes[kKinds] = {{128, 128, 8, 4, 2, 0.49, 3.0}, {128, 64, 8, 3, 1, 0.32, 2.5}, {64, 64, 4, 3, 1, 0.20, 2.5}, {128, 128, 8, 2, 1, 0.39, 3.0}};
 constexpr double kBusyStep3 = 0.62;                  // kind 3, per tile, when every CU works on two (0.55 on operands that are warm in L2)
 constexpr double kBusyStep0 = 0.64;                  // kind 0, per tile, several of them one after the other
 constexpr double kLoneStep1 = 0.36, kLoneStep2 = 0.24;                // TN form, one tile per CU: nothing covers its waits
@@ -298,9 +342,9 @@ ds_status launch_kind(int splits, int M, int N, int K, const void* A, const void
     constexpr TileShape s = kShapes[KIND];
     constexpr int ring = s.stages * (s.bm + s.bn) * T_KD * 2, staging = s.waves * 32 * (s.bn / WN + 4) * 4;
     constexpr int smem = ring > staging ? ring : staging;
-    static_assert(WM * WN == s.waves, "wavefront grid");
+    static_assert(WM * WN * s.ks == s.waves, "wavefront grid");
     static bool attr_set = false;
-    auto kern = gemm_bf16_tile_kernel<EPI, TNF, s.bm, s.bn, WM, WN, s.stages>;
+    auto kern = gemm_bf16_tile_kernel<EPI, TNF, s.bm, s.bn, WM, WN, s.stages, s.ks>;
     if (!attr_set) {
         DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
         attr_set = true;
@@ -320,7 +364,7 @@ ds_status launch_group_kind(const TnGroup& g, int blocks, hipStream_t st) {
     constexpr int ring = s.stages * (s.bm + s.bn) * T_KD * 2, staging = s.waves * 32 * (s.bn / WN + 4) * 4;
     constexpr int smem = ring > staging ? ring : staging;
     static bool attr_set = false;
-    auto kern = gemm_bf16_tile_kernel<DS_EPI_ACC32, true, s.bm, s.bn, WM, WN, s.stages, true>;
+    auto kern = gemm_bf16_tile_kernel<DS_EPI_ACC32, true, s.bm, s.bn, WM, WN, s.stages, s.ks, true>;
     if (!attr_set) {
         DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
         attr_set = true;
@@ -336,7 +380,7 @@ ds_status launch_group_kind(const TnGroup& g, int blocks, hipStream_t st) {
 template <int EPI, bool TNF>
 ds_status launch_form(const TilePick& k, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
                       hipStream_t st) {
-    if (k.kind == 0) return launch_kind<EPI, TNF, 0, 2, 4>(k.splits, M, N, K, A, B, C, p, split_ws, st);
+    if (k.kind == 0) return launch_kind<EPI, TNF, 0, 2, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
     if (k.kind == 3) return launch_kind<EPI, TNF, 3, 2, 4>(k.splits, M, N, K, A, B, C, p, split_ws, st);
     if (k.kind == 1) return launch_kind<EPI, TNF, 1, 4, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
     return launch_kind<EPI, TNF, 2, 2, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
@@ -470,7 +514,7 @@ ds_status launch_tn_group(const TnPick& pick, TnGroup& g, hipStream_t st) {
         if (blocks > 0x7fffffff) return DS_EOVERFLOW;
     }
     switch (pick.kind) {
-    case 0: return launch_group_kind<0, 2, 4>(g, (int)blocks, st);
+    case 0: return launch_group_kind<0, 2, 2>(g, (int)blocks, st);
     case 1: return launch_group_kind<1, 4, 2>(g, (int)blocks, st);
     case 2: return launch_group_kind<2, 2, 2>(g, (int)blocks, st);
     case 3: return launch_group_kind<3, 2, 4>(g, (int)blocks, st);
