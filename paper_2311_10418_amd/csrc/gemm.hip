@@ -871,6 +871,38 @@ ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, 
     return DS_OK;
 }
 
+// Which matrix-core kernel an NT launch (tn: a weight gradient) goes to and what it is expected to take: pick.kind -1 = 256 x 256
+// tiles.
+struct NtChoice {
+    TilePick pick;
+    double cost;
+};
+static NtChoice choose_kernel(bool tn, int epi, int M, int N, int K, size_t wsf, bool colsum, int accumulate) {
+    const BigPlan plan = plan_big(tn, epi, M, N, K, wsf);
+    const double out_us = gemm_output_us(epi, M, N, accumulate);
+    NtChoice c{TilePick{-1, 1, 0.0, 0.0}, big_cost(plan, tn, M, N) + out_us};
+    if (plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
+        // launches that do not fill the chip with 256 x 256 tiles: smaller ones, where the estimates say so (ties go to the large tile)
+        const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, colsum, out_us, accumulate != 0);
+        if (pick.kind >= 0 && pick.versus_large < 0.95 * c.cost) c = NtChoice{pick, pick.versus_large};
+    }
+    return c;
+}
+
+// NT launches whose last rows open another round over the CUs (4 173 x 4 096 outputs: 256 tiles of 256 x 256 and 16 more for 77 rows,
+// whose K loops are then cut into pieces and added up by a launch of their own) go out as two: the rows of the whole rounds
+// first, the rest with the tiles that suit it, where the estimates with 1 us between them are 3 % below that of one.  0: one launch.
+// 4 173 x 4 096 x 1 024: 51 -> 45 us, 4 173 x 4 352 x 1 024: 54 -> 46.
+static int rows_of_whole_rounds(int epi, int M, int N, int K, size_t wsf, bool colsum, int accumulate, double one) {
+    const int n_cu = gemm_cu_count(), tiles_n = N / BN;
+    const long long rounds = (long long)((M + BM - 1) / BM) * tiles_n / n_cu;
+    const long long rows = rounds * n_cu / tiles_n * BM;
+    if (rounds < 1 || rows <= 0 || rows >= M) return 0;
+    const double two = choose_kernel(false, epi, (int)rows, N, K, wsf, colsum, accumulate).cost + 1 +
+                       choose_kernel(false, epi, M - (int)rows, N, K, wsf, colsum, accumulate).cost;
+    return two < 0.97 * one ? (int)rows : 0;
+}
+
 template <int EPI>
 ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const void* A, const void* B, void* C,
                        const GemmEpi& p, bool force_generic, float* split_ws, size_t split_ws_floats, hipStream_t st) {
@@ -880,19 +912,33 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
         const bool ok_b = tb ? (K % BK == 0) : true;
         const bool aligned = ((uintptr_t)A % 16 == 0) && ((uintptr_t)B % 16 == 0) && ((uintptr_t)C % 16 == 0);
         if (ok_n && ok_a && ok_b && aligned && M >= 1 && K >= 1) {
-            // launches that do not fill the chip with 256 x 256 tiles: smaller ones, where the estimates say so
             const bool tn = ta && !tb && EPI == DS_EPI_ACC32;
-            if (tn || (!ta && tb)) {
-                const size_t wsf = split_ws ? split_ws_floats : 0;
-                const BigPlan plan = plan_big(tn, EPI, M, N, K, wsf);
-                if (plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
-                    const double out_us = gemm_output_us(EPI, M, N, p.accumulate);
-                    const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, p.colsum != nullptr, out_us, p.accumulate != 0);
-                    if (pick.kind >= 0 && pick.versus_large < 0.95 * (big_cost(plan, tn, M, N) + out_us))      // (ties go to the large tile)
-                        return launch_gemm_tile(pick, tn, M, N, K, A, B, C, EPI, p, split_ws, st);
-                }
+            const size_t wsf = split_ws ? split_ws_floats : 0;
+            if (!ta && tb) {
+                auto launch = [&](const NtChoice& c, int m, const void* a, void* out, const GemmEpi& q) -> ds_status {
+                    if (c.pick.kind >= 0) return launch_gemm_tile(c.pick, false, m, N, K, a, B, out, EPI, q, split_ws, st);
+                    return launch_nt<EPI, false>(m, N, K, a, B, out, q, split_ws, split_ws_floats, st);
+                };
+                const NtChoice one = choose_kernel(false, EPI, M, N, K, wsf, p.colsum != nullptr, p.accumulate);
+                const int rows = rows_of_whole_rounds(EPI, M, N, K, wsf, p.colsum != nullptr, p.accumulate, one.cost);
+                if (rows == 0) return launch(one, M, A, C, p);
+                const ds_status r = launch(choose_kernel(false, EPI, rows, N, K, wsf, p.colsum != nullptr, p.accumulate), rows, A, C, p);
+                if (r != DS_OK) return r;
+                const size_t at = (size_t)rows * N;
+                auto behind = [&](const void* x) -> const void* { return x ? (const bf16_t*)x + at : nullptr; };
+                GemmEpi q = p;
+                q.R = behind(p.R);
+                q.R2 = behind(p.R2);
+                q.C2 = const_cast<void*>(behind(p.C2));
+                if (p.row_valid) q.row_valid = p.row_valid + rows;
+                if (p.colsum) q.colsum = p.colsum + gemm_colsum_rows(rows) * N;
+                return launch(choose_kernel(false, EPI, M - rows, N, K, wsf, p.colsum != nullptr, p.accumulate), M - rows,
+                              (const bf16_t*)A + (size_t)rows * K, EPI == DS_EPI_ACC32 ? (void*)((float*)C + at) : (void*)((bf16_t*)C + at), q);
             }
-            if (!ta && tb) return launch_nt<EPI, false>(M, N, K, A, B, C, p, split_ws, split_ws_floats, st);
+            if (tn) {
+                const NtChoice c = choose_kernel(true, EPI, M, N, K, wsf, false, p.accumulate);
+                if (c.pick.kind >= 0) return launch_gemm_tile(c.pick, true, M, N, K, A, B, C, EPI, p, split_ws, st);
+            }
             if constexpr (EPI == DS_EPI_ACC32)      // (the TN form addresses a K tile of each operand through a 32-bit buffer length)
                 if (ta && !tb && M <= (1 << 25) && N <= (1 << 25)) return launch_nt<EPI, true>(M, N, K, A, B, C, p, split_ws, split_ws_floats, st);
         }

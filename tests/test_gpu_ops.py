@@ -83,6 +83,34 @@ def test_gemm_epilogues(dt, force):
     assert both_err(g2, acc * ost.gelu(R.astype(np.float64))) <= tol
 
 
+# 256 x 256 tiles for whole rounds over 256 compute units and other tiles for the rows behind them, from one to a tile and a half
+@pytest.mark.parametrize("M", [8193, 8289, 8192 + 385])
+def test_gemm_rows_behind_whole_rounds(M):
+    rng = np.random.default_rng(M)
+    N, K, tol = 2048, 64, 6e-3
+    A, B = _rnd(rng, (M, K), BF), _rnd(rng, (N, K), BF, 0.1)
+    bias, R, R2 = _rnd(rng, (N,), BF), _rnd(rng, (M, N), BF), _rnd(rng, (M, N), BF)
+    valid = np.where(rng.random(M) < 0.8, 1, -1).astype(np.int32)
+    acc = A.astype(np.float64) @ B.T.astype(np.float64)
+    dA, dB, db, dR, dR2 = (to_dev(x, BF) for x in (A, B, bias, R, R2))
+    ws = torch.zeros(1 << 22, dtype=F32, device=DEV)
+
+    def run(epi, dt=BF, **kw):
+        c, c2 = torch.full((M, N), 3.0, dtype=dt, device=DEV), torch.full((M, N), 3.0, dtype=BF, device=DEV)
+        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, epilogue=epi, C2=c2, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        return to_np(c), to_np(c2)
+
+    assert both_err(run(ds.DS_EPI_NONE, bias=db)[0], acc + bias) <= tol
+    c, _ = run(ds.DS_EPI_RESID, bias=db, R=dR, row_valid=torch.from_numpy(valid).to(DEV))
+    assert both_err(c, (acc + bias + R) * (valid[:, None] >= 0)) <= tol and np.all(c[valid < 0] == 0)
+    c, c2 = run(ds.DS_EPI_GELU_D, bias=db)
+    assert both_err(c, ost.gelu_grad(acc + bias)) <= tol and both_err(c2, ost.gelu(acc + bias)) <= tol
+    c, c2 = run(ds.DS_EPI_DGATE, R=dR, R2=dR2)
+    assert both_err(c, acc * R2 * ost.gelu_grad(R.astype(np.float64))) <= tol and both_err(c2, acc * ost.gelu(R.astype(np.float64))) <= tol
+    assert both_err(run(ds.DS_EPI_ACC32, dt=F32, accumulate=True)[0], acc + 3.0) <= 1e-5
+
+
 @pytest.mark.parametrize("dt,force", [(F32, True), (BF, False)])
 @pytest.mark.parametrize("M,N,K", [(256, 512, 3000 + 11), (768, 512, 1000 + 37), (512, 256, 31), (256, 256, 64)])
 def test_gemm_weight_gradient_accumulates_in_fp32(dt, force, M, N, K):

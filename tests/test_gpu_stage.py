@@ -226,7 +226,8 @@ def test_back_to_back_calls_on_a_caller_stream_without_host_synchronisation():
     stage.close()
 
 
-@pytest.mark.parametrize("d_ff,rows", [(1024, [1, 127, 128, 129, 256, 257, 385]), (5632, [129, 257, 384, 385, 641, 769])])
+@pytest.mark.parametrize("d_ff,rows", [(1024, [1, 127, 128, 129, 256, 257, 385]), (5632, [129, 257, 384, 385, 641, 769]),
+                                       (8192, [2089, 2305])])
 def test_bias_gradient_from_partial_column_sums(d_ff, rows):
     """The bias gradient of the MLP's first projection is summed from one partial row per 128 rows, of which an odd count is
     padded to an even one: even and odd counts, full and ragged last tiles, after a larger call with gradients a thousand
