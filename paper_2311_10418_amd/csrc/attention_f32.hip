@@ -228,7 +228,18 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
     load_column<HD>((const float*)a.q + (qrow0 + qi_c) * a.ldq + h * hd, hd, g, qf);
     load_column<HD>((const float*)a.d_o + (qrow0 + qi_c) * a.ldo + h * hd, hd, g, dof);
     const float lse2 = a.lse[(size_t)h * a.lse_stride + qrow0 + qi_c] * kLog2eF;
-    const float delta = a.delta[(size_t)h * a.lse_stride + qrow0 + qi_c];
+    // delta = rowsum(dO * O), for this kernel and, through memory, the dK / dV kernel (a launch of its own took 11.5 us: one wavefront
+    // per row and head of the longest sequence for every sequence)
+    float delta = 0.f;
+    {
+        float4 of[HD / 16];
+        load_column<HD>((const float*)a.o + (qrow0 + qi_c) * a.ldo + h * hd, hd, g, of);
+#pragma unroll
+        for (int dt = 0; dt < HD / 16; ++dt)
+            delta += (of[dt].x * dof[dt].x + of[dt].y * dof[dt].y) + (of[dt].z * dof[dt].z + of[dt].w * dof[dt].w);
+        delta = groups_sum(delta);
+        if (g == 0 && qi < ql) a.delta[(size_t)h * a.lse_stride + qrow0 + qi] = delta;
+    }
     const float c = a.scale * kLog2eF;
     f32x4_t gacc[HD / 16];
 #pragma unroll
@@ -267,6 +278,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
         }
     }
     if (a.mask && kv_end > 0 && s_by_rows) {
+        __threadfence_block();                          // (delta, read back by other lanes)
         for (int q = qw0; q < min(qw0 + 16, ql); ++q) {
             wave_lds_sync();
             stage_row(s_row[wave][0], (const float*)a.q + (qrow0 + q) * a.ldq + h * hd, hd, a.scale, lane);
@@ -417,7 +429,6 @@ ds_status attn_fwd_f32_mfma(const AttnArgs& a, hipStream_t st) {
     return DS_OK;
 }
 
-// (a.delta is complete: attn_delta runs in front)
 ds_status attn_bwd_f32_mfma(const AttnArgs& a, hipStream_t st) {
     if (a.head_dim <= 32) return bwd_f32<32>(a, st);
     if (a.head_dim <= 64) return bwd_f32<64>(a, st);

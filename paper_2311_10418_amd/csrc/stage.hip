@@ -534,10 +534,10 @@ struct Ops {
                          s->lists_kind[cur_slot] == cur_kind) ? 1 : 0;
         return a;
     }
-    // kernels of one attention call: the matrix-core kernels build their lists first unless they are there, the others
-    // compute delta in a launch of its own
+    // kernels of one attention call: the bf16 matrix-core kernels build their lists first unless they are there, the generic
+    // ones compute delta in a launch of its own
     static int attn_launches(const AttnArgs& a, bool bwd) {
-        const int first = attn_mfma_supported(a) ? !a.lists_ready : bwd;
+        const int first = attn_mfma_supported(a) ? !a.lists_ready : bwd && !attn_f32_mfma_supported(a);
         return first + (bwd ? 2 : 1);
     }
     // after a launch that went through the matrix-core kernels: the scratch now holds both lists of this kind
