@@ -246,8 +246,16 @@ __device__ __forceinline__ void lds_dma16_buffer_group(i32x4_t buf, const uint32
 static inline size_t dtype_size(int32_t dtype) { return dtype == DS_DTYPE_BF16 ? 2 : 4; }
 
 // ---- launchers shared between translation units (all enqueue on `st`, return ds_status)
-ds_status launch_mask_rows(int32_t dtype, int32_t rows, int32_t d, const void* in, void* out,
-                           const int32_t* row_valid, hipStream_t st);
+// out = in with the rows whose row_valid is negative replaced by zeros (NaN there included), for up to three tensors of d columns
+constexpr int kMaskBatch = 3;
+struct MaskBatch {
+    int n = 0;
+    const void* in[kMaskBatch];
+    void* out[kMaskBatch];
+    const int32_t* row_valid[kMaskBatch];
+    int32_t rows[kMaskBatch];
+};
+ds_status launch_mask_rows(int32_t dtype, const MaskBatch& b, int32_t d, hipStream_t st);
 // Segments of a padded stream in ascending row order: rows row[i] .. + len[i] - 1 are the canonical rows canon[i] .., the
 // rows from there to row[i + 1] (of the last one: to end) are padding.  3 KB, passed by value.
 constexpr int kRowSegments = 250;

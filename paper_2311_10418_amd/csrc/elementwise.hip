@@ -4,6 +4,7 @@
 // per lane, consecutive lanes touching consecutive addresses.
 #include "common.hpp"
 
+#include <algorithm>
 #include <mutex>
 
 namespace {
@@ -20,14 +21,17 @@ float* g_colsum_scratch_ptr[kMaxDevices];        // device address of the array 
 std::mutex g_colsum_scratch_mutex;
 
 // ------------------------------------------------------------------ row copy kernels
+// blockIdx.y = tensor
 template <class T>
-__global__ __launch_bounds__(256) void mask_rows_kernel(int rows, int d8, const T* __restrict__ in, T* __restrict__ out,
-                                                        const int32_t* __restrict__ row_valid) {
-    const long long total = (long long)rows * d8;
+__global__ __launch_bounds__(256) void mask_rows_kernel(MaskBatch b, int d8) {
+    const int k = blockIdx.y;
+    const T* __restrict__ in = reinterpret_cast<const T*>(b.in[k]);
+    T* __restrict__ out = reinterpret_cast<T*>(b.out[k]);
+    const int32_t* __restrict__ row_valid = b.row_valid[k];
+    const long long total = (long long)b.rows[k] * d8;
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-        const int r = (int)(i / d8);
         float v[8];
-        if (row_valid == nullptr || row_valid[r] >= 0) {
+        if (row_valid[(int)(i / d8)] >= 0) {
             Vec8<T>::load(in + i * 8, v);
         } else {
 #pragma unroll
@@ -812,17 +816,14 @@ ds_status sum_group_run(SumGroup& g, float* partial, size_t partial_floats, hipS
 
 }  // namespace
 
-ds_status launch_mask_rows(int32_t dtype, int32_t rows, int32_t d, const void* in, void* out,
-                           const int32_t* row_valid, hipStream_t st) {
-    if (rows <= 0) return DS_OK;
+ds_status launch_mask_rows(int32_t dtype, const MaskBatch& b, int32_t d, hipStream_t st) {
     if (d % 8) return DS_EINVAL;
-    const long long items = (long long)rows * (d / 8);
-    if (dtype == DS_DTYPE_BF16)
-        hipLaunchKernelGGL(mask_rows_kernel<bf16_t>, dim3(grid_for(items, 256)), dim3(256), 0, st, rows, d / 8,
-                           (const bf16_t*)in, (bf16_t*)out, row_valid);
-    else
-        hipLaunchKernelGGL(mask_rows_kernel<float>, dim3(grid_for(items, 256)), dim3(256), 0, st, rows, d / 8,
-                           (const float*)in, (float*)out, row_valid);
+    long long items = 0;
+    for (int k = 0; k < b.n; ++k) items = std::max(items, (long long)b.rows[k] * (d / 8));
+    if (items <= 0) return DS_OK;
+    const dim3 grid(grid_for(items, 256), b.n);
+    if (dtype == DS_DTYPE_BF16) hipLaunchKernelGGL(mask_rows_kernel<bf16_t>, grid, dim3(256), 0, st, b, d / 8);
+    else hipLaunchKernelGGL(mask_rows_kernel<float>, grid, dim3(256), 0, st, b, d / 8);
     DS_LAUNCH_CHECK();
     return DS_OK;
 }

@@ -469,9 +469,20 @@ struct Ops {
             return ds_norm_bwd(dt, rms, sm.R, d, dy, x, g, stats, resid, dx, (float*)dg, (float*)db, s->partial, accumulate, st);
         });
     }
-    ds_status mask_rows(const Stream& sm, const void* in, void* out) {
+    // What the caller hands in, padding rows zeroed: copies where the stream has padding, all of them in one launch in front
+    MaskBatch masked;
+    const void* mask_later(const Stream& sm, const void* in, void* out) {
+        if (!sm.has_pad) return in;
+        masked.in[masked.n] = in;
+        masked.out[masked.n] = out;
+        masked.row_valid[masked.n] = sm.row_valid;
+        masked.rows[masked.n++] = sm.R;
+        return out;
+    }
+    ds_status mask_rows() {
+        if (masked.n == 0) return DS_OK;
         s->launches++;
-        return timed(s, DS_PROF_OTHER, st, [&] { return launch_mask_rows(dt, sm.R, d, in, out, sm.row_valid, st); });
+        return timed(s, DS_PROF_OTHER, st, [&] { return launch_mask_rows(dt, masked, d, st); });
     }
     ds_status zero_pad(const Stream& sm, void* buf, int cols) {
         if (!sm.has_pad) return DS_OK;
@@ -600,11 +611,9 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
     DS_TRY(op.zero_pads_of_layout(sm));
 
     // ---------------- forward (ForwardPass of every micro-batch)
-    const void* x_in = io->act_in;
-    if (sm.has_pad) {
-        DS_TRY(op.mask_rows(sm, io->act_in, s->x0));
-        x_in = s->x0;
-    }
+    const void* x_in = op.mask_later(sm, io->act_in, s->x0);
+    const void* dy = op.mask_later(sm, io->grad_out, s->dyA);
+    DS_TRY(op.mask_rows());
     const void* x0 = x_in;
     // forward of layer l from its input; x_out = NULL: only what the layer's backward reads (recomputation)
     auto layer_fwd = [&](int l, const void* xl, void* x_out) -> ds_status {
@@ -626,11 +635,6 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
     const bool recompute = s->cfg.recompute == DS_RECOMPUTE_FULL;
 
     // ---------------- backward (BackwardPass of every micro-batch; weight gradients summed over all of them)
-    const void* dy = io->grad_out;
-    if (sm.has_pad) {
-        DS_TRY(op.mask_rows(sm, io->grad_out, s->dyA));
-        dy = s->dyA;
-    }
     void* pp[2] = {s->dyB, s->dyA};
     int flip = 0;
     for (int l = L - 1; l >= 0; --l) {
@@ -752,11 +756,10 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
     }
 
     // ---------------- forward: encoder layers over the input stream
-    const void* x_in = io->act_in;
-    if (E.has_pad) {
-        DS_TRY(op.mask_rows(E, io->act_in, s->x0));
-        x_in = s->x0;
-    }
+    const void* x_in = op.mask_later(E, io->act_in, s->x0);
+    const void* y_in = op.mask_later(D, io->act_in_tgt, s->y0);
+    const void* dy = op.mask_later(D, io->grad_out, s->dyA);
+    DS_TRY(op.mask_rows());
     const void* x0 = x_in;
     const bool recompute = s->cfg.recompute == DS_RECOMPUTE_FULL;
     // forward of encoder layer l from its input; with_out = false: only what its backward reads (recomputation)
@@ -772,11 +775,6 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
     const void* enc_out = x_in;
 
     // ---------------- forward: decoder layers over the target stream
-    const void* y_in = io->act_in_tgt;
-    if (D.has_pad) {
-        DS_TRY(op.mask_rows(D, io->act_in_tgt, s->y0));
-        y_in = s->y0;
-    }
     const void* y0 = y_in;
     // forward of decoder layer l from its input; y_out = NULL: only what its backward reads (recomputation)
     auto dec_layer_fwd = [&](int l, const void* yl, void* y_out) -> ds_status {
@@ -806,11 +804,6 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
     }
 
     // ---------------- backward: decoder layers (last to first); de accumulates the gradient of the encoder output
-    const void* dy = io->grad_out;
-    if (D.has_pad) {
-        DS_TRY(op.mask_rows(D, io->grad_out, s->dyA));
-        dy = s->dyA;
-    }
     void* pp[2] = {s->dyB, s->dyA};
     int flip = 0;
     bool de_set = false;
