@@ -367,6 +367,17 @@ struct Ops {
         wg_pick = pick_tn_group(wg);
         wg.n = 0;
     }
+    // One weight gradient over a stream of its own between those of the layer, while du and d_o are free
+    ds_status wgrad_alone(const Stream& sm, int K, int N, const void* X, const void* dY, void* dW) {
+        const TnGroup layer = wg;
+        const TnPick layer_pick = wg_pick;
+        wgrads_begin(sm, {{K, N}});
+        DS_TRY(wgrad(sm, K, N, X, dY, dW));
+        DS_TRY(wgrads_end());
+        wg = layer;
+        wg_pick = layer_pick;
+        return DS_OK;
+    }
     ds_status wgrad(const Stream& sm, int K, int N, const void* X, const void* dY, void* dW) {
         const TnProblem q{X, dY, dW, K, N};
         if (wg_pick.kind < 0 || wg.n == kTnGroup || !tn_group_takes(q, sm.R, wg.f32)) return wgrad_now(sm.R, K, N, X, dY, dW);
@@ -835,7 +846,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
             DS_TRY(op.zero_pad(E, s->dkvc, 2 * d));
         }
         DS_TRY(op.wgrad(D, d, d, b.uc, s->dqc, gd[l].w_cq));
-        DS_TRY(op.wgrad_now(E.R, d, 2 * d, enc_out, s->dkvc, gd[l].w_ckv));
+        DS_TRY(op.wgrad_alone(E, d, 2 * d, enc_out, s->dkvc, gd[l].w_ckv));      // (d_o: read by the attention backward pass above)
         if (!de_set) {
             DS_TRY(op.dgrad(E, d, 2 * d, s->dkvc, wd[l].w_ckv, de_cur, DS_EPI_NONE, nullptr, nullptr, nullptr));
             de_set = true;
