@@ -12,9 +12,8 @@
 // The bound is the fp32 matrix rate: per 16 x 16 block HD/4 MFMAs of 32 cycles for each product (two forward, three in
 // dQ, four in dK/dV) against 4 exponentials per lane.  Tiles go global -> registers -> LDS, the next tile's reads in
 // flight during the current tile's products; 4 wavefronts per work-group (64 columns), 19 - 54 KB of LDS, so several
-// work-groups per CU cover each other's two barriers per tile.  Sequences are taken last to first: a plan lists them by
-// ascending length, and the long ones should start first.  Measured at
-// 7 684 tokens in 64 sequences (up to 512), 4 heads of 64, causal: forward 40 us, dQ 44, dK/dV 87, against 508, 435 and
+// work-groups per CU cover each other's two barriers per tile.  Which work-group does what: see `column_block`.  Measured at
+// 7 684 tokens in 64 sequences (up to 512), 4 heads of 64, causal: forward 40 us, dQ with delta 51, dK/dV 56, against 508, 435 and
 // 581 for one wavefront per query / key row with shuffled probabilities (attention_generic.hip, which keeps the operands
 // that float4 cannot read): those read every row of the other side once per row of this one.
 #include "attention_rows.hpp"
@@ -109,6 +108,25 @@ __device__ __forceinline__ void store_column(const f32x4_t (&acc)[HD / 16], floa
 __device__ __forceinline__ float groups_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
 __device__ __forceinline__ float groups_sum(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
 
+// A work-group's 64 columns.  The kernel lasts as long as the compute unit with the longest chains of tiles, so those start
+// first: sequences are taken last to first (a plan lists them by ascending length), and of every sequence the block with the
+// most tiles goes first, in the causal forward and dQ kernels the last one, in dK/dV the first.  Blocks are the fastest grid
+// dimension, and an odd number of them: work-groups go to the eight XCDs in turn, and with 8 blocks (512 tokens) every
+// longest chain of dK/dV was on the same one.  Forward and backward, us: 4 heads of 64, 7 684 tokens in sequences of up to 512 in any
+// order, 75 and 204 with 8 blocks, 48 and 130 with 9; head size 128, 129 and 397, 84 and 234; unmasked 75 and 213, 57 and 158; 8 heads,
+// 8 000 tokens, up to 2048 (32 and 33 blocks) 214 and 660, 213 and 662.  First blocks of all sequences before their second ones
+// (rows of heads x sequences, an odd multiple of 8 plus 1) is better there, 178 and 497, but not in a stage, whose sequences come
+// by length: two layers of d = 256, 64 sequences, 1 267 us, 1 227 in such rows, 1 125 as it is; 200 sequences 3 581, 2 965, 2 848.
+struct ColumnBlock { int s, h, first; };                              // first < 0: nothing to do
+
+__device__ __forceinline__ ColumnBlock column_block(const AttnArgs& a, const int32_t* __restrict__ len, bool last_first) {
+    ColumnBlock c = {a.n_seq - 1 - (int)blockIdx.z, (int)blockIdx.y, -1};
+    const int n = (len[c.s] + 63) / 64, b = blockIdx.x;
+    if (b < n) c.first = 64 * (last_first ? n - 1 - b : b);
+    return c;
+}
+dim3 column_grid(const AttnArgs& a, int max_len) { return dim3((max_len + 63) / 64 | 1, a.n_heads, a.n_seq); }
+
 // Causal masks and values that are not finite.  A score that a column does not see is replaced whatever it is; but the second
 // product contracts over whole blocks, with weight 0 for the rows a column does not see, and 0 x Inf would reach it.  So a
 // work-group looks at the operand of its second product as it stores the tiles on its diagonal (the positions of its own
@@ -125,9 +143,10 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
     __shared__ float s_row[4][HD];
     __shared__ int s_by_rows;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), g = lane >> 4;
-    const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 64;
+    const ColumnBlock cb = column_block(a, a.q_len, a.mask);
+    if (cb.first < 0) return;
+    const int s = cb.s, h = cb.h, q0 = cb.first;
     const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
-    if (q0 >= ql) return;
     const long long qrow0 = a.q_row[s], krow0 = a.k_row[s];
     const float* K = (const float*)a.k + krow0 * a.ldk + h * hd;
     const float* V = (const float*)a.v + krow0 * a.ldv + h * hd;
@@ -217,9 +236,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
     __shared__ float s_row[4][2][HD];
     __shared__ int s_by_rows;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), g = lane >> 4;
-    const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 64;
+    const ColumnBlock cb = column_block(a, a.q_len, a.mask);
+    if (cb.first < 0) return;
+    const int s = cb.s, h = cb.h, q0 = cb.first;
     const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
-    if (q0 >= ql) return;
     const long long qrow0 = a.q_row[s], krow0 = a.k_row[s];
     const float* K = (const float*)a.k + krow0 * a.ldk + h * hd;
     const float* V = (const float*)a.v + krow0 * a.ldv + h * hd;
@@ -295,7 +315,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
 // Eight wavefronts: the first key blocks of a long causal sequence meet every query, and their work-groups set the
 // kernel's length.  Wavefronts w and w + 4 own the same 16 keys and take alternate 16-query blocks of every tile; their
 // accumulators are added through LDS at the end.  116 us with four wavefronts, 107 with eight, 86 with at most 128
-// registers (head size up to 64: two work-groups per CU).  At head size 64 that limit spills 2 registers here; the other
+// registers (head size up to 64: two work-groups per CU), all three with eight blocks to a grid row.  At head size 64 that limit spills 2 registers here; the other
 // two kernels need 10 to 25 more than 128 there and lose with it (dQ 53 us instead of 42).
 template <int HD>
 __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel(AttnArgs a) {
@@ -310,9 +330,10 @@ __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel
     __shared__ int s_by_rows;
     const int t = threadIdx.x, lane = t & 63, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6) & 3, half = __builtin_amdgcn_readfirstlane(t >> 8);
-    const int s = a.n_seq - 1 - blockIdx.z, h = blockIdx.y, k0 = blockIdx.x * 64;
+    const ColumnBlock cb = column_block(a, a.k_len, false);
+    if (cb.first < 0) return;
+    const int s = cb.s, h = cb.h, k0 = cb.first;
     const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
-    if (k0 >= kl) return;
     const long long qrow0 = a.q_row[s], krow0 = a.k_row[s];
     const float* Q = (const float*)a.q + qrow0 * a.ldq + h * hd;
     const float* dO = (const float*)a.d_o + qrow0 * a.ldo + h * hd;
@@ -401,9 +422,9 @@ __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel
 
 template <int HD>
 ds_status bwd_f32(const AttnArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<HD>, dim3((a.max_q_len + 63) / 64, a.n_heads, a.n_seq), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<HD>, column_grid(a, a.max_q_len), dim3(256), 0, st, a);
     DS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(attn_bwd_dkv_f32_kernel<HD>, dim3((a.max_k_len + 63) / 64, a.n_heads, a.n_seq), dim3(512), 0, st, a);
+    hipLaunchKernelGGL(attn_bwd_dkv_f32_kernel<HD>, column_grid(a, a.max_k_len), dim3(512), 0, st, a);
     DS_LAUNCH_CHECK();
     return DS_OK;
 }
@@ -420,7 +441,7 @@ bool attn_f32_mfma_supported(const AttnArgs& a) {
 }
 
 ds_status attn_fwd_f32_mfma(const AttnArgs& a, hipStream_t st) {
-    const dim3 grid((a.max_q_len + 63) / 64, a.n_heads, a.n_seq);
+    const dim3 grid = column_grid(a, a.max_q_len);
     if (a.head_dim <= 32) hipLaunchKernelGGL(attn_fwd_f32_kernel<32>, grid, dim3(256), 0, st, a);
     else if (a.head_dim <= 64) hipLaunchKernelGGL(attn_fwd_f32_kernel<64>, grid, dim3(256), 0, st, a);
     else if (a.head_dim <= 96) hipLaunchKernelGGL(attn_fwd_f32_kernel<96>, grid, dim3(256), 0, st, a);

@@ -612,6 +612,35 @@ def test_attention_f32_matrix_cores(hd, causal):
     assert np.all(o_np[~touched] == 0) and np.all(g_np[~touched] == 0)
 
 
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_f32_odd_and_even_numbers_of_blocks(causal):
+    """The grid has an odd number of 64-column blocks, whatever the longest sequence needs or the caller names: the same results."""
+    rng = np.random.default_rng(34)
+    h, hd, lens = 2, 64, [130, 0, 64, 1]
+    d, T, rows, qkv, d_o = _varlen_case(rng, lens, h, hd, F32)
+    dq, ddo = to_dev(qkv, F32), to_dev(d_o, F32)
+    t_rows, t_lens = torch.from_numpy(rows).to(DEV), torch.tensor(lens, dtype=torch.int32, device=DEV)
+    b, table, got = dq.data_ptr(), (t_rows, t_lens, t_rows, t_lens), []
+    for max_len in (130, 193, 600):
+        o, lse, delta = torch.zeros((T, d), device=DEV), torch.zeros((h, T), device=DEV), torch.zeros((h, T), device=DEV)
+        dqkv = torch.zeros((T, 3 * d), device=DEV)
+        gb = dqkv.data_ptr()
+        ds.ds_attention_fwd(b, b + 4 * d, b + 8 * d, o, lse, *table, h, hd, causal, max_len, max_len, 3 * d, 3 * d, 3 * d, d, T)
+        ds.ds_attention_bwd(b, b + 4 * d, b + 8 * d, o, ddo, lse, delta, gb, gb + 4 * d, gb + 8 * d, *table, h, hd, causal,
+                            max_len, max_len, 3 * d, 3 * d, 3 * d, d, T)
+        torch.cuda.synchronize()
+        got.append([to_np(x) for x in (o, lse, dqkv)])
+    for x, y, z in zip(*got):
+        assert np.array_equal(x, y) and np.array_equal(x, z)
+    for r0, l in zip(rows, lens):
+        x = qkv[r0:r0 + l].astype(np.float64)
+        if l:
+            ref_o, cache = ost.attention_fwd(x[:, :d], x[:, d:2 * d], x[:, 2 * d:], h, causal)
+            assert both_err(got[0][0][r0:r0 + l], ref_o) <= TOL[F32], l
+            for i, ref in enumerate(ost.attention_bwd(d_o[r0:r0 + l].astype(np.float64), cache)):
+                assert both_err(got[0][2][r0:r0 + l, i * d:(i + 1) * d], ref) <= TOL[F32], (l, i)
+
+
 @pytest.mark.parametrize("dt", [F32, BF])
 @pytest.mark.parametrize("rows,n", [(1, 8), (31, 264), (33, 2048), (128, 520), (4097, 256), (9000, 4104)])
 def test_column_reductions_at_their_edges(dt, rows, n):
