@@ -118,6 +118,11 @@ struct ds_stage {
 
 namespace {
 
+// whether a_bytes from a on and b_bytes from b on share memory
+bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
 #define DS_TRY(expr)                    \
     do {                                \
         ds_status st__ = (expr);        \
@@ -480,6 +485,11 @@ struct Ops {
             return ds_norm_bwd(dt, rms, sm.R, d, dy, x, g, stats, resid, dx, (float*)dg, (float*)db, s->partial, accumulate, st);
         });
     }
+    // whether two tensors of a stream's rows share memory
+    bool shares_rows(const Stream& sm, const void* a, const void* b) const {
+        const size_t bytes = (size_t)sm.R * d * s->es;
+        return overlap(a, bytes, b, bytes);
+    }
     // What the caller hands in, padding rows zeroed: copies where the stream has padding, all of them in one launch in front
     MaskBatch masked;
     const void* mask_later(const Stream& sm, const void* in, void* out) {
@@ -656,9 +666,11 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
         if (recompute && l != L - 1) DS_TRY(layer_fwd(l, xl_in, nullptr));
         op.wgrads_begin(sm, {{F, d}, {d, F}, {d, d}, {d, 3 * d}});
         op.sums_begin(sm, 2, 5 * (size_t)d + (s->colsum_rows ? 0 : F));
+        // a caller that gets the gradient back in place (one layer, no padding): what is read of dy is read before dx_in is written
+        const bool in_place = op.shares_rows(sm, dx_in, dy);
         // MLP
-        DS_TRY(op.colsum_side(sm, d, dy, g[l].b_2));        // (each column sum right behind its producer, beside the next GEMM)
-        DS_TRY(op.wgrad(sm, F, d, b.a, dy, g[l].w_2));
+        DS_TRY(in_place ? op.colsum(sm, d, dy, g[l].b_2) : op.colsum_side(sm, d, dy, g[l].b_2));   // (each column sum right behind its producer, beside the next GEMM)
+        DS_TRY(in_place ? op.wgrad_now(sm.R, F, d, b.a, dy, g[l].w_2) : op.wgrad(sm, F, d, b.a, dy, g[l].w_2));
         DS_TRY(op.dgrad_gelu_bias(sm, F, d, dy, w[l].w_2, s->dz, b.z, g[l].b_1));
         DS_TRY(op.wgrad(sm, d, F, b.u2, s->dz, g[l].w_1));
         DS_TRY(op.dgrad(sm, d, F, s->dz, w[l].w_1, s->du, DS_EPI_NONE, nullptr, nullptr, nullptr));
@@ -704,11 +716,12 @@ ds_status t5_mlp_fwd(Ops& op, const Stream& sm, const void* xin, void* out, T5Bu
     return op.fwd(sm, d, F, b.a, w_2, b.w2_t, out, DS_EPI_RESID, nullptr, xin, nullptr, true);
 }
 // MLP backward: dy = gradient of the MLP output; writes dy + RMS2-backward(...) (the gradient of xin) into dxin
-ds_status t5_mlp_bwd(Ops& op, const Stream& sm, const void* dy, const void* xin, void* dxin, T5Bufs& b, const void* ln2_g,
+// (dy_kept = false: dy is overwritten before the layer's weight gradients are launched)
+ds_status t5_mlp_bwd(Ops& op, const Stream& sm, const void* dy, bool dy_kept, const void* xin, void* dxin, T5Bufs& b, const void* ln2_g,
                      const void* w_g, const void* w_u, const void* w_2, void* g_ln2, void* g_wg, void* g_wu, void* g_w2) {
     ds_stage* s = op.s;
     const int d = op.d, F = op.F;
-    DS_TRY(op.wgrad(sm, F, d, b.a, dy, g_w2));
+    DS_TRY(dy_kept ? op.wgrad(sm, F, d, b.a, dy, g_w2) : op.wgrad_now(sm.R, F, d, b.a, dy, g_w2));
     DS_TRY(op.dgrad(sm, F, d, dy, w_2, s->dz, DS_EPI_DGATE, b.zg, b.zu, s->dz2));      // dz = d zg, dz2 = d zu
     DS_TRY(op.wgrad(sm, d, F, b.u2, s->dz, g_wg));
     DS_TRY(op.wgrad(sm, d, F, b.u2, s->dz2, g_wu));
@@ -828,7 +841,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         op.wgrads_begin(D, {{F, d}, {d, F}, {d, F}, {d, d}, {d, d}, {d, d}, {d, 3 * d}});
         op.sums_begin(D, 3, 0);
         // MLP: gradient of x2 into dx2
-        DS_TRY(t5_mlp_bwd(op, D, dy, b.x2, s->dx2, b, wd[l].ln2_g, wd[l].w_g, wd[l].w_u, wd[l].w_2, gd[l].ln2_g, gd[l].w_g,
+        DS_TRY(t5_mlp_bwd(op, D, dy, !op.shares_rows(D, dy_in, dy), b.x2, s->dx2, b, wd[l].ln2_g, wd[l].w_g, wd[l].w_u, wd[l].w_2, gd[l].ln2_g, gd[l].w_g,
                           gd[l].w_u, gd[l].w_2));
         // cross-attention: gradient of x1 into dx1, of the encoder output into de
         DS_TRY(op.wgrad(D, d, d, b.oc, s->dx2, gd[l].w_co));
@@ -875,7 +888,7 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         if (recompute && l != Le - 1) DS_TRY(enc_layer_fwd(l, xl_in, false));
         op.sums_begin(E, 2, 0);
         op.wgrads_begin(E, {{F, d}, {d, F}, {d, F}, {d, d}, {d, 3 * d}});
-        DS_TRY(t5_mlp_bwd(op, E, dx, b.x1, s->dx1, b, we[l].ln2_g, we[l].w_g, we[l].w_u, we[l].w_2, ge[l].ln2_g, ge[l].w_g,
+        DS_TRY(t5_mlp_bwd(op, E, dx, true, b.x1, s->dx1, b, we[l].ln2_g, we[l].w_g, we[l].w_u, we[l].w_2, ge[l].ln2_g, ge[l].w_g,
                           ge[l].w_u, ge[l].w_2));
         DS_TRY(t5_self_bwd(op, E, 0, s->dx1, xl_in, dx_in, b, we[l].ln1_g, we[l].w_qkv, we[l].w_o, ge[l].ln1_g, ge[l].w_qkv,
                            ge[l].w_o));

@@ -322,3 +322,29 @@ def test_launch_count_of_a_first_and_a_later_call(dtype_code):
             n.append(stage.last_launch_count())
         stage.close()
         assert n[1] == n[2] and n[0] - n[1] == first_more + (dtype_code == ds.DS_DTYPE_BF16), (cuts, n)
+
+
+# one layer without padding rows: the gradient that the layer hands down overwrites the one it was given.  Rows up to and beyond
+# what one work-group walks, and beyond what is summed in one launch.
+@pytest.mark.parametrize("dtype_code,d,rows", [(ds.DS_DTYPE_F32, 256, 300), (ds.DS_DTYPE_BF16, 256, 300), (ds.DS_DTYPE_BF16, 256, 900),
+                                               (ds.DS_DTYPE_BF16, 1024, 9500)])
+def test_gradient_returned_in_place(dtype_code, d, rows):
+    """grad_in is grad_out: every gradient is the oracle's."""
+    from helpers import params_to_dev, seqs_from_stream, stream_from_seqs, tdtype, to_np, zero_grads_like
+    bf16, tol, F, h = dtype_code == ds.DS_DTYPE_BF16, TOL[dtype_code], 2 * d, d // 64
+    lens = np.asarray([rows - rows // 3 - 1, rows // 3, 1] if rows < 1000 else [250] * (rows // 250))
+    params = wl.draw_params(wl.GPT_KEYS, 1, d, F, seed=8, bf16=bf16)
+    xs, dys = wl.draw_rows(lens, d, seed=8, tag=3, bf16=bf16), wl.draw_rows(lens, d, seed=8, tag=5, bf16=bf16)
+    lo = ds.ds_layout_from_cuts(lens, list(range(len(lens) + 1)))
+    assert lo.total_rows == lo.total_tokens
+    _, r_dx, r_g = ost.gpt_stage_fwd_bwd(xs, dys, params, h)
+    w = params_to_dev(params, tdtype(dtype_code))
+    g = zero_grads_like(w)
+    x, grad = (stream_from_seqs(v, lo, d, tdtype(dtype_code)) for v in (xs, dys))
+    stage = ds.Stage(ds.DS_MODEL_GPT, dtype_code, 1, d, h, F, max_rows=lo.total_rows, max_seqs=lo.n_seq)
+    ds.stage_fwd_bwd(stage, lo, w, x, grad, torch.empty_like(x), grad, g)
+    torch.cuda.synchronize()
+    check_seqs(seqs_from_stream(grad, lo)[0], r_dx, tol, "grad_in")
+    for k, v in r_g[0].items():
+        check(to_np(g[0][k]), v, tol, k)
+    stage.close()

@@ -4,11 +4,12 @@ with a per-micro-batch overhead (padding in both streams, NaN planted in it) and
 micro-batches.  fp32 runs the generic kernels, bf16 the matrix-core kernels."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import stage as ost
 from paper_2311_10418_amd import binding as ds
 from paper_2311_10418_amd import workload as wl
-from helpers import check, check_seqs, run_t5_stage
+from helpers import check, check_seqs, params_to_dev, run_t5_stage, seqs_from_stream, stream_from_seqs, tdtype, to_np, zero_grads_like
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +51,27 @@ def test_t5_stage_matches_oracle(dtype_code):
         print(name, "worst", worst, "%.3e" % errs[worst])
         for p in got["pads"]:
             assert p.size == 0 or np.all(p == 0), name
+
+
+@pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
+def test_decoder_gradient_returned_in_place(dtype_code):
+    """One decoder layer without padding rows, grad_in_tgt is grad_out: every decoder gradient is the oracle's."""
+    bf16, tol = dtype_code == ds.DS_DTYPE_BF16, 2e-2 if dtype_code == ds.DS_DTYPE_BF16 else 1e-4
+    lens, tgts, ep, dp, ex, dx, ddy = _case(bf16)
+    ep, dp, d = ep[:1], dp[:1], CFG["d_model"]
+    _, _, r_dy, _, r_dg = ost.t5_stage_fwd_bwd(ex, dx, ddy, ep, dp, CFG["n_heads"])
+    lo = ds.ds_layout_from_cuts(lens, list(range(len(lens) + 1)), lengths_tgt=tgts)
+    assert lo.total_rows_tgt == int(tgts.sum())
+    dt = tdtype(dtype_code)
+    we, wd = params_to_dev(ep, dt), params_to_dev(dp, dt)
+    ge, gd = zero_grads_like(we), zero_grads_like(wd)
+    x, y, grad = stream_from_seqs(ex, lo, d, dt), stream_from_seqs(dx, lo, d, dt, which=1), stream_from_seqs(ddy, lo, d, dt, which=1)
+    stage = ds.Stage(ds.DS_MODEL_T5, dtype_code, 1, d, CFG["n_heads"], CFG["d_ff"], max_rows=lo.total_rows, max_seqs=lo.n_seq,
+                     n_dec_layers=1, max_rows_tgt=lo.total_rows_tgt)
+    ds.stage_fwd_bwd(stage, lo, we, x, grad, torch.empty_like(y), torch.empty_like(x), ge, weights_dec=wd, grads_dec=gd, act_in_tgt=y,
+                     grad_in_tgt=grad)
+    torch.cuda.synchronize()
+    check_seqs(seqs_from_stream(grad, lo, which=1)[0], r_dy, tol, "grad_in_tgt")
+    for k, v in r_dg[0].items():
+        check(to_np(gd[0][k]), v, tol, k)
+    stage.close()
