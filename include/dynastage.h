@@ -360,7 +360,8 @@ typedef struct {
 /* Activations and gradients of one call, DEVICE pointers, element type = stage dtype, in
  * stream layout ([total_rows, d_model] row-major).  Values at padding rows of the inputs are
  * ignored (they may be NaN); padding rows of the outputs are written as zeros.
- * The gradient may be returned in place: grad_in (GPT) and grad_in_tgt (T5) may share memory with grad_out. */
+ * The gradient may be returned in place: grad_in (GPT) and grad_in_tgt (T5) may share memory with grad_out.
+ * grad_out may be act_out itself: the backward pass then starts from the outputs of this call. */
 typedef struct {
     const void* act_in;       /* GPT: stage input.  T5: encoder-side input                   */
     const void* act_in_tgt;   /* T5: decoder-side input [total_rows_tgt, d]; NULL for GPT     */

@@ -490,7 +490,7 @@ struct Ops {
         const size_t bytes = (size_t)sm.R * d * s->es;
         return overlap(a, bytes, b, bytes);
     }
-    // What the caller hands in, padding rows zeroed: copies where the stream has padding, all of them in one launch in front
+    // What the caller hands in, padding rows zeroed: copies where the stream has padding, in one launch in front
     MaskBatch masked;
     const void* mask_later(const Stream& sm, const void* in, void* out) {
         if (!sm.has_pad) return in;
@@ -503,7 +503,9 @@ struct Ops {
     ds_status mask_rows() {
         if (masked.n == 0) return DS_OK;
         s->launches++;
-        return timed(s, DS_PROF_OTHER, st, [&] { return launch_mask_rows(dt, masked, d, st); });
+        const ds_status r = timed(s, DS_PROF_OTHER, st, [&] { return launch_mask_rows(dt, masked, d, st); });
+        masked.n = 0;
+        return r;
     }
     ds_status zero_pad(const Stream& sm, void* buf, int cols) {
         if (!sm.has_pad) return DS_OK;
@@ -632,8 +634,9 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
     DS_TRY(op.zero_pads_of_layout(sm));
 
     // ---------------- forward (ForwardPass of every micro-batch)
+    const bool grad_is_out = op.shares_rows(sm, io->grad_out, io->act_out);      // then it has its values after the forward pass
     const void* x_in = op.mask_later(sm, io->act_in, s->x0);
-    const void* dy = op.mask_later(sm, io->grad_out, s->dyA);
+    const void* dy = grad_is_out ? io->grad_out : op.mask_later(sm, io->grad_out, s->dyA);
     DS_TRY(op.mask_rows());
     const void* x0 = x_in;
     // forward of layer l from its input; x_out = NULL: only what the layer's backward reads (recomputation)
@@ -654,6 +657,10 @@ ds_status gpt_fwd_bwd(ds_stage* s, const ds_gpt_layer* w, const ds_stage_io* io,
         x_in = x_out;
     }
     const bool recompute = s->cfg.recompute == DS_RECOMPUTE_FULL;
+    if (grad_is_out) {
+        dy = op.mask_later(sm, io->grad_out, s->dyA);
+        DS_TRY(op.mask_rows());
+    }
 
     // ---------------- backward (BackwardPass of every micro-batch; weight gradients summed over all of them)
     void* pp[2] = {s->dyB, s->dyA};
@@ -780,9 +787,10 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
     }
 
     // ---------------- forward: encoder layers over the input stream
+    const bool grad_is_out = op.shares_rows(D, io->grad_out, io->act_out);       // then it has its values after the forward pass
     const void* x_in = op.mask_later(E, io->act_in, s->x0);
     const void* y_in = op.mask_later(D, io->act_in_tgt, s->y0);
-    const void* dy = op.mask_later(D, io->grad_out, s->dyA);
+    const void* dy = grad_is_out ? io->grad_out : op.mask_later(D, io->grad_out, s->dyA);
     DS_TRY(op.mask_rows());
     const void* x0 = x_in;
     const bool recompute = s->cfg.recompute == DS_RECOMPUTE_FULL;
@@ -825,6 +833,11 @@ ds_status t5_fwd_bwd(ds_stage* s, const ds_t5_enc_layer* we, const ds_t5_dec_lay
         void* y_out = (l == Ld - 1) ? io->act_out : s->dec[l].xout;
         DS_TRY(dec_layer_fwd(l, y_in, y_out));
         y_in = y_out;
+    }
+
+    if (grad_is_out) {
+        dy = op.mask_later(D, io->grad_out, s->dyA);
+        DS_TRY(op.mask_rows());
     }
 
     // ---------------- backward: decoder layers (last to first); de accumulates the gradient of the encoder output

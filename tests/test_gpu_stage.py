@@ -348,3 +348,31 @@ def test_gradient_returned_in_place(dtype_code, d, rows):
     for k, v in r_g[0].items():
         check(to_np(g[0][k]), v, tol, k)
     stage.close()
+
+
+@pytest.mark.parametrize("cuts", [[0, 4, 9], list(range(10))])              # with and without padding rows
+@pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
+def test_outputs_as_their_own_gradient(dtype_code, cuts):
+    """grad_out is act_out (the gradient of half the sum of squares): the backward pass starts from this call's outputs."""
+    from helpers import params_to_dev, seqs_from_stream, stream_from_seqs, tdtype, to_np, zero_grads_like
+    bf16, tol, d, F, h = dtype_code == ds.DS_DTYPE_BF16, TOL[dtype_code], 256, 512, 4
+    lens = np.asarray([30, 7, 64, 1, 100, 33, 65, 12, 90])
+    params = wl.draw_params(wl.GPT_KEYS, 2, d, F, seed=9, bf16=bf16)
+    xs = wl.draw_rows(lens, d, seed=9, tag=3, bf16=bf16)
+    lo = ds.ds_layout_from_cuts(lens, cuts)
+    outs = ost.gpt_stage_fwd_bwd(xs, xs, params, h)[0]
+    _, r_dx, r_g = ost.gpt_stage_fwd_bwd(xs, [wl.to_bf16_grid(o) if bf16 else o for o in outs], params, h)
+    dt = tdtype(dtype_code)
+    w = params_to_dev(params, dt)
+    g = zero_grads_like(w)
+    x = stream_from_seqs(xs, lo, d, dt)
+    y, dx = torch.full_like(x, float("nan")), torch.empty_like(x)
+    stage = ds.Stage(ds.DS_MODEL_GPT, dtype_code, 2, d, h, F, max_rows=lo.total_rows, max_seqs=lo.n_seq)
+    ds.stage_fwd_bwd(stage, lo, w, x, y, y, dx, g)
+    torch.cuda.synchronize()
+    check_seqs(seqs_from_stream(y, lo)[0], outs, tol, "act_out")
+    check_seqs(seqs_from_stream(dx, lo)[0], r_dx, tol, "grad_in")
+    for layer, ref in zip(g, r_g):
+        for k, v in ref.items():
+            check(to_np(layer[k]), v, tol, k)
+    stage.close()

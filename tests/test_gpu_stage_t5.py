@@ -75,3 +75,29 @@ def test_decoder_gradient_returned_in_place(dtype_code):
     for k, v in r_dg[0].items():
         check(to_np(gd[0][k]), v, tol, k)
     stage.close()
+
+
+@pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
+def test_decoder_outputs_as_their_own_gradient(dtype_code):
+    """grad_out is act_out, with padding rows: the backward pass starts from this call's outputs."""
+    bf16, tol = dtype_code == ds.DS_DTYPE_BF16, 2e-2 if dtype_code == ds.DS_DTYPE_BF16 else 1e-4
+    lens, tgts, ep, dp, ex, dx, ddy = _case(bf16)
+    d, dt = CFG["d_model"], tdtype(dtype_code)
+    outs = ost.t5_stage_fwd_bwd(ex, dx, ddy, ep, dp, CFG["n_heads"])[0]
+    _, _, r_dy, _, r_dg = ost.t5_stage_fwd_bwd(ex, dx, [wl.to_bf16_grid(o) if bf16 else o for o in outs], ep, dp, CFG["n_heads"])
+    lo = ds.dp_plan(lens, ds.make_cost_model(kind=ds.DS_COST_POLY_T5, fixed=1_500_000), 2048, 4, lengths_tgt=tgts)
+    assert lo.total_rows_tgt > int(tgts.sum())
+    we, wd = params_to_dev(ep, dt), params_to_dev(dp, dt)
+    ge, gd = zero_grads_like(we), zero_grads_like(wd)
+    x, y = stream_from_seqs(ex, lo, d, dt), stream_from_seqs(dx, lo, d, dt, which=1)
+    out, dy = torch.full_like(y, float("nan")), torch.empty_like(y)
+    stage = ds.Stage(ds.DS_MODEL_T5, dtype_code, CFG["n_layers"], d, CFG["n_heads"], CFG["d_ff"], max_rows=lo.total_rows,
+                     max_seqs=lo.n_seq, n_dec_layers=CFG["n_dec_layers"], max_rows_tgt=lo.total_rows_tgt)
+    ds.stage_fwd_bwd(stage, lo, we, x, out, out, torch.empty_like(x), ge, weights_dec=wd, grads_dec=gd, act_in_tgt=y, grad_in_tgt=dy)
+    torch.cuda.synchronize()
+    check_seqs(seqs_from_stream(out, lo, which=1)[0], outs, tol, "act_out")
+    check_seqs(seqs_from_stream(dy, lo, which=1)[0], r_dy, tol, "grad_in_tgt")
+    for layer, ref in zip(gd, r_dg):
+        for k, v in ref.items():
+            check(to_np(layer[k]), v, tol, k)
+    stage.close()
