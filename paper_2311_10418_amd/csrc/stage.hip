@@ -324,20 +324,14 @@ struct Ops {
         if (s->colsum_rows && gemm_colsum_fused(dt, 0, 1, sm.R, K, N, dY, W, dZ, DS_EPI_MULR)) {
             DS_TRY(gemm_raw(DS_PROF_GEMM_DGRAD, 0, 1, sm.R, K, N, dY, W, dZ, DS_EPI_MULR, nullptr, G, nullptr, nullptr, nullptr, 0,
                             s->colsum_rows));
-            if (sums_together) {
-                sums.it[sums.n++] = SumItem{s->colsum_rows, (float*)bias_grad, (int32_t)gemm_colsum_rows(sm.R), K, K, 0};
-                return DS_OK;
-            }
+            if (sums_together) return sum_later(SumItem{s->colsum_rows, (float*)bias_grad, (int32_t)gemm_colsum_rows(sm.R), K, K, 0});
             s->launches++;
             return timed(s, DS_PROF_COLSUM, st, [&] {
                 return launch_reduce_partials((int32_t)gemm_colsum_rows(sm.R), K, s->colsum_rows, (float*)bias_grad, accumulate, st);
             });
         }
         DS_TRY(dgrad(sm, K, N, dY, W, dZ, DS_EPI_MULR, G, nullptr, nullptr));
-        if (sums_together) {
-            sums.it[sums.n++] = SumItem{dZ, (float*)bias_grad, sm.R, K, K, 1};
-            return DS_OK;
-        }
+        if (sums_together) return sum_later(SumItem{dZ, (float*)bias_grad, sm.R, K, K, 1});
         return colsum(sm, K, dZ, bias_grad);
     }
     // dW[K,N] (+)= X[rows,K]^T dY[rows,N]
@@ -374,6 +368,7 @@ struct Ops {
     }
     // One weight gradient over a stream of its own between those of the layer, while du and d_o are free
     ds_status wgrad_alone(const Stream& sm, int K, int N, const void* X, const void* dY, void* dW) {
+        DS_TRY(wgrads_before(K, N, dW));
         const TnGroup layer = wg;
         const TnPick layer_pick = wg_pick;
         wgrads_begin(sm, {{K, N}});
@@ -383,7 +378,18 @@ struct Ops {
         wg_pick = layer_pick;
         return DS_OK;
     }
+    // A gradient in the same memory as one that is collected already (parameters that share theirs): those go out first, one by one,
+    // since the room for a group's partial sums is free at the end of a layer only.
+    ds_status wgrads_before(int K, int N, const void* dW) {
+        bool shared = false;
+        for (int i = 0; i < wg.n; ++i) shared |= overlap(dW, (size_t)K * N * 4, wg.p[i].C, (size_t)wg.p[i].M * wg.p[i].N * 4);
+        if (!shared) return DS_OK;
+        for (int i = 0; i < wg.n; ++i) DS_TRY(wgrad_now(wg.K, wg.p[i].M, wg.p[i].N, wg.p[i].A, wg.p[i].B, wg.p[i].C));
+        wg.n = 0;
+        return DS_OK;
+    }
     ds_status wgrad(const Stream& sm, int K, int N, const void* X, const void* dY, void* dW) {
+        DS_TRY(wgrads_before(K, N, dW));
         const TnProblem q{X, dY, dW, K, N};
         if (wg_pick.kind < 0 || wg.n == kTnGroup || !tn_group_takes(q, sm.R, wg.f32)) return wgrad_now(sm.R, K, N, X, dY, dW);
         wg.p[wg.n++] = q;
@@ -431,8 +437,21 @@ struct Ops {
         sums_together = (size_t)norm_rows * norms * 2 * d <= (size_t)ds_norm_bwd_scratch_floats(1, d) &&
                         (size_t)sm.R * tensor_cols * s->es <= kSumsTogetherBytes;
     }
+    // (two sums into the same memory, of parameters that share a gradient: one launch after the other, in this order)
+    ds_status sum_later(const SumItem& q) {
+        for (int i = 0; i < sums.n; ++i)
+            if (overlap(q.out, (size_t)q.n * 4, sums.it[i].out, (size_t)sums.it[i].n * 4)) {
+                DS_TRY(sums_launch());
+                break;
+            }
+        sums.it[sums.n++] = q;
+        return DS_OK;
+    }
     ds_status sums_end() {
         sums_together = false;
+        return sums_launch();
+    }
+    ds_status sums_launch() {
         if (sums.n == 0) return DS_OK;
         int launched = 0;
         const ds_status r = timed(s, DS_PROF_COLSUM, st, [&] { return launch_sum_group(dt, sums, s->partial_side, kPartialSideFloats, st, &launched); });
@@ -447,10 +466,7 @@ struct Ops {
     // The same on the side stream: starts once everything enqueued so far on the main stream is done, runs beside
     // what is enqueued after it.  x must stay as it is, and out untouched, until join_side().
     ds_status colsum_side(const Stream& sm, int n, const void* x, void* out) {
-        if (sums_together) {
-            sums.it[sums.n++] = SumItem{x, (float*)out, sm.R, n, n, 1};
-            return DS_OK;
-        }
+        if (sums_together) return sum_later(SumItem{x, (float*)out, sm.R, n, n, 1});
         if (!s->side) return colsum(sm, n, x, out);
         s->launches += 2;
         DS_HIP_CHECK(hipEventRecord(s->ev_fork, st));
@@ -475,10 +491,10 @@ struct Ops {
                        const void* resid, void* dx, void* dg, void* db) {
         if (sums_together) {
             float* part = s->partial + (size_t)norms_taken++ * norm_rows * 2 * d;
-            sums.it[sums.n++] = SumItem{part, (float*)dg, norm_rows, d, 2 * d, 0};
-            if (db) sums.it[sums.n++] = SumItem{part + d, (float*)db, norm_rows, d, 2 * d, 0};
             s->launches++;
-            return timed(s, DS_PROF_NORM, st, [&] { return launch_norm_bwd_partials(dt, rms, sm.R, d, dy, x, g, stats, resid, dx, part, st); });
+            DS_TRY(timed(s, DS_PROF_NORM, st, [&] { return launch_norm_bwd_partials(dt, rms, sm.R, d, dy, x, g, stats, resid, dx, part, st); }));
+            DS_TRY(sum_later(SumItem{part, (float*)dg, norm_rows, d, 2 * d, 0}));
+            return db ? sum_later(SumItem{part + d, (float*)db, norm_rows, d, 2 * d, 0}) : DS_OK;
         }
         s->launches += 2;
         return timed(s, DS_PROF_NORM, st, [&] {

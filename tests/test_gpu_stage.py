@@ -376,3 +376,30 @@ def test_outputs_as_their_own_gradient(dtype_code, cuts):
         for k, v in ref.items():
             check(to_np(layer[k]), v, tol, k)
     stage.close()
+
+
+@pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
+def test_parameters_of_a_layer_that_share_a_gradient(dtype_code):
+    """b_o and b_2, the gains and the biases of both norms, w_qkv and w_1 (of the same shape): summed in one buffer each."""
+    from helpers import params_to_dev, stream_from_seqs, tdtype, to_np
+    bf16, tol, d, F, h = dtype_code == ds.DS_DTYPE_BF16, TOL[dtype_code], 256, 768, 4
+    lens = np.asarray([30, 7, 164, 1, 100, 333])
+    params = wl.draw_params(wl.GPT_KEYS, 1, d, F, seed=10, bf16=bf16)
+    xs, dys = wl.draw_rows(lens, d, seed=10, tag=3, bf16=bf16), wl.draw_rows(lens, d, seed=10, tag=5, bf16=bf16)
+    lo = ds.ds_layout_from_cuts(lens, list(range(len(lens) + 1)))
+    ref = ost.gpt_stage_fwd_bwd(xs, dys, params, h)[2][0]
+    dt = tdtype(dtype_code)
+    w = params_to_dev(params, dt)
+    x, dy = stream_from_seqs(xs, lo, d, dt), stream_from_seqs(dys, lo, d, dt)
+    stage = ds.Stage(ds.DS_MODEL_GPT, dtype_code, 1, d, h, F, max_rows=lo.total_rows, max_seqs=lo.n_seq)
+    for _ in range(3):
+        g = {k: torch.zeros(v.shape, dtype=torch.float32, device="cuda:0") for k, v in w[0].items()}
+        for a, b in (("b_2", "b_o"), ("ln2_g", "ln1_g"), ("ln2_b", "ln1_b"), ("w_1", "w_qkv")):
+            g[b] = g[a]
+        ds.stage_fwd_bwd(stage, lo, w, x, dy, torch.empty_like(x), torch.empty_like(x), [g], accumulate=True)
+        torch.cuda.synchronize()
+        for a, b in (("b_2", "b_o"), ("ln2_g", "ln1_g"), ("ln2_b", "ln1_b"), ("w_1", "w_qkv")):
+            check(to_np(g[a]), ref[a] + ref[b], tol, a)
+        for k in ("w_2", "w_o", "b_1", "b_qkv"):
+            check(to_np(g[k]), ref[k], tol, k)
+    stage.close()

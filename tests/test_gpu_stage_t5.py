@@ -101,3 +101,31 @@ def test_decoder_outputs_as_their_own_gradient(dtype_code):
         for k, v in ref.items():
             check(to_np(layer[k]), v, tol, k)
     stage.close()
+
+
+@pytest.mark.parametrize("dtype_code", [ds.DS_DTYPE_F32, ds.DS_DTYPE_BF16])
+def test_decoder_parameters_that_share_a_gradient(dtype_code):
+    """w_g, w_u and (of the same shape here) w_ckv; w_co, w_cq and w_o; the gains of the norms: summed in one buffer each."""
+    bf16, tol = dtype_code == ds.DS_DTYPE_BF16, 2e-2 if dtype_code == ds.DS_DTYPE_BF16 else 1e-4
+    lens, tgts, ep, dp, ex, dx, ddy = _case(bf16)
+    ep, dp, d, dt = ep[:1], dp[:1], CFG["d_model"], tdtype(dtype_code)
+    assert CFG["d_ff"] == 2 * d
+    ref = ost.t5_stage_fwd_bwd(ex, dx, ddy, ep, dp, CFG["n_heads"])[4][0]
+    lo = ds.ds_layout_from_cuts(lens, list(range(len(lens) + 1)), lengths_tgt=tgts)
+    we, wd = params_to_dev(ep, dt), params_to_dev(dp, dt)
+    ge, gd = zero_grads_like(we), zero_grads_like(wd)[0]
+    shared = [("w_g", "w_u", "w_ckv"), ("w_co", "w_cq", "w_o"), ("ln2_g", "lnc_g", "ln1_g")]
+    for names in shared:
+        for k in names[1:]:
+            gd[k] = gd[names[0]]
+    x, y, dy = stream_from_seqs(ex, lo, d, dt), stream_from_seqs(dx, lo, d, dt, which=1), stream_from_seqs(ddy, lo, d, dt, which=1)
+    stage = ds.Stage(ds.DS_MODEL_T5, dtype_code, 1, d, CFG["n_heads"], CFG["d_ff"], max_rows=lo.total_rows, max_seqs=lo.n_seq,
+                     n_dec_layers=1, max_rows_tgt=lo.total_rows_tgt)
+    ds.stage_fwd_bwd(stage, lo, we, x, dy, torch.empty_like(y), torch.empty_like(x), ge, weights_dec=wd, grads_dec=[gd], act_in_tgt=y,
+                     grad_in_tgt=torch.empty_like(y), accumulate=True)
+    torch.cuda.synchronize()
+    for names in shared:
+        check(to_np(gd[names[0]]), sum(ref[k] for k in names), tol, " + ".join(names))
+    for k in ("w_2", "w_qkv"):
+        check(to_np(gd[k]), ref[k], tol, k)
+    stage.close()
