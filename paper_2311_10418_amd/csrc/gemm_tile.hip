@@ -504,6 +504,7 @@ TnPick pick_tn_group(const TnGroup& g) {
 }
 
 ds_status launch_tn_group(const TnPick& pick, TnGroup& g, hipStream_t st) {
+    if (pick.kind < 0 || pick.kind > kTnF32) return DS_EINVAL;
     g.splits = pick.kind >= kTnBig ? pick.splits : 1;
     if (pick.kind == kTnF32) return launch_tn_group_f32(g, st);
     const int bm = pick.kind == kTnBig ? 256 : kShapes[pick.kind].bm, bn = pick.kind == kTnBig ? 256 : kShapes[pick.kind].bn;

@@ -350,9 +350,10 @@ struct Ops {
         if ((!nt && !wg.f32) || shapes.size() > (size_t)kTnGroup) return;
         wg.K = sm.R;
         wg.accumulate = accumulate;
+        int n = 0;
         for (const auto& q : shapes) {
-            wg.p[wg.n] = TnProblem{nullptr, nullptr, nullptr, q.first, q.second};
-            if (!tn_group_takes(wg.p[wg.n++], sm.R, wg.f32)) return;
+            wg.p[n] = TnProblem{nullptr, nullptr, nullptr, q.first, q.second};
+            if (!tn_group_takes(wg.p[n++], sm.R, wg.f32)) return;
         }
         // room for partial sums: the workspace of the other GEMMs and two temporaries that are dead at the end of a layer
         float* const slab[TnGroup::kSlabs] = {s->split_ws, (float*)s->du, (float*)s->d_o};
@@ -363,6 +364,7 @@ struct Ops {
             wg.slab[i] = slab[i];
             wg.slab_end[i] = (int32_t)end;
         }
+        wg.n = n;
         wg_pick = pick_tn_group(wg);
         wg.n = 0;
     }
