@@ -996,9 +996,10 @@ ds_status launch_gemm(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t 
     return DS_EINVAL;
 }
 
-// adds up the partial sums of a group's tiles; blockIdx.y = tile, counted over the whole group
+// adds up the partial sums of a group's tiles; kFinishParts work-groups per tile, tiles counted over the whole group
+constexpr int kFinishParts = 8;
 __global__ __launch_bounds__(256) void tn_group_finish_kernel(TnGroup g) {
-    int at = blockIdx.y * g.splits;                                   // work-group number of the tile's first split, were they in turn
+    int at = blockIdx.x / kFinishParts * g.splits;                                   // work-group number of the tile's first split, were they in turn
     const int i = tn_group_problem(g, at);
     const int N = g.p[i].N, tiles_m = g.p[i].M / BM, tiles_n = N / BN, tile = at / g.splits;
     int tile_m, tile_n;
@@ -1006,7 +1007,7 @@ __global__ __launch_bounds__(256) void tn_group_finish_kernel(TnGroup g) {
     float* C = reinterpret_cast<float*>(g.p[i].C);
     GemmEpi p{};
     p.accumulate = g.accumulate;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < BM * (BN / 8); e += gridDim.x * blockDim.x) {
+    for (int e = blockIdx.x % kFinishParts * blockDim.x + threadIdx.x; e < BM * (BN / 8); e += kFinishParts * blockDim.x) {
         const int r = e / (BN / 8), c8 = (e % (BN / 8)) * 8;
         float v[8];
 #pragma unroll
@@ -1037,7 +1038,7 @@ ds_status launch_tn_group_big(TnGroup& g, int blocks, hipStream_t st) {
                        (const bf16_t*)nullptr, (bf16_t*)nullptr, 0, 0, g.splits, 0, 1, (float*)nullptr, p, 0, (int*)nullptr, g);
     DS_LAUNCH_CHECK();
     if (g.splits > 1) {
-        hipLaunchKernelGGL(tn_group_finish_kernel, dim3(8, (unsigned)(blocks / g.splits)), dim3(256), 0, st, g);
+        hipLaunchKernelGGL(tn_group_finish_kernel, dim3((unsigned)(blocks / g.splits * kFinishParts)), dim3(256), 0, st, g);
         DS_LAUNCH_CHECK();
     }
     return DS_OK;

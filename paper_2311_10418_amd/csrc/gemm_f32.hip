@@ -464,16 +464,17 @@ ds_status launch_split(dim3 grid, int M, int N, int K, const float* A, const flo
     return DS_OK;
 }
 
-// adds up the partial sums of a group's 64 x 128 tiles; blockIdx.y = tile, counted over the whole group
+// adds up the partial sums of a group's 64 x 128 tiles; kFinishParts work-groups per tile, tiles counted over the whole group
+constexpr int kFinishParts = 4;
 __global__ __launch_bounds__(256) void tn_group_f32_finish_kernel(TnGroup g) {
-    int at = blockIdx.y * g.splits;
+    int at = blockIdx.x / kFinishParts * g.splits;
     const int i = tn_group_problem(g, at);
     const int M = g.p[i].M, N = g.p[i].N, tiles_n = (N + G_BN - 1) / G_BN, tiles = (M + G_BM - 1) / G_BM * tiles_n, tile = at / g.splits;
     const int m0 = tile / tiles_n * G_BM, n0 = tile % tiles_n * G_BN;
     float* C = reinterpret_cast<float*>(g.p[i].C);
     GemmEpi p{};
     p.accumulate = g.accumulate;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < G_BM * (G_BN / 8); e += gridDim.x * blockDim.x) {
+    for (int e = blockIdx.x % kFinishParts * blockDim.x + threadIdx.x; e < G_BM * (G_BN / 8); e += kFinishParts * blockDim.x) {
         const int r = e / (G_BN / 8), c8 = (e % (G_BN / 8)) * 8;
         if (m0 + r >= M || n0 + c8 >= N) continue;
         float v[8];
@@ -596,14 +597,14 @@ ds_status launch_tn_group_f32(TnGroup& g, hipStream_t st) {
     for (int i = 0; i < g.n; ++i) {
         g.first[i] = (int32_t)blocks;
         blocks += (long long)((g.p[i].M + G_BM - 1) / G_BM) * ((g.p[i].N + G_BN - 1) / G_BN) * g.splits;
-        if (blocks > 0x7fffffff || blocks / g.splits > 65535) return DS_EOVERFLOW;
+        if (blocks > (1 << 23)) return DS_EOVERFLOW;        // work-items of a grid: 32 bits (2^36 outputs)
     }
     GemmEpi p{};
     p.accumulate = g.accumulate;
     const ds_status r = launch_split<DS_EPI_ACC32, false, false, G_BM, G_BN, true>(dim3((unsigned)blocks), 0, 0, g.K, nullptr, nullptr, nullptr,
                                                                                (steps + g.splits - 1) / g.splits * F_BK, p, g, st);
     if (r != DS_OK || g.splits == 1) return r;
-    hipLaunchKernelGGL(tn_group_f32_finish_kernel, dim3(4, (unsigned)(blocks / g.splits)), dim3(256), 0, st, g);
+    hipLaunchKernelGGL(tn_group_f32_finish_kernel, dim3((unsigned)(blocks / g.splits * kFinishParts)), dim3(256), 0, st, g);
     DS_LAUNCH_CHECK();
     return DS_OK;
 }

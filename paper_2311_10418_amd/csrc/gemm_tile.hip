@@ -512,7 +512,7 @@ ds_status launch_tn_group(const TnPick& pick, TnGroup& g, hipStream_t st) {
     for (int i = 0; i < g.n; ++i) {
         g.first[i] = (int32_t)blocks;
         blocks += (long long)(g.p[i].M / bm) * (g.p[i].N / bn) * g.splits;
-        if (blocks > 0x7fffffff) return DS_EOVERFLOW;
+        if (blocks > (1 << 22)) return DS_EOVERFLOW;        // work-items of a grid: 32 bits (2^34 outputs of the smallest tile)
     }
     switch (pick.kind) {
     case 0: return launch_group_kind<0, 2, 2>(g, (int)blocks, st);

@@ -403,3 +403,46 @@ def test_parameters_of_a_layer_that_share_a_gradient(dtype_code):
         for k in ("w_2", "w_o", "b_1", "b_qkv"):
             check(to_np(g[k]), ref[k], tol, k)
     stage.close()
+
+
+def test_fp32_layer_of_more_than_65535_gradient_tiles():
+    """d = 4096, d_ff = 57 600: the weight gradients of a layer are 65 984 tiles of 64 x 128.  Against the same layer in 64 bits."""
+    d, F, h, lens = 4096, 57600, 32, [5, 12]
+    assert (2 * d * F + 4 * d * d) // (64 * 128) > 65535
+    gen = torch.Generator(device="cuda:0").manual_seed(12)
+
+    def rnd(*shape, scale=1.0):
+        return torch.randn(*shape, device="cuda:0", generator=gen) * scale
+
+    shapes = dict(w_qkv=(d, 3 * d), b_qkv=(3 * d,), w_o=(d, d), w_1=(d, F), b_1=(F,), w_2=(F, d))
+    w = {k: rnd(*shapes.get(k, (d,)), scale=0.02) for k in wl.GPT_KEYS}
+    w["ln1_g"] += 1
+    w["ln2_g"] += 1
+    x, dy = rnd(sum(lens), d), rnd(sum(lens), d)
+    g = {k: torch.full(v.shape, 3.0, device="cuda:0") for k, v in w.items()}
+    lo = ds.ds_layout_from_cuts(np.asarray(lens), [0, 1, 2])
+    rows = [slice(int(r), int(r) + int(l)) for r, l in zip(lo.seq_row, lo.seq_len)]
+    out, dx = torch.empty_like(x), torch.empty_like(x)
+    stage = ds.Stage(ds.DS_MODEL_GPT, ds.DS_DTYPE_F32, 1, d, h, F, max_rows=sum(lens), max_seqs=2)
+    ds.stage_fwd_bwd(stage, lo, [w], x, dy, out, dx, [g])
+    torch.cuda.synchronize()
+    stage.close()
+
+    p = {k: v.double().requires_grad_() for k, v in w.items()}
+    x64 = x.double().requires_grad_()
+    qkv = torch.nn.functional.layer_norm(x64, (d,), p["ln1_g"], p["ln1_b"], 1e-5) @ p["w_qkv"] + p["b_qkv"]
+    heads = []
+    for r in rows:
+        q, k, v = (t.view(-1, h, d // h).transpose(0, 1).contiguous() for t in qkv[r].split(d, dim=1))
+        s = q @ k.transpose(1, 2).contiguous() / (d // h) ** 0.5
+        s = s.masked_fill(torch.ones_like(s, dtype=torch.bool).triu(1), float("-inf"))
+        heads.append((s.softmax(-1) @ v).transpose(0, 1).reshape(-1, d))
+    order = sorted(range(len(rows)), key=lambda i: rows[i].start)
+    x1 = x64 + torch.cat([heads[i] for i in order]) @ p["w_o"] + p["b_o"]
+    z = torch.nn.functional.layer_norm(x1, (d,), p["ln2_g"], p["ln2_b"], 1e-5) @ p["w_1"] + p["b_1"]
+    y = x1 + torch.nn.functional.gelu(z, approximate="tanh") @ p["w_2"] + p["b_2"]
+    y.backward(dy.double())
+    for k, a, b in [("act_out", out, y.detach()), ("grad_in", dx, x64.grad)] + [(k, g[k], p[k].grad) for k in w]:
+        dev = (a.double() - b).abs()
+        assert float(dev.norm() / b.norm()) <= TOL[ds.DS_DTYPE_F32], k
+        assert float((dev / (8 * b.square().mean().sqrt() + b.abs())).max()) <= TOL[ds.DS_DTYPE_F32], k
