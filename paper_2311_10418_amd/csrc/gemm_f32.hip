@@ -204,9 +204,6 @@ __device__ __forceinline__ float maximum3_abs(float a, float b, float c) {      
     asm("v_maximum3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
 }
-// Elements that the split does not represent: Inf, NaN, what rounds to Inf in bf16; and lo needs |x| >= 2^-110 to be exact.  The
-// largest magnitude of eight elements tells (groups of which the largest is below 2^-108, 0 aside).
-__device__ __forceinline__ bool split_fails(float largest) { return !(largest < 0x1.fep127f) || (largest < 0x1p-108f && largest > 0.f); }
 // f(0), f(1), .. f(N - 1) with constant arguments
 template <class F, int... I> __device__ __forceinline__ void unroll_list(F&& f, std::integer_sequence<int, I...>) {
     (f(std::integral_constant<int, I>{}), ...);
@@ -280,10 +277,10 @@ template <int ROWS, bool KC, bool PERM> struct SplitTile {
         }
     }
     // Splitting and storing a tile goes in steps of 3 to 8 vector instructions, handed out between MFMAs: 13 per chunk (an element,
-    // an element, their dword of each plane, four times; then the check and the stores).
+    // an element, their dword of each plane, four times; then the stores).
     static constexpr int STEPS = 13 * NC;
     uint32_t h[2], m[2], l[2], o[3][4];
-    template <int STEP> __device__ __forceinline__ void store_step(int set, char* tile, bool& bad) {
+    template <int STEP> __device__ __forceinline__ void store_step(int set, char* tile, uint32_t& lost) {
         constexpr int i = STEP / 13, q = STEP % 13, pair = q / 3;
         if constexpr (q < 12 && q % 3 < 2) {
             split_one(v[set][i][pair >> 1][(pair & 1) * 2 + q % 3], h[q % 3], m[q % 3], l[q % 3]);
@@ -291,10 +288,9 @@ template <int ROWS, bool KC, bool PERM> struct SplitTile {
             o[0][pair] = upper_halves(h[0], h[1]);
             o[1][pair] = upper_halves(m[0], m[1]);
             o[2][pair] = upper_halves(l[0], l[1]);
-            asm volatile("" : "+v"(o[0][pair]), "+v"(o[1][pair]), "+v"(o[2][pair]));
+            lost |= l[0] | l[1];
+            asm volatile("" : "+v"(o[0][pair]), "+v"(o[1][pair]), "+v"(o[2][pair]), "+v"(lost));
         } else {
-            const f32x4_t a = v[set][i][0], b = v[set][i][1];
-            bad |= split_fails(maximum3_abs(maximum3_abs(a[0], a[1], a[2]), maximum3_abs(a[3], b[0], b[1]), maximum3_abs(b[2], b[3], 0.f)));
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
                 char* d = tile + p * PLANE + lds[i];
@@ -366,7 +362,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(int M, int N, in
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = small[i][j][e] = 0.f;
-    bool bad = false;
+    uint32_t lost = 0;
 
     TA ta;
     TB tb;
@@ -378,8 +374,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(int M, int N, in
     };
     constexpr int STEPS = TA::STEPS + TB::STEPS, MFMAS = 12 * NA * NB;
     auto store_step = [&](auto set, auto k) {
-        if constexpr (k < TA::STEPS) ta.template store_step<k>(set, smem + set * STAGE, bad);
-        else tb.template store_step<k - TA::STEPS>(set, smem + set * STAGE + 3 * TA::PLANE, bad);
+        if constexpr (k < TA::STEPS) ta.template store_step<k>(set, smem + set * STAGE, lost);
+        else tb.template store_step<k - TA::STEPS>(set, smem + set * STAGE + 3 * TA::PLANE, lost);
     };
     const std::integral_constant<int, 0> set0;
     const std::integral_constant<int, 1> set1;
@@ -419,8 +415,57 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(int M, int N, in
         step(set0, set1, k0);
         if (k0 + F_BK < k_end) step(set1, set0, k0 + F_BK);
     }
-    // a value that the split does not represent: the tile again, one multiply-add per product (rare: the values of a diverged model)
-    const bool again = __syncthreads_or(bad);
+    // Where an element has bits that its three parts do not hold, or a result is not finite (an operand that is not, a part that
+    // is not, products next to the largest float): the tile again with fp32 products.
+    bool again = (lost & 0xffff) != 0;
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            float largest[2] = {0.f, 0.f};                            // per 8 columns
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] += small[i][j][e];
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) largest[e >> 3] = maximum3_abs(largest[e >> 3], acc[i][j][e], acc[i][j][e + 1]);
+            const int m = m0 + wm * (BM / 2) + i * 32 + (lane & 31);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int n = n0 + wn * (BN / 2) + 32 * j + 16 * h + 8 * (lane >> 5);
+                again |= m < M && n < N && !(largest[h] < __builtin_inff());
+            }
+        }
+    again = __syncthreads_or(again);
+    if (again) {
+        const float* pa[NA];
+        const float* pb[NB];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int m = min(m0 + wm * (BM / 2) + i * 32 + (lane & 31), M - 1);
+            pa[i] = A + (AKC ? (long long)m * lda : (long long)m);
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int n = min(n0 + wn * (BN / 2) + 32 * j + TB::place(lane & 31), N - 1);
+            pb[j] = B + (BKC ? (long long)n * ldb : (long long)n);
+        }
+#pragma unroll 4
+        for (int k0 = k_begin; k0 < k_end; k0 += 2) {
+            const int k = k0 + (lane >> 5);
+            float fa[NA], fb[NB];
+#pragma unroll
+            for (int i = 0; i < NA; ++i) fa[i] = k < k_end ? pa[i][AKC ? (long long)k : (long long)k * lda] : 0.f;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) fb[j] = k < k_end ? pb[j][BKC ? (long long)k : (long long)k * ldb] : 0.f;
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j], fa[i], acc[i][j], 0, 0, 0);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         const int mt = wm * (BM / 2) + i * 32 + (lane & 31), m = m0 + mt;
@@ -433,16 +478,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(int M, int N, in
                 if (n >= N) continue;                                 // (N is a multiple of 8)
                 float v[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = acc[i][j][8 * h + e] + small[i][j][8 * h + e];
-                if (again) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = 0.f;
-                    for (int k = k_begin; k < k_end; ++k) {
-                        const float a = AKC ? A[(long long)m * lda + k] : A[(long long)k * lda + m];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) v[e] = fmaf(a, BKC ? B[(long long)(n + e) * ldb + k] : B[(long long)k * ldb + n + e], v[e]);
-                    }
-                }
+                for (int e = 0; e < 8; ++e) v[e] = acc[i][j][8 * h + e];
                 if (GRP && partial) Vec8<float>::store(partial + mt * BN + nt, v);
                 else epilogue8<float, EPI>(m, n, N, v, C, p);
             }

@@ -324,6 +324,44 @@ def test_gemm_f32_values_that_bf16_products_do_not_represent():
     assert err.max() <= 4 * np.sqrt(K) * 2.0 ** -24
 
 
+@pytest.mark.parametrize("form", ["NN", "NT"])
+@pytest.mark.parametrize("N", [264, 1024])                                    # 64 x 64 and 64 x 128 tiles
+def test_gemm_f32_products_next_to_overflow(form, N):
+    """Products and sums up to the largest float are finite, as with fp32 products, whatever their bf16 parts round to; larger ones
+    are infinite.  K = 512: one addition rounds by 2^-24, and there are at most three."""
+    M, K = 4100, 512
+    A, B = np.zeros((M, K)), np.zeros((K, N))
+    A[:, 0], B[0] = 1.8446e19, 1.8446e19                                       # 3.4026e38, their upper 8 bits rounded up: 2^128
+    A[1::4, 7], B[7] = -2.0 ** 100, 2.0 ** 27                                  # 3.4026e38 - 1.7014e38
+    A[2::4, 0], A[2::4, 70], B[70] = 2.0 ** 63, 1.7e38 / 2.0 ** 20, 2.0 ** 20    # 1.7014e38 + 1.7e38
+    A[3::4, 300], B[300] = 1e30, 1e8                                           # 3.4026e38 + 1e38: beyond it
+    A, B = A.astype(np.float32), B.astype(np.float32)
+    c = torch.zeros((M, N), dtype=F32, device=DEV)
+    ds.ds_gemm(to_dev(A, F32), to_dev(B.T if form == "NT" else B, F32), c, M, N, K, trans_b=form == "NT")
+    torch.cuda.synchronize()
+    ref, c = A.astype(np.float64) @ B.astype(np.float64), c.cpu().numpy().astype(np.float64)
+    beyond = ref > np.finfo(np.float32).max
+    assert beyond[3::4].all() and not beyond[0::4].any() and not beyond[1::4].any() and not beyond[2::4].any()
+    assert np.all(np.isposinf(c[beyond])) and np.all(np.abs(c - ref)[~beyond] <= 3 * 2.0 ** -24 * ref[~beyond])
+
+
+@pytest.mark.parametrize("form", ["NN", "NT"])
+@pytest.mark.parametrize("exponent", [-112, -124])
+def test_gemm_f32_tiny_values_beside_larger_ones(form, exponent):
+    """A value below 2^-110 keeps all its bits also where its neighbours are larger: one product per result counts, which fp32 rounds
+    by 2^-24."""
+    rng = np.random.default_rng(-exponent)
+    M, N, K = 4096, 256, 64
+    A, B = np.zeros((M, K), np.float32), _rnd(rng, (K, N), F32)
+    A[:, 3], A[:, 2] = rng.uniform(1, 2, M) * 2.0 ** exponent, 2.0 ** -100
+    B[2], B[3] = 0, B[3] * np.float32(2.0 ** 60)
+    c = torch.zeros((M, N), dtype=F32, device=DEV)
+    ds.ds_gemm(to_dev(A, F32), to_dev(B.T if form == "NT" else B, F32), c, M, N, K, trans_b=form == "NT")
+    torch.cuda.synchronize()
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    assert np.all(np.abs(c.cpu().numpy() - ref) <= 2.0 ** -24 * np.abs(ref))
+
+
 @pytest.mark.parametrize("dt", [F32, BF])
 @pytest.mark.parametrize("rms", [False, True])
 @pytest.mark.parametrize("d", [256, 1024, 1536, 2048, 3072, 4096])
