@@ -455,7 +455,8 @@ ds_status ds_unpack(const ds_layout* layout, int32_t which, int32_t dtype, int32
  */
 
 /* C[M,N] = op(A) op(B) (+ epilogue).  trans_a = 0: A is [M,K] row-major; 1: A is [K,M].
- * trans_b = 0: B is [K,N]; 1: B is [N,K].  Accumulation in float32.
+ * trans_b = 0: B is [K,N]; 1: B is [N,K].  Accumulation in float32; DS_DTYPE_F32: every product is taken with a relative error
+ * below 2^-27 (exactly, or from bf16 parts of both factors).
  * epilogue (DS_EPI_*):
  *   NONE     C = acc (+ bias[n])
  *   GELU     C = acc + bias (pre-activation, stored), C2 = GELU_tanh(C)

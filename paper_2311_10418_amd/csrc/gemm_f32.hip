@@ -1,5 +1,5 @@
 // fp32 GEMM on the matrix cores, two kernels:
-//   gemm_f32_split_kernel  six bf16 products per fp32 one, where there are work-groups for it, and all weight gradients of a
+//   gemm_f32_split_kernel  eight bf16 products per fp32 one, where there are work-groups for it, and all weight gradients of a
 //                          layer in one launch; described where it is defined
 //   gemm_f32_mfma_kernel   v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation, one fused multiply-add per product, so nothing
 //                          is rounded that a plain FMA loop would not round; the rest, described here
@@ -182,23 +182,29 @@ __global__ __launch_bounds__(256 * KW) void gemm_f32_mfma_kernel(int M, int N, i
 }
 
 // ---------------------------------------------------------------------------- fp32 products on the bf16 matrix cores
-// x = hi + mid + lo exactly, each a bf16 (8 significant bits of what the one before left), and
-//   a b = hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi) + less than 2^-22 |a b|, of either sign (about 2^-26 in the mean)
-// so six bf16 products give an fp32 one, at 2.5 PFLOP/s / 6 instead of the 157 TFLOP/s of the fp32 matrix instructions.  A
-// product of two bf16 is exact in fp32.  The leading products and the five small ones have accumulators of their own, added at the
+// x = hi + mid + lo exactly, each a bf16 (8 significant bits of what the one before left; three parts of bf16 for one fp32 value are
+// described by Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations",
+// 2019), and
+//   a b = hi hi + (hi mid + mid hi) + (hi lo + mid mid + lo hi) + (mid lo + lo mid) + less than 2^-30 |a b|
+// so eight bf16 products give an fp32 one, at 2.5 PFLOP/s / 8 instead of the 157 TFLOP/s of the fp32 matrix instructions.  A
+// product of two bf16 is exact in fp32.  The leading products and the seven small ones have accumulators of their own, added at the
 // end, so that the small ones are not rounded at the size of the sum, and an MFMA adds 16 products at a time: against 64 bits
-// the results are 1.5 to 3 times closer than those of an fp32 multiply-add per product (N(0, 1) x N(0, 0.02), K = 256 .. 4096:
-// 0.9e-7 .. 4.0e-7 against 2.0e-7 .. 11.5e-7).
-// hi is rounded (half away from zero, so that mid has either sign and what is left out of a sum averages out), mid and lo are
-// truncations of the rest: integer and plain fp32 operations.
+// the results are 1.5 to 3 times closer than those of an fp32 multiply-add per product (N(0, 1) x N(0, 0.02), K = 36 .. 1024:
+// 0.4e-7 .. 1.9e-7 against 1.0e-7 .. 5.7e-7), and where a result is one product as close (largest error 5.99e-8 and 5.96e-8, root
+// mean square 2.53e-8 both).  With the first six products only that was 1.6e-7 and 2.9e-8, and the stage below took 1 077 us
+// instead of 1 137.
+// hi is rounded (half away from zero, so that mid has either sign), mid and lo are truncations of the rest: integer and plain
+// fp32 operations.
 //
-// What bounds it is the splitting: an element costs 6.5 vector instructions per work-group that reads it, and the vector unit and the
-// matrix unit hardly work at the same time (2 wavefronts per SIMD, clocks per MFMA: 16x16x32 18 alone, 27 with four v_and_b32
-// beside it; 32x32x16 33 alone, 34.6 with four, 43 with eight: hence the latter).  The splitting of the next tile is spread between the
-// MFMAs of the current one, pinned there.  4096^3: 840 us against 1190 - 1250; without the splitting (timing build) 495, without
-// the stores of the planes 700.  Loads go through buffers that end with the operand, without a test per lane.
-//   7 684 rows, us, fp32 MFMA -> this: N = 768, K = 256 42 -> 36; N = 256, K = 1024 60 -> 45; N = 1024, K = 256 50 -> 42; N = K = 256 25 -> 16;
-//   12 288 rows, N = 2048, K = 512 238 -> 186; the four weight gradients of d = 256, d_ff = 1024 194 -> 98.
+// What bounds it is the splitting beside the products: an element costs 6.5 vector instructions per work-group that reads it, and the
+// vector unit and the matrix unit hardly work at the same time (2 wavefronts per SIMD, clocks per MFMA: 16x16x32 18 alone, 27 with
+// four v_and_b32 beside it; 32x32x16 33 alone, 34.6 with four, 43 with eight: hence the latter).  The splitting of the next tile is
+// spread between the MFMAs of the current one, pinned there.  4096^3, operands from memory: 955 us against 1 350 - 1 410 (with six
+// products 838; timing builds with six: 495 without the splitting, 700 without the stores of the planes).  Loads go through buffers
+// that end with the operand, without a test per lane.
+//   Operands from memory, us, fp32 MFMA -> this: 7 684 rows, N = 768, K = 256 44 -> 38; N = 256, K = 1024 58 -> 44; N = 1024, K = 256
+//   50 -> 44; N = K = 256 25 -> 17; 12 288 rows, N = 2048, K = 512 257 -> 195.  Two layers of d = 256, d_ff = 1024 over 7 684 tokens,
+//   weight gradients in one launch: 1 449 -> 1 137.
 __device__ __forceinline__ float maximum3_abs(float a, float b, float c) {       // NaN if one is NaN
     float r;
     asm("v_maximum3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
@@ -372,7 +378,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(int M, int N, in
         ta.load(set, k0, k_end, t);
         tb.load(set, k0, k_end, t);
     };
-    constexpr int STEPS = TA::STEPS + TB::STEPS, MFMAS = 12 * NA * NB;
+    constexpr int STEPS = TA::STEPS + TB::STEPS, MFMAS = 16 * NA * NB;
     auto store_step = [&](auto set, auto k) {
         if constexpr (k < TA::STEPS) ta.template store_step<k>(set, smem + set * STAGE, lost);
         else tb.template store_step<k - TA::STEPS>(set, smem + set * STAGE + 3 * TA::PLANE, lost);
@@ -400,8 +406,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(int M, int N, in
                 for (int j = 0; j < NB; ++j) fb[ks][j][q] = TB::frag(sb, q, wn * NB + j, ks, lane);
             }
         unroll<MFMAS>([&](auto n) {
-            constexpr int qa[6] = {0, 1, 0, 1, 2, 0}, qb[6] = {0, 0, 1, 1, 0, 2};
-            constexpr int ks = n / (6 * NA * NB), q = n / (NA * NB) % 6, i = n / NB % NA, j = n % NB;
+            constexpr int qa[8] = {0, 1, 0, 1, 2, 0, 2, 1}, qb[8] = {0, 0, 1, 1, 0, 2, 1, 2};
+            constexpr int ks = n / (8 * NA * NB), q = n / (NA * NB) % 8, i = n / NB % NA, j = n % NB;
             if constexpr (q == 0) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j][0], fa[ks][i][0], acc[i][j], 0, 0, 0);
             else small[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j][qb[q]], fa[ks][i][qa[q]], small[i][j], 0, 0, 0);
             constexpr int from = n * STEPS / MFMAS, to = (n + 1) * STEPS / MFMAS;

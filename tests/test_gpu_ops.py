@@ -325,6 +325,22 @@ def test_gemm_f32_values_that_bf16_products_do_not_represent():
 
 
 @pytest.mark.parametrize("form", ["NN", "NT"])
+@pytest.mark.parametrize("N,K", [(264, 4), (264, 36), (1024, 516)])
+def test_gemm_f32_one_product_per_result(form, N, K):
+    """Rows with one value: a result is one product, rounded by 2^-24 where it is added up, and by less than 2^-26 in all where the seven
+    small ones of its eight bf16 products are (each by at most 2^-23 of their sum, which is below 2^-7 of it)."""
+    rng = np.random.default_rng(K)
+    M = 4100
+    A, B = np.zeros((M, K), np.float32), _rnd(rng, (K, N), F32)
+    A[np.arange(M), rng.integers(0, K, M)] = rng.standard_normal(M)
+    c = torch.zeros((M, N), dtype=F32, device=DEV)
+    ds.ds_gemm(to_dev(A, F32), to_dev(B.T if form == "NT" else B, F32), c, M, N, K, trans_b=form == "NT")
+    torch.cuda.synchronize()
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    assert np.all(np.abs(c.cpu().numpy() - ref) <= (2.0 ** -24 + 2.0 ** -26) * np.abs(ref))
+
+
+@pytest.mark.parametrize("form", ["NN", "NT"])
 @pytest.mark.parametrize("N", [264, 1024])                                    # 64 x 64 and 64 x 128 tiles
 def test_gemm_f32_products_next_to_overflow(form, N):
     """Products and sums up to the largest float are finite, as with fp32 products, whatever their bf16 parts round to; larger ones
