@@ -458,18 +458,22 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(int M, int N, in
             const int n = min(n0 + wn * (BN / 2) + 32 * j + TB::place(lane & 31), N - 1);
             pb[j] = B + (BKC ? (long long)n * ldb : (long long)n);
         }
-#pragma unroll 4
-        for (int k0 = k_begin; k0 < k_end; k0 += 2) {
-            const int k = k0 + (lane >> 5);
-            float fa[NA], fb[NB];
+        for (int k0 = k_begin; k0 < k_end; k0 += 8) {                 // the operands of four steps in flight
+            float fa[4][NA], fb[4][NB];
 #pragma unroll
-            for (int i = 0; i < NA; ++i) fa[i] = k < k_end ? pa[i][AKC ? (long long)k : (long long)k * lda] : 0.f;
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + 2 * u + (lane >> 5);
 #pragma unroll
-            for (int j = 0; j < NB; ++j) fb[j] = k < k_end ? pb[j][BKC ? (long long)k : (long long)k * ldb] : 0.f;
+                for (int i = 0; i < NA; ++i) fa[u][i] = k < k_end ? pa[i][AKC ? (long long)k : (long long)k * lda] : 0.f;
 #pragma unroll
-            for (int i = 0; i < NA; ++i)
+                for (int j = 0; j < NB; ++j) fb[u][j] = k < k_end ? pb[j][BKC ? (long long)k : (long long)k * ldb] : 0.f;
+            }
 #pragma unroll
-                for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j], fa[i], acc[i][j], 0, 0, 0);
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[u][j], fa[u][i], acc[i][j], 0, 0, 0);
         }
     }
 #pragma unroll
