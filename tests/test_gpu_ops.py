@@ -284,7 +284,7 @@ def test_attention_empty_sequences(dt, force):
 
 # ragged rows, columns (not a multiple of a tile) and K: 64 x 64 and 64 x 128 tiles of the fp32 products on the bf16 matrix cores
 @pytest.mark.parametrize("form", ["NN", "NT"])
-@pytest.mark.parametrize("M,N,K", [(4003, 264, 36), (2050, 520, 100), (4096, 256, 256), (8203, 520, 516)])
+@pytest.mark.parametrize("M,N,K", [(4003, 264, 36), (2050, 520, 100), (4096, 256, 256), (8203, 520, 516), (4003, 264, 196), (2050, 520, 228)])
 def test_gemm_f32_as_bf16_products(form, M, N, K):
     """Within the error of fp32 sums: per product less than 2^-22 is left out and every addition rounds by 2^-24, over K of them
     sqrt(K) 2^-24 in the mean; values from 2^-40 to 2^40 in the same row."""
@@ -299,10 +299,11 @@ def test_gemm_f32_as_bf16_products(form, M, N, K):
     assert err.max() <= 4 * np.sqrt(K) * 2.0 ** -24
 
 
-def test_gemm_f32_values_that_bf16_products_do_not_represent():
+@pytest.mark.parametrize("K", [64, 192])                                     # fp32 products and bf16 ones
+def test_gemm_f32_values_that_bf16_products_do_not_represent(K):
     """Inf, NaN, values next to the largest and rows of tiny ones: as with fp32 products."""
     rng = np.random.default_rng(77)
-    M, N, K = 4096, 256, 64
+    M, N = 4096, 256
     A, B = _rnd(rng, (M, K), F32), _rnd(rng, (K, N), F32)
     A[3, 5], A[700, 1], A[701, 2], A[1500, 3] = np.inf, np.nan, -np.inf, 3.4e38
     A[2000] *= np.float32(1e-36)
@@ -325,7 +326,7 @@ def test_gemm_f32_values_that_bf16_products_do_not_represent():
 
 
 @pytest.mark.parametrize("form", ["NN", "NT"])
-@pytest.mark.parametrize("N,K", [(264, 4), (264, 36), (1024, 516)])
+@pytest.mark.parametrize("N,K", [(264, 4), (264, 36), (264, 192), (264, 228), (1024, 516)])
 def test_gemm_f32_one_product_per_result(form, N, K):
     """Rows with one value: a result is one product, rounded by 2^-24 where it is added up, and by less than 2^-26 in all where the seven
     small ones of its eight bf16 products are (each by at most 2^-23 of their sum, which is below 2^-7 of it)."""
@@ -367,7 +368,7 @@ def test_gemm_f32_tiny_values_beside_larger_ones(form, exponent):
     """A value below 2^-110 keeps all its bits also where its neighbours are larger: one product per result counts, which fp32 rounds
     by 2^-24."""
     rng = np.random.default_rng(-exponent)
-    M, N, K = 4096, 256, 64
+    M, N, K = 4096, 256, 192
     A, B = np.zeros((M, K), np.float32), _rnd(rng, (K, N), F32)
     A[:, 3], A[:, 2] = rng.uniform(1, 2, M) * 2.0 ** exponent, 2.0 ** -100
     B[2], B[3] = 0, B[3] * np.float32(2.0 ** 60)
