@@ -543,8 +543,9 @@ ds_status launch_form(int M, int N, int K, const float* A, const float* B, float
     const int n_cu = gemm_cu_count();
     const int gn = (N + F_BN - 1) / F_BN, gm = (M + F_BM - 1) / F_BM;
     const long long lda = AKC ? K : M, ldb = BKC ? K : N, tiles = (long long)gn * gm;
-    // Enough tiles for the CUs: the bf16 form, with 64 x 128 tiles where every CU gets two and the K loop is long enough to pay for
-    // their longer prologue (12 288 rows of d = 512: stage call 5.27 -> 4.87 ms; K = 256: 1.31 -> 1.33), else 64 x 64.  Long loops of
+    // Enough tiles for the CUs: the bf16 form, with 64 x 128 tiles where every CU gets two, the K loop is long enough to pay for
+    // their longer prologue (12 288 rows of d = 512: stage call 5.27 -> 4.87 ms; K = 256: 1.31 -> 1.33) and they add at most an eighth
+    // of columns that do not exist (N = 264, 11 535 rows, K = 1536: 136 us, 111 with 64 x 64 tiles, 125 in the fp32 form), else 64 x 64.  Long loops of
     // few tiles stay, cut over K (1800 x 512 x 2048, 232 tiles: 53 us, 58 with the other), and so do short ones, whose prologue and
     // splitting nothing covers (fp32 form -> this, geometric mean and worst of 30 to 40 shapes with tiles enough, operands from memory:
     // K = 32 1.16 and 1.45, 64 1.08 and 1.34, 96 1.03 and 1.22, 128 0.98 and 1.25, 160 0.95 and 1.10, 192 0.92 and 1.08, 224 0.91 and
@@ -552,7 +553,7 @@ ds_status launch_form(int M, int N, int K, const float* A, const float* B, float
     if constexpr (AKC) {
         const bool fits = K >= 192 && lda <= (1 << 22) && ldb <= (BKC ? 1 << 22 : 1 << 24);       // byte offsets within a tile: 31 bits
         const int gn2 = (N + G_BN - 1) / G_BN;
-        if (fits && (long long)gn2 * gm >= 2 * n_cu && K >= 512)
+        if (fits && (long long)gn2 * gm >= 2 * n_cu && K >= 512 && 2 * gn2 - gn <= gn / 8)
             return launch_split<EPI, AKC, BKC, G_BM, G_BN, false>(dim3(gn2, gm), M, N, K, A, B, C, K, p, NoGroup{}, st);
         if (fits && (tiles >= n_cu * 5 / 4 || (tiles >= n_cu * 7 / 8 && K <= 1024))) return launch_split<EPI, AKC, BKC, 64, 64, false>(dim3(gn, gm), M, N, K, A, B, C, K, p, NoGroup{}, st);
     }
