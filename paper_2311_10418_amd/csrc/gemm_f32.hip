@@ -262,11 +262,12 @@ template <int ROWS, bool KC, bool PERM> struct SplitTile {
     }
     // The tile at k0, through a buffer that ends where the operand does: rows (KC) or k rows past the end read as zeros, without a
     // test per lane.  What else lies outside: k beyond k_end in the last tile of KC operands is replaced by zeros, columns
-    // beyond the operand's (not KC) belong to outputs that are not stored.
+    // beyond the operand's (not KC) belong to outputs that are not stored.  The buffer's length stays below 2^31, beyond every offset
+    // within a tile and below that of the replaced ones, however long the operand is.
     __device__ __forceinline__ void load(int set, int k0, int k_end, int t) {
         const int left = k_end - k0;
         const long long end = KC ? (long long)rows * ld - k0 : (long long)left * ld - rows;
-        const uint32_t bytes = left <= 0 || end <= 0 ? 0u : (uint32_t)(end < 0x3fffffff ? end * 4 : 0xfffffffc);
+        const uint32_t bytes = left <= 0 || end <= 0 ? 0u : (uint32_t)(end < 0x1fffffff ? end * 4 : 0x7ffffffc);
         __amdgpu_buffer_rsrc_t buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base + (KC ? (long long)k0 : (long long)k0 * ld)), 0,
                                                                        (int)bytes, 0x00020000);
         constexpr int second = KC ? 32 : 16;                          // bytes from the first half of a chunk to the second

@@ -299,6 +299,16 @@ def test_gemm_f32_as_bf16_products(form, M, N, K):
     assert err.max() <= 4 * np.sqrt(K) * 2.0 ** -24
 
 
+def test_gemm_f32_operands_beyond_4_gib():
+    """Ones, 1216 x (2^20 + 4) both (4.75 GiB each): every result is the length of the contraction, whose last K tile holds 4 values."""
+    M, K = 1216, (1 << 20) + 4
+    a, c = torch.ones((M, K), dtype=F32, device=DEV), torch.zeros((M, M), dtype=F32, device=DEV)
+    b = torch.ones_like(a)
+    ds.ds_gemm(a, b, c, M, M, K, trans_b=True)
+    torch.cuda.synchronize()
+    assert bool((c == K).all())
+
+
 @pytest.mark.parametrize("K", [64, 192])                                     # fp32 products and bf16 ones
 def test_gemm_f32_values_that_bf16_products_do_not_represent(K):
     """Inf, NaN, values next to the largest and rows of tiny ones: as with fp32 products."""
