@@ -893,11 +893,16 @@ static NtChoice choose_kernel(bool tn, int epi, int M, int N, int K, size_t wsf,
 // whose K loops are then cut into pieces and added up by a launch of their own) go out as two: the rows of the whole rounds
 // first, the rest with the tiles that suit it, where the estimates with 1 us between them are 3 % below that of one.  0: one launch.
 // 4 173 x 4 096 x 1 024: 51 -> 45 us, 4 173 x 4 352 x 1 024: 54 -> 46.
+// Below K = 512 one launch cuts no K loop, and from two rounds on its tiles are drawn, so that the last ones run beside others; what
+// a second launch costs then is not in the estimates.  Of 292 shapes (N = 256 .. 8192, 1 to 8 rounds, operands from memory, plain and
+// residual outputs) for which they say two, two launches / one, geometric mean and worst: K = 64 and 128, 1.06 and 1.41; K = 256 .. 448
+// two rounds 0.95 and 1.04 (the exception below), one round 0.98 and 1.08, more 1.03 and 1.25; K = 512 and more 0.91 and 1.05.
 static int rows_of_whole_rounds(int epi, int M, int N, int K, size_t wsf, bool colsum, int accumulate, double one) {
     const int n_cu = gemm_cu_count(), tiles_n = N / BN;
     const long long rounds = (long long)((M + BM - 1) / BM) * tiles_n / n_cu;
     const long long rows = rounds * n_cu / tiles_n * BM;
     if (rounds < 1 || rows <= 0 || rows >= M) return 0;
+    if (K < 512 && (rounds != 2 || K < 256)) return 0;
     const double two = choose_kernel(false, epi, (int)rows, N, K, wsf, colsum, accumulate).cost + 1 +
                        choose_kernel(false, epi, M - (int)rows, N, K, wsf, colsum, accumulate).cost;
     return two < 0.97 * one ? (int)rows : 0;

@@ -84,10 +84,12 @@ def test_gemm_epilogues(dt, force):
 
 
 # 256 x 256 tiles for whole rounds over 256 compute units and other tiles for the rows behind them, from one to a tile and a half
+# (one launch at K = 64)
+@pytest.mark.parametrize("K", [64, 512])
 @pytest.mark.parametrize("M", [8193, 8289, 8192 + 385])
-def test_gemm_rows_behind_whole_rounds(M):
+def test_gemm_rows_behind_whole_rounds(M, K):
     rng = np.random.default_rng(M)
-    N, K, tol = 2048, 64, 6e-3
+    N, tol = 2048, 6e-3
     A, B = _rnd(rng, (M, K), BF), _rnd(rng, (N, K), BF, 0.1)
     bias, R, R2 = _rnd(rng, (N,), BF), _rnd(rng, (M, N), BF), _rnd(rng, (M, N), BF)
     valid = np.where(rng.random(M) < 0.8, 1, -1).astype(np.int32)
