@@ -147,11 +147,33 @@ def test_layout_too_large_for_workspace_is_rejected():
     stage.close()
 
 
-def test_stage_call_can_be_captured_in_a_graph_and_replays_identically():
+def _overlap_case(size):
+    """A small padded batch, whose bias and norm gradients are summed in one launch at the end of a layer, and one whose tensors are too
+    large for that (over 96 MiB): their column sums go to the stage's own stream."""
+    if size == "together":
+        cfg, lens, params, xs, dys = _small_case(True, n_seq=12)
+        return cfg, params, xs, dys, ds.dp_plan(lens, ds.make_cost_model(fixed=2_000_000), cfg["cap"], cfg["num_stages"])
+    cfg, lens = dict(n_layers=1, d_model=2048, n_heads=16, d_ff=512), np.asarray([450, 500] * 6)
+    params = wl.draw_params(wl.GPT_KEYS, 1, 2048, 512, seed=13, bf16=True)
+    xs, dys = wl.draw_rows(lens, 2048, seed=13, tag=3, bf16=True), wl.draw_rows(lens, 2048, seed=13, tag=5, bf16=True)
+    return cfg, params, xs, dys, ds.ds_layout_from_cuts(lens, list(range(0, 13, 2)))
+
+
+def _column_sum_launches(stage, call):
+    stage.profile_enable(True)
+    stage.profile_read()
+    call()
+    torch.cuda.synchronize()
+    n = stage.profile_read()["colsum"][1]
+    stage.profile_enable(False)
+    return n
+
+
+@pytest.mark.parametrize("size", ["together", "side stream"])
+def test_stage_call_can_be_captured_in_a_graph_and_replays_identically(size):
     """With its layout already bound (one eager call), stage_fwd_bwd only enqueues kernels: it can be captured in a
     HIP graph; every replay, with eager work and synchronisation in between, reproduces the eager result bit for bit."""
-    cfg, lens, params, xs, dys = _small_case(True, n_seq=12)
-    lo = ds.dp_plan(lens, ds.make_cost_model(fixed=2_000_000), cfg["cap"], cfg["num_stages"])
+    cfg, params, xs, dys, lo = _overlap_case(size)
     from helpers import params_to_dev, stream_from_seqs, zero_grads_like
     d = cfg["d_model"]
     stage = ds.Stage(ds.DS_MODEL_GPT, ds.DS_DTYPE_BF16, cfg["n_layers"], d, cfg["n_heads"], cfg["d_ff"],
@@ -172,6 +194,7 @@ def test_stage_call_can_be_captured_in_a_graph_and_replays_identically():
         call()
     torch.cuda.synchronize()
     ref = snapshot()
+    assert _column_sum_launches(stage, call) == cfg["n_layers"] * (1 if size == "together" else 4)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         call()
@@ -193,13 +216,13 @@ def test_stage_call_can_be_captured_in_a_graph_and_replays_identically():
     stage.close()
 
 
-def test_back_to_back_calls_on_a_caller_stream_without_host_synchronisation():
+@pytest.mark.parametrize("size", ["together", "side stream"])
+def test_back_to_back_calls_on_a_caller_stream_without_host_synchronisation(size):
     """The bias-gradient column sums run on a stream of the stage's own and are joined before a call returns control of
     the caller's stream: calls enqueued back to back on a stream of the caller's, with nothing in between, leave the same
     bits as one call followed by a synchronisation, and buffers the caller overwrites right behind a call are not read
     late."""
-    cfg, lens, params, xs, dys = _small_case(True, n_seq=12)
-    lo = ds.dp_plan(lens, ds.make_cost_model(fixed=2_000_000), cfg["cap"], cfg["num_stages"])
+    cfg, params, xs, dys, lo = _overlap_case(size)
     from helpers import params_to_dev, stream_from_seqs, zero_grads_like
     d = cfg["d_model"]
     stage = ds.Stage(ds.DS_MODEL_GPT, ds.DS_DTYPE_BF16, cfg["n_layers"], d, cfg["n_heads"], cfg["d_ff"],
@@ -212,6 +235,8 @@ def test_back_to_back_calls_on_a_caller_stream_without_host_synchronisation():
     ds.stage_fwd_bwd(stage, lo, w, x, dy, out, dx, grads, accumulate=False)
     torch.cuda.synchronize()
     ref = [out.clone(), dx.clone()] + [g[k].clone() for g in grads for k in g]
+    assert _column_sum_launches(stage, lambda: ds.stage_fwd_bwd(stage, lo, w, x, dy, out, dx, grads, accumulate=False)) == \
+        cfg["n_layers"] * (1 if size == "together" else 4)
     dy_copy = dy.clone()
     st = torch.cuda.Stream()
     torch.cuda.synchronize()
@@ -327,7 +352,7 @@ def test_launch_count_of_a_first_and_a_later_call(dtype_code):
 # one layer without padding rows: the gradient that the layer hands down overwrites the one it was given.  Rows up to and beyond
 # what one work-group walks, and beyond what is summed in one launch.
 @pytest.mark.parametrize("dtype_code,d,rows", [(ds.DS_DTYPE_F32, 256, 300), (ds.DS_DTYPE_BF16, 256, 300), (ds.DS_DTYPE_BF16, 256, 900),
-                                               (ds.DS_DTYPE_BF16, 1024, 9500)])
+                                               (ds.DS_DTYPE_BF16, 1024, 10500)])
 def test_gradient_returned_in_place(dtype_code, d, rows):
     """grad_in is grad_out: every gradient is the oracle's."""
     from helpers import params_to_dev, seqs_from_stream, stream_from_seqs, tdtype, to_np, zero_grads_like
@@ -446,3 +471,25 @@ def test_fp32_layer_of_more_than_65535_gradient_tiles():
         dev = (a.double() - b).abs()
         assert float(dev.norm() / b.norm()) <= TOL[ds.DS_DTYPE_F32], k
         assert float((dev / (8 * b.square().mean().sqrt() + b.abs())).max()) <= TOL[ds.DS_DTYPE_F32], k
+
+
+@pytest.mark.parametrize("rows,launches", [(10_900, 1), (11_500, 4)])
+def test_fp32_column_sums_together_and_on_the_side_stream(rows, launches):
+    """d = 256, d_ff = 1024 in fp32: the summed tensors take 9 216 bytes a row, below and above 96 MiB.  Every bias and norm gradient is
+    the oracle's."""
+    from helpers import params_to_dev, stream_from_seqs, to_np
+    d, F = 256, 1024
+    lens = np.asarray([100] * (rows // 100))
+    params = wl.draw_params(wl.GPT_KEYS, 1, d, F, seed=14)
+    xs, dys = wl.draw_rows(lens, d, seed=14, tag=3), wl.draw_rows(lens, d, seed=14, tag=5)
+    lo = ds.ds_layout_from_cuts(lens, list(range(len(lens) + 1)))
+    ref = ost.gpt_stage_fwd_bwd(xs, dys, params, 4)[2][0]
+    w = params_to_dev(params, torch.float32)
+    x, dy = stream_from_seqs(xs, lo, d, torch.float32), stream_from_seqs(dys, lo, d, torch.float32)
+    g = [{k: torch.full(v.shape, 3.0, device="cuda:0") for k, v in w[0].items()}]
+    stage = ds.Stage(ds.DS_MODEL_GPT, ds.DS_DTYPE_F32, 1, d, 4, F, max_rows=rows, max_seqs=len(lens))
+    out, dx = torch.empty_like(x), torch.empty_like(x)
+    assert _column_sum_launches(stage, lambda: ds.stage_fwd_bwd(stage, lo, w, x, dy, out, dx, g)) == launches
+    for k in ("b_qkv", "b_o", "b_1", "b_2", "ln1_g", "ln1_b", "ln2_g", "ln2_b"):
+        check(to_np(g[0][k]), ref[k], TOL[ds.DS_DTYPE_F32], k)
+    stage.close()
