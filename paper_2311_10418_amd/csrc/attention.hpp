@@ -28,6 +28,7 @@ struct AttnArgs {
     // DEVICE [n_heads][q_total_rows][8] bf16 each: {hi, lo, 0 x 6} splits of lse/scale and of delta, written by the
     // dQ kernel, fetched by the dK/dV kernel straight into LDS
     void *aug_lse, *aug_delta;
+    int32_t last_first;                               // fp32 forward and dQ kernels: a sequence's last block of queries first
 };
 
 size_t attn_scratch_bytes(int n_heads, int head_dim, int q_total_rows, int k_total_rows, int n_seq);

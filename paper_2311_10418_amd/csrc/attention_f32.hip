@@ -108,15 +108,20 @@ __device__ __forceinline__ void store_column(const f32x4_t (&acc)[HD / 16], floa
 __device__ __forceinline__ float groups_max(float v) { v = fmaxf(v, __shfl_xor(v, 16, 64)); return fmaxf(v, __shfl_xor(v, 32, 64)); }
 __device__ __forceinline__ float groups_sum(float v) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); }
 
-// A work-group's 64 columns.  The kernel lasts as long as the compute unit with the longest chains of tiles, so those start
-// first: sequences are taken last to first (a plan lists them by ascending length), and of every sequence the block with the
-// most tiles goes first, in the causal forward and dQ kernels the last one, in dK/dV the first.  Blocks are the fastest grid
-// dimension, and an odd number of them: work-groups go to the eight XCDs in turn, and with 8 blocks (512 tokens) every
-// longest chain of dK/dV was on the same one.  Forward and backward, us: 4 heads of 64, 7 684 tokens in sequences of up to 512 in any
-// order, 75 and 204 with 8 blocks, 48 and 130 with 9; head size 128, 129 and 397, 84 and 234; unmasked 75 and 213, 57 and 158; 8 heads,
-// 8 000 tokens, up to 2048 (32 and 33 blocks) 214 and 660, 213 and 662.  First blocks of all sequences before their second ones
-// (rows of heads x sequences, an odd multiple of 8 plus 1) is better there, 178 and 497, but not in a stage, whose sequences come
-// by length: two layers of d = 256, 64 sequences, 1 267 us, 1 227 in such rows, 1 125 as it is; 200 sequences 3 581, 2 965, 2 848.
+// A work-group's 64 columns.  The kernel lasts as long as the compute unit with the longest chains of tiles.  Sequences are taken
+// last to first (a plan lists them by ascending length), blocks are the fastest grid dimension, and work-groups go to the eight
+// XCDs in turn.
+//   dK/dV: the first block of every sequence has the longest chain and goes first, and the number of blocks per grid row is odd: with
+//   8 (512 tokens) all of those were on the same XCD.  Backward pass, us, causal: 8 heads of 64, 5 168 tokens in 46 sequences 216 -> 123;
+//   4 heads of 32, 14 575 tokens in 133 (16 blocks) 279 -> 120; 2 heads of 128, 7 254 tokens in 40 214 -> 159.
+//   Forward and dQ: a causal sequence's last block has the longest chain.  From 640 blocks on (2.5 per CU) they go last to first, in an
+//   odd number per grid row as well: forward, us, 8 heads of 64, 15 799 tokens (16 blocks) 176 -> 124; 4 heads of 128 unmasked, 10 673
+//   tokens 162 -> 99; 4 heads of 32, 14 575 tokens 62 -> 48.  Below that every block is resident at once, and it counts which other one a
+//   long chain shares its CU with: in ascending order the XCD with the last blocks has few others (2 heads of 96, 8 sequences of up to
+//   1024: 85 us, 120 last to first in an odd number; 8 heads of 32, 4 sequences of up to 1024: 40 and 48).
+//   Over 210 batches (2 to 8 heads, 500 to 16 700 tokens in any order) this takes 0.99 of the time of ascending, even rows forward (9
+//   more than 3 % longer, worst 15 %; without the line at 640 36, worst 40 %), and 0.88 backward, delta in the dQ kernel included.
+// A stage's sequences come by length: two layers of d = 256, 64 sequences, the same with and without the line (1 115 us).
 struct ColumnBlock { int s, h, first; };                              // first < 0: nothing to do
 
 __device__ __forceinline__ ColumnBlock column_block(const AttnArgs& a, const int32_t* __restrict__ len, bool last_first) {
@@ -125,7 +130,9 @@ __device__ __forceinline__ ColumnBlock column_block(const AttnArgs& a, const int
     if (b < n) c.first = 64 * (last_first ? n - 1 - b : b);
     return c;
 }
-dim3 column_grid(const AttnArgs& a, int max_len) { return dim3((max_len + 63) / 64 | 1, a.n_heads, a.n_seq); }
+constexpr int kManyBlocks = 640;
+bool many_blocks(const AttnArgs& a) { return (long long)a.n_heads * (a.q_total_rows / 64 + a.n_seq / 2) >= kManyBlocks; }
+dim3 column_grid(const AttnArgs& a, int max_len, bool odd) { return dim3((max_len + 63) / 64 | (odd ? 1 : 0), a.n_heads, a.n_seq); }
 
 // Causal masks and values that are not finite.  A score that a column does not see is replaced whatever it is; but the second
 // product contracts over whole blocks, with weight 0 for the rows a column does not see, and 0 x Inf would reach it.  So a
@@ -143,7 +150,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
     __shared__ float s_row[4][HD];
     __shared__ int s_by_rows;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), g = lane >> 4;
-    const ColumnBlock cb = column_block(a, a.q_len, a.mask);
+    const ColumnBlock cb = column_block(a, a.q_len, a.last_first);
     if (cb.first < 0) return;
     const int s = cb.s, h = cb.h, q0 = cb.first;
     const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
@@ -236,7 +243,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
     __shared__ float s_row[4][2][HD];
     __shared__ int s_by_rows;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), g = lane >> 4;
-    const ColumnBlock cb = column_block(a, a.q_len, a.mask);
+    const ColumnBlock cb = column_block(a, a.q_len, a.last_first);
     if (cb.first < 0) return;
     const int s = cb.s, h = cb.h, q0 = cb.first;
     const int ql = a.q_len[s], kl = a.k_len[s], hd = a.head_dim;
@@ -315,8 +322,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(AttnArgs a) {
 // Eight wavefronts: the first key blocks of a long causal sequence meet every query, and their work-groups set the
 // kernel's length.  Wavefronts w and w + 4 own the same 16 keys and take alternate 16-query blocks of every tile; their
 // accumulators are added through LDS at the end.  116 us with four wavefronts, 107 with eight, 86 with at most 128
-// registers (head size up to 64: two work-groups per CU), all three with eight blocks to a grid row.  At head size 64 that limit spills 2 registers here; the other
-// two kernels need 10 to 25 more than 128 there and lose with it (dQ 53 us instead of 42).
+// registers (head size up to 64: two work-groups per CU), all three with eight blocks to a grid row.  At head size 64 it takes 127;
+// the other two kernels need 20 to 35 more than 128 there and lose with that limit (dQ 53 us instead of 42).
 template <int HD>
 __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel(AttnArgs a) {
     typedef F32Tile<HD, 512> Tile;
@@ -421,10 +428,12 @@ __global__ __launch_bounds__(512, HD <= 64 ? 4 : 2) void attn_bwd_dkv_f32_kernel
 }
 
 template <int HD>
-ds_status bwd_f32(const AttnArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<HD>, column_grid(a, a.max_q_len), dim3(256), 0, st, a);
+ds_status bwd_f32(AttnArgs a, hipStream_t st) {
+    const bool many = many_blocks(a);
+    a.last_first = a.mask && many;
+    hipLaunchKernelGGL(attn_bwd_dq_f32_kernel<HD>, column_grid(a, a.max_q_len, many), dim3(256), 0, st, a);
     DS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(attn_bwd_dkv_f32_kernel<HD>, column_grid(a, a.max_k_len), dim3(512), 0, st, a);
+    hipLaunchKernelGGL(attn_bwd_dkv_f32_kernel<HD>, column_grid(a, a.max_k_len, true), dim3(512), 0, st, a);
     DS_LAUNCH_CHECK();
     return DS_OK;
 }
@@ -440,8 +449,11 @@ bool attn_f32_mfma_supported(const AttnArgs& a) {
     return !a.d_o || (al(a.d_o) && al(a.dq) && al(a.dk) && al(a.dv));
 }
 
-ds_status attn_fwd_f32_mfma(const AttnArgs& a, hipStream_t st) {
-    const dim3 grid = column_grid(a, a.max_q_len);
+ds_status attn_fwd_f32_mfma(const AttnArgs& args, hipStream_t st) {
+    AttnArgs a = args;
+    const bool many = many_blocks(a);
+    a.last_first = a.mask && many;
+    const dim3 grid = column_grid(a, a.max_q_len, many);
     if (a.head_dim <= 32) hipLaunchKernelGGL(attn_fwd_f32_kernel<32>, grid, dim3(256), 0, st, a);
     else if (a.head_dim <= 64) hipLaunchKernelGGL(attn_fwd_f32_kernel<64>, grid, dim3(256), 0, st, a);
     else if (a.head_dim <= 96) hipLaunchKernelGGL(attn_fwd_f32_kernel<96>, grid, dim3(256), 0, st, a);

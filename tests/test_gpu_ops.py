@@ -679,11 +679,14 @@ def test_attention_f32_matrix_cores(hd, causal):
     assert np.all(o_np[~touched] == 0) and np.all(g_np[~touched] == 0)
 
 
+# few blocks; 1 008 of them, which go last to first in the causal forward and dQ kernels
+@pytest.mark.parametrize("h,lens", [(2, [130, 0, 64, 1]), (8, [130, 0, 64, 1] + 80 * [65])])
 @pytest.mark.parametrize("causal", [True, False])
-def test_attention_f32_odd_and_even_numbers_of_blocks(causal):
-    """The grid has an odd number of 64-column blocks, whatever the longest sequence needs or the caller names: the same results."""
+def test_attention_f32_odd_and_even_numbers_of_blocks(causal, h, lens):
+    """The number of 64-column blocks per grid row may be more than the longest sequence needs, by the kernel's choice or the
+    caller's: the same results."""
     rng = np.random.default_rng(34)
-    h, hd, lens = 2, 64, [130, 0, 64, 1]
+    hd = 64
     d, T, rows, qkv, d_o = _varlen_case(rng, lens, h, hd, F32)
     dq, ddo = to_dev(qkv, F32), to_dev(d_o, F32)
     t_rows, t_lens = torch.from_numpy(rows).to(DEV), torch.tensor(lens, dtype=torch.int32, device=DEV)
