@@ -5,8 +5,8 @@
 // products are 6).
 //
 // Three tiles, all direct-to-LDS with the operand layouts of the large kernel, 64-deep K tiles in a ring of stages:
-//   0: 128 x 128, 8 wavefronts, 4 stages (128 KB: one work-group per CU): four of 64 x 64 twice, each four taking one of the two
-//      32-deep steps of every K tile (KS = 2); the halves of the contraction meet in LDS at the end
+//   0: 128 x 128, 8 wavefronts, 4 stages (128 KB: one work-group per CU).  8 of 64 x 32 or, for long loops, four of 64 x 64 twice, each
+//      four taking one of the two 32-deep steps of every K tile (KS = 2); the halves of the contraction meet in LDS at the end
 //   3: 128 x 128, 8 wavefronts of 64 x 32, 2 stages (64 KB: two per CU)
 //   1: 128 x  64, 8 wavefronts of 32 x 32, 3 stages ( 72 KB: two per CU)
 //   2:  64 x  64, 4 wavefronts of 32 x 32, 3 stages ( 48 KB: three per CU)
@@ -16,9 +16,9 @@
 // 0.49 us for kind 0, 0.32 and 0.20 for 1 and 2, for kind 3 0.39 while the chip is not full and 0.55 - 0.62 per tile when every CU
 // works on two.  Four wavefronts of 64 x 64 alone on the 128 x 128 tile are slower at every shape tried (N = 2048, K = 8192,
 // M = 1757: 89 us and, with 32-deep tiles and two work-groups per CU, 73, against 60); eight of them, two to a SIMD, with half the
-// K steps each read a third less from LDS than eight of 64 x 32 and have one burst of 16 MFMAs per barrier: 1024 x 4096 TN over
-// 4173 tokens, operands warm, 55 -> 51 us, NT 4096 x 1024 x 4096 43.2 -> 40.6; from memory as before (54, 52): there the transfers are
-// the limit (timing build without the products 52 and 48).  At 128 x 64 the same changes nothing.
+// K steps each read a third less from LDS than eight of 64 x 32 and have one burst of 16 MFMAs per barrier: 4096 x 1024 TN over
+// 4173 tokens, operands warm, 50.4 -> 44.4 us, from memory as before (53.3): there the transfers are the limit (timing build without
+// the products 52).  At 128 x 64 the same changes nothing.
 //
 // Which one: the tile and split count with the smallest estimate (pick_gemm_tile), compared with the same kind of
 // estimate for the large kernel.  Measured, 256 x 256 kernel -> this, us (M, N, K; ds_gemm_ws on an idle card):
@@ -327,24 +327,30 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_bf16_tile_kernel(int M
     }
 }
 
-struct TileShape { int bm, bn, waves, stages, ks; double step, fixed; };
+struct TileShape { int bm, bn, waves, stages; double step, fixed; };
 // step: microseconds per K tile of a CU that has one tile; fixed: around the K loop
 constexpr int kKinds = 4;
-constexpr TileShape kShapes[kKinds] = {{128, 128, 8, 4, 2, 0.49, 3.0}, {128, 64, 8, 3, 1, 0.32, 2.5}, {64, 64, 4, 3, 1, 0.20, 2.5}, {128, 128, 8, 2, 1, 0.39, 3.0}};
+constexpr TileShape kShapes[kKinds] = {{128, 128, 8, 4, 0.49, 3.0}, {128, 64, 8, 3, 0.32, 2.5}, {64, 64, 4, 3, 0.20, 2.5}, {128, 128, 8, 2, 0.39, 3.0}};
 constexpr double kBusyStep3 = 0.62;                  // kind 3, per tile, when every CU works on two (0.55 on operands that are warm in L2)
 constexpr double kBusyStep0 = 0.64;                  // kind 0, per tile, several of them one after the other
 constexpr double kLoneStep1 = 0.36, kLoneStep2 = 0.24;                // TN form, one tile per CU: nothing covers its waits
 constexpr double kColdStep0Nt = 0.51, kColdStep0Tn = 0.55;           // kind 0, operands from memory
 
-template <int EPI, bool TNF, int KIND, int WM, int WN>
+// Kind 0 with two groups of wavefronts (KS = 2) where every work-group has at least 32 K tiles.  Meeting in LDS at the end costs about a
+// microsecond, which shorter loops do not earn: two groups / one, geometric means of 10 to 21 NT shapes that go to this tile, operands
+// from memory and warm, K = 256 1.10 and 1.04, 512 1.05 and 0.99, 768 1.05 and 1.01, 1024 1.04 and 1.00, 1536 1.03 and 0.97, 2048
+// 1.02 and 0.95, 3072 1.02 and 0.93, 4096 1.01 and 0.92, 8192 1.01 and 0.92.
+bool two_step_groups(int K, int splits) { return ((K + T_KD - 1) / T_KD + splits - 1) / splits >= 32; }
+
+template <int EPI, bool TNF, int KIND, int WM, int WN, int KS = 1>
 ds_status launch_kind(int splits, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
                       hipStream_t st) {
     constexpr TileShape s = kShapes[KIND];
     constexpr int ring = s.stages * (s.bm + s.bn) * T_KD * 2, staging = s.waves * 32 * (s.bn / WN + 4) * 4;
     constexpr int smem = ring > staging ? ring : staging;
-    static_assert(WM * WN * s.ks == s.waves, "wavefront grid");
+    static_assert(WM * WN * KS == s.waves, "wavefront grid");
     static bool attr_set = false;
-    auto kern = gemm_bf16_tile_kernel<EPI, TNF, s.bm, s.bn, WM, WN, s.stages, s.ks>;
+    auto kern = gemm_bf16_tile_kernel<EPI, TNF, s.bm, s.bn, WM, WN, s.stages, KS>;
     if (!attr_set) {
         DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
         attr_set = true;
@@ -358,13 +364,13 @@ ds_status launch_kind(int splits, int M, int N, int K, const void* A, const void
     return DS_OK;
 }
 
-template <int KIND, int WM, int WN>
+template <int KIND, int WM, int WN, int KS = 1>
 ds_status launch_group_kind(const TnGroup& g, int blocks, hipStream_t st) {
     constexpr TileShape s = kShapes[KIND];
     constexpr int ring = s.stages * (s.bm + s.bn) * T_KD * 2, staging = s.waves * 32 * (s.bn / WN + 4) * 4;
     constexpr int smem = ring > staging ? ring : staging;
     static bool attr_set = false;
-    auto kern = gemm_bf16_tile_kernel<DS_EPI_ACC32, true, s.bm, s.bn, WM, WN, s.stages, s.ks, true>;
+    auto kern = gemm_bf16_tile_kernel<DS_EPI_ACC32, true, s.bm, s.bn, WM, WN, s.stages, KS, true>;
     if (!attr_set) {
         DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
         attr_set = true;
@@ -380,7 +386,8 @@ ds_status launch_group_kind(const TnGroup& g, int blocks, hipStream_t st) {
 template <int EPI, bool TNF>
 ds_status launch_form(const TilePick& k, int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
                       hipStream_t st) {
-    if (k.kind == 0) return launch_kind<EPI, TNF, 0, 2, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
+    if (k.kind == 0 && two_step_groups(K, k.splits)) return launch_kind<EPI, TNF, 0, 2, 2, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
+    if (k.kind == 0) return launch_kind<EPI, TNF, 0, 2, 4>(k.splits, M, N, K, A, B, C, p, split_ws, st);
     if (k.kind == 3) return launch_kind<EPI, TNF, 3, 2, 4>(k.splits, M, N, K, A, B, C, p, split_ws, st);
     if (k.kind == 1) return launch_kind<EPI, TNF, 1, 4, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
     return launch_kind<EPI, TNF, 2, 2, 2>(k.splits, M, N, K, A, B, C, p, split_ws, st);
@@ -515,7 +522,9 @@ ds_status launch_tn_group(const TnPick& pick, TnGroup& g, hipStream_t st) {
         if (blocks > (1 << 22)) return DS_EOVERFLOW;        // work-items of a grid: 32 bits (2^34 outputs of the smallest tile)
     }
     switch (pick.kind) {
-    case 0: return launch_group_kind<0, 2, 2>(g, (int)blocks, st);
+    case 0:
+        if (two_step_groups(g.K, 1)) return launch_group_kind<0, 2, 2, 2>(g, (int)blocks, st);
+        return launch_group_kind<0, 2, 4>(g, (int)blocks, st);
     case 1: return launch_group_kind<1, 4, 2>(g, (int)blocks, st);
     case 2: return launch_group_kind<2, 2, 2>(g, (int)blocks, st);
     case 3: return launch_group_kind<3, 2, 4>(g, (int)blocks, st);

@@ -965,6 +965,8 @@ def test_attention_bf16_hidden_half_blocks_with_values_that_are_not_finite(hd):
     (129, 5632, 64, 0), (129, 5632, 128, 0), (129, 5632, 320, 0), (256, 8192, 320, 0), (641, 512, 4096, 1 << 22),
     # 128 x 128, four stages
     (383, 5632, 320, 0), (384, 5632, 320, 0), (385, 5632, 320, 0), (385, 7680, 256, 0), (129, 2304, 8192, 1 << 22),
+    # the same with two groups of wavefronts: 32, 33 and, split, more K tiles
+    (383, 5632, 2048, 0), (385, 5632, 2112, 0), (129, 2304, 16384, 1 << 22),
     # 128 x 128, two stages
     (1537, 3840, 128, 0), (1537, 3840, 192, 0), (767, 6144, 320, 0), (768, 6144, 320, 0), (769, 6144, 320, 0), (756, 6144, 2048, 0),
     (385, 4864, 8192, 1 << 22),
@@ -989,6 +991,8 @@ def test_gemm_every_macro_tile_nt(M, N, K, ws_floats):
     # 128 x 64 tiles: one and three (ragged) K tiles, split; 128 x 128 with four stages, whole and split; with two, two to four K tiles
     # (the first two of these when they add, else 256 x 256)
     (256, 4352, 33, 0), (256, 4352, 129, 0), (256, 1536, 6000, 1 << 22), (1792, 1792, 577, 0), (256, 2816, 9001, 1 << 22),
+    # 128 x 128 with two groups of wavefronts: 33 (the last one ragged) and, split, more K tiles
+    (1792, 1792, 2049, 0), (256, 2816, 20001, 1 << 22),
     (2560, 3328, 129, 0), (2560, 3328, 200, 0), (2560, 6656, 65, 0),
     # 256 x 256 (32-deep K tiles): one, a ragged few, ranges of the contraction, whole tiles and a split remainder
     (10240, 3328, 1, 0), (10240, 3328, 97, 0), (256, 5632, 12000, 1 << 24), (10240, 3328, 250, 1 << 22)])
