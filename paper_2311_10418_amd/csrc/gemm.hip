@@ -897,12 +897,17 @@ static NtChoice choose_kernel(bool tn, int epi, int M, int N, int K, size_t wsf,
 // a second launch costs then is not in the estimates.  Of 292 shapes (N = 256 .. 8192, 1 to 8 rounds, operands from memory, plain and
 // residual outputs) for which they say two, two launches / one, geometric mean and worst: K = 64 and 128, 1.06 and 1.41; K = 256 .. 448
 // two rounds 0.95 and 1.04 (the exception below), one round 0.98 and 1.08, more 1.03 and 1.25; K = 512 and more 0.91 and 1.05.
+// Behind one round, rows that fill more than a tenth of another are not worth it either below K = 1536: half a launch more of tiles that
+// read and write as much as they multiply.  Of another 220 (all of K >= 512, remainders of any size, epilogues with up to two more
+// operands and results), 46 such, from memory and warm: 0.97 and 0.98, worst 1.13 and 1.11; the rest 0.93 and 0.90, worst 1.08 and 1.00.
 static int rows_of_whole_rounds(int epi, int M, int N, int K, size_t wsf, bool colsum, int accumulate, double one) {
     const int n_cu = gemm_cu_count(), tiles_n = N / BN;
     const long long rounds = (long long)((M + BM - 1) / BM) * tiles_n / n_cu;
     const long long rows = rounds * n_cu / tiles_n * BM;
     if (rounds < 1 || rows <= 0 || rows >= M) return 0;
     if (K < 512 && (rounds != 2 || K < 256)) return 0;
+    const long long behind = (long long)((M + BM - 1) / BM) * tiles_n - rows / BM * tiles_n;
+    if (rounds == 1 && K < 1536 && 10 * behind > n_cu) return 0;
     const double two = choose_kernel(false, epi, (int)rows, N, K, wsf, colsum, accumulate).cost + 1 +
                        choose_kernel(false, epi, M - (int)rows, N, K, wsf, colsum, accumulate).cost;
     return two < 0.97 * one ? (int)rows : 0;
