@@ -168,7 +168,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
         A = reinterpret_cast<const bf16_t*>(grp.p[i].A);
         B = reinterpret_cast<const bf16_t*>(grp.p[i].B);
         C = reinterpret_cast<bf16_t*>(grp.p[i].C);
-        // one block of the workspace per (tile, split): tile_index * splits + split, tiles counted over the whole group
+        // one block of the workspace per (split, tile): the problem's first one + split * its tiles + tile
         if (splits > 1) split_ws = grp.block(grp.first[i] + logical);
         tiles_m = M / BM;
         tiles_n = N / BN;
@@ -506,8 +506,13 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
 #pragma unroll
             for (int i = 0; i < TM; ++i) prefetch_pass(i);
         }
-        // accumulation: what is added to, fetched one pass ahead (the four gradients of a layer at d = 2048, d_ff = 8192 over 1 797
-        // tokens: 252 -> 242 us; streaming stores and lines requested at the start of the K loop: slower)
+        // Accumulation: what is added to, fetched one pass ahead (four gradients of a layer together, d = 2048, d_ff = 8192, 1 797 tokens:
+        // 252 -> 242 us; one gradient of 8192 x 2048 over 1 797 tokens 86 -> 77, 4096 x 16384 over 2 048 360 -> 331; streaming stores and lines
+        // requested at the start of the K loop: slower).  It takes the TN kernel from 222 to 232 registers, so that a wavefront of the column
+        // sums on the stage's side stream no longer fits beside two of these: those sums wait for the gaps between launches (their
+        // group's time at d = 2048, 65 536 tokens 4 -> 20 ms in four calls), and the calls take the same time (35.98 ms; d = 4096: 137.7).
+        // Eight or 16 registers of prefetch (221 in all) let the sums run beside, and the calls take 0.2 to 1 % longer, the adding
+        // gradients 2 to 5 %.
         constexpr bool PRE_OLD = EPI == DS_EPI_ACC32 && TNF;
         const bool adds = PRE_OLD && direct && p.accumulate;
         float old[2][NPSS][8];

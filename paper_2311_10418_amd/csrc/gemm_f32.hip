@@ -352,7 +352,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(int M, int N, in
         C = reinterpret_cast<float*>(grp.p[i].C);
         lda = M;
         ldb = N;
-        // one block of the workspace per (tile, split), as in the bf16 kernels
+        // one block of the workspace per (split, tile): the problem's first one + split * its tiles + tile
         if (grp.splits > 1) partial = grp.block(grp.first[i] + l);
         const int tn = (N + BN - 1) / BN, tiles = (M + BM - 1) / BM * tn;
         split = l / tiles;
@@ -622,6 +622,8 @@ ds_status launch_gemm_f32_mfma(int32_t ta, int32_t tb, int32_t M, int32_t N, int
 
 // K loops per tile: as many as give the fewest K tiles, one after another, at two work-groups per CU (0.84 us per K tile of the
 // two, 8 around a loop), 5 for the launch that adds up the partial sums and their round trip at 4 TB/s; at least 8 K tiles each.
+// Always one launch: a stage call with it takes 0.57 to 0.96 of the time with one launch per gradient at all of 51 sizes (d = 128 ..
+// 1024, 256 to 40 000 tokens), 0.85 in the mean.
 TnPick pick_tn_group_f32(const TnGroup& g) {
     const int steps = (g.K + F_BK - 1) / F_BK, slots = 2 * gemm_cu_count();
     long long tiles = 0;

@@ -275,7 +275,7 @@ static ds_status plan_impl(const int32_t* len, const int32_t* len_tgt, int32_t n
         // relaxes the slices it adds and, from positions whose f has fallen, the slices admitted before, in ascending order of
         // position.  That gives what scanning every admitted slice again for every candidate gives, ties (the smallest split
         // index among equal sums) included: a slice that attains a NEW minimum has itself just been added or had its f fall,
-        // and among slices that attain the old one only such slices can be new.  At 208 samples and 13 K candidates the scan
+        // and among slices that attain the old one only such slices can be new.  At 208 samples (11 923 slices) the scan
         // took 46 ms.
         struct Edge { int64_t t; int32_t j; };
         std::vector<std::vector<Edge>> admitted(n);                   // by start position

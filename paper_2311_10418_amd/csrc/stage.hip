@@ -86,9 +86,11 @@ struct ds_stage {
          *dx1 = nullptr, *dx2 = nullptr, *d_o = nullptr, *dqkv = nullptr, *dqc = nullptr, *dkvc = nullptr, *de = nullptr,
          *deB = nullptr;
     float *delta = nullptr, *partial = nullptr, *split_ws = nullptr;
-    // Bias-gradient column sums (decoder-only stage) run on a stream of their own beside the GEMMs that follow their
-    // producer: nothing on the main stream reads what they write, so they only have to be back before the tensor they
-    // read is overwritten (joined at the end of every layer's backward pass).  Same priority as the caller's stream.
+    // Bias-gradient column sums (decoder-only stage, where a layer's are too large to go out together) run on a stream of their own:
+    // nothing on the main stream reads what they write, so they only have to be back before the tensor they read is
+    // overwritten (joined at the end of every layer's backward pass).  They run beside the input-gradient GEMMs and in the gaps
+    // between launches; beside the 256 x 256 weight-gradient kernel there are no registers for them.  Same priority as the
+    // caller's stream.
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     float* partial_side = nullptr;     // their partial sums (the main stream's `partial` belongs to the norm kernels)
