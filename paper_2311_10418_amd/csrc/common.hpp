@@ -42,13 +42,6 @@ template <> struct Vec8<float> {
         *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
         *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
     }
-    // streaming store: the line is not kept in L2 (outputs far larger than the cache would only evict operands
-    // that other work-groups are about to read again)
-    static __device__ __forceinline__ void store_nt(float* p, const float (&v)[8]) {
-        const f32x4_t a = {v[0], v[1], v[2], v[3]}, b = {v[4], v[5], v[6], v[7]};
-        __builtin_nontemporal_store(a, reinterpret_cast<f32x4_t*>(p));
-        __builtin_nontemporal_store(b, reinterpret_cast<f32x4_t*>(p + 4));
-    }
 };
 template <> struct Vec8<bf16_t> {
     static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) {
@@ -61,12 +54,6 @@ template <> struct Vec8<bf16_t> {
 #pragma unroll
         for (int i = 0; i < 8; ++i) a[i] = (bf16_t)v[i];
         *reinterpret_cast<bf16x8_t*>(p) = a;
-    }
-    static __device__ __forceinline__ void store_nt(bf16_t* p, const float (&v)[8]) {
-        bf16x8_t a;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] = (bf16_t)v[i];
-        __builtin_nontemporal_store(a, reinterpret_cast<bf16x8_t*>(p));
     }
 };
 
@@ -98,14 +85,14 @@ __device__ __forceinline__ void gelu_and_grad_f(float z, float& gelu, float& gra
     const float w = z * z;
     const float s = gelu_sigmoid(z, w);
     gelu = z * s;
-    grad = s * __builtin_fmaf(z * __builtin_fmaf(c6a, w, c2), 1.0f - s, 1.0f);
+    grad = __builtin_fmaf(__builtin_fmaf(-s, s, s), z * __builtin_fmaf(c6a, w, c2), s);
 }
 __device__ __forceinline__ float gelu_grad_f(float z) {
     constexpr float c2 = 2.0f * 0.7978845608028654f, c6a = 3.0f * 0.044715f * c2;
     const float w = z * z;
     const float s = gelu_sigmoid(z, w);
     const float zdu = z * __builtin_fmaf(c6a, w, c2);                                // z * 2 u'
-    return s * __builtin_fmaf(zdu, 1.0f - s, 1.0f);
+    return __builtin_fmaf(__builtin_fmaf(-s, s, s), zdu, s);
 }
 
 // One direct global -> LDS transfer, 16 bytes per lane (global_load_lds_dwordx4): the wavefront's 64 chunks land at
@@ -209,6 +196,31 @@ __device__ __forceinline__ i32x4_t make_raw_buffer(const void* base, uint32_t by
     d[3] = 0x00020000;
     return d;
 }
+// The same for loads and stores that the compiler sees (and counts): 16 or 4 bytes per lane at byte offset `off`; beyond the end
+// zeros are read and nothing is written.
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+__device__ __forceinline__ buffer_t make_buffer(const void* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+template <class T> __device__ __forceinline__ void buffer_load16(buffer_t b, uint32_t off, T& dst) {
+    static_assert(sizeof(T) == 16, "16 bytes per lane");
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0);
+    __builtin_memcpy(&dst, &v, 16);
+}
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u32x2_t buffer_load8(buffer_t b, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0); }
+__device__ __forceinline__ f32x4_t bf16x4_to_f32(u32x2_t v) {
+    return f32x4_t{__builtin_bit_cast(float, v[0] << 16), __builtin_bit_cast(float, v[0] & 0xFFFF0000u), __builtin_bit_cast(float, v[1] << 16),
+                   __builtin_bit_cast(float, v[1] & 0xFFFF0000u)};
+}
+__device__ __forceinline__ int32_t buffer_load4(buffer_t b, uint32_t off) { return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0); }
+template <class T> __device__ __forceinline__ void buffer_store16(const T& v, buffer_t b, uint32_t off) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), b, off, 0, 0);
+}
+template <class T> __device__ __forceinline__ void buffer_store16_nt(const T& v, buffer_t b, uint32_t off) {       // streaming
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), b, off, 0, 2);
+}
 // Four direct transfers of 64 x 16 bytes under one M0, two through each of two buffers: they land at lds_addr,
 // + 1024, + 2048, + 3072.  As with lds_dma16_group the immediate offsets (0, 1024, 2048, 3072) are added to the
 // memory offsets too, range check included: the caller builds the buffers 3072 bytes early and 3072 bytes longer
@@ -222,6 +234,14 @@ __device__ __forceinline__ void lds_dma16_buffers_2x2(i32x4_t buf_a, uint32_t a0
                  "buffer_load_dwordx4 %2, %5, 0 offen offset:2048 lds\n\t"
                  "buffer_load_dwordx4 %3, %5, 0 offen offset:3072 lds"
                  : : "v"(a0), "v"(a1), "v"(b0), "v"(b1), "s"(buf_a), "s"(buf_b), "s"(m0v) : "memory", "m0");
+}
+
+// One direct transfer of 64 x 16 bytes through a raw buffer, with an M0 of its own: for a wavefront that issues its transfers singly,
+// several MFMAs apart, where no write of M0 has to wait for the transfer before it.  Lanes whose offset is at or beyond the
+// buffer's length bring zeros.
+__device__ __forceinline__ void lds_dma16_buffer(i32x4_t buf, uint32_t lane_off, uint32_t lds_addr) {
+    const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_addr);
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(lane_off), "s"(buf), "s"(m0v) : "memory", "m0");
 }
 
 // N direct transfers of 64 x 16 bytes under one M0 through ONE raw buffer (see lds_dma16_buffers_2x2: the buffer starts

@@ -84,23 +84,33 @@ constexpr int BM = 256, BN = 256, BK = 64;
 // NT form: C[M,N] = A[M,K] * B[N,K]^T, both operands k-contiguous (K % 64 == 0, N % 256 == 0).
 // TN form: C[M,N] = A[K,M]^T * B[K,N], both operands with the contraction index as the row (weight gradients).
 //
-// 256x256 macro tile, 8 wavefronts (2 per SIMD) in a 2x4 arrangement, each owning a 128x64 accumulator block:
-// 8 x 4 blocks of v_mfma_f32_16x16x32_bf16, 128 accumulator registers.  Operands go global -> LDS directly
-// (global_load_lds_dwordx4): no staging registers, no LDS write instructions.  A wavefront instruction deposits
-// 64 x 16 bytes at consecutive LDS addresses; the XOR swizzle that makes the fragment reads conflict-free is
-// obtained by choosing WHICH global chunk each lane fetches.  NT: 64-deep K tiles (whole 128-byte lines per row),
-// two 64 KB stages, one barrier per tile.  TN: 32 k-rows of 512 bytes per tile, ring of 4 stages of 32 KB, three
-// tiles in flight while one is consumed, fragments through the LDS transpose read.  Tile indices past the end
-// are clamped (a few redundant loads into a free stage) so that the wait counts are the same at every step.
+// 256x256 macro tile, 4 wavefronts (one per SIMD) in a 2x2 arrangement, each owning a 128x128 accumulator block: 8 x 8
+// blocks of v_mfma_f32_16x16x32_bf16, 256 accumulator registers of the 512 a lone wavefront has.  Operands go global ->
+// LDS directly (no staging registers, no LDS write instructions): a wavefront instruction deposits 64 x 16 bytes at
+// consecutive LDS addresses, and the XOR swizzle that makes the fragment reads conflict-free is obtained by choosing
+// WHICH global chunk each lane fetches.  K tiles are 64 deep; an operand's part of one is a unit of 32 KB.
 //
-// Why 8 wavefronts: measured on MI355X, one 4-wavefront work-group cannot pull more than about 40-50 GB/s from
-// L2 however many loads it keeps in flight, which is what a 256x256x(bf16) tile needs at full MFMA rate; the rate
-// scales with the number of wavefronts on the CU; and a single wavefront per SIMD cannot keep the matrix pipe
-// busy with the 16x16x32 shape (it needs two issuing).
-constexpr int NT_DK = 32, NT_NS = 4, NT_HALF = 256 * NT_DK * 2, NT_STAGE = 2 * NT_HALF;
-constexpr int NT_WM = 2, NT_WN = 4;             // wavefront grid of a work-group: 2 x 4, each wavefront 128 x 64
-// how a K tile's direct-load instructions are spread over the MFMA groups of the main loops (see the loops)
-constexpr int NT_G0 = 1, NT_G1 = 1, NT_G2 = 0;       // (in transfer groups: the A part, the B part)
+// LDS holds a ring of five units (160 KB): while tile t is multiplied (units A(t), B(t)), A(t+1), B(t+1) and A(t+2) have
+// landed or are on their way.  A tile is two steps of 64 MFMAs, the fragments of a step read during the one before it;
+// the one barrier of a tile stands between its steps, where every fragment of it is in registers, so that its two units
+// are free for B(t+2) and A(t+3).  Between its MFMAs a wavefront issues one fragment read every three and, singly, the
+// eight transfers of B at every fourth and those of A at every eighth, over both steps.
+//
+// What it is bound by: the power limit on long launches (without transfers and reads the same loop reaches 1 850 to 1 970
+// TFLOP/s on random operands), short K loops by what stands around them.  Why this shape: with eight wavefronts of 128 x 64
+// in a ring of two 64 KB stages (the kernel before this one) every K tile took 192 KB of fragment reads from LDS, here 128,
+// and a transfer had three quarters of a tile to arrive, here one to two and a half tiles.  Before -> after, us, operands from memory:
+// NT 4096 x 4096 x 4096 113 -> 97, 65 582 x 2048 x 8192 with a residual 1 600 -> 1 530, 32 768 x 4096 x 16 384 3 224 -> 2 952, 65 629 x 1024 x
+// 1024 193 -> 181; TN 8192 x 2048 x 65 582 1 606 -> 1 461, 4096 x 16 384 x 32 768 3 169 -> 2 985, 2048 x 6144 x 65 582 1 358 -> 1 240.  The
+// price is one wavefront per SIMD in the epilogue, where vector instructions issue every 5.3 clocks instead of every 2.7 to 4.2: 65 629 x
+// 2816 x 1024 with the gated GELU 490 -> 506, with its derivative 565 -> 575, 65 582 x 8192 x 2048 with GELU and derivative 1 957 -> 1 942.
+// Tried: two 64 KB stages with this wavefront shape (4096 x 4096 x 16 384 519 us, ring 378); all transfers right behind the
+// barrier, one every two MFMAs (5 to 8 % slower); 32x32x16 instructions (5 to 9 % slower); 256 x 128 tiles, two work-groups
+// of four wavefronts to a CU (15 to 20 % slower: half as many transfers again).
+constexpr int UNIT = 256 * BK * 2, RING = 5 * UNIT;      // one operand's K tile in LDS; the whole ring
+constexpr int NT_WM = 2;                        // rows of wavefronts in a work-group
+constexpr int NT_DB = 4, NT_DA = 8;             // a transfer of B every NT_DB, of A every NT_DA MFMAs
+constexpr int NT_A1 = (64 - 8 * NT_DB - 2) / NT_DA + 1;         // transfers of A in a tile's second step; the rest go in the first step of the next
 // tile number -> tile coordinates: groups of NT_GROUP tile rows, column-major inside a group
 constexpr int NT_GROUP = 4;
 __host__ __device__ __forceinline__ void nt_tile_coords(int logical, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
@@ -113,44 +123,35 @@ __host__ __device__ __forceinline__ void nt_tile_coords(int logical, int tiles_m
     tile_n = in_group / gs;
 }
 
-// WM x WN wavefronts per work-group; each owns a (256/WM) x (256/WN) accumulator block.
-//
-// TN form (weight gradients): C[M,N] = A[K,M]^T * B[K,N], both operands row-major with the
-// contraction index (tokens) as the ROW.  A K tile is then 32 rows of 512 contiguous bytes per
-// operand, fetched as whole rows, and the MFMA fragments (8 consecutive k for one m or n per lane)
-// come out of LDS through the transpose read ds_read_b64_tr_b16, 4 k-rows per read; both operands
-// use the same k order, so the contraction is unchanged.  K may be ragged: rows past the end read
-// zeros.  This form needs no transposed copies of the activations.
+// TN form (weight gradients): a K tile is 64 rows of 512 contiguous bytes per operand, fetched as whole rows, and the
+// MFMA fragments (8 consecutive k for one m or n per lane) come out of LDS through the transpose read
+// ds_read_b64_tr_b16, 4 k-rows per read; both operands use the same k order, so the contraction is unchanged.  K may be
+// ragged: rows past the end read zeros.  This form needs no transposed copies of the activations.
 //
 // PS (persistent form, NT only, no uniform split-K): the first ps_wgs work-groups, one per compute unit, stay resident
 // and take the n_main unsplit tiles one after another; the tail pieces are ordinary work-groups behind them.  The
 // tiles keep their XCD-contiguous numbering: work-group w serves the run of XCD w % 8, starts with tile w / 8 of that
 // run and draws every further one from that XCD's counter (ps_ctr[xcd], one atomic per tile, issued a whole main
 // loop before its result is needed), so a faster compute unit takes more tiles, as under the hardware dispatcher.
-// What persistence buys: the first K tile of the NEXT tile is requested before the epilogue of the current one
-// starts (into stage 0, while the epilogue stages through LDS above it), so neither the latency of that first fetch
+// What persistence buys: the first two K tiles of the NEXT tile are requested before the epilogue of the current one
+// starts (into units 0 to 3, while the epilogue stages through unit 4), so neither the latency of that first fetch
 // nor the end of one work-group and the start of the next leaves the matrix cores idle.  The last work-group to
 // finish puts the counters back to zero (ps_ctr[8] counts the finished ones).
 //
 // GRP (TN form): the work-groups of several weight gradients over the same K rows (grp), problem after problem.
-template <int EPI, int WM, int WN, bool TNF, bool PS, bool GRP = false>
-__global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
-                                                                       const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
-                                                                       int tiles_m, int tiles_n, int splits,
-                                                                       int n_main, int tail_splits,
-                                                                       float* __restrict__ split_ws, GemmEpi p,
-                                                                       int ps_wgs, int* __restrict__ ps_ctr,
-                                                                       std::conditional_t<GRP, TnGroup, NoGroup> grp) {
+template <int EPI, bool TNF, bool PS, bool GRP = false>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
+                                                              const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
+                                                              int tiles_m, int tiles_n, int splits,
+                                                              int n_main, int tail_splits,
+                                                              float* __restrict__ split_ws, GemmEpi p,
+                                                              int ps_wgs, int* __restrict__ ps_ctr,
+                                                              std::conditional_t<GRP, TnGroup, NoGroup> grp) {
     static_assert(!(PS && TNF), "the persistent form exists for the NT kernel only");
     static_assert(!GRP || (TNF && EPI == DS_EPI_ACC32), "groups are of weight gradients");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int NW = WM * WN;                    // wavefronts
-    constexpr int TM = 256 / WM / 32, TN = 256 / WN / 32;   // 32x32 MFMA tiles per wavefront
-    static_assert(16 % NW == 0, "wavefront count must divide 16");
-    constexpr int STG_LD = TN * 32 + 4;            // fp32 row stride of the epilogue staging block
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6;
-    const int wm = wave / WN, wn = wave % WN;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
 
     // ---- work-group id -> (tile, split).  Two regimes share the kernel:
     //  * uniform split-K (weight gradients): every tile is cut into `splits` K ranges, partial sums go to split_ws
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
     //  * tail split-K (everything else): the first n_main tiles, a whole number of rounds over the compute units,
     //    run unsplit; each of the remaining tiles is cut into tail_splits K ranges so that the last, partly filled
     //    round costs 1/tail_splits of a round; their partial sums go to split_ws as [tail tile][split][256][256].
-    // Tiles are numbered so that each XCD works on contiguous runs, in groups of 8 tile rows (L2 reuse).
+    // Tiles are numbered so that each XCD works on contiguous runs, in groups of 4 tile rows (L2 reuse).
     int logical, split, nsplit;
     if constexpr (GRP) {
         logical = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -206,436 +207,374 @@ __global__ __launch_bounds__(WM * WN * 64, 1) void gemm_bf16_nt_kernel(int M, in
         }
     }
 
-    // K tiles: TN form 32 k-rows of 512 bytes, ring of 4 stages; NT form 64 k (one whole 128-byte line per row and
-    // request, which is what the L2 serves at full rate), 2 stages
-    constexpr int DK = TNF ? NT_DK : 64;
-    constexpr int NS = TNF ? NT_NS : 2;
-    constexpr int HALF = 256 * DK * 2, STAGE = 2 * HALF;
-    constexpr int LPW = HALF / 1024 / NW;          // direct-load instructions per operand per wavefront per K tile
-    static_assert(NS * STAGE == NT_NS * NT_STAGE, "both forms use the same 128 KB of LDS");
-    const int nt_total = TNF ? (K + DK - 1) / DK : K / DK;
+    const int nt_total = TNF ? (K + BK - 1) / BK : K / BK;
     const int per_split = (nt_total + nsplit - 1) / nsplit;
-    const int t_begin = split * per_split;
-    const int t_end = (t_begin + per_split) < nt_total ? (t_begin + per_split) : nt_total;
+    // (divisions go through vector registers: what steers the K loop comes back to scalar ones)
+    const int t_begin = __builtin_amdgcn_readfirstlane(split * per_split);
+    const int t_end = __builtin_amdgcn_readfirstlane((t_begin + per_split) < nt_total ? (t_begin + per_split) : nt_total);
 
-    // accumulators: TM16 x TN16 blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16: at the chip's power limit this shape
-    // sustains about a sixth more than 32x32x16 on random operands, at the same LDS traffic per flop)
-    constexpr int TM16 = 2 * TM, TN16 = 2 * TN, HA = TM16 / 2;
-    f32x4_t acc[TM16][TN16];
-
-    // what the transfers of a tile need: its corner, the operand bases there and the per-lane offsets (set_tile)
+    // What the transfers of a tile need: its corner and the operand bases there (set_tile), and per-lane offsets that are the same for every
+    // tile.  An operand's K tile is 32 transfers, eight per wavefront: NT 8 rows of 128 bytes each, TN 2 k-rows of 512.
     int tile_m = 0, tile_n = 0, m0 = 0, n0 = 0;
     const char* pa = nullptr;
     const char* pb = nullptr;
-    uint32_t offAg[LPW], offBg[LPW];                                // per-lane offsets as a transfer group wants them
+    uint32_t len_a = 0;                             // NT: length of A's rows from m0 on
     auto set_tile = [&](int lg) {
         nt_tile_coords(lg, tiles_m, tiles_n, tile_m, tile_n);
+        tile_m = __builtin_amdgcn_readfirstlane(tile_m);
+        tile_n = __builtin_amdgcn_readfirstlane(tile_n);
         m0 = tile_m * BM;
         n0 = tile_n * BN;
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            const int u = (wave * LPW + i) * 64 + lane;
-            uint32_t oa, ob;
-            if constexpr (!TNF) {                                    // 16-byte unit of the 256 x 8 tile (128-byte rows)
-                const int row = u >> 3, slot = u & 7;
-                const int chunk = slot ^ ((row >> 1) & 7);
-                int ra_ = m0 + row;
-                ra_ = ra_ < M ? ra_ : M - 1;                        // rows past the edge: clamped, never stored
-                oa = (uint32_t)(((long long)(ra_ - m0) * K + chunk * 8) * 2);
-                ob = (uint32_t)(((long long)row * K + chunk * 8) * 2);
-                offAg[i] = dma_lane_offset<LPW>(oa, i);
-                offBg[i] = dma_lane_offset<LPW>(ob, i);
-            } else {                                                // 16-byte unit of the 32 k-row tile (512-byte rows)
-                const int row = u >> 5, pos = u & 31;
-                const int chunk = (((pos >> 1) ^ (row & 7)) << 1) | (pos & 1);
-                oa = (uint32_t)(((long long)row * M + chunk * 8) * 2);
-                ob = (uint32_t)(((long long)row * N + chunk * 8) * 2);
-                offAg[i] = dma_lane_offset<2 * LPW>(oa, i);         // group of four: A, A, B, B
-                offBg[i] = dma_lane_offset<2 * LPW>(ob, LPW + i);
-            }
-        }
+        const uint64_t bytes = (uint64_t)(uint32_t)(M - m0 < BM ? M - m0 : BM) * (uint32_t)K * 2u;
+        len_a = bytes > 0xFFFFFFFFu ? 0xFFFFFFFFu : (uint32_t)bytes;
         pa = reinterpret_cast<const char*>(A) + (TNF ? (long long)m0 * 2 : (long long)m0 * K * 2);
         pb = reinterpret_cast<const char*>(B) + (TNF ? (long long)n0 * 2 : (long long)n0 * K * 2);
     };
     set_tile(logical);
-    bool primed = false;                            // persistent: the first K tile of this tile is already on its way
-    constexpr int PS_SLOT = 65536 + NW * 32 * (TN * 32 + 4) * 4;    // LDS word through which wavefront 0 hands on the next tile
-    constexpr int STG_OFF = PS ? 65536 : 0;         // epilogue staging: above stage 0, which already receives the next tile
+    uint32_t offA[8], offB[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int u = (wave * 8 + i) * 64 + lane;                   // 16-byte unit of the tile
+        const int row = TNF ? u >> 5 : u >> 3, pos = TNF ? u & 31 : u & 7;
+        const int chunk = TNF ? (((pos >> 1) ^ (row & 7)) << 1) | (pos & 1) : pos ^ ((row >> 1) & 7);
+        offA[i] = ((uint32_t)row * (uint32_t)(TNF ? M : K) + chunk * 8) * 2;
+        offB[i] = TNF ? ((uint32_t)row * (uint32_t)N + chunk * 8) * 2 : offA[i];
+    }
+    const uint32_t lds0 = lds_address(smem);
+    // The A (part 0) or B (1) part of K tile `tile` as a raw buffer, and its transfer i (0..7) into ring unit `unit`.  Tiles past the
+    // end are buffers of length zero: they fetch nothing, but the wait counts are the same at every step.  TN: the buffer ends
+    // at the last k-row, so that rows past a ragged K arrive as zeros; NT: at the last row of A.
+    auto part = [&](int which, int tile) {
+        const uint32_t inside = (uint32_t)((tile - t_end) >> 31);   // all ones before the end
+        if constexpr (TNF) {
+            const uint32_t ld2 = (uint32_t)(which ? N : M) * 2u;
+            const int left = K - tile * BK;
+            return make_raw_buffer((which ? pb : pa) + (long long)tile * BK * ld2, (uint32_t)(left < BK ? left : BK) * ld2 & inside);
+        } else {
+            return make_raw_buffer((which ? pb : pa) + (long long)tile * (BK * 2), (which ? 0xFFFFFFFFu : len_a) & inside);
+        }
+    };
+    const uint32_t lds_wave = lds0 + (uint32_t)wave * 8192;
+    auto transfer_a = [&](i32x4_t buf, int unit, int i) { lds_dma16_buffer(buf, offA[i], lds_wave + (uint32_t)unit * UNIT + i * 1024); };
+    auto transfer_b = [&](i32x4_t buf, int unit, int i) { lds_dma16_buffer(buf, offB[i], lds_wave + (uint32_t)unit * UNIT + i * 1024); };
+    auto first_transfer = [&](int tile, int h, int i) {             // transfer i (0..15) of the first (h = 0) or second K tile: units 0 to 3
+        if (i < 8) transfer_a(part(0, tile), 2 * h, i);
+        else transfer_b(part(1, tile), 2 * h + 1, i - 8);
+    };
+    // fragments: fb[s] / fa[s] = the 8 column / row units of this wavefront, 32-deep step s of a tile.
+    // NT: 128-byte rows: 16 consecutive rows at one chunk index must hit 16 different 16-byte units of a 256-byte
+    // window: rows 2q and 2q+1 differ by 128 bytes, the XOR with (row/2)%8 separates the 8 row pairs.
+    // TN: 512-byte k-rows.  One fragment (16 features x 32 k) is two transpose reads, each 16 k-rows x 32 bytes: lane
+    // (i = lane%16, g = lane/16) addresses k-row 4g + i/4 (+16 for the second read) at features (i%4)*4 of the
+    // 16-feature unit and receives feature i at k-rows 4g..4g+3.  The 32 lanes served together touch 8 k-rows, so the
+    // 32-byte unit index is XORed with row%8.
+    bf16x8_t fa[2][8], fb[2][8];
+    const int fr = lane & 15, fg = lane >> 4;
+    const int nt_lane[2] = {fr * 128 + ((fg ^ ((fr >> 1) & 7)) << 4), fr * 128 + (((4 + fg) ^ ((fr >> 1) & 7)) << 4)};
+    const int tr_row = 4 * fg + (fr >> 2), tr_lane = tr_row * 512 + (lane & 3) * 8;
+    auto fragment = [&](int unit, int part, int s, int x) -> bf16x8_t {       // part: this wavefront's row or column in the 2 x 2 grid
+        if constexpr (TNF) {
+            typedef short s16x4_t __attribute__((ext_vector_type(4)));
+            typedef short s16x8_t __attribute__((ext_vector_type(8)));
+            typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
+            const char* q = smem + unit * UNIT + part * 256 + tr_lane + ((x ^ (tr_row & 7)) << 5) + s * (32 * 512);
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)q);
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(q + 16 * 512));
+            const s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            return __builtin_bit_cast(bf16x8_t, v);
+        } else {
+            return *reinterpret_cast<const bf16x8_t*>(smem + unit * UNIT + part * (128 * 128) + nt_lane[s] + x * 2048);
+        }
+    };
+    auto read = [&](int ua, int ub, int s, int r) {                 // read r (0..15) of a step: the column units first
+        if (r < 8) fb[s][r] = fragment(ub, wn, s, r);
+        else fa[s][r - 8] = fragment(ua, wm, s, r - 8);
+    };
+    f32x4_t acc[8][8], start[8];
+    // One step: 64 MFMAs on the fragments of 32-deep step s, the reads of the next step (from units ua, ub) and what tr(q) issues
+    // between them, in exactly this order.  Operands swapped on purpose: the accumulator block is C^T (rows = n, columns =
+    // m), so a lane holds 4 CONSECUTIVE n per block and the epilogue stages with 16-byte writes.  Boustrophedon order:
+    // consecutive MFMAs share one operand and the other changes to its neighbour (about 2 % more sustained MFMA rate at the
+    // power limit than row-major order).  first: the step that starts the accumulators (from the bias: its
+    // columns are those of a lane's registers);
+    // last: nothing left to read.
+    auto step = [&](auto first_t, auto last_t, int s, int ua, int ub, auto&& tr) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) {
+                const int j = (i & 1) ? 7 - jj : jj, q = i * 8 + jj;
+                if (!decltype(last_t)::value && q % 3 == 0 && q / 3 < 16) read(ua, ub, s ^ 1, q / 3);
+                tr(q);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[s][j], fa[s][i], decltype(first_t)::value ? start[j] : acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    auto wrap = [](int u) { return u >= 5 ? u - 5 : u; };
+    const bool direct = !tail && splits == 1;      // this work-group applies the epilogue itself
+    u32x2_t bias[8];                                // of the columns of this lane's accumulators
+    auto load_bias = [&]() {
+        const auto b = make_buffer(reinterpret_cast<const bf16_t*>(p.bias) + n0 + wn * 128, direct && p.bias ? 256u : 0u);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) bias[j] = buffer_load8(b, (uint32_t)(j * 16 + 4 * fg) * 2);
+    };
+    if constexpr (EPI != DS_EPI_ACC32) load_bias();
+    bool primed = false;                            // persistent: the first two K tiles of this tile are already on their way
     for (;;) {
-        // the epilogue below belongs to the tile the main loop has just finished, not to the one set_tile has moved on to
-        const int em0 = m0, en0 = n0, etile_m = tile_m, elogical = logical;
         int next_local = 0x7fffffff;
+        if (!primed) {
 #pragma unroll
-        for (int i = 0; i < TM16; ++i)
+            for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int j = 0; j < TN16; ++j)
+                for (int i = 0; i < 16; ++i) first_transfer(t_begin + h, h, i);
+            }
+        }
+        if constexpr (PS) {
+            // the tile after this one: drawn now, needed after the main loop (first tiles of a run: one per work-group)
+            if (persistent && t == 0)
+                next_local = (ps_wgs >> 3) + __hip_atomic_fetch_add(ps_ctr + (blockIdx.x & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < 8; ++j) start[j] = EPI != DS_EPI_ACC32 ? bf16x4_to_f32(bias[j]) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        // the first K tile is there: behind its transfers came those of the second one and, persistent, at least the previous tile's stores
+        constexpr int BEHIND = 16 + 32 * (epilogue_second<EPI>() || EPI == DS_EPI_ACC32 ? 2 : 1);
+        if (PS && primed) __builtin_amdgcn_s_waitcnt(vmcnt_imm(BEHIND < 63 ? BEHIND : 63));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(16));
+        __builtin_amdgcn_s_barrier();
+        // A(tl + 2) is issued in part in the second step of tile tl - 1, the rest in the first step of tile tl
+        i32x4_t a2 = part(0, t_begin + 2);
+#pragma unroll
+        for (int i = 0; i < NT_A1; ++i) transfer_a(a2, 4, i);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) read(0, 1, 0, r);
+        int tl = t_begin, ua = 0;                   // ua: unit of A(tl); those of B(tl), A(tl+1), B(tl+1), A(tl+2) follow it in the ring
+        auto rest_of_a = [&](int q) {
+            const int x = q + 64 - 8 * NT_DB - 1;
+            if (x % NT_DA == 0 && x / NT_DA >= NT_A1 && x / NT_DA < 8) transfer_a(a2, wrap(ua + 4), x / NT_DA);
+        };
+        const std::true_type yes;
+        const std::false_type no;
+        step(yes, no, 0, 0, 1, rest_of_a);
+        while (tl + 1 < t_end) {
+            const int na = wrap(ua + 2), nb = wrap(ua + 3), ub = wrap(ua + 1);
+            const i32x4_t b2 = part(1, tl + 2);
+            a2 = part(0, tl + 3);
+            // tile tl+1 has landed for this wavefront (A(tl+2) may be outstanding), its reads of tile tl are done, then everybody's:
+            // the units of tile tl are free
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(8) & 0xF0FF);
+            __builtin_amdgcn_s_barrier();
+            step(no, no, 1, na, nb, [&](int q) {
+                const int x = q - 8 * NT_DB - 1;
+                if (q % NT_DB == 1 && q / NT_DB < 8) transfer_b(b2, ua, q / NT_DB);
+                if (x >= 0 && x % NT_DA == 0 && x / NT_DA < NT_A1) transfer_a(a2, ub, x / NT_DA);
+            });
+            ua = na;
+            ++tl;
+            step(no, no, 0, ua, nb, rest_of_a);
+        }
 
-        if (t_begin < t_end) {
-            const uint32_t lds0 = lds_address(smem);
-            const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-            const long long tile_step_a = TNF ? (long long)DK * M * 2 : DK * 2;
-            const long long tile_step_b = TNF ? (long long)DK * N * 2 : DK * 2;
-            const int frag_row = lane & 15, frag_grp = lane >> 4;       // operand row / k group of this lane
-            const int t_last = t_end - 1;
-            // The transfers of a K tile, in the groups the main loops hand out between their MFMAs (a wavefront cannot issue
-            // anything else while a transfer of its own passes the address stage of the texture path, so they are neither
-            // issued in one burst after the barrier, which left the matrix cores idle for about a quarter of every tile,
-            // nor one at a time with an M0 of their own: a write of M0 waits for the transfer before it).
-            //   NT form: s = 0 / 1 = this wavefront's part of the A / B tile, LPW transfers under one M0; wavefront-uniform
-            //     base in scalar registers + per-lane offsets that never change (stepping along K costs no vector
-            //     instruction); LDS destinations are scalar integers, not generic pointers.
-            //   TN form: s = 0 = both parts (A, A, B, B in one 4 KB block of LDS per wavefront), through two buffer
-            //     descriptors whose lengths end at the last row of a ragged K: rows past the end read zeros, with no
-            //     per-lane test.
-            auto issue_one = [&](int tile, int stage, int s) {
-                tile = tile < t_last ? tile : t_last;
-                if constexpr (TNF) {
-                    static_assert(!TNF || LPW == 2, "one group = two A and two B transfers");
-                    const int k_left = K - tile * DK;
-                    const uint32_t rows = (uint32_t)(k_left < DK ? k_left : DK);
-                    const i32x4_t buf_a = make_raw_buffer(pa + tile * tile_step_a - 3072, rows * (uint32_t)M * 2u + 3072u);
-                    const i32x4_t buf_b = make_raw_buffer(pb + tile * tile_step_b - 3072, rows * (uint32_t)N * 2u + 3072u);
-                    lds_dma16_buffers_2x2(buf_a, offAg[0], offAg[1], buf_b, offBg[0], offBg[1],
-                                          lds0 + stage * STAGE + wave_u * (2 * LPW * 1024));
-                } else {
-                    const uint32_t dst_g = lds0 + stage * STAGE + (s ? HALF : 0) + wave_u * (LPW * 1024);
-                    if (s) lds_dma16_group<LPW>(dma_group_base<LPW>(pb + tile * tile_step_b), offBg, dst_g);
-                    else lds_dma16_group<LPW>(dma_group_base<LPW>(pa + tile * tile_step_a), offAg, dst_g);
-                }
-            };
-            auto issue = [&](int tile, int stage) {
+        // ---- epilogue, 16 rows x 64 columns (a pass) at a time through a block of LDS that is private to the wavefront: two times 16 rows of 64
+        // floats, 16-byte chunk c of row r at c ^ r.  Pass s takes columns 64 (s % 2) .. of rows 16 (s / 2) ..; a lane finishes rows
+        // lane / 8 and lane / 8 + 8 of it (g = 0, 1), 8 columns each.
+        const int em0 = m0 + wm * 128, en0 = n0 + wn * 128, etile_m = tile_m, elogical = logical;
+        int elane = lane;                              // (opaque, so that no address of the epilogue is kept in registers over the K loop)
+        asm volatile("" : "+v"(elane));
+        const int rd_row = elane >> 3, rd_col = (elane & 7) * 8, wr_row = elane & 15, wr_col = elane >> 4;
+        // The wavefront's 128 rows of a tensor of M x N elements of es bytes as a raw buffer that ends behind the last one which exists, so
+        // that every access is made, without a branch: rows past M are read as zeros and not written.  (With branches around the rows
+        // the compiler cannot count what is in flight and waits for everything, its own last store included, in front of every row:
+        // 65 582 x 2048 x 2048 with a residual 487 -> 572 us.)  on = false: an empty buffer
+        const int row_cnt = M - em0 < 0 ? 0 : M - em0 < 128 ? M - em0 : 128;
+        auto rows = [&](const void* tensor, int es, bool on) {
+            return make_buffer(reinterpret_cast<const char*>(tensor) + ((size_t)em0 * N + en0) * es, on ? (uint32_t)row_cnt * (uint32_t)N * es : 0u);
+        };
+        const uint32_t lane_off = (uint32_t)rd_row * (uint32_t)N + rd_col;       // elements
+        auto at = [&](int s, int g, int es) { return lane_off * es + (uint32_t)(((s >> 1) * 16 + g * 8) * N * es) + (s & 1) * 64 * es; };
+        // What the epilogue reads from memory: PRE passes ahead, the first ones before the next tile's transfers
+        constexpr bool READS = epilogue_reads<EPI>(), READS2 = EPI == DS_EPI_DGATE, OLD = EPI == DS_EPI_ACC32;
+        constexpr int PRE = READS2 || OLD ? 4 : 8;
+        EpiPre<bf16_t> pre[PRE][2];
+        f32x4_t old[PRE][2][2];                       // accumulation: what is added to
+        const buffer_t in_r = rows(READS ? p.R : C, 2, READS && direct), in_r2 = rows(READS2 ? p.R2 : C, 2, READS2 && direct);
+        const buffer_t in_valid = make_buffer(p.row_valid + em0, EPI == DS_EPI_RESID && direct && p.row_valid ? row_cnt * 4u : 0u);
+        const buffer_t in_old = rows(C, 4, OLD && direct && p.accumulate);
+        auto prefetch_pass = [&](int s) {
 #pragma unroll
-                for (int s = 0; s < (TNF ? 1 : 2); ++s) issue_one(tile, stage, s);
-            };
-            // NT: 128-byte rows: 16 consecutive rows at one chunk index must hit 16 different 16-byte units of a 256-byte
-            // window: rows 2q and 2q+1 differ by 128 bytes, the XOR with (row/2)%8 separates the 8 row pairs
-            auto off64 = [](int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); };
-            // TN: 512-byte rows.  One operand fragment (16 features x 32 k) is two transpose reads, each 16 k-rows x 32
-            // bytes: lane (i = lane%16, g = lane/16) addresses k-row 4g + i/4 (+16 for the second read) at features
-            // (i%4)*4 of the 16-feature unit and receives feature i at k-rows 4g..4g+3.  The 32 lanes served together
-            // touch 8 k-rows, so the 32-byte unit index is XORed with row%8.  Both operands use the same k order, so the
-            // contraction is unchanged.
-            const int tr_x = 4 * ((lane >> 4) & 1) + ((lane >> 2) & 3);
-            // (LDS layout of a TN stage: per wavefront w one 4 KB block = k-rows 4w .. 4w+3 of the A tile, then of the B tile)
-            const int tr_base = (lane >> 4) * 4096 + ((lane & 15) >> 2) * 512 + (lane & 3) * 8;
-            auto read_tr = [&](const char* base, int unit) {
-                typedef short s16x4_t __attribute__((ext_vector_type(4)));
-                typedef short s16x8_t __attribute__((ext_vector_type(8)));
-                typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
-                const char* q = base + tr_base + ((unit ^ tr_x) << 5);
-                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)q);
-                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(q + 4 * 4096));
-                const s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                return __builtin_bit_cast(bf16x8_t, v);
-            };
-            // fragments of 32-deep k step `ks` of a stage: HA of this wavefront's TM16 row units (half h), all TN16 column units
-            auto load_a = [&](int stage, int ks, int h, bf16x8_t (&fa)[HA]) {
-                const char* a_base = smem + stage * STAGE;
-#pragma unroll
-                for (int i = 0; i < HA; ++i) {
-                    if constexpr (TNF) fa[i] = read_tr(a_base, wm * TM16 + h * HA + i);
-                    else fa[i] = *reinterpret_cast<const bf16x8_t*>(a_base + off64(wm * (TM * 32) + (h * HA + i) * 16 + frag_row, ks * 4 + frag_grp));
-                }
-            };
-            auto load_b = [&](int stage, int ks, bf16x8_t (&fb)[TN16]) {
-                const char* b_base = smem + stage * STAGE + (TNF ? 2 * 1024 : HALF);
-#pragma unroll
-                for (int j = 0; j < TN16; ++j) {
-                    if constexpr (TNF) fb[j] = read_tr(b_base, wn * TN16 + j);
-                    else fb[j] = *reinterpret_cast<const bf16x8_t*>(b_base + off64(wn * (TN * 32) + j * 16 + frag_row, ks * 4 + frag_grp));
-                }
-            };
-            // One half step: HA x TN16 MFMAs on row units h*HA.., with transfers [s0, s0 + cnt) of K tile `tile` handed
-            // out evenly between them.  Operands swapped on purpose: the accumulator block is C^T (rows = n, columns =
-            // m), so a lane holds 4 CONSECUTIVE n per block and the epilogue stages with 16-byte writes.
-            auto mma_dma = [&](int h, const bf16x8_t (&fa)[HA], const bf16x8_t (&fb)[TN16], int tile, int stage, int s0, int cnt) {
-                int done = 0;
-#pragma unroll
-                for (int i = 0; i < HA; ++i)
-#pragma unroll
-                    for (int jj = 0; jj < TN16; ++jj) {
-                        // boustrophedon order: consecutive MFMAs share one operand and the other changes to its neighbour
-                        // (measured: about 2 % more sustained MFMA rate at the power limit than row-major order)
-                        const int j = (i & 1) ? TN16 - 1 - jj : jj;
-                        const int q = i * TN16 + jj;
-#ifdef X_QPOS
-                        if (done < cnt && q == (2 * done + 1) * (HA * TN16) / (2 * cnt)) {
-#else
-                        if (done < cnt && q == done * (HA * TN16) / cnt) {
-#endif
-                            __builtin_amdgcn_sched_barrier(0);
-                            issue_one(tile, stage, s0 + done);
-                            __builtin_amdgcn_sched_barrier(0);
-                            ++done;
-                        }
-                        acc[h * HA + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[h * HA + i][j], 0, 0, 0);
-                    }
-            };
-            // Software pipeline: the fragments of the next half step are read from LDS while the MFMAs of the current
-            // one run, ACROSS the tile boundary too, so that no wavefront waits on LDS latency right after the barrier
-            // (all 8 wavefronts leave it together, so nobody would be left to cover for the others).
-            bf16x8_t fax[HA], fay[HA], fbx[TN16], fby[TN16];
-            // transfers per K tile and wavefront: NVM instructions, handed out in NTR groups (TN: one, NT: A part, B part)
-            constexpr int NVM = 2 * LPW, NTR = TNF ? 1 : 2;
-            if constexpr (TNF) {
-                // one 32-deep k step per tile, two half steps; the transfers of tile tl+3 go out in the first one, before the
-                // barrier of iteration tl
-                issue(t_begin, 0);
-                issue(t_begin + 1, 1);
-                issue(t_begin + 2, 2);
-                __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NVM));         // tile t_begin: at most the two newest tiles outstanding
-                __builtin_amdgcn_s_barrier();
-                load_b(0, 0, fbx);
-                load_a(0, 0, 0, fax);
-                auto tn_iter = [&](int tl, bf16x8_t (&fb_cur)[TN16], bf16x8_t (&fb_next)[TN16]) {
-                    const int st_ = (tl - t_begin) & (NS - 1);
-                    // stage (tl-1)%4 is free: every wavefront finished reading it before the barrier it has passed last
-                    load_a(st_, 0, 1, fay);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mma_dma(0, fax, fb_cur, tl + 3, (st_ + 3) & (NS - 1), 0, 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    // tile tl+1: this wavefront's part has landed (tile tl+2 and the new transfers outstanding), its LDS
-                    // reads are done ...
-                    __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * NVM) & 0xF0FF);        // vmcnt(2 NVM) lgkmcnt(0)
-                    __builtin_amdgcn_s_barrier();                       // ... and everyone's
-                    load_b((st_ + 1) & (NS - 1), 0, fb_next);           // past the last tile: a stale but valid stage, unused
-                    load_a((st_ + 1) & (NS - 1), 0, 0, fax);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mma_dma(1, fay, fb_cur, tl + 3, (st_ + 3) & (NS - 1), 1, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                };
-                int tl = t_begin;
-                for (; tl + 1 < t_end; tl += 2) {
-                    tn_iter(tl, fbx, fby);
-                    tn_iter(tl + 1, fby, fbx);
-                }
-                if (tl < t_end) tn_iter(tl, fbx, fby);
-            } else {
-                // two 64 KB stages, two 32-deep k steps = four half steps per tile, one barrier per tile.  Transfers of
-                // tile tl+1 ride on the four half steps between two barriers: NT_G0 on the one right after the barrier
-                // (the last half step of tile tl-1), then NT_G1, NT_G2, the rest
-                static_assert(NT_G0 + NT_G1 + NT_G2 <= NTR, "more transfers scheduled than a tile has");
-                if (!primed) issue(t_begin, 0);
-                if constexpr (PS) {
-                    // the tile after this one: drawn now, needed after the main loop (first tiles of a run: one per work-group)
-                    if (persistent && t == 0)
-                        next_local = (ps_wgs >> 3) + __hip_atomic_fetch_add(ps_ctr + (blockIdx.x & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                __builtin_amdgcn_s_waitcnt(0x0F70);                     // vmcnt(0) (persistent: the previous tile's stores too)
-                __builtin_amdgcn_s_barrier();
-#pragma unroll
-                for (int s_ = 0; s_ < NT_G0; ++s_) issue_one(t_begin + 1, 1, s_);
-                load_b(0, 0, fbx);
-                load_a(0, 0, 0, fax);
-                for (int tl = t_begin; tl < t_end; ++tl) {
-                    const int st_ = (tl - t_begin) & 1;
-                    load_a(st_, 0, 1, fay);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mma_dma(0, fax, fbx, tl + 1, st_ ^ 1, NT_G0, NT_G1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_b(st_, 1, fby);
-                    load_a(st_, 1, 0, fax);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mma_dma(1, fay, fbx, tl + 1, st_ ^ 1, NT_G0 + NT_G1, NT_G2);
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_a(st_, 1, 1, fay);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mma_dma(0, fax, fby, tl + 1, st_ ^ 1, NT_G0 + NT_G1 + NT_G2, NTR - NT_G0 - NT_G1 - NT_G2);
-                    __builtin_amdgcn_sched_barrier(0);
-                    __builtin_amdgcn_s_waitcnt(0x0070);                 // vmcnt(0) lgkmcnt(0): tile tl+1 landed, reads of tile tl done
-                    __builtin_amdgcn_s_barrier();
-                    // this stage is free from here on: tile tl+2 starts to arrive in it
-                    load_b(st_ ^ 1, 0, fbx);                            // past the last tile: a reloaded copy of it, unused
-                    load_a(st_ ^ 1, 0, 0, fax);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mma_dma(1, fay, fby, tl + 2, st_, 0, NT_G0);
-                    __builtin_amdgcn_sched_barrier(0);
+            for (int g = 0; g < 2; ++g) {
+                EpiPre<bf16_t>& e = pre[s % PRE][g];
+                if constexpr (READS) buffer_load16(in_r, at(s, g, 2), e.r);
+                if constexpr (READS2) buffer_load16(in_r2, at(s, g, 2), e.r2);
+                e.valid = 0;
+                if constexpr (EPI == DS_EPI_RESID) e.valid = buffer_load4(in_valid, (uint32_t)((s >> 1) * 16 + g * 8 + rd_row) * 4);
+                if constexpr (OLD) {
+                    buffer_load16(in_old, at(s, g, 4), old[s % PRE][g][0]);
+                    buffer_load16(in_old, at(s, g, 4) + 16, old[s % PRE][g][1]);
                 }
             }
-            // drain the redundant tail transfers before LDS is reused by the epilogue (explicit: the compiler does not
-            // see transfers issued by lds_dma16)
-            __builtin_amdgcn_s_waitcnt(0x0070);     // vmcnt(0) lgkmcnt(0)
-            if constexpr (PS) {
-                if (persistent && t == 0) *reinterpret_cast<volatile int*>(smem + PS_SLOT) = next_local;
+        };
+        // The last tile's second step: all its fragments are in registers, so the ring is free once everybody has got here (and nothing is
+        // on its way into it: explicit, the compiler does not see the transfers).  In front of its products go the first reads of the
+        // epilogue, between them the transfers of the next tile's first K tile; those of the second one follow between the passes.
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        char* stg = smem + 4 * UNIT + wave * 8192;
+        int next_logical = -1;
+        __builtin_amdgcn_s_barrier();
+        if constexpr (PS) {
+            // the number of the next tile reaches the other wavefronts through a word of each one's own block (behind the barrier: the
+            // unit may have held this tile)
+            if (persistent && t == 0) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) *reinterpret_cast<volatile int*>(smem + 4 * UNIT + w * 8192) = next_local;
             }
+            __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0)
             __builtin_amdgcn_s_barrier();
         }
-        int next_logical = -1;
         if constexpr (PS) {
             if (persistent) {
-                const int nl = __builtin_amdgcn_readfirstlane(*reinterpret_cast<volatile int*>(smem + PS_SLOT));
+                const int nl = __builtin_amdgcn_readfirstlane(*reinterpret_cast<volatile int*>(stg));
                 if (nl < run_cnt) {
-                    // the next tile's first K tile goes out before this tile's epilogue: stage 0 is free, the staging block
-                    // lies above it
                     next_logical = run_start + nl;
                     set_tile(next_logical);
-                    const uint32_t lds0 = lds_address(smem);
-                    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-#pragma unroll
-                    for (int s_ = 0; s_ < 2; ++s_) {
-                        const uint32_t dst_g = lds0 + (s_ ? HALF : 0) + wave_u * (LPW * 1024);
-                        if (s_) lds_dma16_group<LPW>(dma_group_base<LPW>(pb + t_begin * (long long)(DK * 2)), offBg, dst_g);
-                        else lds_dma16_group<LPW>(dma_group_base<LPW>(pa + t_begin * (long long)(DK * 2)), offAg, dst_g);
-                    }
+                    if constexpr (EPI != DS_EPI_ACC32) load_bias();
                     primed = true;
                 }
             }
         }
-
-        auto epilogue = [&]() {
-        // ---- epilogue through LDS: per wavefront a [32][STG_LD] fp32 staging block
-        float* stage = reinterpret_cast<float*>(smem + STG_OFF) + wave * (32 * STG_LD);
-        constexpr int LPR = TN * 4;                    // lanes per staged row (8 columns each)
-        const int rd_row = lane / LPR, rd_col = (lane % LPR) * 8;
-        constexpr int NPSS = 32 / (64 / LPR);          // staged rows each lane finishes per pass
-        const bool direct = !tail && splits == 1;      // this work-group applies the epilogue itself
-        // what the epilogue reads from memory, for every row this lane will finish: all in flight before the first pass
-        // (one pass ahead only for the two-operand gated form, which would not fit in registers otherwise)
-        constexpr bool PRE_ALL = EPI != DS_EPI_DGATE;
-        EpiPre<bf16_t> pre[TM][NPSS];
-        auto prefetch_pass = [&](int i) {
+        if constexpr (READS || OLD) {
 #pragma unroll
-            for (int pss = 0; pss < NPSS; ++pss) {
-                const int m = em0 + wm * (TM * 32) + i * 32 + pss * (64 / LPR) + rd_row;
-                if (m < M) epilogue_prefetch<bf16_t, EPI>(m, en0 + wn * (TN * 32) + rd_col, N, p, pre[i][pss]);
-            }
-        };
-        if (epilogue_reads<EPI>() && direct && PRE_ALL) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) prefetch_pass(i);
+            for (int s = 0; s < PRE; ++s) prefetch_pass(s);
         }
-        // Accumulation: what is added to, fetched one pass ahead (four gradients of a layer together, d = 2048, d_ff = 8192, 1 797 tokens:
-        // 252 -> 242 us; one gradient of 8192 x 2048 over 1 797 tokens 86 -> 77, 4096 x 16384 over 2 048 360 -> 331; streaming stores and lines
-        // requested at the start of the K loop: slower).  It takes the TN kernel from 222 to 232 registers, so that a wavefront of the column
-        // sums on the stage's side stream no longer fits beside two of these: those sums wait for the gaps between launches (their
-        // group's time at d = 2048, 65 536 tokens 4 -> 20 ms in four calls), and the calls take the same time (35.98 ms; d = 4096: 137.7).
-        // Eight or 16 registers of prefetch (221 in all) let the sums run beside, and the calls take 0.2 to 1 % longer, the adding
-        // gradients 2 to 5 %.
-        constexpr bool PRE_OLD = EPI == DS_EPI_ACC32 && TNF;
-        const bool adds = PRE_OLD && direct && p.accumulate;
-        float old[2][NPSS][8];
-        auto fetch_old = [&](int i, float (&dst)[NPSS][8]) {
+        const int next_begin = next_logical < 0 ? t_end : t_begin;      // (no next tile: buffers of length zero, drained behind the loop)
+        const i32x4_t next_a = part(0, next_begin + 1), next_b = part(1, next_begin + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        step(no, yes, 1, 0, 0, [&](int q) {
+            if (PS && q % 4 == 1) first_transfer(next_begin, 0, q / 4);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        // put: the accumulators of pass s into its half of the staging block; get: the 2 x 8 columns of this lane back from it.  A pass is put
+        // and read while the one before it is finished.
+        struct Pass { float4 x[2][2]; };
+        auto put = [&](int s) {
+            char* blk = stg + (s & 1) * 4096 + wr_row * 256;
 #pragma unroll
-            for (int pss = 0; pss < NPSS; ++pss) {
-                const int m = em0 + wm * (TM * 32) + i * 32 + pss * (64 / LPR) + rd_row;
-                if (m < M) Vec8<float>::load(reinterpret_cast<const float*>(C) + (size_t)m * N + en0 + wn * (TN * 32) + rd_col, dst[pss]);
-            }
+            for (int j = 0; j < 4; ++j)         // lane = row m (lane%16); its 4 registers = columns 4*(lane/16) + 0..3 of a block
+                *reinterpret_cast<f32x4_t*>(blk + (((4 * j + wr_col) ^ wr_row) << 4)) = acc[s >> 1][(s & 1) * 4 + j];
         };
-        if (adds) fetch_old(0, old[0]);
-        if constexpr (EPI == DS_EPI_NONE) {
-            // Plain output (+ bias): nothing is computed after the transposition, so the bias is added and the value
-            // rounded to bf16 BEFORE staging: half the LDS traffic of the fp32 staging below, which bounds the epilogue.
-            if (direct) {
-                bf16_t* stage_h = reinterpret_cast<bf16_t*>(stage);
-                constexpr int LD_H = TN * 32 + 8;                       // bf16 row stride (144 bytes: 8-byte writes of 16 rows spread over the banks)
-                float bias4[TN16][4];
+        auto get = [&](int s) {
+            Pass v;
 #pragma unroll
-                for (int j = 0; j < TN16; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        bias4[j][e] = p.bias ? (float)reinterpret_cast<const bf16_t*>(p.bias)[en0 + wn * (TN * 32) + j * 16 + 4 * (lane >> 4) + e] : 0.f;
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    wave_lds_sync();
-#pragma unroll
-                    for (int i2 = 0; i2 < 2; ++i2)
-#pragma unroll
-                        for (int j = 0; j < TN16; ++j) {
-                            typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
-                            const f32x4_t a4 = acc[2 * i + i2][j];
-                            const bf16x4_t h4 = {(bf16_t)(a4[0] + bias4[j][0]), (bf16_t)(a4[1] + bias4[j][1]),
-                                                 (bf16_t)(a4[2] + bias4[j][2]), (bf16_t)(a4[3] + bias4[j][3])};
-                            *reinterpret_cast<bf16x4_t*>(stage_h + (i2 * 16 + (lane & 15)) * LD_H + j * 16 + 4 * (lane >> 4)) = h4;
-                        }
-                    wave_lds_sync();
-#pragma unroll
-                    for (int pss = 0; pss < NPSS; ++pss) {
-                        const int row = pss * (64 / LPR) + rd_row;
-                        const int m = em0 + wm * (TM * 32) + i * 32 + row;
-                        const int n = en0 + wn * (TN * 32) + rd_col;
-                        if (m < M) {
-                            const bf16x8_t v = *reinterpret_cast<const bf16x8_t*>(stage_h + row * LD_H + rd_col);
-                            __builtin_nontemporal_store(v, reinterpret_cast<bf16x8_t*>(C + (size_t)m * N + n));
-                        }
-                    }
-                }
-                return;
+            for (int g = 0; g < 2; ++g) {
+                const int row = g * 8 + rd_row;
+                const char* r = stg + (s & 1) * 4096 + row * 256;
+                v.x[g][0] = *reinterpret_cast<const float4*>(r + (((rd_col >> 2) ^ row) << 4));
+                v.x[g][1] = *reinterpret_cast<const float4*>(r + ((((rd_col >> 2) + 1) ^ row) << 4));
             }
-        }
-        // column sums of what this lane writes (DGELU: the bias gradient of the layer below comes out of this kernel
-        // instead of a pass over the stored tensor); every lane finishes TM * NPSS rows of the same 8 columns
-        float csum[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) csum[j] = 0.f;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            if (epilogue_reads<EPI>() && direct && !PRE_ALL) prefetch_pass(i);
-            if (adds && i + 1 < TM) fetch_old(i + 1, old[(i + 1) & 1]);
+            return v;
+        };
+        // every pass: out(s, g, v) gets the 8 columns of row g of this lane; after(s) follows.  rolled: g in a loop, for what is long per row
+        // (unrolled over all 32 rows of a lane such kernels come to 45 to 64 KB of code, which a launch fetches from memory)
+        auto passes = [&](auto rolled, auto&& out, auto&& after) {
             wave_lds_sync();            // the staging block is private to the wavefront: no work-group barrier (which would
                                         // also wait for the global stores of the previous pass to be acknowledged)
-#pragma unroll
-            for (int i2 = 0; i2 < 2; ++i2)
-#pragma unroll
-                for (int j = 0; j < TN16; ++j) {    // lane = row m (lane%16 of block 2i+i2); its 4 registers = columns 4*(lane/16) + 0..3
-                    const f32x4_t a4 = acc[2 * i + i2][j];
-                    *reinterpret_cast<float4*>(stage + (i2 * 16 + (lane & 15)) * STG_LD + j * 16 + 4 * (lane >> 4)) =
-                        make_float4(a4[0], a4[1], a4[2], a4[3]);
-                }
+            put(0);
             wave_lds_sync();
+            Pass cur = get(0);
 #pragma unroll
-            for (int pss = 0; pss < NPSS; ++pss) {
-                const int row = pss * (64 / LPR) + rd_row;
-                const int m = em0 + wm * (TM * 32) + i * 32 + row;
-                const int n = en0 + wn * (TN * 32) + rd_col;
-                if (m < M) {
-                    float v[8];
-                    const float4 x0 = *reinterpret_cast<const float4*>(stage + row * STG_LD + rd_col);
-                    const float4 x1 = *reinterpret_cast<const float4*>(stage + row * STG_LD + rd_col + 4);
-                    v[0] = x0.x; v[1] = x0.y; v[2] = x0.z; v[3] = x0.w; v[4] = x1.x; v[5] = x1.y; v[6] = x1.z; v[7] = x1.w;
-                    if (GRP && splits > 1) {
-                        Vec8<float>::store(split_ws + (size_t)(m - em0) * BN + (n - en0), v);
-                    } else if (tail) {
-                        Vec8<float>::store(split_ws + ((size_t)((elogical - n_main) * tail_splits + split) * BM + (m - em0)) * BN + (n - en0), v);
-                    } else if (splits > 1) {
-                        Vec8<float>::store(split_ws + ((size_t)split * M + m) * N + n, v);
-                    } else if (epilogue_reads<EPI>()) {
-                        epilogue8<bf16_t, EPI>(m, n, N, v, C, p, &pre[i][pss]);
-                        if constexpr (EPI == DS_EPI_DGELU || EPI == DS_EPI_MULR) {
+            for (int s = 0; s < 16; ++s) {
+                Pass next = cur;
+                if (s + 1 < 16) {
+                    put(s + 1);
+                    wave_lds_sync();
+                    next = get(s + 1);
+                }
+                auto row_of = [&](int g) {
+                    const float4 x0 = g ? cur.x[1][0] : cur.x[0][0], x1 = g ? cur.x[1][1] : cur.x[0][1];
+                    float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                    out(s, g, v);
+                };
+                if constexpr (decltype(rolled)::value) {
+#pragma unroll 1
+                    for (int g = 0; g < 2; ++g) row_of(g);
+                } else {
+                    row_of(0);
+                    row_of(1);
+                }
+                after(s);
+                if constexpr (PS) {
+                    if (s < 8) transfer_a(next_a, 2, s);
+                    else transfer_b(next_b, 3, s - 8);
+                }
+                cur = next;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // column sums of what this lane writes (DGELU: the bias gradient of the layer below comes out of this kernel
+        // instead of a pass over the stored tensor); every lane finishes 16 rows of the same 16 columns
+        constexpr bool SUMS = EPI == DS_EPI_DGELU || EPI == DS_EPI_MULR;
+        float csum[2][8];
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) csum[j] += v[j];
-                        }
-                    } else if (PRE_OLD) {
-                        if (adds) {
+        for (int j = 0; j < 8; ++j) csum[0][j] = csum[1][j] = 0.f;
+        if (!direct) {
+            // partial sums: [split][M][N], or blocks of a whole tile (rows past M are never read there)
+            const bool block = GRP || tail;
+            float* dst = GRP ? split_ws
+                       : tail ? split_ws + (size_t)((elogical - n_main) * tail_splits + split) * (BM * BN) : split_ws + (size_t)split * M * N;
+            const buffer_t out = block ? make_buffer(dst + (size_t)(wm * 128) * BN + wn * 128, 128 * BN * 4) : rows(dst, 4, true);
+            const uint32_t ld = block ? BN : N, off = ((uint32_t)rd_row * ld + rd_col) * 4;
+            passes(no, [&](int s, int g, float (&v)[8]) {
+                const uint32_t o = off + ((s >> 1) * 16 + g * 8) * ld * 4 + (s & 1) * 256;
+                buffer_store16(f32x4_t{v[0], v[1], v[2], v[3]}, out, o);
+                buffer_store16(f32x4_t{v[4], v[5], v[6], v[7]}, out, o + 16);
+            }, [](int) {});
+        } else {
+            constexpr bool LONG = EPI == DS_EPI_GELU || EPI == DS_EPI_GELU_D || EPI == DS_EPI_DGELU || EPI == DS_EPI_GATE || EPI == DS_EPI_DGATE;
+            const buffer_t out = rows(C, OLD ? 4 : 2, true), out2 = rows(epilogue_second<EPI>() ? p.C2 : C, 2, epilogue_second<EPI>());
+            passes(std::integral_constant<bool, LONG>{}, [&](int s, int g, float (&v)[8]) {
+                if constexpr (OLD) {
+                    buffer_store16(f32x4_t{v[0], v[1], v[2], v[3]} + old[s % PRE][g][0], out, at(s, g, 4));
+                    buffer_store16(f32x4_t{v[4], v[5], v[6], v[7]} + old[s % PRE][g][1], out, at(s, g, 4) + 16);
+                } else {
+                    bf16x8_t one, two;
+                    EpiPre<bf16_t> e = pre[s % PRE][0];
+                    if constexpr (READS) {
+                        if (g) e = pre[s % PRE][1];
+                    }
+                    epilogue_values<bf16_t, EPI>(v, e, one, two);
+                    buffer_store16_nt(one, out, at(s, g, 2));
+                    if constexpr (epilogue_second<EPI>()) buffer_store16_nt(two, out2, at(s, g, 2));
+                    if constexpr (SUMS) {
+                        const bool exists = (s >> 1) * 16 + g * 8 + rd_row < row_cnt;
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) v[j] += old[i & 1][pss][j];
-                        }
-                        Vec8<float>::store(reinterpret_cast<float*>(C) + (size_t)m * N + n, v);
-                    } else {
-                        epilogue8<bf16_t, EPI>(m, n, N, v, C, p);
+                        for (int j = 0; j < 8; ++j) csum[s & 1][j] += exists ? v[j] : 0.f;
                     }
                 }
-            }
+            }, [&](int s) {
+                if ((READS || OLD) && s + PRE < 16) prefetch_pass(s + PRE);
+            });
         }
-        if constexpr (EPI == DS_EPI_DGELU || EPI == DS_EPI_MULR) {
+        if constexpr (SUMS) {
             if (direct && p.colsum) {
-                // lanes l, l + LPR, l + 2 LPR, ... hold the same columns: fold them, then one row of partial sums per
+                // lanes l, l + 8, l + 16, ... hold the same columns: fold them, then one row of partial sums per
                 // (tile row, wavefront row), written whether or not the wavefront had a valid row
 #pragma unroll
-                for (int o = LPR; o < 64; o <<= 1)
+                for (int h = 0; h < 2; ++h) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) csum[j] += __shfl_xor(csum[j], o, 64);
-                if (lane < LPR)
-                    Vec8<float>::store(p.colsum + (size_t)(etile_m * WM + wm) * N + en0 + wn * (TN * 32) + rd_col, csum);
+                    for (int o = 8; o < 64; o <<= 1)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) csum[h][j] += __shfl_xor(csum[h][j], o, 64);
+                    if (lane < 8) Vec8<float>::store(p.colsum + (size_t)(etile_m * NT_WM + wm) * N + en0 + h * 64 + rd_col, csum[h]);
+                }
             }
         }
-        };
-        epilogue();
+        // (not persistent: one tile.  The compiler is kept from knowing, because without the loop around the tile it moves accumulators between
+        // the two halves of the register file inside the K loop, hundreds of copies a tile)
+        if constexpr (!PS) asm volatile("" : "+s"(next_logical));
         if (next_logical < 0) break;
         logical = next_logical;
+        if constexpr (!PS) set_tile(logical);
     }   // for (;;): persistent work-groups go on with their next tile
     if constexpr (PS) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);         // no transfer may still be writing LDS when the work-group ends
         if (persistent && t == 0) {
             // every persistent work-group ends with a draw beyond its run; the last one to finish clears the counters
             const int done = __hip_atomic_fetch_add(ps_ctr + 8, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -732,7 +671,7 @@ static int choose_splits(int tiles, int nt, int M, int N, size_t split_ws_floats
     int best = 1;
     double best_cost = 1e30;
     for (int sp = 1; sp <= 16; ++sp) {
-        if (sp > 1 && (sp > nt / 16 || (size_t)sp * M * N > split_ws_floats)) break;
+        if (sp > 1 && (sp > nt / 8 || (size_t)sp * M * N > split_ws_floats)) break;
         const int per = (nt + sp - 1) / sp;
         if ((nt + per - 1) / per != sp) continue;               // every split must own at least one K tile
         const double rounds = (double)(((long long)tiles * sp + n_cu - 1) / n_cu);
@@ -745,14 +684,14 @@ static int choose_splits(int tiles, int nt, int M, int N, size_t split_ws_floats
 // How a launch of the 256 x 256 kernel divides its tiles: uniform splits (weight gradients), or whole tiles and a tail
 // whose K loops are cut into tail_splits pieces.
 struct BigPlan {
-    int tiles_m, tiles_n, nt;      // nt: K tiles as the kernel counts them (32-deep in the TN form, 64 in the NT form)
+    int tiles_m, tiles_n, nt;      // nt: 64-deep K tiles
     int splits, n_main, tail_splits;
 };
 static BigPlan plan_big(bool tnf, int epi, int M, int N, int K, size_t split_ws_floats) {
     BigPlan b;
     b.tiles_m = (M + BM - 1) / BM;
     b.tiles_n = N / BN;
-    b.nt = tnf ? (K + NT_DK - 1) / NT_DK : K / 64;
+    b.nt = (K + BK - 1) / BK;
     const int tiles = b.tiles_m * b.tiles_n;
     b.splits = epi == DS_EPI_ACC32 && split_ws_floats ? choose_splits(tiles, b.nt, M, N, split_ws_floats) : 1;
     // tail split-K: the tiles beyond the last whole round over the compute units share that round; a launch with
@@ -782,7 +721,7 @@ static BigPlan plan_big(bool tnf, int epi, int M, int N, int K, size_t split_ws_
 // the compute units; 0.1 per piece of partial sums (256 KB written and read back) and 4 for the launch that adds them.
 static double big_cost(const BigPlan& b, bool tnf, int M, int N) {
     const int n_cu = gemm_cu_count(), tiles = b.tiles_m * b.tiles_n;
-    const double steps = tnf ? 0.5 * b.nt : b.nt, step = tnf ? 1.15 : 1.25;
+    const double steps = b.nt, step = tnf ? 1.15 : 1.25;
     auto rounds = [&](double work_groups) { return std::ceil(work_groups / n_cu); };
     if (b.splits > 1)
         return rounds((double)tiles * b.splits) * (steps / b.splits * step + 4) + 2e-6 * (double)b.splits * M * N + 4;
@@ -819,12 +758,9 @@ template <int EPI, bool TNF>
 ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, float* split_ws,
                     size_t split_ws_floats, hipStream_t st) {
     static bool attr_set = false;
-    constexpr int WM = NT_WM, WN = NT_WN;
-    auto kern = gemm_bf16_nt_kernel<EPI, WM, WN, TNF, false>;
-    constexpr int stg = WM * WN * 32 * ((256 / WN) + 4) * 4;
-    const int smem = NT_NS * NT_STAGE > stg ? NT_NS * NT_STAGE : stg;
+    auto kern = gemm_bf16_nt_kernel<EPI, TNF, false>;
     if (!attr_set) {
-        DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, RING));
         attr_set = true;
     }
     const BigPlan plan = plan_big(TNF, EPI, M, N, K, split_ws ? split_ws_floats : 0);
@@ -837,16 +773,14 @@ ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, 
         const int n_cu = gemm_cu_count();
         if (splits == 1 && n_cu % 8 == 0 && n_main >= 2 * n_cu) {
             static bool ps_attr_set = false;
-            auto kern_ps = gemm_bf16_nt_kernel<EPI, WM, WN, false, true>;
-            constexpr int smem_ps = 65536 + stg + 64;              // stage 0 | epilogue staging | hand-over word
-            static_assert(smem_ps >= NT_NS * NT_STAGE && smem_ps <= 160 * 1024, "LDS of the persistent form");
+            auto kern_ps = gemm_bf16_nt_kernel<EPI, false, true>;
             if (!ps_attr_set) {
-                DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern_ps), hipFuncAttributeMaxDynamicSharedMemorySize, smem_ps));
+                DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern_ps), hipFuncAttributeMaxDynamicSharedMemorySize, RING));
                 ps_attr_set = true;
             }
             int* ctr = ps_counters();
             if (ctr) {
-                hipLaunchKernelGGL(kern_ps, dim3(n_cu + (tiles - n_main) * tail_splits), dim3(WM * WN * 64), smem_ps, st, M, N, K,
+                hipLaunchKernelGGL(kern_ps, dim3(n_cu + (tiles - n_main) * tail_splits), dim3(256), RING, st, M, N, K,
                                    (const bf16_t*)A, (const bf16_t*)B, (bf16_t*)C, tiles_m, tiles_n, splits, n_main, tail_splits,
                                    split_ws, p, n_cu, ctr, NoGroup{});
                 launched = true;
@@ -854,7 +788,7 @@ ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, 
         }
     }
     if (!launched)
-        hipLaunchKernelGGL(kern, dim3(total), dim3(WM * WN * 64), smem, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, (bf16_t*)C,
+        hipLaunchKernelGGL(kern, dim3(total), dim3(256), RING, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, (bf16_t*)C,
                            tiles_m, tiles_n, splits, n_main, tail_splits, split_ws, p, 0, (int*)nullptr, NoGroup{});
     DS_LAUNCH_CHECK();
     if (splits > 1) {
@@ -926,7 +860,7 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
         const bool ok_a = ta ? (M % BM == 0) : (K % BK == 0);
         const bool ok_b = tb ? (K % BK == 0) : true;
         const bool aligned = ((uintptr_t)A % 16 == 0) && ((uintptr_t)B % 16 == 0) && ((uintptr_t)C % 16 == 0);
-        if (ok_n && ok_a && ok_b && aligned && M >= 1 && K >= 1) {
+        if (ok_n && ok_a && ok_b && aligned && M >= 1 && K >= 1 && N < (1 << 23)) {      // (128 rows of fp32 within a 32-bit buffer length)
             const bool tn = ta && !tb && EPI == DS_EPI_ACC32;
             const size_t wsf = split_ws ? split_ws_floats : 0;
             if (!ta && tb) {
@@ -955,7 +889,7 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
                 if (c.pick.kind >= 0) return launch_gemm_tile(c.pick, true, M, N, K, A, B, C, EPI, p, split_ws, st);
             }
             if constexpr (EPI == DS_EPI_ACC32)      // (the TN form addresses a K tile of each operand through a 32-bit buffer length)
-                if (ta && !tb && M <= (1 << 25) && N <= (1 << 25)) return launch_nt<EPI, true>(M, N, K, A, B, C, p, split_ws, split_ws_floats, st);
+                if (ta && !tb && M < (1 << 25) && N < (1 << 25)) return launch_nt<EPI, true>(M, N, K, A, B, C, p, split_ws, split_ws_floats, st);
         }
     }
     if (dtype == DS_DTYPE_BF16) return launch_generic<bf16_t, EPI>(ta, tb, M, N, K, A, B, C, p, st);
@@ -1039,17 +973,15 @@ __global__ __launch_bounds__(256) void tn_group_finish_kernel(TnGroup g) {
 }
 
 ds_status launch_tn_group_big(TnGroup& g, int blocks, hipStream_t st) {
-    auto kern = gemm_bf16_nt_kernel<DS_EPI_ACC32, NT_WM, NT_WN, true, false, true>;
-    constexpr int stg = NT_WM * NT_WN * 32 * ((256 / NT_WN) + 4) * 4;
-    constexpr int smem = NT_NS * NT_STAGE > stg ? NT_NS * NT_STAGE : stg;
+    auto kern = gemm_bf16_nt_kernel<DS_EPI_ACC32, true, false, true>;
     static bool attr_set = false;
     if (!attr_set) {
-        DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, RING));
         attr_set = true;
     }
     GemmEpi p{};
     p.accumulate = g.accumulate;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NT_WM * NT_WN * 64), smem, st, 0, 0, g.K, (const bf16_t*)nullptr,
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), RING, st, 0, 0, g.K, (const bf16_t*)nullptr,
                        (const bf16_t*)nullptr, (bf16_t*)nullptr, 0, 0, g.splits, 0, 1, (float*)nullptr, p, 0, (int*)nullptr, g);
     DS_LAUNCH_CHECK();
     if (g.splits > 1) {

@@ -22,7 +22,7 @@ __device__ __forceinline__ int tn_group_problem(const TnGroup& g, int& l) {
 
 // ---------------------------------------------------------------------------- epilogues
 // Applied to 8 consecutive columns n..n+7 of row m; acc holds the fp32 accumulators.
-// What an epilogue reads besides the accumulators, fetched ahead of time (8 elements of R, of R2, the row flag),
+// What an epilogue reads besides the accumulators, fetched ahead of time (8 elements of R, of R2, the row's entry of row_valid),
 // so that a caller can issue these loads for several rows at once instead of one dependent round trip per row.
 // Kept in storage precision (16 bytes per operand for bf16) so that a whole tile's worth fits in registers.
 template <class T> struct EpiPre {
@@ -44,7 +44,7 @@ __device__ __forceinline__ void epilogue_prefetch(int m, int n, int N, const Gem
     const size_t off = (size_t)m * N + n;
     q.valid = 1;
     if (EPI == DS_EPI_RESID) {
-        if (p.row_valid) q.valid = p.row_valid[m] >= 0;
+        if (p.row_valid) q.valid = p.row_valid[m];
         load8_raw(reinterpret_cast<const T*>(p.R) + off, q.r);
     } else if (EPI == DS_EPI_DGELU || EPI == DS_EPI_GATE || EPI == DS_EPI_MULR) {
         load8_raw(reinterpret_cast<const T*>(p.R) + off, q.r);
@@ -57,6 +57,68 @@ template <int EPI> constexpr bool epilogue_reads() {
     return EPI == DS_EPI_RESID || EPI == DS_EPI_DGELU || EPI == DS_EPI_GATE || EPI == DS_EPI_DGATE || EPI == DS_EPI_MULR;
 }
 
+// whether there is a second output
+template <int EPI> constexpr bool epilogue_second() {
+    return EPI == DS_EPI_GELU || EPI == DS_EPI_GELU_D || EPI == DS_EPI_GATE || EPI == DS_EPI_DGATE;
+}
+// 8 floats as they are stored
+template <class T> struct Pack8 { typedef T type __attribute__((ext_vector_type(8))); };
+template <class T> __device__ __forceinline__ typename Pack8<T>::type pack8(const float (&v)[8]) {
+    typename Pack8<T>::type a;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = from_f32<T>(v[i]);
+    return a;
+}
+// streaming store: the line is not kept in L2 (outputs far larger than the cache would only evict operands that other work-groups
+// are about to read again)
+__device__ __forceinline__ void store8_nt(bf16_t* p, const Pack8<bf16_t>::type& v) { __builtin_nontemporal_store(v, reinterpret_cast<bf16x8_t*>(p)); }
+__device__ __forceinline__ void store8_nt(float* p, const Pack8<float>::type& v) {
+    const f32x4_t a = {v[0], v[1], v[2], v[3]}, b = {v[4], v[5], v[6], v[7]};
+    __builtin_nontemporal_store(a, reinterpret_cast<f32x4_t*>(p));
+    __builtin_nontemporal_store(b, reinterpret_cast<f32x4_t*>(p + 4));
+}
+// The epilogue proper (all but ACC32), after the bias: acc becomes what is stored to C, one and two the stored forms of it and of the
+// second output
+template <class T, int EPI>
+__device__ __forceinline__ void epilogue_values(float (&acc)[8], const EpiPre<T>& q, typename Pack8<T>::type& one, typename Pack8<T>::type& two) {
+    float b[8];
+    if (EPI == DS_EPI_GELU) {
+        // round the pre-activation to storage precision first, so that forward and backward see the same z
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b[j] = gelu_f(to_f32(from_f32<T>(acc[j])));
+    } else if (EPI == DS_EPI_GELU_D) {
+        // what the layer's backward needs of the pre-activation is GELU'(z) alone: it is computed here, where the
+        // logistic term is at hand anyway, and stored in place of z; the backward epilogue is then one multiplication
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float z = acc[j];
+            gelu_and_grad_f(z, b[j], acc[j]);
+        }
+    } else if (EPI == DS_EPI_MULR) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] *= to_f32(q.r[j]);
+    } else if (EPI == DS_EPI_RESID) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = q.valid >= 0 ? acc[j] + to_f32(q.r[j]) : 0.f;
+    } else if (EPI == DS_EPI_DGELU) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] *= gelu_grad_f(to_f32(q.r[j]));
+    } else if (EPI == DS_EPI_GATE) {
+        // acc = u Wu (stored); second output = GELU(R) * acc with R = u Wg
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b[j] = gelu_f(to_f32(q.r[j])) * to_f32(from_f32<T>(acc[j]));
+    } else if (EPI == DS_EPI_DGATE) {
+        // acc = da; R = zg, R2 = zu; outputs dzg = da * zu * GELU'(zg) and dzu = da * GELU(zg)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float zg = to_f32(q.r[j]);
+            b[j] = acc[j] * gelu_f(zg);
+            acc[j] = acc[j] * to_f32(q.r2[j]) * gelu_grad_f(zg);
+        }
+    }
+    one = pack8<T>(acc);
+    if (epilogue_second<EPI>()) two = pack8<T>(b);
+}
 template <class T, int EPI>
 __device__ __forceinline__ void epilogue8(int m, int n, int N, float (&acc)[8], T* __restrict__ C, const GemmEpi& p,
                                           const EpiPre<T>* pre = nullptr) {
@@ -78,90 +140,15 @@ __device__ __forceinline__ void epilogue8(int m, int n, int N, float (&acc)[8], 
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[j] += b[j];
     }
-    if (EPI == DS_EPI_NONE) {
-        Vec8<T>::store_nt(C + off, acc);
-    } else if (EPI == DS_EPI_GELU) {
-        // round the pre-activation to storage precision first, so that forward and backward see the same z
-        float z[8], a[8];
-        Vec8<T>::store_nt(C + off, acc);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { z[j] = to_f32(from_f32<T>(acc[j])); a[j] = gelu_f(z[j]); }
-        Vec8<T>::store_nt(reinterpret_cast<T*>(p.C2) + off, a);
-    } else if (EPI == DS_EPI_GELU_D) {
-        // what the layer's backward needs of the pre-activation is GELU'(z) alone: it is computed here, where the
-        // logistic term is at hand anyway, and stored in place of z; the backward epilogue is then one multiplication
-        float dz[8], a[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) gelu_and_grad_f(acc[j], a[j], dz[j]);
-        Vec8<T>::store_nt(C + off, dz);
-        Vec8<T>::store_nt(reinterpret_cast<T*>(p.C2) + off, a);
-    } else if (EPI == DS_EPI_MULR) {
-        float r[8];
-        if (pre) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) r[j] = to_f32(pre->r[j]);
-        } else {
-            Vec8<T>::load(reinterpret_cast<const T*>(p.R) + off, r);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] *= r[j];
-        Vec8<T>::store_nt(C + off, acc);
-    } else if (EPI == DS_EPI_RESID) {
-        if (pre) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] = pre->valid ? acc[j] + to_f32(pre->r[j]) : 0.f;
-        } else if (p.row_valid && p.row_valid[m] < 0) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-        } else {
-            float r[8];
-            Vec8<T>::load(reinterpret_cast<const T*>(p.R) + off, r);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] += r[j];
-        }
-        Vec8<T>::store_nt(C + off, acc);
-    } else if (EPI == DS_EPI_DGELU) {
-        float z[8];
-        if (pre) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) z[j] = to_f32(pre->r[j]);
-        } else {
-            Vec8<T>::load(reinterpret_cast<const T*>(p.R) + off, z);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] *= gelu_grad_f(z[j]);
-        Vec8<T>::store_nt(C + off, acc);
-    } else if (EPI == DS_EPI_GATE) {
-        // acc = u Wu (stored); C2 = GELU(R) * acc with R = u Wg
-        float zg[8], a[8];
-        Vec8<T>::store_nt(C + off, acc);
-        if (pre) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) zg[j] = to_f32(pre->r[j]);
-        } else {
-            Vec8<T>::load(reinterpret_cast<const T*>(p.R) + off, zg);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] = gelu_f(zg[j]) * to_f32(from_f32<T>(acc[j]));
-        Vec8<T>::store_nt(reinterpret_cast<T*>(p.C2) + off, a);
-    } else if (EPI == DS_EPI_DGATE) {
-        // acc = da; R = zg, R2 = zu; C = dzg = da * zu * GELU'(zg); C2 = dzu = da * GELU(zg)
-        float zg[8], zu[8], o1[8], o2[8];
-        if (pre) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) { zg[j] = to_f32(pre->r[j]); zu[j] = to_f32(pre->r2[j]); }
-        } else {
-            Vec8<T>::load(reinterpret_cast<const T*>(p.R) + off, zg);
-            Vec8<T>::load(reinterpret_cast<const T*>(p.R2) + off, zu);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            o1[j] = acc[j] * zu[j] * gelu_grad_f(zg[j]);
-            o2[j] = acc[j] * gelu_f(zg[j]);
-        }
-        Vec8<T>::store_nt(C + off, o1);
-        Vec8<T>::store(reinterpret_cast<T*>(p.C2) + off, o2);
+    EpiPre<T> own;
+    if (epilogue_reads<EPI>() && !pre) {
+        epilogue_prefetch<T, EPI>(m, n, N, p, own);
+        pre = &own;
     }
+    typename Pack8<T>::type one, two;
+    epilogue_values<T, EPI>(acc, epilogue_reads<EPI>() ? *pre : own, one, two);
+    store8_nt(C + off, one);
+    if (epilogue_second<EPI>()) store8_nt(reinterpret_cast<T*>(p.C2) + off, two);
 }
 
 // sum the split-K partials ([split][M][N]) in split order and apply the epilogue; one thread per 8 columns

@@ -1010,3 +1010,48 @@ def test_gemm_every_macro_tile_weight_gradient(M, N, K, ws_floats):
     ds.ds_gemm(dX, ddY, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, accumulate=True, workspace=ws)
     torch.cuda.synchronize()
     assert both_err(to_np(c), 2 * ref) <= 1e-5
+
+
+@pytest.mark.parametrize("K", [64, 128, 192, 320, 384, 448])
+@pytest.mark.parametrize("M", [4097, 4133, 4224])
+def test_gemm_ring_of_k_tiles_nt(M, K):
+    """256 x 256 tiles whose K loop is shorter than, as long as and longer than the ring of LDS units (one to seven K tiles), persistent
+    (544 tiles) with the tiles behind the last whole round; the last tile row has 1, 37 and 128 rows.  bf16 results: one rounding,
+    2^-9 of each value; the rows behind the last one are not written."""
+    N = 8192
+    rng = np.random.default_rng(43)
+    dA, dB, dR = (to_dev(_rnd(rng, s, BF, f), BF) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((M, N), 1.0)))
+    db = to_dev(_rnd(rng, (N,), BF), BF)
+    valid = torch.from_numpy(np.where(rng.random(M) < 0.8, 1, -1).astype(np.int32)).to(DEV)
+    acc = torch.matmul(dA.double(), dB.double().t().contiguous())
+    ws = _ws(1 << 22)
+    c, c2 = (torch.empty((M + 1, N), dtype=BF, device=DEV) for _ in range(2))
+    for kw, ref, ref2 in ((dict(bias=db), acc + db.double(), None),
+                          (dict(epilogue=ds.DS_EPI_RESID, bias=db, R=dR, row_valid=valid), (acc + db.double() + dR.double()) * (valid >= 0).double()[:, None], None),
+                          (dict(epilogue=ds.DS_EPI_GATE, R=dR), acc, torch.nn.functional.gelu(dR.double(), approximate="tanh") * acc)):
+        c.fill_(7.0)
+        c2.fill_(7.0)
+        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, workspace=ws, C2=c2, **kw)
+        torch.cuda.synchronize()
+        for got, want in ((c, ref), (c2, ref2)):
+            if want is not None:
+                assert float((got[:M].double() - want).norm() / want.norm()) <= 6e-3
+                assert bool(((got[:M].double() - want).abs() <= 6e-3 * (8 * want.square().mean().sqrt() + want.abs())).all())
+            assert bool((got[M] == 7.0).all())
+
+
+@pytest.mark.parametrize("K", [1, 63, 65, 128, 200, 321, 450])
+def test_gemm_ring_of_k_tiles_weight_gradient(K):
+    """The same for weight gradients (576 tiles, one work-group each): one to eight K tiles, the last one ragged, overwriting and adding; rows
+    behind the last one hold NaN.  fp32 sums: 1e-5."""
+    M, N = 8192, 4608
+    rng = np.random.default_rng(44)
+    dX, ddY = (torch.cat([to_dev(_rnd(rng, (K, n), BF), BF), torch.full((64, n), float("nan"), dtype=BF, device=DEV)]) for n in (M, N))
+    ref = torch.matmul(dX[:K].double().t().contiguous(), ddY[:K].double())
+    c = torch.full((M, N), 3.0, dtype=F32, device=DEV)
+    for times in (1, 2):
+        ds.ds_gemm(dX, ddY, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, accumulate=times == 2)
+        torch.cuda.synchronize()
+        want = times * ref
+        assert float((c.double() - want).norm() / want.norm()) <= 1e-5
+        assert bool(((c.double() - want).abs() <= 1e-5 * (8 * want.square().mean().sqrt() + want.abs())).all())
