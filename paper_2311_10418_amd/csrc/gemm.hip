@@ -107,10 +107,17 @@ constexpr int BM = 256, BN = 256, BK = 64;
 // Tried: two 64 KB stages with this wavefront shape (4096 x 4096 x 16 384 519 us, ring 378); all transfers right behind the
 // barrier, one every two MFMAs (5 to 8 % slower); 32x32x16 instructions (5 to 9 % slower); 256 x 128 tiles, two work-groups
 // of four wavefronts to a CU (15 to 20 % slower: half as many transfers again).
+//
+// NT launches of at most one round have two lower tiles besides, 192 x 256 and 128 x 256 (NUA = 6, 4: wavefronts of 96 x 128 and
+// 64 x 128, the units of A only partly filled); choose_kernel has the rule and what they measured.
 constexpr int UNIT = 256 * BK * 2, RING = 5 * UNIT;      // one operand's K tile in LDS; the whole ring
 constexpr int NT_WM = 2;                        // rows of wavefronts in a work-group
-constexpr int NT_DB = 4, NT_DA = 8;             // a transfer of B every NT_DB, of A every NT_DA MFMAs
-constexpr int NT_A1 = (64 - 8 * NT_DB - 2) / NT_DA + 1;         // transfers of A in a tile's second step; the rest go in the first step of the next
+template <int NUA> struct Issue {               // where in its steps a wavefront issues what
+    static constexpr int STEP = NUA * 8;                            // MFMAs of a step
+    static constexpr int RD = NUA == 8 ? 3 : 2;                     // a fragment read every RD,
+    static constexpr int DB = NUA / 2, DA = NUA == 4 ? 4 : NUA;     // a transfer of B every DB, of A every DA MFMAs
+    static constexpr int ALL = (STEP - 8 * DB - 2) / DA + 1, A1 = ALL < NUA ? ALL : NUA;    // transfers of A in a tile's second step; the rest go in the next step
+};
 // tile number -> tile coordinates: groups of NT_GROUP tile rows, column-major inside a group
 constexpr int NT_GROUP = 4;
 __host__ __device__ __forceinline__ void nt_tile_coords(int logical, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
@@ -139,7 +146,7 @@ __host__ __device__ __forceinline__ void nt_tile_coords(int logical, int tiles_m
 // finish puts the counters back to zero (ps_ctr[8] counts the finished ones).
 //
 // GRP (TN form): the work-groups of several weight gradients over the same K rows (grp), problem after problem.
-template <int EPI, bool TNF, bool PS, bool GRP = false>
+template <int EPI, bool TNF, bool PS, bool GRP = false, int NUA = 8>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
                                                               const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
                                                               int tiles_m, int tiles_n, int splits,
@@ -149,7 +156,10 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
                                                               std::conditional_t<GRP, TnGroup, NoGroup> grp) {
     static_assert(!(PS && TNF), "the persistent form exists for the NT kernel only");
     static_assert(!GRP || (TNF && EPI == DS_EPI_ACC32), "groups are of weight gradients");
+    static_assert(NUA == 8 || !(TNF || PS), "lower tiles: NT, one round");
     extern __shared__ __attribute__((aligned(16))) char smem[];
+    typedef Issue<NUA> Z;
+    constexpr int WA = NUA * 16, TA = 2 * WA;       // rows of a wavefront, of a tile
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
 
@@ -214,7 +224,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
     const int t_end = __builtin_amdgcn_readfirstlane((t_begin + per_split) < nt_total ? (t_begin + per_split) : nt_total);
 
     // What the transfers of a tile need: its corner and the operand bases there (set_tile), and per-lane offsets that are the same for every
-    // tile.  An operand's K tile is 32 transfers, eight per wavefront: NT 8 rows of 128 bytes each, TN 2 k-rows of 512.
+    // tile.  An operand's K tile is 32 transfers, eight per wavefront (of A, NUA): NT 8 rows of 128 bytes each, TN 2 k-rows of 512.
     int tile_m = 0, tile_n = 0, m0 = 0, n0 = 0;
     const char* pa = nullptr;
     const char* pb = nullptr;
@@ -223,25 +233,28 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         nt_tile_coords(lg, tiles_m, tiles_n, tile_m, tile_n);
         tile_m = __builtin_amdgcn_readfirstlane(tile_m);
         tile_n = __builtin_amdgcn_readfirstlane(tile_n);
-        m0 = tile_m * BM;
+        m0 = tile_m * TA;
         n0 = tile_n * BN;
-        const uint64_t bytes = (uint64_t)(uint32_t)(M - m0 < BM ? M - m0 : BM) * (uint32_t)K * 2u;
+        const uint64_t bytes = (uint64_t)(uint32_t)(M - m0 < TA ? M - m0 : TA) * (uint32_t)K * 2u;
         len_a = bytes > 0xFFFFFFFFu ? 0xFFFFFFFFu : (uint32_t)bytes;
         pa = reinterpret_cast<const char*>(A) + (TNF ? (long long)m0 * 2 : (long long)m0 * K * 2);
         pb = reinterpret_cast<const char*>(B) + (TNF ? (long long)n0 * 2 : (long long)n0 * K * 2);
     };
     set_tile(logical);
-    uint32_t offA[8], offB[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int u = (wave * 8 + i) * 64 + lane;                   // 16-byte unit of the tile
+    uint32_t offA[NUA], offB[8];
+    auto lane_offset = [&](int first, uint32_t ld) {
+        const int u = first * 64 + lane;                            // 16-byte unit of the tile
         const int row = TNF ? u >> 5 : u >> 3, pos = TNF ? u & 31 : u & 7;
         const int chunk = TNF ? (((pos >> 1) ^ (row & 7)) << 1) | (pos & 1) : pos ^ ((row >> 1) & 7);
-        offA[i] = ((uint32_t)row * (uint32_t)(TNF ? M : K) + chunk * 8) * 2;
-        offB[i] = TNF ? ((uint32_t)row * (uint32_t)N + chunk * 8) * 2 : offA[i];
+        return ((uint32_t)row * ld + chunk * 8) * 2;
+    };
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        offB[i] = lane_offset(wave * 8 + i, (uint32_t)(TNF ? N : K));
+        if (i < NUA) offA[i] = TNF || NUA != 8 ? lane_offset(wave * NUA + i, (uint32_t)(TNF ? M : K)) : offB[i];
     }
     const uint32_t lds0 = lds_address(smem);
-    // The A (part 0) or B (1) part of K tile `tile` as a raw buffer, and its transfer i (0..7) into ring unit `unit`.  Tiles past the
+    // The A (part 0) or B (1) part of K tile `tile` as a raw buffer, and its transfer i into ring unit `unit`.  Tiles past the
     // end are buffers of length zero: they fetch nothing, but the wait counts are the same at every step.  TN: the buffer ends
     // at the last k-row, so that rows past a ragged K arrive as zeros; NT: at the last row of A.
     auto part = [&](int which, int tile) {
@@ -254,25 +267,25 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
             return make_raw_buffer((which ? pb : pa) + (long long)tile * (BK * 2), (which ? 0xFFFFFFFFu : len_a) & inside);
         }
     };
-    const uint32_t lds_wave = lds0 + (uint32_t)wave * 8192;
-    auto transfer_a = [&](i32x4_t buf, int unit, int i) { lds_dma16_buffer(buf, offA[i], lds_wave + (uint32_t)unit * UNIT + i * 1024); };
-    auto transfer_b = [&](i32x4_t buf, int unit, int i) { lds_dma16_buffer(buf, offB[i], lds_wave + (uint32_t)unit * UNIT + i * 1024); };
-    auto first_transfer = [&](int tile, int h, int i) {             // transfer i (0..15) of the first (h = 0) or second K tile: units 0 to 3
-        if (i < 8) transfer_a(part(0, tile), 2 * h, i);
-        else transfer_b(part(1, tile), 2 * h + 1, i - 8);
+    const uint32_t lds_a = lds0 + (uint32_t)wave * (NUA * 1024), lds_b = lds0 + (uint32_t)wave * 8192;
+    auto transfer_a = [&](i32x4_t buf, int unit, int i) { lds_dma16_buffer(buf, offA[i], lds_a + (uint32_t)unit * UNIT + i * 1024); };
+    auto transfer_b = [&](i32x4_t buf, int unit, int i) { lds_dma16_buffer(buf, offB[i], lds_b + (uint32_t)unit * UNIT + i * 1024); };
+    auto first_transfer = [&](int tile, int h, int i) {             // transfer i (0 .. NUA + 7) of the first (h = 0) or second K tile: units 0 to 3
+        if (i < NUA) transfer_a(part(0, tile), 2 * h, i);
+        else transfer_b(part(1, tile), 2 * h + 1, i - NUA);
     };
-    // fragments: fb[s] / fa[s] = the 8 column / row units of this wavefront, 32-deep step s of a tile.
+    // fragments: fb[s] / fa[s] = the 8 column / NUA row units of this wavefront, 32-deep step s of a tile.
     // NT: 128-byte rows: 16 consecutive rows at one chunk index must hit 16 different 16-byte units of a 256-byte
     // window: rows 2q and 2q+1 differ by 128 bytes, the XOR with (row/2)%8 separates the 8 row pairs.
     // TN: 512-byte k-rows.  One fragment (16 features x 32 k) is two transpose reads, each 16 k-rows x 32 bytes: lane
     // (i = lane%16, g = lane/16) addresses k-row 4g + i/4 (+16 for the second read) at features (i%4)*4 of the
     // 16-feature unit and receives feature i at k-rows 4g..4g+3.  The 32 lanes served together touch 8 k-rows, so the
     // 32-byte unit index is XORed with row%8.
-    bf16x8_t fa[2][8], fb[2][8];
+    bf16x8_t fa[2][NUA], fb[2][8];
     const int fr = lane & 15, fg = lane >> 4;
     const int nt_lane[2] = {fr * 128 + ((fg ^ ((fr >> 1) & 7)) << 4), fr * 128 + (((4 + fg) ^ ((fr >> 1) & 7)) << 4)};
     const int tr_row = 4 * fg + (fr >> 2), tr_lane = tr_row * 512 + (lane & 3) * 8;
-    auto fragment = [&](int unit, int part, int s, int x) -> bf16x8_t {       // part: this wavefront's row or column in the 2 x 2 grid
+    auto fragment = [&](int unit, int part, int rows, int s, int x) -> bf16x8_t {     // part: this wavefront's row or column in the 2 x 2 grid
         if constexpr (TNF) {
             typedef short s16x4_t __attribute__((ext_vector_type(4)));
             typedef short s16x8_t __attribute__((ext_vector_type(8)));
@@ -283,15 +296,15 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
             const s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             return __builtin_bit_cast(bf16x8_t, v);
         } else {
-            return *reinterpret_cast<const bf16x8_t*>(smem + unit * UNIT + part * (128 * 128) + nt_lane[s] + x * 2048);
+            return *reinterpret_cast<const bf16x8_t*>(smem + unit * UNIT + part * (rows * 128) + nt_lane[s] + x * 2048);
         }
     };
-    auto read = [&](int ua, int ub, int s, int r) {                 // read r (0..15) of a step: the column units first
-        if (r < 8) fb[s][r] = fragment(ub, wn, s, r);
-        else fa[s][r - 8] = fragment(ua, wm, s, r - 8);
+    auto read = [&](int ua, int ub, int s, int r) {                 // read r (0 .. NUA + 7) of a step: the column units first
+        if (r < 8) fb[s][r] = fragment(ub, wn, 128, s, r);
+        else fa[s][r - 8] = fragment(ua, wm, WA, s, r - 8);
     };
-    f32x4_t acc[8][8], start[8];
-    // One step: 64 MFMAs on the fragments of 32-deep step s, the reads of the next step (from units ua, ub) and what tr(q) issues
+    f32x4_t acc[NUA][8], start[8];
+    // One step: NUA x 8 MFMAs on the fragments of 32-deep step s, the reads of the next step (from units ua, ub) and what tr(q) issues
     // between them, in exactly this order.  Operands swapped on purpose: the accumulator block is C^T (rows = n, columns =
     // m), so a lane holds 4 CONSECUTIVE n per block and the epilogue stages with 16-byte writes.  Boustrophedon order:
     // consecutive MFMAs share one operand and the other changes to its neighbour (about 2 % more sustained MFMA rate at the
@@ -300,11 +313,11 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
     // last: nothing left to read.
     auto step = [&](auto first_t, auto last_t, int s, int ua, int ub, auto&& tr) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < NUA; ++i)
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) {
                 const int j = (i & 1) ? 7 - jj : jj, q = i * 8 + jj;
-                if (!decltype(last_t)::value && q % 3 == 0 && q / 3 < 16) read(ua, ub, s ^ 1, q / 3);
+                if (!decltype(last_t)::value && q % Z::RD == 0 && q / Z::RD < NUA + 8) read(ua, ub, s ^ 1, q / Z::RD);
                 tr(q);
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[s][j], fa[s][i], decltype(first_t)::value ? start[j] : acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
@@ -326,7 +339,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) first_transfer(t_begin + h, h, i);
+                for (int i = 0; i < NUA + 8; ++i) first_transfer(t_begin + h, h, i);
             }
         }
         if constexpr (PS) {
@@ -339,18 +352,18 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         // the first K tile is there: behind its transfers came those of the second one and, persistent, at least the previous tile's stores
         constexpr int BEHIND = 16 + 32 * (epilogue_second<EPI>() || EPI == DS_EPI_ACC32 ? 2 : 1);
         if (PS && primed) __builtin_amdgcn_s_waitcnt(vmcnt_imm(BEHIND < 63 ? BEHIND : 63));
-        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(16));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(NUA + 8));
         __builtin_amdgcn_s_barrier();
         // A(tl + 2) is issued in part in the second step of tile tl - 1, the rest in the first step of tile tl
         i32x4_t a2 = part(0, t_begin + 2);
 #pragma unroll
-        for (int i = 0; i < NT_A1; ++i) transfer_a(a2, 4, i);
+        for (int i = 0; i < Z::A1; ++i) transfer_a(a2, 4, i);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) read(0, 1, 0, r);
+        for (int r = 0; r < NUA + 8; ++r) read(0, 1, 0, r);
         int tl = t_begin, ua = 0;                   // ua: unit of A(tl); those of B(tl), A(tl+1), B(tl+1), A(tl+2) follow it in the ring
         auto rest_of_a = [&](int q) {
-            const int x = q + 64 - 8 * NT_DB - 1;
-            if (x % NT_DA == 0 && x / NT_DA >= NT_A1 && x / NT_DA < 8) transfer_a(a2, wrap(ua + 4), x / NT_DA);
+            const int x = q + Z::STEP - 8 * Z::DB - 1;
+            if (x % Z::DA == 0 && x / Z::DA >= Z::A1 && x / Z::DA < NUA) transfer_a(a2, wrap(ua + 4), x / Z::DA);
         };
         const std::true_type yes;
         const std::false_type no;
@@ -361,12 +374,12 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
             a2 = part(0, tl + 3);
             // tile tl+1 has landed for this wavefront (A(tl+2) may be outstanding), its reads of tile tl are done, then everybody's:
             // the units of tile tl are free
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(8) & 0xF0FF);
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(NUA) & 0xF0FF);
             __builtin_amdgcn_s_barrier();
             step(no, no, 1, na, nb, [&](int q) {
-                const int x = q - 8 * NT_DB - 1;
-                if (q % NT_DB == 1 && q / NT_DB < 8) transfer_b(b2, ua, q / NT_DB);
-                if (x >= 0 && x % NT_DA == 0 && x / NT_DA < NT_A1) transfer_a(a2, ub, x / NT_DA);
+                const int x = q - 8 * Z::DB - 1;
+                if (q % Z::DB == 1 && q / Z::DB < 8) transfer_b(b2, ua, q / Z::DB);
+                if (x >= 0 && x % Z::DA == 0 && x / Z::DA < Z::A1) transfer_a(a2, ub, x / Z::DA);
             });
             ua = na;
             ++tl;
@@ -376,15 +389,16 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         // ---- epilogue, 16 rows x 64 columns (a pass) at a time through a block of LDS that is private to the wavefront: two times 16 rows of 64
         // floats, 16-byte chunk c of row r at c ^ r.  Pass s takes columns 64 (s % 2) .. of rows 16 (s / 2) ..; a lane finishes rows
         // lane / 8 and lane / 8 + 8 of it (g = 0, 1), 8 columns each.
-        const int em0 = m0 + wm * 128, en0 = n0 + wn * 128, etile_m = tile_m, elogical = logical;
+        constexpr int NP = 2 * NUA;                     // passes
+        const int em0 = m0 + wm * WA, en0 = n0 + wn * 128, etile_m = tile_m, elogical = logical;
         int elane = lane;                              // (opaque, so that no address of the epilogue is kept in registers over the K loop)
         asm volatile("" : "+v"(elane));
         const int rd_row = elane >> 3, rd_col = (elane & 7) * 8, wr_row = elane & 15, wr_col = elane >> 4;
-        // The wavefront's 128 rows of a tensor of M x N elements of es bytes as a raw buffer that ends behind the last one which exists, so
+        // The wavefront's rows of a tensor of M x N elements of es bytes as a raw buffer that ends behind the last one which exists, so
         // that every access is made, without a branch: rows past M are read as zeros and not written.  (With branches around the rows
         // the compiler cannot count what is in flight and waits for everything, its own last store included, in front of every row:
         // 65 582 x 2048 x 2048 with a residual 487 -> 572 us.)  on = false: an empty buffer
-        const int row_cnt = M - em0 < 0 ? 0 : M - em0 < 128 ? M - em0 : 128;
+        const int row_cnt = M - em0 < 0 ? 0 : M - em0 < WA ? M - em0 : WA;
         auto rows = [&](const void* tensor, int es, bool on) {
             return make_buffer(reinterpret_cast<const char*>(tensor) + ((size_t)em0 * N + en0) * es, on ? (uint32_t)row_cnt * (uint32_t)N * es : 0u);
         };
@@ -480,9 +494,9 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
             wave_lds_sync();
             Pass cur = get(0);
 #pragma unroll
-            for (int s = 0; s < 16; ++s) {
+            for (int s = 0; s < NP; ++s) {
                 Pass next = cur;
-                if (s + 1 < 16) {
+                if (s + 1 < NP) {
                     put(s + 1);
                     wave_lds_sync();
                     next = get(s + 1);
@@ -509,7 +523,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
             }
         };
         // column sums of what this lane writes (DGELU: the bias gradient of the layer below comes out of this kernel
-        // instead of a pass over the stored tensor); every lane finishes 16 rows of the same 16 columns
+        // instead of a pass over the stored tensor); every lane finishes 2 NUA rows of the same 16 columns
         constexpr bool SUMS = EPI == DS_EPI_DGELU || EPI == DS_EPI_MULR;
         float csum[2][8];
 #pragma unroll
@@ -549,7 +563,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
                     }
                 }
             }, [&](int s) {
-                if ((READS || OLD) && s + PRE < 16) prefetch_pass(s + PRE);
+                if ((READS || OLD) && s + PRE < NP) prefetch_pass(s + PRE);
             });
         }
         if constexpr (SUMS) {
@@ -562,7 +576,19 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
                     for (int o = 8; o < 64; o <<= 1)
 #pragma unroll
                         for (int j = 0; j < 8; ++j) csum[h][j] += __shfl_xor(csum[h][j], o, 64);
-                    if (lane < 8) Vec8<float>::store(p.colsum + (size_t)(etile_m * NT_WM + wm) * N + en0 + h * 64 + rd_col, csum[h]);
+                    if (NUA == 8 && lane < 8) Vec8<float>::store(p.colsum + (size_t)(etile_m * NT_WM + wm) * N + en0 + h * 64 + rd_col, csum[h]);
+                }
+                if constexpr (NUA == 4) {
+                    // one row per tile row: the two wavefronts of a column add theirs in LDS.  Two rows are counted per 256
+                    // (gemm_colsum_rows): the last one may have no tile
+                    float* red = reinterpret_cast<float*>(smem);
+                    if (lane < 8) {
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) Vec8<float>::store(red + wm * BN + wn * 128 + h * 64 + rd_col, csum[h]);
+                    }
+                    __syncthreads();
+                    p.colsum[(size_t)etile_m * N + n0 + t] = red[t] + red[BN + t];
+                    if (etile_m + 1 == tiles_m && (tiles_m & 1)) p.colsum[(size_t)(etile_m + 1) * N + n0 + t] = 0.f;
                 }
             }
         }
@@ -810,8 +836,34 @@ ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, 
     return DS_OK;
 }
 
+// NT, every tile unsplit, tiles of 32 NUA rows
+template <int EPI, int NUA>
+ds_status launch_nt_lower(int M, int N, int K, const void* A, const void* B, void* C, const GemmEpi& p, hipStream_t st) {
+    static bool attr_set = false;
+    auto kern = gemm_bf16_nt_kernel<EPI, false, false, false, NUA>;
+    if (!attr_set) {
+        DS_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, RING));
+        attr_set = true;
+    }
+    const int tiles_m = (M + 32 * NUA - 1) / (32 * NUA), tiles_n = N / BN, tiles = tiles_m * tiles_n;
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(256), RING, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, (bf16_t*)C, tiles_m,
+                       tiles_n, 1, tiles, 1, (float*)nullptr, p, 0, (int*)nullptr, NoGroup{});
+    DS_LAUNCH_CHECK();
+    return DS_OK;
+}
+
 // Which matrix-core kernel an NT launch (tn: a weight gradient) goes to and what it is expected to take: pick.kind -1 = 256 x 256
-// tiles.
+// tiles, kLower192 and kLower128 = 192 x 256 and 128 x 256.
+//
+// The lower tiles are for launches that leave CUs idle with 256 x 256 tiles and still fit into one round with these: the K loop of a
+// CU is shorter by what its tile is lower, less what a transfer, a fragment read and a wait cost per MFMA.  Measured per K tile
+// and around them, microseconds, operands from memory / warm: 256 rows 1.25 / 1.15 and 4 (big_cost); 192 rows 1.07 / 0.85, 128 rows 0.99 / 0.65.
+// Of 110 shapes whose launch is one round (N = 256 .. 8192, K = 64 .. 8192, plain and residual outputs), with these against without,
+// geometric means: from memory 0.97, warm 0.95; below K = 512 on at least two thirds of the CUs 0.83 and 0.93, on fewer 1.11 and 1.05 (not
+// taken: where a launch is mostly its ends, small tiles on all CUs are better).  Of the rest 2 lose more than 3 % of the mean of both, at
+// worst 6 %.  (Estimates of 1.05 and 0.85, closer to the warm rates: 0.99 and 0.95.)
+constexpr int kLower192 = 100, kLower128 = 101;
+constexpr double kStep192 = 1.10, kStep128 = 1.05;
 struct NtChoice {
     TilePick pick;
     double cost;
@@ -820,6 +872,13 @@ static NtChoice choose_kernel(bool tn, int epi, int M, int N, int K, size_t wsf,
     const BigPlan plan = plan_big(tn, epi, M, N, K, wsf);
     const double out_us = gemm_output_us(epi, M, N, accumulate);
     NtChoice c{TilePick{-1, 1, 0.0, 0.0}, big_cost(plan, tn, M, N) + out_us};
+    if (!tn)
+        for (const int rows : {192, 128}) {
+            const long long work_groups = ((long long)M + rows - 1) / rows * (N / BN);
+            if (work_groups > gemm_cu_count() || (colsum && rows != 128) || (K < 512 && 3 * work_groups < 2 * gemm_cu_count())) continue;
+            const double cost = plan.nt * (rows == 192 ? kStep192 : kStep128) + 4 * rows / 256.0 + out_us;
+            if (cost < c.cost) c = NtChoice{TilePick{rows == 192 ? kLower192 : kLower128, 1, cost, cost}, cost};
+        }
     if (plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
         // launches that do not fill the chip with 256 x 256 tiles: smaller ones, where the estimates say so (ties go to the large tile)
         const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, colsum, out_us, accumulate != 0);
@@ -865,6 +924,8 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
             const size_t wsf = split_ws ? split_ws_floats : 0;
             if (!ta && tb) {
                 auto launch = [&](const NtChoice& c, int m, const void* a, void* out, const GemmEpi& q) -> ds_status {
+                    if (c.pick.kind == kLower192) return launch_nt_lower<EPI, 6>(m, N, K, a, B, out, q, st);
+                    if (c.pick.kind == kLower128) return launch_nt_lower<EPI, 4>(m, N, K, a, B, out, q, st);
                     if (c.pick.kind >= 0) return launch_gemm_tile(c.pick, false, m, N, K, a, B, out, EPI, q, split_ws, st);
                     return launch_nt<EPI, false>(m, N, K, a, B, out, q, split_ws, split_ws_floats, st);
                 };

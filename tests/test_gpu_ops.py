@@ -994,7 +994,7 @@ def test_gemm_every_macro_tile_nt(M, N, K, ws_floats):
     # 128 x 128 with two groups of wavefronts: 33 (the last one ragged) and, split, more K tiles
     (1792, 1792, 2049, 0), (256, 2816, 20001, 1 << 22),
     (2560, 3328, 129, 0), (2560, 3328, 200, 0), (2560, 6656, 65, 0),
-    # 256 x 256 (32-deep K tiles): one, a ragged few, ranges of the contraction, whole tiles and a split remainder
+    # 256 x 256 (64-deep K tiles): one, a ragged few, ranges of the contraction, whole tiles and a split remainder
     (10240, 3328, 1, 0), (10240, 3328, 97, 0), (256, 5632, 12000, 1 << 24), (10240, 3328, 250, 1 << 22)])
 def test_gemm_every_macro_tile_weight_gradient(M, N, K, ws_floats):
     """The same for weight gradients, overwriting and adding; rows behind the last one hold NaN.  fp32 sums: 1e-5."""
@@ -1038,6 +1038,29 @@ def test_gemm_ring_of_k_tiles_nt(M, K):
                 assert float((got[:M].double() - want).norm() / want.norm()) <= 6e-3
                 assert bool(((got[:M].double() - want).abs() <= 6e-3 * (8 * want.square().mean().sqrt() + want.abs())).all())
             assert bool((got[M] == 7.0).all())
+
+
+@pytest.mark.parametrize("K", [64, 128, 192, 320, 448])
+@pytest.mark.parametrize("M,N", [(3456, 3072), (3457, 3072), (3647, 3072), (769, 8192), (897, 8192), (1024, 8192), (130, 256)])
+def test_gemm_lower_tiles_nt(M, N, K):
+    """Launches of one round, which lower tiles of 192 x 256 and 128 x 256 may take: full last tile rows, ones of a single row and one row short, K
+    loops around the length of the ring of LDS units.  bf16 results: one rounding, 2^-9 of each value; the rows behind the last one are
+    not written."""
+    rng = np.random.default_rng(45)
+    dA, dB, dR = (to_dev(_rnd(rng, s, BF, f), BF) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((M, N), 1.0)))
+    db = to_dev(_rnd(rng, (N,), BF), BF)
+    valid = torch.from_numpy(np.where(rng.random(M) < 0.8, 1, -1).astype(np.int32)).to(DEV)
+    acc = torch.matmul(dA.double(), dB.double().t().contiguous())
+    ws = _ws(1 << 22)
+    c = torch.empty((M + 1, N), dtype=BF, device=DEV)
+    for kw, want in ((dict(bias=db), acc + db.double()),
+                     (dict(epilogue=ds.DS_EPI_RESID, bias=db, R=dR, row_valid=valid), (acc + db.double() + dR.double()) * (valid >= 0).double()[:, None])):
+        c.fill_(7.0)
+        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        assert float((c[:M].double() - want).norm() / want.norm()) <= 6e-3
+        assert bool(((c[:M].double() - want).abs() <= 6e-3 * (8 * want.square().mean().sqrt() + want.abs())).all())
+        assert bool((c[M] == 7.0).all())
 
 
 @pytest.mark.parametrize("K", [1, 63, 65, 128, 200, 321, 450])

@@ -285,6 +285,23 @@ def test_bias_gradient_from_partial_column_sums(d_ff, rows):
     used.close()
 
 
+@pytest.mark.parametrize("rows", [641, 768, 897, 1024])
+def test_bias_gradient_from_column_sums_of_lower_tiles(rows):
+    """The same where the product is one round of 128 x 256 tiles, which give one partial row each: even and odd counts of tile rows."""
+    lens = np.array([rows], np.int32)
+    params = wl.draw_params(wl.GPT_KEYS, 1, 256, 8192, seed=4, bf16=True)
+    xs = wl.draw_embedded_tokens(lens, 256, seed=rows, bf16=True)
+    dys = wl.draw_rows(lens, 256, seed=rows, tag=5, bf16=True)
+    lo = ds.ds_layout_from_cuts(lens, [0, 1])
+    cfg = dict(n_layers=1, d_model=256, n_heads=4, d_ff=8192)
+    stage = ds.Stage(ds.DS_MODEL_GPT, ds.DS_DTYPE_BF16, 1, 256, 4, 8192, max_rows=1024, max_seqs=4)
+    run_gpt_stage(lo, cfg, params, xs, [1000.0 * y for y in dys], ds.DS_DTYPE_BF16, stage=stage)     # (fills the partial rows)
+    got = run_gpt_stage(lo, cfg, params, xs, dys, ds.DS_DTYPE_BF16, stage=stage)
+    stage.close()
+    ref = ost.gpt_stage_fwd_bwd(xs, dys, params, 4)
+    check(got[2][0]["b_1"], ref[2][0]["b_1"], TOL[ds.DS_DTYPE_BF16], "b_1 %d" % rows)
+
+
 # d, d_ff, tokens -> the tile that the weight gradients of a layer go out with, in one launch: 64 x 64; 128 x 64; 128 x 128 one
 # per CU; two per CU; 256 x 256; 256 x 256 with split contractions; fp32: ragged tiles of 64 x 128, whole and split.  Token counts that
 # are no multiple of a K tile.
