@@ -2,9 +2,9 @@
 // the paper's section "Micro-batch Construction" (Eq1, Eq2, memory cap), and layout builders
 // for the padding and packing baselines of section "Background".
 //
-// Design notes.  The candidate set of t_max is every distinct admissible slice cost.  Slices
-// are sorted by cost once; as t_max grows, newly admissible slices are switched on
-// incrementally, so each candidate only re-runs the O(N^2) recurrence, with one exactness-
+// Design notes.  The candidate set of t_max is every distinct admissible slice cost.  The scan starts at
+// the smallest one that has a partition at all (a minimax recurrence) with one O(N^2) pass; as t_max
+// grows, newly admissible slices, sorted by cost, are switched on incrementally, with one exactness-
 // preserving cut-off: f(N; t_max) never increases with t_max, so once
 // (c-1)*t_max + f(N; +inf) can no longer beat the incumbent objective the scan stops.
 #include "../../include/dynastage.h"
@@ -225,31 +225,38 @@ static ds_status plan_impl(const int32_t* len, const int32_t* len_tgt, int32_t n
             return false;
         });
 
-        // 2. admissible slices and their costs, by end point.  The order is ascending, so a slice [i, j) is as long as its
-        // last sample, and once it exceeds the cap every longer one does.  The lower bound of the sum term, f(N; +inf), comes
-        // out of the same pass, with the partition that attains it.
+        // 2. admissible slices and their costs, by start point.  The order is ascending, so a slice [i, j) is as long as its
+        // last sample, and once it exceeds the cap every longer one does: the slices that start at i end at i + 1 .. last[i], and
+        // costs(i)[j - i - 1] is what [i, j) costs.  The lower bound of the sum term, f(N; +inf), comes out of the same pass, with the
+        // partition that attains it, and so does lowest[N], the smallest t_max that admits a partition.
         CostEval cost{cm};
-        std::vector<Slice> slices;
-        std::vector<int64_t> f(n + 1), f_cost(n + 1, 0);
+        std::vector<int64_t> slice_cost;
+        std::vector<size_t> offset(n);
+        std::vector<int32_t> last(n);
+        std::vector<int64_t> f(n + 1, kInf), f_cost(n + 1, 0), lowest(n + 1, kInf);
         std::vector<int32_t> arg(n + 1, -1), best_arg;
         bool sum_overflow = false;
         f[0] = 0;
-        for (int32_t j = 1; j <= n; ++j) {
-            const int64_t L = len[lo->perm[j - 1]];
-            int64_t Lt = 0, bv = kInf;
-            for (int32_t i = j - 1; i >= 0; --i) {
-                if (len_tgt) Lt = std::max<int64_t>(Lt, len_tgt[lo->perm[i]]);
-                const int64_t bsz = j - i;
+        lowest[0] = 0;
+        for (int32_t i = 0; i < n; ++i) {
+            int64_t Lt = 0;
+            int32_t j = i + 1;
+            offset[i] = slice_cost.size();
+            for (; j <= n; ++j) {
+                const int64_t L = len[lo->perm[j - 1]], bsz = j - i;
                 if (bsz * L > cap) break;
+                if (len_tgt) Lt = std::max<int64_t>(Lt, len_tgt[lo->perm[j - 1]]);
                 int64_t t, v;
                 if (cost(bsz, L, Lt, &t) != DS_OK) return first_cost_error(*lo, len, len_tgt, cost, cap);
-                slices.push_back({t, i, j});
+                slice_cost.push_back(t);
+                lowest[j] = std::min(lowest[j], std::max(lowest[i], t));
                 if (f[i] == kInf) continue;
                 if (__builtin_add_overflow(f[i], t, &v)) { sum_overflow = true; continue; }
-                if (v < bv) { bv = v; arg[j] = i; f_cost[j] = t; }
+                if (v < f[j] || (v == f[j] && v != kInf)) { f[j] = v; arg[j] = i; f_cost[j] = t; }
             }
-            f[j] = bv;
+            last[i] = j - 1;
         }
+        auto costs = [&](int32_t i) { return slice_cost.data() + offset[i]; };
         if (sum_overflow) return DS_EOVERFLOW;
         const int64_t f_inf = f[n];
         if (f_inf == kInf) return DS_EINFEASIBLE;
@@ -263,34 +270,67 @@ static ds_status plan_impl(const int32_t* len, const int32_t* len_tgt, int32_t n
         int64_t t_top = 0, t_beyond = kInf;
         for (int32_t pos = n; pos > 0; pos = arg[pos]) t_top = std::max(t_top, f_cost[pos]);
         if (!quantised(t_top, &t_top)) t_top = kInf;                  // not representable: an error only if the scan gets there
-        size_t kept = 0;
-        for (const Slice& sl : slices) {
-            if (sl.t <= t_top) slices[kept++] = sl;
-            else t_beyond = std::min(t_beyond, sl.t);
+        // Candidates below lowest[N] have no partition.  The scan starts there, with every slice admitted up to it (all_up_to), unless a
+        // sum on the way could overflow, which is an error at the first candidate that meets it. (A plan of 208 samples,
+        // 11 923 slices: 9 946 of them lie at or below lowest[N] and are neither sorted nor scanned one candidate at a time: 494 -> 67 us.)
+        int64_t all_up_to, longest;
+        if (!quantised(lowest[n], &all_up_to)) return DS_EOVERFLOW;
+        if (__builtin_mul_overflow(t_top, (int64_t)n, &longest)) all_up_to = -1;
+        std::vector<Slice> slices;
+        for (int32_t i = 0; i < n; ++i) {
+            const int64_t* t = costs(i);
+            for (int32_t j = i + 1; j <= last[i]; ++j, ++t) {
+                if (*t <= all_up_to) continue;
+                if (*t <= t_top) slices.push_back({*t, i, j});
+                else t_beyond = std::min(t_beyond, *t);
+            }
         }
-        slices.resize(kept);
         sort_by_cost(slices);
 
-        // 3. Eq2 for ascending t_max, incrementally.  f(.; t_max) only falls as t_max admits more slices, so a candidate
+        // 3. Eq2 for ascending t_max.  f(.; t_max) only falls as t_max admits more slices, so a candidate
         // relaxes the slices it adds and, from positions whose f has fallen, the slices admitted before, in ascending order of
         // position.  That gives what scanning every admitted slice again for every candidate gives, ties (the smallest split
         // index among equal sums) included: a slice that attains a NEW minimum has itself just been added or had its f fall,
-        // and among slices that attain the old one only such slices can be new.  At 208 samples (11 923 slices) the scan
+        // and among slices that attain the old one only such slices can be new.  At 208 samples (11 923 slices) scanning again
         // took 46 ms.
-        struct Edge { int64_t t; int32_t j; };
-        std::vector<std::vector<Edge>> admitted(n);                   // by start position
-        std::vector<int32_t> n_old(n, 0);                             // slices admitted by earlier candidates
+        std::vector<int64_t> added(n, -1), next_added(slices.size());  // slices of the candidate in hand, by start position
+        std::vector<int32_t> reach(n, 0);                             // last end of an admitted slice, by start position
         std::vector<char> fallen(n + 1, 0);
         std::vector<uint64_t> todo(((size_t)n + 63) / 64, 0);         // positions to relax from
-        std::fill(f.begin(), f.end(), kInf);
-        f[0] = 0;
         int64_t bestJ = kInf, bestT = 0;
         bool found = false, cut_off = false;
+        auto candidate = [&](int64_t T) {                             // false: overflow
+            int64_t J;
+            if (f[n] == kInf) return true;
+            if (__builtin_mul_overflow(w, T, &J) || __builtin_add_overflow(J, f[n], &J)) return false;
+            if (!found || J < bestJ) {
+                found = true;
+                bestJ = J;
+                bestT = T;
+                best_arg = arg;
+            }
+            return true;
+        };
+        std::fill(f.begin(), f.end(), kInf);
+        f[0] = 0;
+        if (all_up_to >= 0) {
+            for (int32_t i = 0; i < n; ++i) {
+                const int64_t* t = costs(i);
+                for (int32_t j = i + 1; j <= last[i]; ++j, ++t) {
+                    if (*t > all_up_to) continue;
+                    reach[i] = j;
+                    if (f[i] == kInf || f[i] + *t >= f[j]) continue;
+                    f[j] = f[i] + *t;
+                    arg[j] = i;
+                }
+            }
+            if (!candidate(all_up_to)) return DS_EOVERFLOW;
+        }
         size_t k = 0;
         while (k < slices.size()) {
             int64_t T;
             if (!quantised(slices[k].t, &T)) return DS_EOVERFLOW;
-            const size_t first = k;
+            const size_t k0 = k;
             while (k < slices.size() && slices[k].t <= T) ++k;
             // cut-off: no t_max >= T can strictly improve on the incumbent
             if (found) {
@@ -299,47 +339,47 @@ static ds_status plan_impl(const int32_t* len, const int32_t* len_tgt, int32_t n
                     return DS_EOVERFLOW;
                 if (lb >= bestJ) { cut_off = true; break; }
             }
-            for (size_t q = first; q < k; ++q) {
-                admitted[slices[q].i].push_back({slices[q].t, slices[q].j});
-                todo[(size_t)slices[q].i >> 6] |= 1ull << (slices[q].i & 63);
+            for (size_t q = k0; q < k; ++q) {
+                const int32_t i = slices[q].i;
+                next_added[q] = added[i];
+                added[i] = (int64_t)q;
+                reach[i] = std::max(reach[i], slices[q].j);
+                todo[(size_t)i >> 6] |= 1ull << (i & 63);
             }
             // relax (Eq2); every slice leads to a later position
+            auto relax = [&](int32_t i, int32_t j, int64_t t) {       // false: overflow
+                int64_t v;
+                if (__builtin_add_overflow(f[i], t, &v)) return false;
+                if (v < f[j]) {
+                    f[j] = v;
+                    arg[j] = i;
+                    if (j < n) {
+                        fallen[j] = 1;
+                        todo[(size_t)j >> 6] |= 1ull << (j & 63);
+                    }
+                } else if (v == f[j] && i < arg[j]) {
+                    arg[j] = i;
+                }
+                return true;
+            };
             for (size_t word = 0; word < todo.size(); ++word) {
                 while (todo[word]) {
                     const int32_t i = (int32_t)(word * 64) + __builtin_ctzll(todo[word]);
                     todo[word] &= todo[word] - 1;
-                    std::vector<Edge>& edges = admitted[i];
-                    if (f[i] != kInf) {
-                        for (size_t q = fallen[i] ? 0 : (size_t)n_old[i]; q < edges.size(); ++q) {
-                            int64_t v;
-                            if (__builtin_add_overflow(f[i], edges[q].t, &v)) return DS_EOVERFLOW;
-                            const int32_t j = edges[q].j;
-                            if (v < f[j]) {
-                                f[j] = v;
-                                arg[j] = i;
-                                if (j < n) {
-                                    fallen[j] = 1;
-                                    todo[(size_t)j >> 6] |= 1ull << (j & 63);
-                                }
-                            } else if (v == f[j] && i < arg[j]) {
-                                arg[j] = i;
-                            }
-                        }
+                    if (f[i] == kInf) {                               // (nothing reaches it yet)
+                    } else if (fallen[i]) {
+                        const int64_t* t = costs(i);
+                        for (int32_t j = i + 1; j <= reach[i]; ++j, ++t)
+                            if (*t <= T && !relax(i, j, *t)) return DS_EOVERFLOW;
+                    } else {
+                        for (int64_t q = added[i]; q >= 0; q = next_added[q])
+                            if (!relax(i, slices[q].j, slices[q].t)) return DS_EOVERFLOW;
                     }
                     fallen[i] = 0;
-                    n_old[i] = (int32_t)edges.size();
+                    added[i] = -1;
                 }
             }
-            if (f[n] == kInf) continue;
-            int64_t J;
-            if (__builtin_mul_overflow(w, T, &J) || __builtin_add_overflow(J, f[n], &J))
-                return DS_EOVERFLOW;
-            if (!found || J < bestJ) {
-                found = true;
-                bestJ = J;
-                bestT = T;
-                best_arg = arg;
-            }
+            if (!candidate(T)) return DS_EOVERFLOW;
         }
         if (found && !cut_off && t_beyond != kInf) {                  // the candidate at which the cut-off stops must be representable
             int64_t T, lb;

@@ -257,3 +257,19 @@ def test_sampled_cost_that_no_candidate_reaches():
              [1,        1,            big + 2]]                  # three
     assert _same_as_scan([1, 2, 3], table, 9, 1, 2 ** 61) == ([0, 1, 3], big + 1, half + 3)
     assert _same_as_scan([1, 2, 3], table, 9, 2, 2 ** 61) == ds.DS_EOVERFLOW
+
+
+@pytest.mark.parametrize("spread", [1, 40, 2 ** 57])
+def test_scan_starts_at_the_smallest_feasible_candidate(spread):
+    """Candidates without a partition are passed over, slices admitted by then tie or not, cost more where they are longer or not; sums that
+    could leave int64 (2^57) are met in the order of the candidates."""
+    rng = np.random.default_rng(26)
+    for _ in range(120):
+        n = int(rng.integers(1, 24))
+        lmax = int(rng.integers(1, 9))
+        lens = rng.integers(1, lmax + 1, size=n).astype(np.int32)
+        table = rng.integers(1, 4, size=(n, lmax)) * spread + rng.integers(0, 2, size=(n, lmax))
+        if rng.random() < 0.5:
+            table = np.sort(np.sort(table, axis=0), axis=1)
+        quantum = int(rng.choice([0, 1, 2 * spread, spread + 1]))
+        _same_as_scan(lens, table.tolist(), int(rng.choice([lmax, 2 * lmax, n * lmax])), int(rng.choice([1, 2, 5])), quantum)
