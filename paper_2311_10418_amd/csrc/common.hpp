@@ -221,21 +221,6 @@ template <class T> __device__ __forceinline__ void buffer_store16(const T& v, bu
 template <class T> __device__ __forceinline__ void buffer_store16_nt(const T& v, buffer_t b, uint32_t off) {       // streaming
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), b, off, 0, 2);
 }
-// Four direct transfers of 64 x 16 bytes under one M0, two through each of two buffers: they land at lds_addr,
-// + 1024, + 2048, + 3072.  As with lds_dma16_group the immediate offsets (0, 1024, 2048, 3072) are added to the
-// memory offsets too, range check included: the caller builds the buffers 3072 bytes early and 3072 bytes longer
-// and passes lane offsets a0 + 3072, a1 + 2048, b0 + 1024, b1.
-__device__ __forceinline__ void lds_dma16_buffers_2x2(i32x4_t buf_a, uint32_t a0, uint32_t a1, i32x4_t buf_b, uint32_t b0,
-                                                      uint32_t b1, uint32_t lds_addr) {
-    const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_addr);
-    asm volatile("s_mov_b32 m0, %6\n\ts_nop 0\n\t"
-                 "buffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
-                 "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
-                 "buffer_load_dwordx4 %2, %5, 0 offen offset:2048 lds\n\t"
-                 "buffer_load_dwordx4 %3, %5, 0 offen offset:3072 lds"
-                 : : "v"(a0), "v"(a1), "v"(b0), "v"(b1), "s"(buf_a), "s"(buf_b), "s"(m0v) : "memory", "m0");
-}
-
 // One direct transfer of 64 x 16 bytes through a raw buffer, with an M0 of its own: for a wavefront that issues its transfers singly,
 // several MFMAs apart, where no write of M0 has to wait for the transfer before it.  Lanes whose offset is at or beyond the
 // buffer's length bring zeros.
@@ -244,8 +229,9 @@ __device__ __forceinline__ void lds_dma16_buffer(i32x4_t buf, uint32_t lane_off,
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(lane_off), "s"(buf), "s"(m0v) : "memory", "m0");
 }
 
-// N direct transfers of 64 x 16 bytes under one M0 through ONE raw buffer (see lds_dma16_buffers_2x2: the buffer starts
-// 1024 (N - 1) bytes early and is as much longer, lane offsets come from dma_lane_offset<N>).
+// N direct transfers of 64 x 16 bytes under one M0 through ONE raw buffer.  As with lds_dma16_group the immediate offsets are
+// added to the memory offsets too, range check included: the buffer starts 1024 (N - 1) bytes early and is as much longer, lane offsets
+// come from dma_lane_offset<N>.
 template <int N>
 __device__ __forceinline__ void lds_dma16_buffer_group(i32x4_t buf, const uint32_t (&off)[N], uint32_t lds_addr) {
     static_assert(N == 1 || N == 2 || N == 4, "group sizes in use");

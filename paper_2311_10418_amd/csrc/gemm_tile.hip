@@ -21,7 +21,8 @@
 // the products 52).  At 128 x 64 the same changes nothing.
 //
 // Which one: the tile and split count with the smallest estimate (pick_gemm_tile), compared with the same kind of
-// estimate for the large kernel.  Measured, 256 x 256 kernel -> this, us (M, N, K; ds_gemm_ws on an idle card):
+// estimate for the large kernel.  Measured, 256 x 256 kernel (as it was with eight wavefronts) -> this, us (M, N, K; ds_gemm_ws on
+// an idle card):
 //   NT 256, 768, 256: 10.2 -> 4.8    756, 2048, 2048: 36 -> 13      756, 8192, 2048: 43 -> 29    756, 2048, 8192: 50 -> 40
 //      1757, 2048, 2048: 37 -> 20    1757, 6144, 2048: 43 (50 with these: stays)    756, 6144, 2048: 42 -> 28
 //   TN 256, 1024, 250: 17 -> 5       2048, 2048, 756: 47 -> 18       2048, 2048, 1757: 43 -> 26  1024, 4096, 4173: 58 -> 47
@@ -413,7 +414,7 @@ int gemm_cu_count() {
 // versus_large differs in two places that matter only against the other kernel, whose constants hold for operands from memory:
 // kind 0 counts its step from memory, and of the output only the reading (out_read: half of out_us) is hidden, by half;
 // writing goes at the rate of the memory either way (2048 x 8192 over 126 tokens: 30.9 us on 128 x 64 tiles, 24.5 on
-// 256 x 256 ones).  Of 1 500 random shapes of stages with d = 256 .. 2048 (96 to 16 000 rows, operands from memory) 12 take
+// 256 x 256 ones).  Against that kernel with eight wavefronts, of 1 500 random shapes of stages with d = 256 .. 2048 (96 to 16 000 rows, operands from memory) 12 take
 // over 3 % longer than on the large kernel, at most 12 %; with the rates of warm operands throughout it was 40 of 1 100, up to
 // 21 %.
 TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us, bool out_read) {
