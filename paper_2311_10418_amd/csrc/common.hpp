@@ -196,7 +196,7 @@ __device__ __forceinline__ i32x4_t make_raw_buffer(const void* base, uint32_t by
     d[3] = 0x00020000;
     return d;
 }
-// The same for loads and stores that the compiler sees (and counts): 16 or 4 bytes per lane at byte offset `off`; beyond the end
+// The same for loads and stores that the compiler sees (and counts): 16, 4 or 2 bytes per lane at byte offset `off`; beyond the end
 // zeros are read and nothing is written.
 typedef __amdgpu_buffer_rsrc_t buffer_t;
 __device__ __forceinline__ buffer_t make_buffer(const void* base, uint32_t bytes) {
@@ -208,12 +208,7 @@ template <class T> __device__ __forceinline__ void buffer_load16(buffer_t b, uin
     const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0);
     __builtin_memcpy(&dst, &v, 16);
 }
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u32x2_t buffer_load8(buffer_t b, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0); }
-__device__ __forceinline__ f32x4_t bf16x4_to_f32(u32x2_t v) {
-    return f32x4_t{__builtin_bit_cast(float, v[0] << 16), __builtin_bit_cast(float, v[0] & 0xFFFF0000u), __builtin_bit_cast(float, v[1] << 16),
-                   __builtin_bit_cast(float, v[1] & 0xFFFF0000u)};
-}
+__device__ __forceinline__ uint16_t buffer_load2(buffer_t b, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b16(b, off, 0, 0); }
 __device__ __forceinline__ int32_t buffer_load4(buffer_t b, uint32_t off) { return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0); }
 template <class T> __device__ __forceinline__ void buffer_store16(const T& v, buffer_t b, uint32_t off) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), b, off, 0, 0);

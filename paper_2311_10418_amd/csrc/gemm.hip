@@ -303,14 +303,12 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         if (r < 8) fb[s][r] = fragment(ub, wn, 128, s, r);
         else fa[s][r - 8] = fragment(ua, wm, WA, s, r - 8);
     };
-    f32x4_t acc[NUA][8], start[8];
+    f32x4_t acc[NUA][8];
     // One step: NUA x 8 MFMAs on the fragments of 32-deep step s, the reads of the next step (from units ua, ub) and what tr(q) issues
     // between them, in exactly this order.  Operands swapped on purpose: the accumulator block is C^T (rows = n, columns =
     // m), so a lane holds 4 CONSECUTIVE n per block and the epilogue stages with 16-byte writes.  Boustrophedon order:
     // consecutive MFMAs share one operand and the other changes to its neighbour (about 2 % more sustained MFMA rate at the
-    // power limit than row-major order).  first: the step that starts the accumulators (from the bias: its
-    // columns are those of a lane's registers);
-    // last: nothing left to read.
+    // power limit than row-major order).  first: the step that starts the accumulators; last: nothing left to read.
     auto step = [&](auto first_t, auto last_t, int s, int ua, int ub, auto&& tr) {
 #pragma unroll
         for (int i = 0; i < NUA; ++i)
@@ -319,19 +317,22 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
                 const int j = (i & 1) ? 7 - jj : jj, q = i * 8 + jj;
                 if (!decltype(last_t)::value && q % Z::RD == 0 && q / Z::RD < NUA + 8) read(ua, ub, s ^ 1, q / Z::RD);
                 tr(q);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[s][j], fa[s][i], decltype(first_t)::value ? start[j] : acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[s][j], fa[s][i], decltype(first_t)::value ? f32x4_t{0.f, 0.f, 0.f, 0.f} : acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
     };
     auto wrap = [](int u) { return u >= 5 ? u - 5 : u; };
     const bool direct = !tail && splits == 1;      // this work-group applies the epilogue itself
-    u32x2_t bias[8];                                // of the columns of this lane's accumulators
+    // The bias is the last term of every sum, as in the kernels with smaller tiles and for split contractions: a row does not depend on
+    // the tile that takes it.  (It can't be the first: 1 + 2^24 - 2^24.)
+    constexpr bool BIAS = EPI == DS_EPI_NONE || EPI == DS_EPI_GELU || EPI == DS_EPI_RESID || EPI == DS_EPI_GELU_D;
+    bf16x8_t bias[2];                               // of the columns this lane finishes in the epilogue; none: zeros
     auto load_bias = [&]() {
         const auto b = make_buffer(reinterpret_cast<const bf16_t*>(p.bias) + n0 + wn * 128, direct && p.bias ? 256u : 0u);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) bias[j] = buffer_load8(b, (uint32_t)(j * 16 + 4 * fg) * 2);
+        for (int h = 0; h < 2; ++h) buffer_load16(b, (uint32_t)(lane & 7) * 16 + h * 128, bias[h]);
     };
-    if constexpr (EPI != DS_EPI_ACC32) load_bias();
+    if constexpr (BIAS) load_bias();
     bool primed = false;                            // persistent: the first two K tiles of this tile are already on their way
     for (;;) {
         int next_local = 0x7fffffff;
@@ -347,8 +348,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
             if (persistent && t == 0)
                 next_local = (ps_wgs >> 3) + __hip_atomic_fetch_add(ps_ctr + (blockIdx.x & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) start[j] = EPI != DS_EPI_ACC32 ? bf16x4_to_f32(bias[j]) : f32x4_t{0.f, 0.f, 0.f, 0.f};
         // the first K tile is there: behind its transfers came those of the second one and, persistent, at least the previous tile's stores
         constexpr int BEHIND = 16 + 32 * (epilogue_second<EPI>() || EPI == DS_EPI_ACC32 ? 2 : 1);
         if (PS && primed) __builtin_amdgcn_s_waitcnt(vmcnt_imm(BEHIND < 63 ? BEHIND : 63));
@@ -430,6 +429,11 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         // on its way into it: explicit, the compiler does not see the transfers).  In front of its products go the first reads of the
         // epilogue, between them the transfers of the next tile's first K tile; those of the second one follow between the passes.
         __builtin_amdgcn_s_waitcnt(0x0070);
+        float column[2][8];                             // the bias
+        if constexpr (BIAS) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) column[0][j] = (float)bias[0][j], column[1][j] = (float)bias[1][j];
+        }
         char* stg = smem + 4 * UNIT + wave * 8192;
         int next_logical = -1;
         __builtin_amdgcn_s_barrier();
@@ -449,7 +453,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
                 if (nl < run_cnt) {
                     next_logical = run_start + nl;
                     set_tile(next_logical);
-                    if constexpr (EPI != DS_EPI_ACC32) load_bias();
+                    if constexpr (BIAS) load_bias();
                     primed = true;
                 }
             }
@@ -459,12 +463,26 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
             for (int s = 0; s < PRE; ++s) prefetch_pass(s);
         }
         const int next_begin = next_logical < 0 ? t_end : t_begin;      // (no next tile: buffers of length zero, drained behind the loop)
-        const i32x4_t next_a = part(0, next_begin + 1), next_b = part(1, next_begin + 1);
         __builtin_amdgcn_sched_barrier(0);
         step(no, yes, 1, 0, 0, [&](int q) {
             if (PS && q % 4 == 1) first_transfer(next_begin, 0, q / 4);
         });
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!BIAS && EPI != DS_EPI_ACC32) {
+            // a bias where the interface names none: one product of it (columns x k, all but k = 0 zero) with ones adds it to a block
+            if (direct && p.bias) {
+                const auto b = make_buffer(reinterpret_cast<const bf16_t*>(p.bias) + en0, 256u);
+                const float ones = lane < 16 ? 1.f : 0.f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float v = __builtin_bit_cast(float, (uint32_t)buffer_load2(b, lane < 16 ? (uint32_t)(j * 16 + lane) * 2 : 256u) << 16);
+#pragma unroll
+                    for (int i = 0; i < NUA; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, ones, acc[i][j], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const i32x4_t next_a = part(0, next_begin + 1), next_b = part(1, next_begin + 1);
         // put: the accumulators of pass s into its half of the staging block; get: the 2 x 8 columns of this lane back from it.  A pass is put
         // and read while the one before it is finished.
         struct Pass { float4 x[2][2]; };
@@ -548,6 +566,10 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
                     buffer_store16(f32x4_t{v[0], v[1], v[2], v[3]} + old[s % PRE][g][0], out, at(s, g, 4));
                     buffer_store16(f32x4_t{v[4], v[5], v[6], v[7]} + old[s % PRE][g][1], out, at(s, g, 4) + 16);
                 } else {
+                    if constexpr (BIAS) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) v[j] += column[s & 1][j];
+                    }
                     bf16x8_t one, two;
                     EpiPre<bf16_t> e = pre[s % PRE][0];
                     if constexpr (READS) {

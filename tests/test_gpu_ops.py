@@ -1078,3 +1078,25 @@ def test_gemm_ring_of_k_tiles_weight_gradient(K):
         want = times * ref
         assert float((c.double() - want).norm() / want.norm()) <= 1e-5
         assert bool(((c.double() - want).abs() <= 1e-5 * (8 * want.square().mean().sqrt() + want.abs())).all())
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (40, 256, 256), (300, 2304, 512),                                    # small tiles
+    (897, 8192, 192), (3457, 3072, 192), (1537, 3840, 1024),             # one round of 128- and 192-row tiles
+    (3073, 4608, 64), (4133, 8192, 128), (10713, 4608, 512)])            # 256 x 256, one tile per work-group and persistent
+def test_gemm_bias_is_the_last_term(M, N, K):
+    """Products 2^24 and -2^24 at the two ends of the contraction cancel before the bias is added, on whatever tile: the output is the bias
+    itself (a sum that starts with the bias loses it)."""
+    rng = np.random.default_rng(46)
+    a, b = torch.zeros((M, K), dtype=BF, device=DEV), torch.zeros((N, K), dtype=BF, device=DEV)
+    a[:, 0] = a[:, K - 1] = 4096.0
+    b[:, 0], b[:, K - 1] = 4096.0, -4096.0
+    bias = to_dev(_rnd(rng, (N,), BF), BF)
+    r = to_dev(_rnd(rng, (M, N), BF), BF)
+    want = bias.float().expand(M, N)
+    c, c2 = (torch.empty((M, N), dtype=BF, device=DEV) for _ in range(2))
+    for epi, kw, ref in ((ds.DS_EPI_NONE, {}, want), (ds.DS_EPI_RESID, dict(R=r), want + r.float()), (ds.DS_EPI_GELU, {}, want),
+                         (ds.DS_EPI_GATE, dict(R=r), want), (ds.DS_EPI_MULR, dict(R=r), want * r.float())):
+        ds.ds_gemm(a, b, c, M, N, K, trans_b=True, epilogue=epi, bias=bias, C2=c2, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(c, ref.to(BF)), epi
