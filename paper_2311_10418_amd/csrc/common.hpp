@@ -85,14 +85,14 @@ __device__ __forceinline__ void gelu_and_grad_f(float z, float& gelu, float& gra
     const float w = z * z;
     const float s = gelu_sigmoid(z, w);
     gelu = z * s;
-    grad = __builtin_fmaf(__builtin_fmaf(-s, s, s), z * __builtin_fmaf(c6a, w, c2), s);
+    grad = s * __builtin_fmaf(z * __builtin_fmaf(c6a, w, c2), 1.0f - s, 1.0f);
 }
 __device__ __forceinline__ float gelu_grad_f(float z) {
     constexpr float c2 = 2.0f * 0.7978845608028654f, c6a = 3.0f * 0.044715f * c2;
     const float w = z * z;
     const float s = gelu_sigmoid(z, w);
     const float zdu = z * __builtin_fmaf(c6a, w, c2);                                // z * 2 u'
-    return __builtin_fmaf(__builtin_fmaf(-s, s, s), zdu, s);
+    return s * __builtin_fmaf(zdu, 1.0f - s, 1.0f);
 }
 
 // One direct global -> LDS transfer, 16 bytes per lane (global_load_lds_dwordx4): the wavefront's 64 chunks land at

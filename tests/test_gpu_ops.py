@@ -1100,3 +1100,32 @@ def test_gemm_bias_is_the_last_term(M, N, K):
         ds.ds_gemm(a, b, c, M, N, K, trans_b=True, epilogue=epi, bias=bias, C2=c2, **kw)
         torch.cuda.synchronize()
         assert torch.equal(c, ref.to(BF)), epi
+
+
+@pytest.mark.parametrize("generic", [False, True])
+def test_gelu_derivative_from_the_logistic_term(generic):
+    """fp32, arguments that are powers of two: GELU(z) / z is the logistic term s, and GELU'(z) = s (1 + z (1 - s) 2 u') in that order of
+    operations (what a stage's outputs depend on from one version to the next), bit for bit."""
+    f32 = np.float32
+    z = np.array([sign * 2.0 ** e for e in range(-12, 4) for sign in (1, -1)], f32)
+    M, N, K = 64, z.size, 8
+    a, b = torch.zeros((M, K), device=DEV), torch.zeros((N, K), device=DEV)
+    a[:, 0] = 1.0
+    b[:, 0] = torch.from_numpy(z).to(DEV)
+    grad, gelu = (torch.empty((M, N), device=DEV) for _ in range(2))
+    ds.ds_gemm(a, b, grad, M, N, K, trans_b=True, epilogue=ds.DS_EPI_GELU_D, C2=gelu, force_generic=generic)
+    back = torch.empty((M, N), device=DEV)
+    b[:, 0] = 1.0
+    ds.ds_gemm(a, b, back, M, N, K, trans_b=True, epilogue=ds.DS_EPI_DGELU, R=torch.from_numpy(z).to(DEV).expand(M, N).contiguous(), force_generic=generic)
+    torch.cuda.synchronize()
+
+    def fma(x, y, t):                                       # (the product is exact in 64 bits)
+        return f32(np.float64(x) * np.float64(y) + np.float64(t))
+
+    c2 = f32(2) * f32(0.7978845608028654)
+    c6a = f32(3) * f32(0.044715) * c2
+    for i in range(N):
+        s = f32(gelu[0, i].item()) / z[i]
+        assert abs(float(s) - 1 / (1 + np.exp(-2 * 0.7978845608028654 * (float(z[i]) + 0.044715 * float(z[i]) ** 3)))) <= 2e-6
+        want = s * fma(z[i] * fma(c6a, z[i] * z[i], c2), f32(1) - s, f32(1))
+        assert bool((grad[:, i] == float(want)).all()) and bool((back[:, i] == float(want)).all()), z[i]
