@@ -71,10 +71,23 @@ template <class T> __device__ __forceinline__ typename Pack8<T>::type pack8(cons
 }
 // Ordinary stores: the kernels that end here (tiles smaller than 256 x 256, fp32, sums of split contractions) write outputs that the next
 // launch reads back from the caches.  With streaming stores, which the 256 x 256 kernel uses for its far larger ones: a call of five short
-// sequences through two layers of d = 256 185.6 -> 194.2 us, d = 768 micro-batches one by one (2 100 tokens) 1 980 -> 2 112,
-// encoder-decoder d = 256 over 5 421 tokens 412 -> 427, d = 256 fp32 over 7 684 1 122 -> 1 135.
+// sequences through two layers of d = 256 191 -> 199 us, d = 768 micro-batches one by one (2 050 tokens, two layers) 1 597 -> 1 693,
+// encoder-decoder d = 512 over 1 138 tokens 380 -> 402, d = 256 fp32 over 40 000 4 374 -> 4 475.  A launch that nothing follows is
+// the slower for them, because its end waits for the caches to be written back: 957 x 2816 x 1024 with GELU 17.9 -> 18.9 us, 2 280 x 2048 x 512
+// with a bias 15.1 -> 15.8, fp32 with short contractions most, 9 381 x 1536 x 128 46.8 -> 48.6.
 template <class T> __device__ __forceinline__ void store8(T* p, const typename Pack8<T>::type& v) {
     __builtin_memcpy(__builtin_assume_aligned(p, 16), &v, sizeof v);
+}
+// Streaming ones for what the forward pass leaves to the backward pass (the pre-activation or derivative of a GELU, the ungated product):
+// nothing reads it soon, and it only makes that wait longer: with ordinary stores for both outputs 1 274 x 3072 x 1024 with GELU 19.4 -> 20.1 us (one
+// launch after another 14.5 -> 15.4), fp32 42 095 x 2048 x 64 218 -> 227; whole calls take the same time either way.
+template <int EPI> constexpr bool epilogue_keeps_first() { return EPI == DS_EPI_GELU || EPI == DS_EPI_GELU_D || EPI == DS_EPI_GATE; }
+template <class T> __device__ __forceinline__ void store8_streaming(T* p, const typename Pack8<T>::type& v) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 part[sizeof v / 16];
+    __builtin_memcpy(part, &v, sizeof v);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof v / 16); ++i) __builtin_nontemporal_store(part[i], reinterpret_cast<u32x4*>(p) + i);
 }
 // The epilogue proper (all but ACC32), after the bias: acc becomes what is stored to C, one and two the stored forms of it and of the
 // second output
@@ -146,7 +159,8 @@ __device__ __forceinline__ void epilogue8(int m, int n, int N, float (&acc)[8], 
     }
     typename Pack8<T>::type one, two;
     epilogue_values<T, EPI>(acc, epilogue_reads<EPI>() ? *pre : own, one, two);
-    store8(C + off, one);
+    if (epilogue_keeps_first<EPI>()) store8_streaming(C + off, one);
+    else store8(C + off, one);
     if (epilogue_second<EPI>()) store8(reinterpret_cast<T*>(p.C2) + off, two);
 }
 
