@@ -256,13 +256,13 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
     const uint32_t lds0 = lds_address(smem);
     // The A (part 0) or B (1) part of K tile `tile` as a raw buffer, and its transfer i into ring unit `unit`.  Tiles past the
     // end are buffers of length zero: they fetch nothing, but the wait counts are the same at every step.  TN: the buffer ends
-    // at the last k-row, so that rows past a ragged K arrive as zeros; NT: at the last row of A.
+    // behind this tile's columns of the last k-row, so that rows past a ragged K arrive as zeros; NT: at the last row of A.
     auto part = [&](int which, int tile) {
         const uint32_t inside = (uint32_t)((tile - t_end) >> 31);   // all ones before the end
         if constexpr (TNF) {
             const uint32_t ld2 = (uint32_t)(which ? N : M) * 2u;
             const int left = K - tile * BK;
-            return make_raw_buffer((which ? pb : pa) + (long long)tile * BK * ld2, (uint32_t)(left < BK ? left : BK) * ld2 & inside);
+            return make_raw_buffer((which ? pb : pa) + (long long)tile * BK * ld2, ((uint32_t)((left < BK ? left : BK) - 1) * ld2 + 512u) & inside);
         } else {
             return make_raw_buffer((which ? pb : pa) + (long long)tile * (BK * 2), (which ? 0xFFFFFFFFu : len_a) & inside);
         }
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
             return make_buffer(reinterpret_cast<const char*>(tensor) + ((size_t)em0 * N + en0) * es, on ? (uint32_t)row_cnt * (uint32_t)N * es : 0u);
         };
         const uint32_t lane_off = (uint32_t)rd_row * (uint32_t)N + rd_col;       // elements
-        auto at = [&](int s, int g, int es) { return lane_off * es + (uint32_t)(((s >> 1) * 16 + g * 8) * N * es) + (s & 1) * 64 * es; };
+        auto at = [&](int s, int g, int es) { return (lane_off + (uint32_t)((s >> 1) * 16 + g * 8) * (uint32_t)N + (s & 1) * 64) * es; };
         // What the epilogue reads from memory: PRE passes ahead, the first ones before the next tile's transfers
         constexpr bool READS = epilogue_reads<EPI>(), READS2 = EPI == DS_EPI_DGATE, OLD = EPI == DS_EPI_ACC32;
         constexpr int PRE = READS2 || OLD ? 4 : 8;
@@ -779,12 +779,17 @@ static double big_cost(const BigPlan& b, bool tnf, int M, int N) {
     return t;
 }
 
+// persistent form: one resident work-group per compute unit for the unsplit tiles, when each has several to do
+static bool nt_persistent(const BigPlan& b) {
+    const int n_cu = gemm_cu_count();
+    return b.splits == 1 && n_cu % 8 == 0 && b.n_main >= 2 * n_cu;
+}
+
 // Tile counters of the persistent form: 64 slots of [8 per-XCD counters, 1 count of finished work-groups], all zero
 // between launches (the last work-group of a launch clears its slot).  Launches take the slots in turn, so two
 // launches can only share one if more than 64 are in flight on a device at the same time.
 constexpr int PS_SLOTS = 64;
 __device__ int g_ps_ctr[PS_SLOTS][16];
-constexpr bool NT_PERSISTENT = true;
 static int* ps_counters() {
     static std::mutex mu;
     static int* base[64] = {};
@@ -816,10 +821,9 @@ ds_status launch_nt(int M, int N, int K, const void* A, const void* B, void* C, 
     const int splits = plan.splits, n_main = plan.n_main, tail_splits = plan.tail_splits;
     const int total = splits > 1 ? tiles * splits : n_main + (tiles - n_main) * tail_splits;
     bool launched = false;
-    if constexpr (!TNF && NT_PERSISTENT) {
-        // persistent form: one resident work-group per compute unit for the unsplit tiles, when each has several to do
+    if constexpr (!TNF) {
         const int n_cu = gemm_cu_count();
-        if (splits == 1 && n_cu % 8 == 0 && n_main >= 2 * n_cu) {
+        if (nt_persistent(plan)) {
             static bool ps_attr_set = false;
             auto kern_ps = gemm_bf16_nt_kernel<EPI, false, true>;
             if (!ps_attr_set) {
@@ -893,16 +897,18 @@ struct NtChoice {
 static NtChoice choose_kernel(bool tn, int epi, int M, int N, int K, size_t wsf, bool colsum, int accumulate) {
     const BigPlan plan = plan_big(tn, epi, M, N, K, wsf);
     const double out_us = gemm_output_us(epi, M, N, accumulate);
-    NtChoice c{TilePick{-1, 1, 0.0, 0.0}, big_cost(plan, tn, M, N) + out_us};
-    if (!tn)
+    const bool fits = gemm_big_width(epi, N);
+    NtChoice c{TilePick{-1, 1, 0.0, 0.0}, fits ? big_cost(plan, tn, M, N) + out_us : 1e30};
+    if (!tn && fits)
         for (const int rows : {192, 128}) {
             const long long work_groups = ((long long)M + rows - 1) / rows * (N / BN);
             if (work_groups > gemm_cu_count() || (colsum && rows != 128) || (K < 512 && 3 * work_groups < 2 * gemm_cu_count())) continue;
             const double cost = plan.nt * (rows == 192 ? kStep192 : kStep128) + 4 * rows / 256.0 + out_us;
             if (cost < c.cost) c = NtChoice{TilePick{rows == 192 ? kLower192 : kLower128, 1, cost, cost}, cost};
         }
-    if (plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
-        // launches that do not fill the chip with 256 x 256 tiles: smaller ones, where the estimates say so (ties go to the large tile)
+    if (!fits || (long long)plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
+        // launches that do not fill the chip with 256 x 256 tiles: smaller ones, where the estimates say so (ties go to the large tile);
+        // outputs too wide for these
         const TilePick pick = pick_gemm_tile(tn, M, N, K, wsf, colsum, out_us, accumulate != 0);
         if (pick.kind >= 0 && pick.versus_large < 0.95 * c.cost) c = NtChoice{pick, pick.versus_large};
     }
@@ -933,46 +939,57 @@ static int rows_of_whole_rounds(int epi, int M, int N, int K, size_t wsf, bool c
     return two < 0.97 * one ? (int)rows : 0;
 }
 
+// Whether a bf16 product goes to the matrix cores: NT, or TN with fp32 output (a K tile of each operand there is addressed through a 32-bit
+// buffer length)
+static bool matrix_cores_take(int ta, int tb, int epi, int M, int N, int K, const void* A, const void* B, const void* C) {
+    if (M < 1 || K < 1 || N % BN || (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15)) return false;
+    if (!ta && tb) return K % BK == 0;
+    return ta && !tb && epi == DS_EPI_ACC32 && M % BM == 0 && M <= (1 << 25) && N <= (1 << 25);
+}
+
+// The launches of a product that matrix_cores_take: one, or the rows of the whole rounds and the rows behind them
+struct Launches {
+    int n, rows[2];
+    NtChoice c[2];
+};
+static Launches choose_launches(bool tn, int epi, int M, int N, int K, size_t wsf, bool colsum, int accumulate) {
+    Launches l{1, {M, 0}, {choose_kernel(tn, epi, M, N, K, wsf, colsum, accumulate), {}}};
+    const int rows = tn || !gemm_big_width(epi, N) ? 0 : rows_of_whole_rounds(epi, M, N, K, wsf, colsum, accumulate, l.c[0].cost);
+    if (rows > 0) {
+        l = Launches{2, {rows, M - rows}, {}};
+        for (int i = 0; i < 2; ++i) l.c[i] = choose_kernel(tn, epi, l.rows[i], N, K, wsf, colsum, accumulate);
+    }
+    return l;
+}
+
 template <int EPI>
 ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const void* A, const void* B, void* C,
                        const GemmEpi& p, bool force_generic, float* split_ws, size_t split_ws_floats, hipStream_t st) {
-    if (dtype == DS_DTYPE_BF16 && !force_generic) {
-        const bool ok_n = N % BN == 0;
-        const bool ok_a = ta ? (M % BM == 0) : (K % BK == 0);
-        const bool ok_b = tb ? (K % BK == 0) : true;
-        const bool aligned = ((uintptr_t)A % 16 == 0) && ((uintptr_t)B % 16 == 0) && ((uintptr_t)C % 16 == 0);
-        if (ok_n && ok_a && ok_b && aligned && M >= 1 && K >= 1 && N < (1 << 23)) {      // (128 rows of fp32 within a 32-bit buffer length)
-            const bool tn = ta && !tb && EPI == DS_EPI_ACC32;
-            const size_t wsf = split_ws ? split_ws_floats : 0;
-            if (!ta && tb) {
-                auto launch = [&](const NtChoice& c, int m, const void* a, void* out, const GemmEpi& q) -> ds_status {
-                    if (c.pick.kind == kLower192) return launch_nt_lower<EPI, 6>(m, N, K, a, B, out, q, st);
-                    if (c.pick.kind == kLower128) return launch_nt_lower<EPI, 4>(m, N, K, a, B, out, q, st);
-                    if (c.pick.kind >= 0) return launch_gemm_tile(c.pick, false, m, N, K, a, B, out, EPI, q, split_ws, st);
-                    return launch_nt<EPI, false>(m, N, K, a, B, out, q, split_ws, split_ws_floats, st);
-                };
-                const NtChoice one = choose_kernel(false, EPI, M, N, K, wsf, p.colsum != nullptr, p.accumulate);
-                const int rows = rows_of_whole_rounds(EPI, M, N, K, wsf, p.colsum != nullptr, p.accumulate, one.cost);
-                if (rows == 0) return launch(one, M, A, C, p);
-                const ds_status r = launch(choose_kernel(false, EPI, rows, N, K, wsf, p.colsum != nullptr, p.accumulate), rows, A, C, p);
-                if (r != DS_OK) return r;
-                const size_t at = (size_t)rows * N;
-                auto behind = [&](const void* x) -> const void* { return x ? (const bf16_t*)x + at : nullptr; };
-                GemmEpi q = p;
-                q.R = behind(p.R);
-                q.R2 = behind(p.R2);
-                q.C2 = const_cast<void*>(behind(p.C2));
-                if (p.row_valid) q.row_valid = p.row_valid + rows;
-                if (p.colsum) q.colsum = p.colsum + gemm_colsum_rows(rows) * N;
-                return launch(choose_kernel(false, EPI, M - rows, N, K, wsf, p.colsum != nullptr, p.accumulate), M - rows,
-                              (const bf16_t*)A + (size_t)rows * K, EPI == DS_EPI_ACC32 ? (void*)((float*)C + at) : (void*)((bf16_t*)C + at), q);
-            }
-            if (tn) {
-                const NtChoice c = choose_kernel(true, EPI, M, N, K, wsf, false, p.accumulate);
-                if (c.pick.kind >= 0) return launch_gemm_tile(c.pick, true, M, N, K, A, B, C, EPI, p, split_ws, st);
-            }
-            if constexpr (EPI == DS_EPI_ACC32)      // (the TN form addresses a K tile of each operand through a 32-bit buffer length)
-                if (ta && !tb && M < (1 << 25) && N < (1 << 25)) return launch_nt<EPI, true>(M, N, K, A, B, C, p, split_ws, split_ws_floats, st);
+    if (dtype == DS_DTYPE_BF16 && !force_generic && matrix_cores_take(ta, tb, EPI, M, N, K, A, B, C)) {
+        const bool tn = ta;
+        const Launches l = choose_launches(tn, EPI, M, N, K, split_ws ? split_ws_floats : 0, p.colsum != nullptr, p.accumulate);
+        GemmEpi q = p;
+        size_t row = 0;
+        for (int i = 0; i < l.n; ++i) {
+            const TilePick& pick = l.c[i].pick;
+            const int m = l.rows[i];
+            const void* a = (const bf16_t*)A + row * K;
+            void* out = EPI == DS_EPI_ACC32 ? (void*)((float*)C + row * N) : (void*)((bf16_t*)C + row * N);
+            ds_status r;
+            if (pick.kind >= 0 && pick.kind < kLower192) r = launch_gemm_tile(pick, tn, m, N, K, a, B, out, EPI, q, split_ws, st);
+            else if (pick.kind == kLower192) r = launch_nt_lower<EPI, 6>(m, N, K, a, B, out, q, st);
+            else if (pick.kind == kLower128) r = launch_nt_lower<EPI, 4>(m, N, K, a, B, out, q, st);
+            else if (!tn) r = launch_nt<EPI, false>(m, N, K, a, B, out, q, split_ws, split_ws_floats, st);
+            else if constexpr (EPI == DS_EPI_ACC32) r = launch_nt<EPI, true>(m, N, K, a, B, out, q, split_ws, split_ws_floats, st);
+            else r = DS_EINVAL;
+            if (r != DS_OK || i + 1 == l.n) return r;
+            row = (size_t)m;
+            auto behind = [&](const void* x) -> const void* { return x ? (const bf16_t*)x + row * N : nullptr; };
+            q.R = behind(p.R);
+            q.R2 = behind(p.R2);
+            q.C2 = const_cast<void*>(behind(p.C2));
+            if (p.row_valid) q.row_valid = p.row_valid + row;
+            if (p.colsum) q.colsum = p.colsum + gemm_colsum_rows(m) * N;
         }
     }
     if (dtype == DS_DTYPE_BF16) return launch_generic<bf16_t, EPI>(ta, tb, M, N, K, A, B, C, p, st);
@@ -985,12 +1002,30 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
 
 bool gemm_colsum_fused(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B,
                        const void* C, int32_t epilogue) {
-    // the conditions under which dispatch_epi takes launch_nt<DS_EPI_DGELU or DS_EPI_MULR, false> (two rows of partial column
-    // sums per tile row) or, with p.colsum set, a 128-row tile of gemm_tile.hip (one per tile row)
+    // every matrix-core kernel of an NT product fills p.colsum: two rows of partial column sums per tile row of 256, one per 128 rows of the
+    // 128 x 256 tile and the 128-row tiles of gemm_tile.hip (the only other ones that choose_kernel takes when p.colsum is set)
     static_assert(NT_WM == 2, "two rows of partial column sums per tile row");
-    if ((epilogue != DS_EPI_DGELU && epilogue != DS_EPI_MULR) || dtype != DS_DTYPE_BF16 || ta || !tb) return false;
-    if (N % BN || K % BK || M < 1 || K < 1) return false;
-    return ((uintptr_t)A % 16 == 0) && ((uintptr_t)B % 16 == 0) && ((uintptr_t)C % 16 == 0);
+    return (epilogue == DS_EPI_DGELU || epilogue == DS_EPI_MULR) && dtype == DS_DTYPE_BF16 && !ta && tb &&
+           matrix_cores_take(ta, tb, epilogue, M, N, K, A, B, C);
+}
+
+// What ds_gemm_ws does with a bf16 product of 16-byte aligned operands, for the tests, which want each kernel at its edges: the number
+// of launches (0: the plain FMA kernel), and of each its rows, tile (TilePick::kind), splits of the contraction, whole tiles, pieces of
+// every other tile, whether it is persistent.  colsum: with the stage's column sums.
+extern "C" int32_t ds_gemm_launches(int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, int32_t epilogue, int64_t workspace_floats,
+                                    int32_t colsum, int32_t accumulate, int32_t (*out)[6]) {
+    if (!matrix_cores_take(ta, tb, epilogue, M, N, K, nullptr, nullptr, nullptr)) return 0;
+    if (colsum && !gemm_colsum_fused(DS_DTYPE_BF16, ta, tb, M, N, K, nullptr, nullptr, nullptr, epilogue)) return 0;
+    const size_t wsf = (size_t)workspace_floats;
+    const Launches l = choose_launches(ta != 0, epilogue, M, N, K, wsf, colsum != 0, accumulate);
+    for (int i = 0; i < l.n; ++i) {
+        const TilePick& k = l.c[i].pick;
+        const BigPlan b = plan_big(ta != 0, epilogue, l.rows[i], N, K, wsf);
+        const bool big = k.kind < 0;
+        const int32_t v[6] = {l.rows[i], k.kind, big ? b.splits : k.splits, big ? b.n_main : 0, big ? b.tail_splits : 0, big && !ta && nt_persistent(b)};
+        for (int e = 0; e < 6; ++e) out[i][e] = v[e];
+    }
+    return l.n;
 }
 
 // Shared with the stage driver.

@@ -9,7 +9,7 @@ struct GemmEpi {
     void* C2;                  // second output
     const int32_t* row_valid;  // rows with a negative entry are written as zeros (RESID epilogue)
     int accumulate;            // ACC32: add to C instead of overwriting
-    // DGELU and MULR epilogues of the bf16 NT kernels (gemm_colsum_fused says when; 256 x 256 tiles or 128-row ones): partial
+    // DGELU and MULR epilogues of the bf16 NT kernels (gemm_colsum_fused says when; tiles of 256 rows or of 128): partial
     // column sums of the OUTPUT (before its rounding to bf16), float32 [gemm_colsum_rows(M)][N], every entry written;
     // NULL = not wanted
     float* colsum;
@@ -18,6 +18,9 @@ struct GemmEpi {
 // true if launch_gemm with these arguments and p.colsum set fills p.colsum (otherwise it ignores the field)
 bool gemm_colsum_fused(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B,
                        const void* C, int32_t epilogue);
+// 256 x 256 tiles and the lower ones of that kernel: a wavefront's 128 rows of every tensor of the output's shape have to fit into a
+// 32-bit buffer length.  Wider outputs go to the smaller tiles.
+inline bool gemm_big_width(int32_t epilogue, int32_t N) { return (uint64_t)N * 128 * (epilogue == DS_EPI_ACC32 ? 4 : 2) <= 0xFFFFFFFFu; }
 inline size_t gemm_colsum_rows(int32_t M) { return (size_t)((M + 255) / 256) * 2; }
 
 ds_status launch_gemm(int32_t dtype, int32_t ta, int32_t tb, int32_t M, int32_t N, int32_t K, const void* A, const void* B,
@@ -83,7 +86,7 @@ TnPick pick_tn_group_f32(const TnGroup& g);
 ds_status launch_tn_group_f32(TnGroup& g, hipStream_t st);
 inline bool tn_group_takes(const TnProblem& q, int32_t K, bool f32) {
     return q.M > 0 && q.N > 0 && K > 0 && q.M % (f32 ? 4 : 256) == 0 && q.N % (f32 ? 8 : 256) == 0 && q.M <= (1 << 24) && q.N <= (1 << 24) &&
-           (((uintptr_t)q.A | (uintptr_t)q.B | (uintptr_t)q.C) & 15) == 0;
+           (f32 || gemm_big_width(DS_EPI_ACC32, q.N)) && (((uintptr_t)q.A | (uintptr_t)q.B | (uintptr_t)q.C) & 15) == 0;
 }
 
 // compute units of the current device (256 where it cannot be asked)

@@ -81,7 +81,7 @@ template <int ROWS, bool KC, int NW> struct OperandTile {
             lds_dma16_group<LP>(dma_group_base<LP>(base + (long long)tile * (T_KD * 2)), off, lds + lds_wave);
         } else {
             const int left = K - tile * T_KD;
-            const uint32_t bytes = (uint32_t)(left < T_KD ? left : T_KD) * (uint32_t)ld2;
+            const uint32_t bytes = (uint32_t)((left < T_KD ? left : T_KD) - 1) * (uint32_t)ld2 + ROWS * 2;     // to the end of this tile's columns
             const i32x4_t buf = make_raw_buffer(base + (long long)tile * T_KD * ld2 - 1024 * (LP - 1), bytes + 1024u * (LP - 1));
             lds_dma16_buffer_group<LP>(buf, off, lds + lds_wave);
         }
@@ -419,7 +419,7 @@ int gemm_cu_count() {
 // 21 %.
 TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us, bool out_read) {
     TilePick best{-1, 1, 0.0, 0.0};
-    if (tn && (M > (1 << 24) || N > (1 << 24))) return best;          // a K tile is addressed through a 32-bit buffer length
+    if (tn && (M > (1 << 25) || N > (1 << 25))) return best;          // a K tile is addressed through a 32-bit buffer length
     const int n_cu = gemm_cu_count(), nt = (K + T_KD - 1) / T_KD;
     for (int k = 0; k < kKinds; ++k) {
         const TileShape& s = kShapes[k];

@@ -1,6 +1,8 @@
 """Shared plumbing for the GPU parity tests: move seeded inputs to the device in a layout's stream
 order, run the HIP path through the C ABI, bring results back per sequence, compare with the
 oracle.  No method arithmetic here."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -167,3 +169,13 @@ def run_t5_stage(layout, cfg, enc_params, dec_params, enc_xs, dec_xs, ddec, dtyp
            "pads": [pad_o, pad_e, pad_d]}
     stage.close()
     return res
+
+
+def gemm_launches(M, N, K, trans_a=False, epilogue=ds.DS_EPI_NONE, ws_floats=0, colsum=False, accumulate=False):
+    """The launches ds_gemm makes of a bf16 product (NT, or with trans_a a weight gradient), as dicts: rows, tile ("256", "192" and "128"
+    high and 256 wide, or "128x128", "128x64", "64x64", "128x128/2" = with two LDS stages), splits of the contraction, whole tiles, pieces of every
+    other tile, persistent.  Host code only."""
+    out = (ctypes.c_int32 * 6 * 2)()
+    n = ds.lib().ds_gemm_launches(int(trans_a), int(not trans_a), M, N, K, epilogue, ctypes.c_int64(ws_floats), int(colsum), int(accumulate), out)
+    tiles = {-1: "256", 100: "192", 101: "128", 0: "128x128", 1: "128x64", 2: "64x64", 3: "128x128/2"}
+    return [dict(rows=o[0], tile=tiles[o[1]], splits=o[2], whole=o[3], pieces=o[4], persistent=bool(o[5])) for o in list(out)[:n]]

@@ -10,7 +10,7 @@ import torch
 from oracle import stage as ost
 from paper_2311_10418_amd import binding as ds
 from paper_2311_10418_amd import workload as wl
-from helpers import DEV, both_err, to_dev, to_np
+from helpers import DEV, both_err, gemm_launches, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -1129,3 +1129,45 @@ def test_gelu_derivative_from_the_logistic_term(generic):
         assert abs(float(s) - 1 / (1 + np.exp(-2 * 0.7978845608028654 * (float(z[i]) + 0.044715 * float(z[i]) ** 3)))) <= 2e-6
         want = s * fma(z[i] * fma(c6a, z[i] * z[i], c2), f32(1) - s, f32(1))
         assert bool((grad[:, i] == float(want)).all()) and bool((back[:, i] == float(want)).all()), z[i]
+
+
+@pytest.mark.parametrize("N", [(1 << 24) - 256, 1 << 24])
+def test_gemm_widest_outputs_nt(N):
+    """The widest output on 256 x 256 tiles (128 rows of bf16 are 2^32 - 65 536 bytes) and the next one, on smaller tiles; 130 rows.  Every column
+    against others of the same product where it is cheap: all rows of 4 096 columns, and the row behind the last one."""
+    M, K = 130, 64
+    assert gemm_launches(M, N, K, epilogue=ds.DS_EPI_MULR)[0]["tile"] == ("256" if N < 1 << 24 else "64x64")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(6)
+    a = torch.randn((M, K), device=DEV, generator=gen).to(BF)
+    b = torch.empty((N, K), dtype=BF, device=DEV)
+    r = torch.empty((M, N), dtype=BF, device=DEV)
+    for t in (b, r):
+        for part in t.view(-1).split(1 << 26):
+            part.copy_(torch.randn(part.numel(), device=DEV, generator=gen))
+    c = torch.full((M + 1, N), 7.0, dtype=BF, device=DEV)
+    ds.ds_gemm(a, b, c, M, N, K, trans_b=True, epilogue=ds.DS_EPI_MULR, R=r)
+    torch.cuda.synchronize()
+    cols = torch.cat([torch.arange(512), torch.arange(N - 512, N), torch.randint(0, N, (3072,), generator=torch.Generator().manual_seed(7))]).to(DEV)
+    want = torch.matmul(a.double(), b[cols].double().t().contiguous()) * r[:, cols].double()
+    got = c[:M][:, cols].double()
+    assert float((got - want).norm() / want.norm()) <= 4e-3
+    assert bool(((got - want).abs() <= 4e-3 * (8 * want.square().mean().sqrt() + want.abs())).all())
+    assert bool((c[M] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N", [(256, (1 << 23) - 256), (256, 1 << 23), (1 << 23, 256)])
+def test_gemm_widest_weight_gradients(M, N):
+    """The same for weight gradients of three tokens: fp32 outputs of 2^31 elements; 256 x 256 tiles up to 2^23 - 256 columns."""
+    K = 3
+    assert gemm_launches(M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32)[0]["tile"] == ("128x128/2" if N == 1 << 23 else "256")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(8)
+    x, dy = (torch.randn((K, n), device=DEV, generator=gen).to(BF) for n in (M, N))
+    c = torch.full((M, N), 7.0, device=DEV)
+    ds.ds_gemm(x, dy, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32)
+    torch.cuda.synchronize()
+    for i in range(0, max(M, N), 1 << 20):                   # (in pieces along the wide side)
+        s = slice(i, min(i + (1 << 20), max(M, N)))
+        got, want = (c[:, s], x.float().t() @ dy[:, s].float()) if N > M else (c[s], x[:, s].float().t() @ dy.float())
+        assert bool(((got - want).abs() <= 1e-5).all()), i      # three products of a few units each: 2^-23 of their sum
