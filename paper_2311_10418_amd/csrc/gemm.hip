@@ -712,14 +712,14 @@ ds_status launch_generic(int ta, int tb, int M, int N, int K, const void* A, con
     return DS_OK;
 }
 
-// number of K splits of a weight-gradient GEMM: the fewest that bring the work-group count closest to a whole
-// number of rounds over the compute units (time ~ rounds x split length)
-static int choose_splits(int tiles, int nt, int M, int N, size_t split_ws_floats) {
+// number of K splits of a product with fp32 output: the fewest that bring the work-group count closest to a whole
+// number of rounds over the compute units (time ~ rounds x split length), of 512 rows or more for a weight gradient, 1 024 for an NT product
+static int choose_splits(bool tnf, int tiles, int nt, int M, int N, size_t split_ws_floats) {
     const int n_cu = gemm_cu_count();
     int best = 1;
     double best_cost = 1e30;
     for (int sp = 1; sp <= 16; ++sp) {
-        if (sp > 1 && (sp > nt / 8 || (size_t)sp * M * N > split_ws_floats)) break;
+        if (sp > 1 && (sp > nt / (tnf ? 8 : 16) || (size_t)sp * M * N > split_ws_floats)) break;
         const int per = (nt + sp - 1) / sp;
         if ((nt + per - 1) / per != sp) continue;               // every split must own at least one K tile
         const double rounds = (double)(((long long)tiles * sp + n_cu - 1) / n_cu);
@@ -741,7 +741,7 @@ static BigPlan plan_big(bool tnf, int epi, int M, int N, int K, size_t split_ws_
     b.tiles_n = N / BN;
     b.nt = (K + BK - 1) / BK;
     const int tiles = b.tiles_m * b.tiles_n;
-    b.splits = epi == DS_EPI_ACC32 && split_ws_floats ? choose_splits(tiles, b.nt, M, N, split_ws_floats) : 1;
+    b.splits = epi == DS_EPI_ACC32 && split_ws_floats ? choose_splits(tnf, tiles, b.nt, M, N, split_ws_floats) : 1;
     // tail split-K: the tiles beyond the last whole round over the compute units share that round; a launch with
     // fewer tiles than compute units (small micro-batches) is all tail, so that the K loop is spread over the chip
     b.n_main = tiles;

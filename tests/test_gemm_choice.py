@@ -55,3 +55,9 @@ def test_launches_cover_the_rows_once():
                 assert not x["persistent"] or x["whole"] >= 512
             if colsum:
                 assert x["tile"] not in ("192", "64x64")
+
+
+def test_fp32_outputs_of_nt_products_split_into_long_pieces():
+    """Contractions of 2 816 are cut in two at most (pieces of 1 024 and more): on 204 large tiles, whole."""
+    l = gemm_launches(4318, 3072, 2816, epilogue=ds.DS_EPI_ACC32, ws_floats=1 << 26)
+    assert [(x["tile"], x["splits"]) for x in l] == [("256", 1)]
