@@ -888,6 +888,9 @@ ds_status launch_nt_lower(int M, int N, int K, const void* A, const void* B, voi
 // geometric means: from memory 0.97, warm 0.95; below K = 512 on at least two thirds of the CUs 0.83 and 0.93, on fewer 1.11 and 1.05 (not
 // taken: where a launch is mostly its ends, small tiles on all CUs are better).  Of the rest 2 lose more than 3 % of the mean of both, at
 // worst 6 %.  (Estimates of 1.05 and 0.85, closer to the warm rates: 0.99 and 0.95.)
+// Of another 60 shapes that go to them from each epilogue, from memory and warm: 192 rows 0.86 to 0.94 and 0.83 to 0.89, 128 rows 0.88 to 0.97 and
+// 0.88 to 0.98, at worst 5 % over in the mean of both (128 rows of K = 2816 from memory alone 1.03, warm 0.87), but for the derivative of the GELU
+// on 128 rows, 1.05 and 1.04, at worst 1.11: these go on without (11 operations an element with one wavefront per SIMD).
 constexpr int kLower192 = 100, kLower128 = 101;
 constexpr double kStep192 = 1.10, kStep128 = 1.05;
 struct NtChoice {
@@ -898,7 +901,8 @@ static NtChoice choose_kernel(bool tn, int epi, int M, int N, int K, size_t wsf,
     const BigPlan plan = plan_big(tn, epi, M, N, K, wsf);
     const double out_us = gemm_output_us(epi, M, N, accumulate);
     const bool fits = gemm_big_width(epi, N);
-    NtChoice c{TilePick{-1, 1, 0.0, 0.0}, fits ? big_cost(plan, tn, M, N) + out_us : 1e30};
+    const NtChoice big{TilePick{-1, 1, 0.0, 0.0}, fits ? big_cost(plan, tn, M, N) + out_us : 1e30};
+    NtChoice c = big;
     if (!tn && fits)
         for (const int rows : {192, 128}) {
             const long long work_groups = ((long long)M + rows - 1) / rows * (N / BN);
@@ -906,6 +910,7 @@ static NtChoice choose_kernel(bool tn, int epi, int M, int N, int K, size_t wsf,
             const double cost = plan.nt * (rows == 192 ? kStep192 : kStep128) + 4 * rows / 256.0 + out_us;
             if (cost < c.cost) c = NtChoice{TilePick{rows == 192 ? kLower192 : kLower128, 1, cost, cost}, cost};
         }
+    if (epi == DS_EPI_DGELU && c.pick.kind == kLower128) c = big;
     if (!fits || (long long)plan.tiles_m * plan.tiles_n <= 2 * gemm_cu_count()) {
         // launches that do not fill the chip with 256 x 256 tiles: smaller ones, where the estimates say so (ties go to the large tile);
         // outputs too wide for these

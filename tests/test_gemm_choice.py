@@ -61,3 +61,10 @@ def test_fp32_outputs_of_nt_products_split_into_long_pieces():
     """Contractions of 2 816 are cut in two at most (pieces of 1 024 and more): on 204 large tiles, whole."""
     l = gemm_launches(4318, 3072, 2816, epilogue=ds.DS_EPI_ACC32, ws_floats=1 << 26)
     assert [(x["tile"], x["splits"]) for x in l] == [("256", 1)]
+
+
+def test_gelu_derivative_keeps_off_the_128_row_tile():
+    """Its epilogue takes longer there than the K loop saves, alone of the epilogues."""
+    for M, N, K in ((6700, 1024, 128), (3633, 2048, 2816), (9130, 768, 768)):
+        assert [x["tile"] for x in gemm_launches(M, N, K, epilogue=ds.DS_EPI_MULR, ws_floats=1 << 24)] == ["128"]
+        assert [x["tile"] for x in gemm_launches(M, N, K, epilogue=ds.DS_EPI_DGELU, ws_floats=1 << 24)] == ["128x128/2"]
