@@ -458,7 +458,11 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
                 }
             }
         }
-        if constexpr (READS || OLD) {
+        if constexpr (READS) {
+#pragma unroll
+            for (int s = 0; s < PRE; ++s) prefetch_pass(s);
+        }
+        if (OLD && p.accumulate) {
 #pragma unroll
             for (int s = 0; s < PRE; ++s) prefetch_pass(s);
         }
@@ -546,10 +550,12 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         float csum[2][8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) csum[0][j] = csum[1][j] = 0.f;
-        if (!direct) {
-            // partial sums: [split][M][N], or blocks of a whole tile (rows past M are never read there)
-            const bool block = GRP || tail;
-            float* dst = GRP ? split_ws
+        if (!direct || (OLD && !p.accumulate)) {
+            // an output that is not added to (with the reads and additions of the other form, of nothing, gradients over a few hundred tokens took 3 %
+            // longer), or partial sums: [split][M][N], or blocks of a whole tile (rows past M are never read there)
+            const bool block = (GRP || tail) && !direct;
+            float* dst = direct ? reinterpret_cast<float*>(C)
+                       : GRP ? split_ws
                        : tail ? split_ws + (size_t)((elogical - n_main) * tail_splits + split) * (BM * BN) : split_ws + (size_t)split * M * N;
             const buffer_t out = block ? make_buffer(dst + (size_t)(wm * 128) * BN + wn * 128, 128 * BN * 4) : rows(dst, 4, true);
             const uint32_t ld = block ? BN : N, off = ((uint32_t)rd_row * ld + rd_col) * 4;
