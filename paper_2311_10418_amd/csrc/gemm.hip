@@ -989,8 +989,10 @@ ds_status dispatch_epi(int dtype, int ta, int tb, int M, int N, int K, const voi
             ds_status r;
             if (pick.kind >= 0 && pick.kind < kLower192) r = launch_gemm_tile(pick, tn, m, N, K, a, B, out, EPI, q, split_ws, st);
             else if (pick.kind == kLower192) r = launch_nt_lower<EPI, 6>(m, N, K, a, B, out, q, st);
-            else if (pick.kind == kLower128) r = launch_nt_lower<EPI, 4>(m, N, K, a, B, out, q, st);
-            else if (!tn) r = launch_nt<EPI, false>(m, N, K, a, B, out, q, split_ws, split_ws_floats, st);
+            else if (pick.kind == kLower128) {
+                if constexpr (EPI == DS_EPI_DGELU) r = DS_EINVAL;       // (choose_kernel keeps it off these)
+                else r = launch_nt_lower<EPI, 4>(m, N, K, a, B, out, q, st);
+            } else if (!tn) r = launch_nt<EPI, false>(m, N, K, a, B, out, q, split_ws, split_ws_floats, st);
             else if constexpr (EPI == DS_EPI_ACC32) r = launch_nt<EPI, true>(m, N, K, a, B, out, q, split_ws, split_ws_floats, st);
             else r = DS_EINVAL;
             if (r != DS_OK || i + 1 == l.n) return r;

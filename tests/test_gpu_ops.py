@@ -549,46 +549,83 @@ def test_gemm_weight_gradient_split_over_the_contraction(M, N, K):
     assert both_err(to_np(plain), ref) <= 1e-5
 
 
-@pytest.mark.parametrize("use_ws", [False, True])
-def test_gemm_nt_persistent_form(use_ws):
-    """A launch with at least two unsplit tiles per compute unit takes the persistent form of the NT kernel (resident
-    work-groups drawing tiles from per-XCD counters; with a workspace the last tiles are split pieces behind them):
-    every tile against the reference, ragged M, several epilogues; again on another stream and a third time, bit for
-    bit the same (the counters a launch leaves behind are those the next one starts from)."""
+def _close(got, want, tol):
+    """both_err(...) <= tol on the device."""
+    err = got.double() - want
+    return float(err.norm() / want.norm()) <= tol and bool((err.abs() <= tol * (8 * want.square().mean().sqrt() + want.abs())).all())
+
+
+def _nt_epilogues_on_device(M, N, K, ws, epilogues, form, repeat=False):
+    """C = A B^T with each of the epilogues against float64 on the device, 6e-3 (bf16: one rounding, 2^-9 of each value; fp32 output 1e-5); the
+    row behind the last one of both outputs is not written; every product goes out as `form` says.  repeat: again on another stream and a third
+    time, bit for bit the same."""
     rng = np.random.default_rng(21)
-    M, N, K = 256 * 40 + 57, 3328, 512                     # 41 x 13 = 533 tiles
-    A, B = _rnd(rng, (M, K), BF), _rnd(rng, (N, K), BF, 0.1)
-    bias, R = _rnd(rng, (N,), BF), _rnd(rng, (M, N), BF)
-    valid = np.where(rng.random(M) < 0.9, 1, -1).astype(np.int32)
-    acc = A.astype(np.float64) @ B.astype(np.float64).T
-    dA, dB, db, dR = (to_dev(x, BF) for x in (A, B, bias, R))
-    dvalid = torch.from_numpy(valid).to(DEV)
-    ws = _ws(64 * 256 * 256) if use_ws else None
+    dA, dB = to_dev(_rnd(rng, (M, K), BF), BF), to_dev(_rnd(rng, (N, K), BF, 0.1), BF)
+    db = to_dev(_rnd(rng, (N,), BF), BF)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(21)
+    dR, dR2 = (torch.randn((M, N), device=DEV, generator=gen).to(BF) for _ in range(2))
+    valid = torch.from_numpy(np.where(rng.random(M) < 0.9, 1, -1).astype(np.int32)).to(DEV)
+    acc, b, r = torch.matmul(dA.double(), dB.double().t().contiguous()), db.double(), dR.double()
     side = torch.cuda.Stream()
     torch.cuda.synchronize()
-    tol = 6e-3
 
-    def run(epi, stream=None, **kw):
-        c = torch.zeros((M, N), dtype=BF, device=DEV)
-        c2 = torch.zeros((M, N), dtype=BF, device=DEV)
-        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, epilogue=epi, C2=c2, workspace=ws, stream=stream, **kw)
-        torch.cuda.synchronize()
-        return to_np(c), to_np(c2)
+    def gelu(z):
+        return torch.nn.functional.gelu(z, approximate="tanh")
 
-    for epi, kw, want, want2 in [
-            (ds.DS_EPI_NONE, dict(bias=db), acc + bias, None),
-            (ds.DS_EPI_RESID, dict(bias=db, R=dR, row_valid=dvalid), (acc + bias + R) * (valid[:, None] >= 0), None),
-            (ds.DS_EPI_GELU_D, dict(bias=db), ost.gelu_grad(acc + bias), ost.gelu(acc + bias)),
-            (ds.DS_EPI_MULR, dict(R=dR), acc * R, None)]:
-        c, c2 = run(epi, **kw)
-        assert both_err(c, want) <= tol
-        if want2 is not None:
-            assert both_err(c2, want2) <= tol
-        for stream in (side.cuda_stream, None):
-            d, d2 = run(epi, stream=stream, **kw)
-            assert np.array_equal(c, d)
-            if want2 is not None:
-                assert np.array_equal(c2, d2)
+    def gelu_grad(z):
+        u = 0.7978845608028654 * (z + 0.044715 * z ** 3)
+        t = torch.tanh(u)
+        return 0.5 * (1 + t) + 0.5 * z * (1 - t * t) * 0.7978845608028654 * (1 + 3 * 0.044715 * z * z)
+
+    cases = {ds.DS_EPI_NONE: (dict(bias=db), lambda: (acc + b, None)),
+             ds.DS_EPI_GELU: (dict(bias=db), lambda: (acc + b, gelu(acc + b))),
+             ds.DS_EPI_RESID: (dict(bias=db, R=dR, row_valid=valid), lambda: ((acc + b + r) * (valid >= 0).double()[:, None], None)),
+             ds.DS_EPI_DGELU: (dict(R=dR), lambda: (acc * gelu_grad(r), None)),
+             ds.DS_EPI_ACC32: (dict(), lambda: (acc, None)),
+             ds.DS_EPI_GATE: (dict(R=dR), lambda: (acc, gelu(r) * acc)),
+             ds.DS_EPI_DGATE: (dict(R=dR, R2=dR2), lambda: (acc * dR2.double() * gelu_grad(r), acc * gelu(r))),
+             ds.DS_EPI_GELU_D: (dict(bias=db), lambda: (gelu_grad(acc + b), gelu(acc + b))),
+             ds.DS_EPI_MULR: (dict(R=dR), lambda: (acc * r, None))}
+    for epi in epilogues:
+        assert form(gemm_launches(M, N, K, epilogue=epi, ws_floats=0 if ws is None else ws.numel())), epi
+        kw, ref = cases[epi]
+        want, want2 = ref()
+        f32 = epi == ds.DS_EPI_ACC32
+        for times in ((1, 2) if f32 else (1,)):
+            first = None
+            for stream in ((None, side.cuda_stream, None) if repeat else (None,)):
+                c = torch.full((M + 1, N), 7.0, dtype=F32 if f32 else BF, device=DEV)
+                c2 = torch.full((M + 1, N), 7.0, dtype=BF, device=DEV)
+                if times == 2:
+                    c[:M] = want.float()
+                torch.cuda.synchronize()
+                ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, epilogue=epi, C2=c2, workspace=ws, stream=stream, accumulate=times == 2, **kw)
+                torch.cuda.synchronize()
+                if first is None:
+                    first = c, c2
+                    assert _close(c[:M], times * want, 1e-5 if f32 else 6e-3), (epi, times)
+                    if want2 is not None:
+                        assert _close(c2[:M], want2, 6e-3), epi
+                    assert bool((c[M] == 7.0).all()) and bool((c2[M if want2 is not None else 0:] == 7.0).all()), epi
+                else:
+                    assert torch.equal(c, first[0]) and torch.equal(c2, first[1]), epi
+
+
+EVERY_EPILOGUE = (ds.DS_EPI_NONE, ds.DS_EPI_GELU, ds.DS_EPI_RESID, ds.DS_EPI_DGELU, ds.DS_EPI_ACC32, ds.DS_EPI_GATE, ds.DS_EPI_DGATE,
+                  ds.DS_EPI_GELU_D, ds.DS_EPI_MULR)
+
+
+@pytest.mark.parametrize("M,N,K,ws_floats,whole,pieces", [(10713, 4608, 512, 0, 756, 1), (4767, 8192, 4096, 1 << 24, 512, 2)])
+def test_gemm_nt_persistent_form(M, N, K, ws_floats, whole, pieces):
+    """A launch with at least two unsplit tiles per compute unit takes the persistent form of the NT kernel (resident
+    work-groups drawing tiles from per-XCD counters): three rounds, the last partly filled, with a ragged last row of tiles; two rounds with split
+    pieces of the other tiles behind them.  Every epilogue but the fp32 output of the second; each three times, bit for bit the same (the counters a
+    launch leaves behind are those the next one starts from)."""
+    def form(l):
+        return len(l) == 1 and l[0]["persistent"] and (l[0]["whole"], l[0]["pieces"]) == (whole, pieces)
+
+    _nt_epilogues_on_device(M, N, K, _ws(ws_floats) if ws_floats else None, [e for e in EVERY_EPILOGUE if pieces == 1 or e != ds.DS_EPI_ACC32], form, repeat=True)
 
 
 def test_mfma_probe_runs_and_is_deterministic():
@@ -960,21 +997,25 @@ def test_attention_bf16_hidden_half_blocks_with_values_that_are_not_finite(hd):
     assert np.isinf(got[:, d + hd + 5]).all() and np.array_equal(np.isnan(got[:, d:]), np.isnan(ref[:, d:]))       # dV of the last case
 
 
-@pytest.mark.parametrize("M,N,K,ws_floats", [
-    # 128 x 64 tiles (three stages): one to five K tiles, row edges, the contraction split
-    (129, 5632, 64, 0), (129, 5632, 128, 0), (129, 5632, 320, 0), (256, 8192, 320, 0), (641, 512, 4096, 1 << 22),
-    # 128 x 128, four stages
-    (383, 5632, 320, 0), (384, 5632, 320, 0), (385, 5632, 320, 0), (385, 7680, 256, 0), (129, 2304, 8192, 1 << 22),
+@pytest.mark.parametrize("M,N,K,ws_floats,tile", [
+    # three stages: one to five K tiles, row edges, the contraction split
+    (129, 5632, 64, 0, "128x64"), (129, 5632, 128, 0, "128x64"), (129, 5632, 320, 0, "128x64"), (256, 8192, 320, 0, "128x64"), (641, 512, 4096, 1 << 22, "128x64"),
+    # four stages
+    (383, 5632, 320, 0, "128x128"), (384, 5632, 320, 0, "128x128"), (385, 5632, 320, 0, "128x128"), (385, 7680, 256, 0, "128x128"), (129, 2304, 8192, 1 << 22, "128x128"),
     # the same with two groups of wavefronts: 32, 33 and, split, more K tiles
-    (383, 5632, 2048, 0), (385, 5632, 2112, 0), (129, 2304, 16384, 1 << 22),
-    # 128 x 128, two stages
-    (1537, 3840, 128, 0), (1537, 3840, 192, 0), (767, 6144, 320, 0), (768, 6144, 320, 0), (769, 6144, 320, 0), (756, 6144, 2048, 0),
-    (385, 4864, 8192, 1 << 22),
-    # 256 x 256: whole tiles of one and three K tiles; whole tiles and a split remainder; every tile split
-    (3073, 4608, 64, 0), (3073, 4608, 192, 0), (3329, 4864, 1024, 1 << 22), (129, 5888, 8192, 1 << 24)])
-def test_gemm_every_macro_tile_nt(M, N, K, ws_floats):
-    """C = A B^T at shapes that the estimates send to each of the macro tiles, whole and split over the contraction (the groups
-    above, on 256 compute units).  bf16 results: one rounding, 2^-9 of each value."""
+    (383, 5632, 2048, 0, "128x128"), (385, 5632, 2112, 0, "128x128"), (129, 2304, 16384, 1 << 22, "128x128"),
+    # two stages: two, three and five K tiles, many, the contraction split
+    (1281, 6144, 128, 0, "128x128/2"), (513, 7424, 192, 0, "128x128/2"), (767, 6144, 320, 0, "128x128/2"), (768, 6144, 320, 0, "128x128/2"), (769, 6144, 320, 0, "128x128/2"),
+    (756, 6144, 2048, 0, "128x128/2"), (385, 4864, 8192, 1 << 22, "128x128/2"),
+    # whole tiles of one and three K tiles; whole tiles and a split remainder; every tile split
+    (3073, 4608, 64, 0, "256"), (3073, 4608, 192, 0, "256"), (5157, 3328, 1024, 40 << 16, "256 and pieces"), (336, 6144, 8192, 1 << 26, "256 pieces")])
+def test_gemm_every_macro_tile_nt(M, N, K, ws_floats, tile):
+    """C = A B^T at shapes that the estimates send to each of the macro tiles, whole and split over the contraction (on 256 compute units).
+    bf16 results: one rounding, 2^-9 of each value."""
+    for epi in (ds.DS_EPI_NONE, ds.DS_EPI_MULR):
+        l, = gemm_launches(M, N, K, epilogue=epi, ws_floats=ws_floats)
+        assert l["tile"] == tile.split()[0]
+        assert (l["pieces"] > 1, l["whole"] > 0) == ("pieces" in tile, "256" in tile and tile != "256 pieces")
     rng = np.random.default_rng(41)
     dA, dB, dR = (to_dev(_rnd(rng, s, BF, f), BF) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((M, N), 1.0)))
     acc = torch.matmul(dA.double(), dB.double().t().contiguous())
@@ -987,17 +1028,20 @@ def test_gemm_every_macro_tile_nt(M, N, K, ws_floats):
         assert both_err(to_np(c)[:M], ref.cpu().numpy()) <= 4e-3 and np.all(to_np(c)[M] == 7.0)
 
 
-@pytest.mark.parametrize("M,N,K,ws_floats", [
-    # 128 x 64 tiles: one and three (ragged) K tiles, split; 128 x 128 with four stages, whole and split; with two, two to four K tiles
-    # (the first two of these when they add, else 256 x 256)
-    (256, 4352, 33, 0), (256, 4352, 129, 0), (256, 1536, 6000, 1 << 22), (1792, 1792, 577, 0), (256, 2816, 9001, 1 << 22),
-    # 128 x 128 with two groups of wavefronts: 33 (the last one ragged) and, split, more K tiles
-    (1792, 1792, 2049, 0), (256, 2816, 20001, 1 << 22),
-    (2560, 3328, 129, 0), (2560, 3328, 200, 0), (2560, 6656, 65, 0),
-    # 256 x 256 (64-deep K tiles): one, a ragged few, ranges of the contraction, whole tiles and a split remainder
-    (10240, 3328, 1, 0), (10240, 3328, 97, 0), (256, 5632, 12000, 1 << 24), (10240, 3328, 250, 1 << 22)])
-def test_gemm_every_macro_tile_weight_gradient(M, N, K, ws_floats):
+@pytest.mark.parametrize("M,N,K,ws_floats,tiles", [
+    # one tile for both or for overwriting and adding; one and three (ragged) K tiles, split; four stages, whole and split
+    (256, 4352, 33, 0, "128x64"), (256, 4352, 129, 0, "128x64"), (256, 1536, 6000, 1 << 22, "128x64"), (1792, 1792, 577, 0, "128x128 64x64"), (256, 2816, 9001, 1 << 22, "128x128"),
+    # two groups of wavefronts: 33 (the last one ragged) and, split, more K tiles
+    (1792, 1792, 2049, 0, "128x128"), (256, 2816, 20001, 1 << 22, "128x128"),
+    # two stages: two to four K tiles
+    (2560, 3328, 129, 0, "256 128x128/2"), (2560, 3328, 200, 0, "256 128x128/2"), (2560, 6656, 65, 0, "128x128/2"),
+    # 64-deep K tiles: one, a ragged few, ranges of the contraction, whole tiles, whole tiles and split ones
+    (10240, 3328, 1, 0, "256"), (10240, 3328, 97, 0, "256"), (256, 5632, 12000, 1 << 24, "256"), (10240, 3328, 250, 1 << 22, "256"), (9472, 1792, 971, 1 << 24, "256")])
+def test_gemm_every_macro_tile_weight_gradient(M, N, K, ws_floats, tiles):
     """The same for weight gradients, overwriting and adding; rows behind the last one hold NaN.  fp32 sums: 1e-5."""
+    for adds, tile in zip((False, True), (tiles.split() * 2)[:2]):
+        l, = gemm_launches(M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, ws_floats=ws_floats, accumulate=adds)
+        assert l["tile"] == tile and (l["splits"] > 1 or l["pieces"] > 1) == (K in (6000, 9001, 20001, 12000, 971))
     rng = np.random.default_rng(42)
     X, dY = _rnd(rng, (K, M), BF), _rnd(rng, (K, N), BF)
     dX, ddY = (torch.cat([to_dev(a, BF), torch.full((64, a.shape[1]), float("nan"), dtype=BF, device=DEV)]) for a in (X, dY))
@@ -1013,54 +1057,28 @@ def test_gemm_every_macro_tile_weight_gradient(M, N, K, ws_floats):
 
 
 @pytest.mark.parametrize("K", [64, 128, 192, 320, 384, 448])
-@pytest.mark.parametrize("M", [4097, 4133, 4224])
+@pytest.mark.parametrize("M", [6145, 6181, 6272])
 def test_gemm_ring_of_k_tiles_nt(M, K):
     """256 x 256 tiles whose K loop is shorter than, as long as and longer than the ring of LDS units (one to seven K tiles), persistent
-    (544 tiles) with the tiles behind the last whole round; the last tile row has 1, 37 and 128 rows.  bf16 results: one rounding,
-    2^-9 of each value; the rows behind the last one are not written."""
-    N = 8192
-    rng = np.random.default_rng(43)
-    dA, dB, dR = (to_dev(_rnd(rng, s, BF, f), BF) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((M, N), 1.0)))
-    db = to_dev(_rnd(rng, (N,), BF), BF)
-    valid = torch.from_numpy(np.where(rng.random(M) < 0.8, 1, -1).astype(np.int32)).to(DEV)
-    acc = torch.matmul(dA.double(), dB.double().t().contiguous())
-    ws = _ws(1 << 22)
-    c, c2 = (torch.empty((M + 1, N), dtype=BF, device=DEV) for _ in range(2))
-    for kw, ref, ref2 in ((dict(bias=db), acc + db.double(), None),
-                          (dict(epilogue=ds.DS_EPI_RESID, bias=db, R=dR, row_valid=valid), (acc + db.double() + dR.double()) * (valid >= 0).double()[:, None], None),
-                          (dict(epilogue=ds.DS_EPI_GATE, R=dR), acc, torch.nn.functional.gelu(dR.double(), approximate="tanh") * acc)):
-        c.fill_(7.0)
-        c2.fill_(7.0)
-        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, workspace=ws, C2=c2, **kw)
-        torch.cuda.synchronize()
-        for got, want in ((c, ref), (c2, ref2)):
-            if want is not None:
-                assert float((got[:M].double() - want).norm() / want.norm()) <= 6e-3
-                assert bool(((got[:M].double() - want).abs() <= 6e-3 * (8 * want.square().mean().sqrt() + want.abs())).all())
-            assert bool((got[M] == 7.0).all())
+    (800 tiles, three rounds and some behind); the last tile row has 1, 37 and 128 rows."""
+    def form(l):
+        return len(l) == 1 and l[0]["persistent"] and l[0]["whole"] == 800
+
+    _nt_epilogues_on_device(M, 8192, K, _ws(1 << 22), (ds.DS_EPI_NONE, ds.DS_EPI_RESID, ds.DS_EPI_GATE) if K != 320 else EVERY_EPILOGUE, form)
 
 
-@pytest.mark.parametrize("K", [64, 128, 192, 320, 448])
-@pytest.mark.parametrize("M,N", [(3456, 3072), (3457, 3072), (3647, 3072), (769, 8192), (897, 8192), (1024, 8192), (130, 256)])
-def test_gemm_lower_tiles_nt(M, N, K):
-    """Launches of one round, which lower tiles of 192 x 256 and 128 x 256 may take: full last tile rows, ones of a single row and one row short, K
-    loops around the length of the ring of LDS units.  bf16 results: one rounding, 2^-9 of each value; the rows behind the last one are
-    not written."""
-    rng = np.random.default_rng(45)
-    dA, dB, dR = (to_dev(_rnd(rng, s, BF, f), BF) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((M, N), 1.0)))
-    db = to_dev(_rnd(rng, (N,), BF), BF)
-    valid = torch.from_numpy(np.where(rng.random(M) < 0.8, 1, -1).astype(np.int32)).to(DEV)
-    acc = torch.matmul(dA.double(), dB.double().t().contiguous())
-    ws = _ws(1 << 22)
-    c = torch.empty((M + 1, N), dtype=BF, device=DEV)
-    for kw, want in ((dict(bias=db), acc + db.double()),
-                     (dict(epilogue=ds.DS_EPI_RESID, bias=db, R=dR, row_valid=valid), (acc + db.double() + dR.double()) * (valid >= 0).double()[:, None])):
-        c.fill_(7.0)
-        ds.ds_gemm(dA, dB, c, M, N, K, trans_b=True, workspace=ws, **kw)
-        torch.cuda.synchronize()
-        assert float((c[:M].double() - want).norm() / want.norm()) <= 6e-3
-        assert bool(((c[:M].double() - want).abs() <= 6e-3 * (8 * want.square().mean().sqrt() + want.abs())).all())
-        assert bool((c[M] == 7.0).all())
+@pytest.mark.parametrize("M,N,K,tile", [
+    *[(M, 3072, K, "192") for M in (3456, 3457, 3647) for K in (64, 128, 192, 320, 448)], (3457, 3072, 576, "192"), (3647, 3072, 2048, "192"),
+    *[(M, 8192, K, "128") for M in (769, 897, 1024) for K in (64, 128, 192, 320, 448)], (897, 8192, 576, "128"), (1009, 8192, 2048, "128")])
+def test_gemm_lower_tiles_nt(M, N, K, tile):
+    """Launches of one round on lower tiles, 192 x 256 and 128 x 256: full last tile rows, ones of a single row and one row short, K
+    loops around the length of the ring of LDS units and long ones; every epilogue that goes there on both sides of it and in the long ones."""
+    every = [e for e in EVERY_EPILOGUE if tile != "128" or e != ds.DS_EPI_DGELU]
+
+    def form(l):
+        return [x["tile"] for x in l] == [tile]
+
+    _nt_epilogues_on_device(M, N, K, _ws(1 << 22), every if K in (192, 576, 2048) else (ds.DS_EPI_NONE, ds.DS_EPI_RESID), form)
 
 
 @pytest.mark.parametrize("K", [1, 63, 65, 128, 200, 321, 450])
@@ -1068,6 +1086,7 @@ def test_gemm_ring_of_k_tiles_weight_gradient(K):
     """The same for weight gradients (576 tiles, one work-group each): one to eight K tiles, the last one ragged, overwriting and adding; rows
     behind the last one hold NaN.  fp32 sums: 1e-5."""
     M, N = 8192, 4608
+    assert gemm_launches(M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32)[0]["whole"] == 576
     rng = np.random.default_rng(44)
     dX, ddY = (torch.cat([to_dev(_rnd(rng, (K, n), BF), BF), torch.full((64, n), float("nan"), dtype=BF, device=DEV)]) for n in (M, N))
     ref = torch.matmul(dX[:K].double().t().contiguous(), ddY[:K].double())
@@ -1080,11 +1099,11 @@ def test_gemm_ring_of_k_tiles_weight_gradient(K):
         assert bool(((c.double() - want).abs() <= 1e-5 * (8 * want.square().mean().sqrt() + want.abs())).all())
 
 
-@pytest.mark.parametrize("M,N,K", [
-    (40, 256, 256), (300, 2304, 512),                                    # small tiles
-    (897, 8192, 192), (3457, 3072, 192), (1537, 3840, 1024),             # one round of 128- and 192-row tiles
-    (3073, 4608, 64), (4133, 8192, 128), (10713, 4608, 512)])            # 256 x 256, one tile per work-group and persistent
-def test_gemm_bias_is_the_last_term(M, N, K):
+@pytest.mark.parametrize("M,N,K,tile", [
+    (300, 2304, 512, "64x64"), (129, 5632, 128, "128x64"), (385, 7680, 256, "128x128"), (1281, 6144, 128, "128x128/2"),
+    (897, 8192, 192, "128"), (1537, 3840, 1024, "128"), (3457, 3072, 192, "192"),
+    (3073, 4608, 64, "256"), (4133, 8192, 128, "256"), (10713, 4608, 512, "256")])              # (the last two persistent)
+def test_gemm_bias_is_the_last_term(M, N, K, tile):
     """Products 2^24 and -2^24 at the two ends of the contraction cancel before the bias is added, on whatever tile: the output is the bias
     itself (a sum that starts with the bias loses it)."""
     rng = np.random.default_rng(46)
@@ -1097,6 +1116,7 @@ def test_gemm_bias_is_the_last_term(M, N, K):
     c, c2 = (torch.empty((M, N), dtype=BF, device=DEV) for _ in range(2))
     for epi, kw, ref in ((ds.DS_EPI_NONE, {}, want), (ds.DS_EPI_RESID, dict(R=r), want + r.float()), (ds.DS_EPI_GELU, {}, want),
                          (ds.DS_EPI_GATE, dict(R=r), want), (ds.DS_EPI_MULR, dict(R=r), want * r.float())):
+        assert [x["tile"] for x in gemm_launches(M, N, K, epilogue=epi)] == [tile]
         ds.ds_gemm(a, b, c, M, N, K, trans_b=True, epilogue=epi, bias=bias, C2=c2, **kw)
         torch.cuda.synchronize()
         assert torch.equal(c, ref.to(BF)), epi
