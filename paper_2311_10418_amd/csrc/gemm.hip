@@ -100,10 +100,12 @@ constexpr int BM = 256, BN = 256, BK = 64;
 // TFLOP/s on random operands), short K loops by what stands around them.  Why this shape: with eight wavefronts of 128 x 64
 // in a ring of two 64 KB stages (the kernel before this one) every K tile took 192 KB of fragment reads from LDS, here 128,
 // and a transfer had three quarters of a tile to arrive, here one to two and a half tiles.  Before -> after, us, operands from memory:
-// NT 4096 x 4096 x 4096 113 -> 97, 65 582 x 2048 x 8192 with a residual 1 600 -> 1 530, 32 768 x 4096 x 16 384 3 224 -> 2 952, 65 629 x 1024 x
-// 1024 193 -> 181; TN 8192 x 2048 x 65 582 1 606 -> 1 461, 4096 x 16 384 x 32 768 3 169 -> 2 985, 2048 x 6144 x 65 582 1 358 -> 1 240.  The
-// price is one wavefront per SIMD in the epilogue, where vector instructions issue every 5.3 clocks instead of every 2.7 to 4.2: 65 629 x
-// 2816 x 1024 with the gated GELU 490 -> 506, with its derivative 565 -> 575, 65 582 x 8192 x 2048 with GELU and derivative 1 957 -> 1 942.
+// NT 4096 x 4096 x 4096 114 -> 96, 65 582 x 2048 x 8192 with a residual 1 623 -> 1 530, 32 768 x 4096 x 16 384 3 156 -> 2 903, 65 580 x 1024 x
+// 1024 143 -> 136; TN 8192 x 2048 x 65 582 1 601 -> 1 488, 4096 x 16 384 x 32 768 3 158 -> 2 945.  The price is one wavefront per SIMD in the
+// epilogue, where vector instructions issue every 5.3 clocks instead of every 2.7 to 4.2: what an epilogue computes gains little over that
+// kernel (65 629 x 2816 x 1024 with the gated GELU 480 -> 473, with its derivative 549 -> 522, 65 580 x 8192 x 2048 with GELU and derivative 1 900 ->
+// 1 845), and a short K loop in front of it nothing: 24 shapes each of large outputs, geometric means, K = 256 0.96 to 1.01 by epilogue, K = 512 0.90
+// to 1.00, K = 1024 0.92 to 0.98, K = 2048 0.88 to 0.96.
 // Tried: two 64 KB stages with this wavefront shape (4096 x 4096 x 16 384 519 us, ring 378); all transfers right behind the
 // barrier, one every two MFMAs (5 to 8 % slower); 32x32x16 instructions (5 to 9 % slower); 256 x 128 tiles, two work-groups
 // of four wavefronts to a CU (15 to 20 % slower: half as many transfers again).
@@ -773,6 +775,10 @@ static BigPlan plan_big(bool tnf, int epi, int M, int N, int K, size_t split_ws_
 // Estimated time of that plan in microseconds (see gemm_tile.hip for the other side of the comparison and the fit): 1.15
 // (TN) or 1.25 (NT, operands from memory; 1.15 warm) per 64-deep K tile of a 256 x 256 tile and 4 around it, per round over
 // the compute units; 0.1 per piece of partial sums (256 KB written and read back) and 4 for the launch that adds them.
+// The rates were fitted to the kernel with eight wavefronts.  The choices hold with four: of 400 random NT products (six epilogues, K = 256 .. 8192, up
+// to 46 000 rows) and 300 weight gradients (64 to 46 000 tokens) for which they decide something, what is taken takes 0.5 % and 0.9 % longer than the best of
+// itself, no smaller tiles and only smaller tiles (mean of operands from memory and warm); 13 and 21 of them over 3 %, 1 and 8 over 10 %, at worst 18 % (weight gradients of
+// 70 to 200 tokens, where 128 x 64 tiles are estimated too low).
 static double big_cost(const BigPlan& b, bool tnf, int M, int N) {
     const int n_cu = gemm_cu_count(), tiles = b.tiles_m * b.tiles_n;
     const double steps = b.nt, step = tnf ? 1.15 : 1.25;
@@ -934,6 +940,8 @@ static NtChoice choose_kernel(bool tn, int epi, int M, int N, int K, size_t wsf,
 // a second launch costs then is not in the estimates.  Of 292 shapes (N = 256 .. 8192, 1 to 8 rounds, operands from memory, plain and
 // residual outputs) for which they say two, two launches / one, geometric mean and worst: K = 64 and 128, 1.06 and 1.41; K = 256 .. 448
 // two rounds 0.95 and 1.04 (the exception below), one round 0.98 and 1.08, more 1.03 and 1.25; K = 512 and more 0.91 and 1.05.
+// (All with the kernel of eight wavefronts.  With four, 300 random products that go out as two against one launch: 0.94 from memory and 0.91 warm, 3 of
+// them over 3 % longer, at worst 6 %.)
 // Behind one round, rows that fill more than a tenth of another are not worth it either below K = 1536: half a launch more of tiles that
 // read and write as much as they multiply.  Of another 220 (all of K >= 512, remainders of any size, epilogues with up to two more
 // operands and results), 46 such, from memory and warm: 0.97 and 0.98, worst 1.13 and 1.11; the rest 0.93 and 0.90, worst 1.08 and 1.00.

@@ -416,7 +416,7 @@ int gemm_cu_count() {
 // writing goes at the rate of the memory either way (2048 x 8192 over 126 tokens: 30.9 us on 128 x 64 tiles, 24.5 on
 // 256 x 256 ones).  Against that kernel with eight wavefronts, of 1 500 random shapes of stages with d = 256 .. 2048 (96 to 16 000 rows, operands from memory) 12 take
 // over 3 % longer than on the large kernel, at most 12 %; with the rates of warm operands throughout it was 40 of 1 100, up to
-// 21 %.
+// 21 %.  (Against the one with four: big_cost.)
 TilePick pick_gemm_tile(bool tn, int32_t M, int32_t N, int32_t K, size_t split_ws_floats, bool colsum, double out_us, bool out_read) {
     TilePick best{-1, 1, 0.0, 0.0};
     if (tn && (M > (1 << 25) || N > (1 << 25))) return best;          // a K tile is addressed through a 32-bit buffer length
@@ -468,7 +468,10 @@ ds_status launch_gemm_tile(const TilePick& pick, bool tn, int32_t M, int32_t N, 
 // with the step a CU takes for a K tile, operands from memory, when it has one tile / several:
 //   128 x 128 0.85 / 0.85, 128 x 64 0.60 / 0.50, 64 x 64 0.45 / 0.36, 128 x 128 two per CU 0.85 / 0.75, 256 x 256 1.60.
 // Splits only with 256 x 256 tiles (smaller ones have enough work-groups), as far as the blocks for partial sums go.
-// Estimate / measured (d, d_ff, tokens; the four gradients of a layer): 2048, 8192, 16384: 1335 / 1334; 1024, 4096, 16384 (4
+// (256 x 256: of the kernel with eight wavefronts.  That with four takes 1.43 to 1.46 on long contractions; with 1.40 here 18 stages took the same time within
+// 0.4 %, with 1.20 three of d = 768 3 to 4 % longer.)
+// Estimate / measured (d, d_ff, tokens; the four gradients of a layer; the first two and the fourth on 256 x 256 tiles of eight
+// wavefronts): 2048, 8192, 16384: 1335 / 1334; 1024, 4096, 16384 (4
 // splits) 443 / 408; 768, 3072, 1500 (128 x 128, two per CU) 43 / 51; 512, 2048, 9000 (5 splits) 95 / 97; 256, 1024, 228 (64 x 64)
 // 9 / 10.
 static double tn_cost(double mn, int per, double out_us, int blocks, TnPick& best) {

@@ -88,9 +88,9 @@ struct ds_stage {
     float *delta = nullptr, *partial = nullptr, *split_ws = nullptr;
     // Bias-gradient column sums (decoder-only stage, where a layer's are too large to go out together) run on a stream of their own:
     // nothing on the main stream reads what they write, so they only have to be back before the tensor they read is
-    // overwritten (joined at the end of every layer's backward pass).  They run beside the input-gradient GEMMs and in the gaps
-    // between launches; beside the 256 x 256 weight-gradient kernel there are no registers for them.  Same priority as the
-    // caller's stream.
+    // overwritten (joined at the end of every layer's backward pass).  They run in the gaps between launches and beside those that leave LDS:
+    // the 256 x 256 GEMM takes all 160 KB of a CU, the column sums 9 KB and their second stage 0.5 or 2 KB, so that none of them runs
+    // beside it.  On the main stream, or together at the end of the layer, calls take the same time within 1 %.  Same priority as the caller's stream.
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     float* partial_side = nullptr;     // their partial sums (the main stream's `partial` belongs to the norm kernels)
