@@ -219,12 +219,15 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         }
     }
 
-    const int nt_total = TNF ? (K + BK - 1) / BK : K / BK;
-    const int per_split = (nt_total + nsplit - 1) / nsplit;
-    // (divisions go through vector registers: what steers the K loop comes back to scalar ones)
-    const int t_begin = __builtin_amdgcn_readfirstlane(split * per_split);
-    const int t_end = __builtin_amdgcn_readfirstlane((t_begin + per_split) < nt_total ? (t_begin + per_split) : nt_total);
-
+    // This work-group's part of the contraction: NT whole K tiles; TN whole 32-row steps (a product's depth), k_len rows from row k_first on,
+    // counted in K tiles from there.  (Divisions go through vector registers: what steers the K loop comes back to scalar ones.)
+    constexpr int DEPTH = TNF ? BK / 2 : BK;
+    const int steps = TNF ? (K + DEPTH - 1) / DEPTH : K / DEPTH, per_split = (steps + nsplit - 1) / nsplit;
+    const int s_begin = split * per_split, s_end = s_begin + per_split < steps ? s_begin + per_split : steps;
+    const int k_first = __builtin_amdgcn_readfirstlane(s_begin * DEPTH);
+    const int k_len = __builtin_amdgcn_readfirstlane((s_end * DEPTH < K ? s_end * DEPTH : K) - s_begin * DEPTH);
+    const int t_begin = TNF ? 0 : __builtin_amdgcn_readfirstlane(s_begin);
+    const int t_end = TNF ? (k_len + BK - 1) / BK : __builtin_amdgcn_readfirstlane(s_end);
     // What the transfers of a tile need: its corner and the operand bases there (set_tile), and per-lane offsets that are the same for every
     // tile.  An operand's K tile is 32 transfers, eight per wavefront (of A, NUA): NT 8 rows of 128 bytes each, TN 2 k-rows of 512.
     int tile_m = 0, tile_n = 0, m0 = 0, n0 = 0;
@@ -239,8 +242,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         n0 = tile_n * BN;
         const uint64_t bytes = (uint64_t)(uint32_t)(M - m0 < TA ? M - m0 : TA) * (uint32_t)K * 2u;
         len_a = bytes > 0xFFFFFFFFu ? 0xFFFFFFFFu : (uint32_t)bytes;
-        pa = reinterpret_cast<const char*>(A) + (TNF ? (long long)m0 * 2 : (long long)m0 * K * 2);
-        pb = reinterpret_cast<const char*>(B) + (TNF ? (long long)n0 * 2 : (long long)n0 * K * 2);
+        pa = reinterpret_cast<const char*>(A) + (TNF ? ((long long)k_first * M + m0) * 2 : (long long)m0 * K * 2);
+        pb = reinterpret_cast<const char*>(B) + (TNF ? ((long long)k_first * N + n0) * 2 : (long long)n0 * K * 2);
     };
     set_tile(logical);
     uint32_t offA[NUA], offB[8];
@@ -263,7 +266,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
         const uint32_t inside = (uint32_t)((tile - t_end) >> 31);   // all ones before the end
         if constexpr (TNF) {
             const uint32_t ld2 = (uint32_t)(which ? N : M) * 2u;
-            const int left = K - tile * BK;
+            const int left = k_len - tile * BK;
             return make_raw_buffer((which ? pb : pa) + (long long)tile * BK * ld2, ((uint32_t)((left < BK ? left : BK) - 1) * ld2 + 512u) & inside);
         } else {
             return make_raw_buffer((which ? pb : pa) + (long long)tile * (BK * 2), (which ? 0xFFFFFFFFu : len_a) & inside);
@@ -722,12 +725,12 @@ ds_status launch_generic(int ta, int tb, int M, int N, int K, const void* A, con
 
 // number of K splits of a product with fp32 output: the fewest that bring the work-group count closest to a whole
 // number of rounds over the compute units (time ~ rounds x split length), of 512 rows or more for a weight gradient, 1 024 for an NT product
-static int choose_splits(bool tnf, int tiles, int nt, int M, int N, size_t split_ws_floats) {
+static int choose_splits(int tiles, int nt, int M, int N, size_t split_ws_floats) {
     const int n_cu = gemm_cu_count();
     int best = 1;
     double best_cost = 1e30;
     for (int sp = 1; sp <= 16; ++sp) {
-        if (sp > 1 && (sp > nt / (tnf ? 8 : 16) || (size_t)sp * M * N > split_ws_floats)) break;
+        if (sp > 1 && (sp > nt / 16 || (size_t)sp * M * N > split_ws_floats)) break;
         const int per = (nt + sp - 1) / sp;
         if ((nt + per - 1) / per != sp) continue;               // every split must own at least one K tile
         const double rounds = (double)(((long long)tiles * sp + n_cu - 1) / n_cu);
@@ -740,16 +743,16 @@ static int choose_splits(bool tnf, int tiles, int nt, int M, int N, size_t split
 // How a launch of the 256 x 256 kernel divides its tiles: uniform splits (weight gradients), or whole tiles and a tail
 // whose K loops are cut into tail_splits pieces.
 struct BigPlan {
-    int tiles_m, tiles_n, nt;      // nt: 64-deep K tiles
+    int tiles_m, tiles_n, nt;      // nt: what the contraction is cut in, NT 64-deep K tiles, TN 32-deep steps
     int splits, n_main, tail_splits;
 };
 static BigPlan plan_big(bool tnf, int epi, int M, int N, int K, size_t split_ws_floats) {
     BigPlan b;
     b.tiles_m = (M + BM - 1) / BM;
     b.tiles_n = N / BN;
-    b.nt = (K + BK - 1) / BK;
+    b.nt = tnf ? (K + BK / 2 - 1) / (BK / 2) : K / BK;
     const int tiles = b.tiles_m * b.tiles_n;
-    b.splits = epi == DS_EPI_ACC32 && split_ws_floats ? choose_splits(tnf, tiles, b.nt, M, N, split_ws_floats) : 1;
+    b.splits = epi == DS_EPI_ACC32 && split_ws_floats ? choose_splits(tiles, b.nt, M, N, split_ws_floats) : 1;
     // tail split-K: the tiles beyond the last whole round over the compute units share that round; a launch with
     // fewer tiles than compute units (small micro-batches) is all tail, so that the K loop is spread over the chip
     b.n_main = tiles;
@@ -781,7 +784,7 @@ static BigPlan plan_big(bool tnf, int epi, int M, int N, int K, size_t split_ws_
 // 70 to 200 tokens, where 128 x 64 tiles are estimated too low).
 static double big_cost(const BigPlan& b, bool tnf, int M, int N) {
     const int n_cu = gemm_cu_count(), tiles = b.tiles_m * b.tiles_n;
-    const double steps = b.nt, step = tnf ? 1.15 : 1.25;
+    const double steps = tnf ? 0.5 * b.nt : b.nt, step = tnf ? 1.15 : 1.25;
     auto rounds = [&](double work_groups) { return std::ceil(work_groups / n_cu); };
     if (b.splits > 1)
         return rounds((double)tiles * b.splits) * (steps / b.splits * step + 4) + 2e-6 * (double)b.splits * M * N + 4;

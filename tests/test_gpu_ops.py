@@ -1035,13 +1035,13 @@ def test_gemm_every_macro_tile_nt(M, N, K, ws_floats, tile):
     (1792, 1792, 2049, 0, "128x128"), (256, 2816, 20001, 1 << 22, "128x128"),
     # two stages: two to four K tiles
     (2560, 3328, 129, 0, "256 128x128/2"), (2560, 3328, 200, 0, "256 128x128/2"), (2560, 6656, 65, 0, "128x128/2"),
-    # 64-deep K tiles: one, a ragged few, ranges of the contraction, whole tiles, whole tiles and split ones
+    # 64-deep K tiles: one, a ragged few, ranges of the contraction, whole tiles and split ones (two pieces and seven)
     (10240, 3328, 1, 0, "256"), (10240, 3328, 97, 0, "256"), (256, 5632, 12000, 1 << 24, "256"), (10240, 3328, 250, 1 << 22, "256"), (9472, 1792, 971, 1 << 24, "256")])
 def test_gemm_every_macro_tile_weight_gradient(M, N, K, ws_floats, tiles):
     """The same for weight gradients, overwriting and adding; rows behind the last one hold NaN.  fp32 sums: 1e-5."""
     for adds, tile in zip((False, True), (tiles.split() * 2)[:2]):
         l, = gemm_launches(M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, ws_floats=ws_floats, accumulate=adds)
-        assert l["tile"] == tile and (l["splits"] > 1 or l["pieces"] > 1) == (K in (6000, 9001, 20001, 12000, 971))
+        assert l["tile"] == tile and (l["splits"] > 1 or l["pieces"] > 1) == (K in (6000, 9001, 20001, 12000, 250, 971))
     rng = np.random.default_rng(42)
     X, dY = _rnd(rng, (K, M), BF), _rnd(rng, (K, N), BF)
     dX, ddY = (torch.cat([to_dev(a, BF), torch.full((64, a.shape[1]), float("nan"), dtype=BF, device=DEV)]) for a in (X, dY))
@@ -1191,3 +1191,22 @@ def test_gemm_widest_weight_gradients(M, N):
         s = slice(i, min(i + (1 << 20), max(M, N)))
         got, want = (c[:, s], x.float().t() @ dy[:, s].float()) if N > M else (c[s], x[:, s].float().t() @ dy.float())
         assert bool(((got - want).abs() <= 1e-5).all()), i      # three products of a few units each: 2^-23 of their sum
+
+
+def test_gemm_weight_gradient_pieces_of_whole_steps():
+    """A contraction is cut into pieces of whole 32-row steps, the products' depth: of 375 steps ten times 35 and once 25.  Every step adds 1, and 2^24 in
+    the first row swallows the ones of its own piece, one at a time (2^24 + 1 rounds back); the others are counted exactly and added piece by piece."""
+    M, N, K = 256, 5632, 12000
+    l, = gemm_launches(M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, ws_floats=1 << 24)
+    assert (l["tile"], l["splits"]) == ("256", 11)
+    x, dy = torch.zeros((K, M), dtype=BF, device=DEV), torch.zeros((K, N), dtype=BF, device=DEV)
+    x[::32] = 1.0
+    dy[::32] = 1.0
+    x[0] = dy[0] = 4096.0
+    c = torch.zeros((M, N), dtype=F32, device=DEV)
+    ds.ds_gemm(x, dy, c, M, N, K, trans_a=True, epilogue=ds.DS_EPI_ACC32, workspace=_ws(1 << 24))
+    torch.cuda.synchronize()
+    want = np.float32(2 ** 24)
+    for n in [35] * 9 + [25]:
+        want = np.float32(want + np.float32(n))
+    assert bool((c == float(want)).all()), (c.unique(), want)
