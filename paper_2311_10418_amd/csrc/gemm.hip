@@ -592,7 +592,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_kernel(int M, int N, int 
                     if constexpr (SUMS) {
                         const bool exists = (s >> 1) * 16 + g * 8 + rd_row < row_cnt;
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) csum[s & 1][j] += exists ? v[j] : 0.f;
+                        for (int j = 0; j < 8; ++j) csum[s & 1][j] = exists ? csum[s & 1][j] + v[j] : csum[s & 1][j];    // (one fused multiply-add per term)
                     }
                 }
             }, [&](int s) {
