@@ -100,12 +100,11 @@ constexpr int BM = 256, BN = 256, BK = 64;
 // TFLOP/s on random operands), short K loops by what stands around them.  Why this shape: with eight wavefronts of 128 x 64
 // in a ring of two 64 KB stages (the kernel before this one) every K tile took 192 KB of fragment reads from LDS, here 128,
 // and a transfer had three quarters of a tile to arrive, here one to two and a half tiles.  Before -> after, us, operands from memory:
-// NT 4096 x 4096 x 4096 114 -> 96, 65 582 x 2048 x 8192 with a residual 1 623 -> 1 530, 32 768 x 4096 x 16 384 3 156 -> 2 903, 65 580 x 1024 x
-// 1024 143 -> 136; TN 8192 x 2048 x 65 582 1 601 -> 1 488, 4096 x 16 384 x 32 768 3 158 -> 2 945.  The price is one wavefront per SIMD in the
-// epilogue, where vector instructions issue every 5.3 clocks instead of every 2.7 to 4.2: what an epilogue computes gains little over that
-// kernel (65 629 x 2816 x 1024 with the gated GELU 480 -> 473, with its derivative 549 -> 522, 65 580 x 8192 x 2048 with GELU and derivative 1 900 ->
-// 1 845), and a short K loop in front of it nothing: 24 shapes each of large outputs, geometric means, K = 256 0.96 to 1.01 by epilogue, K = 512 0.90
-// to 1.00, K = 1024 0.92 to 0.98, K = 2048 0.88 to 0.96.
+// NT 4096 x 4096 x 4096 114 -> 98, 65 582 x 2048 x 8192 with a residual 1 642 -> 1 541, 32 768 x 4096 x 16 384 3 182 -> 2 923, 65 580 x 1024 x
+// 1024 142 -> 137; TN 8192 x 2048 x 65 582 1 633 -> 1 476, 4096 x 16 384 x 32 768 3 246 -> 3 001, 2048 x 6144 x 65 582 1 327 -> 1 206.  The price is
+// one wavefront per SIMD in the epilogue, where vector instructions issue every 5.3 clocks instead of every 2.7 to 4.2: 65 629 x 2816 x 1024
+// with the gated GELU 474 -> 475, with its derivative 555 -> 526, 65 580 x 8192 x 2048 with GELU and derivative 1 946 -> 1 877.  Of 14 large outputs each,
+// geometric means by epilogue: K = 256 0.94 to 1.01, K = 512 0.90 to 1.00, K = 1024 0.92 to 0.99, K = 2048 0.91 to 0.95.
 // Tried: two 64 KB stages with this wavefront shape (4096 x 4096 x 16 384 519 us, ring 378); all transfers right behind the
 // barrier, one every two MFMAs (5 to 8 % slower); 32x32x16 instructions (5 to 9 % slower); 256 x 128 tiles, two work-groups
 // of four wavefronts to a CU (15 to 20 % slower: half as many transfers again).
